@@ -204,7 +204,7 @@ int t5_gemm_bf16(const void* A, const void* B, float* C, int M, int N, int K, in
   if (!A || !B || !C) return T5_ERR_NULL;
   GemmDesc g = gemm1(M, N, K, A, lda, a_kc ? 1 : 0, B, ldb, b_kc ? 1 : 0, IN_BF16);
   GemmEpi e = a_kc ? epi(EPI_STORE, C, ldc, IN_F32) : epi(EPI_SPLIT_F32, C, ldc, IN_F32);
-  if (!gemm_mfma_supported(g, e)) return T5_ERR_UNSUPPORTED;
+  if (K % 64 != 0 || !gemm_mfma_supported(g, e)) return T5_ERR_UNSUPPORTED;
   hipStream_t st = (hipStream_t)stream;
   T5_STEP("gemm_bf16", launch_gemm_mfma(g, e, st));
   return T5_OK;

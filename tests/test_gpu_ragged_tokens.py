@@ -1,0 +1,50 @@
+"""Weight gradients over a number of tokens that is not a multiple of the k-tile: the last, zero-filled k-tile of the
+m-contiguous GEMM, alone (fewer tokens than one tile), after whole tiles, on the last of several k-slices, in the
+two-pass reproducible reduction and in grouped launches."""
+from dataclasses import replace
+
+import pytest
+
+import synth_inputs as SI
+from oracle import t5_oracle as O
+from parity_util import block_floors, check_bf16, make_case, rel_err, run_block_gpu
+
+pytestmark = pytest.mark.gpu
+
+BASE = SI.BlockConfig("ragged_tokens", 60, 1, 33, 128, 2, 64, 256, attn_scale=0.125)
+
+
+@pytest.mark.parametrize("batch,seq", [(1, 33), (1, 63), (1, 65), (3, 43), (5, 205), (7, 331)])
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_block_ragged_tokens(batch, seq, deterministic):
+    cfg = replace(BASE, batch=batch, seq=seq, deterministic=deterministic, name=f"ragged_tokens_{batch}x{seq}")
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
+    check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
+
+
+def test_stack_ragged_tokens_grouped():
+    """Two layers with grouped weight gradients over 5 x 37 tokens against the same layers launched one by one
+    (reproducible mode): two float32 summation orders of the same products."""
+    import torch
+    import paper_2203_17189_amd as P
+    from parity_util import to_dev, to_np
+    sc = SI.StackConfig("ragged_stack", SI.BlockConfig("ragged_stack", 61, 5, 37, 128, 2, 64, 256, causal=True,
+                                                       attn_scale=0.125), 2, 192)
+    w = SI.make_stack_weights(sc)
+    dw = {k: [{n: to_dev(v, "bf16") for n, v in lw.items()} for lw in t] if k == "layers" else to_dev(t, "bf16")
+          for k, t in w.items()}
+    tok, tgt = (torch.from_numpy(a).cuda() for a in SI.make_tokens(sc))
+    out = []
+    for det in (False, True):
+        s = replace(sc, block=replace(sc.block, deterministic=det))
+        _, g = P.t5_stack_loss_and_grad(s, tok, tgt, dw)
+        torch.cuda.synchronize()
+        out.append(g)
+    for l in range(2):
+        for n, a in out[0]["layers"][l].items():
+            # K = 185 products of float32-accumulated bf16 pairs: reordering moves a sum by a few ulps of its largest term
+            assert rel_err(to_np(a), to_np(out[1]["layers"][l][n]))[0] <= 2e-5, (l, n)
