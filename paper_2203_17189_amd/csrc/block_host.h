@@ -257,6 +257,13 @@ GemmDesc gemm1(int M, int N, int K, const void* A, int lda, int a_kc, const void
   g.a_kc = a_kc; g.b_kc = b_kc; g.in_type = ty;
   return g;
 }
+// The same with the columns of B taken from nsrc matrices of n_each columns (k-major, as the weights are stored).
+GemmDesc gemm_cols(int M, int n_each, int K, const void* A, int lda, const void* const* Bs, int nsrc, int ty) {
+  GemmDesc g = gemm1(M, nsrc * n_each, K, A, lda, 1, Bs[0], n_each, 0, ty);
+  for (int s = 1; s < nsrc; ++s) g.seg[s].B = Bs[s];
+  g.nsrc = nsrc; g.nsrc_cols = n_each;
+  return g;
+}
 GemmEpi epi(int kind, void* out0, int ld0, int out_type) {
   GemmEpi e;
   std::memset(&e, 0, sizeof(e));
@@ -287,6 +294,7 @@ size_t wgrad_partials_bytes(const Dims& D) {
 
 hipError_t run_gemm(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   if (gemm_mfma_supported(g, e)) return launch_gemm_mfma(g, e, st);
+  if (gemm_f32_supported(g, e)) return launch_gemm_f32(g, e, st);
   return launch_gemm_simple(g, e, st);
 }
 
@@ -403,7 +411,11 @@ int fwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
     T5_STEP("gemm_qkv", run_gemm(g, epi(EPI_STORE, S.qkv, 3 * D.I, ty), st));
   } else {
     const void* ws3[3] = {w->wq, w->wk, w->wv};
-    for (int j = 0; j < 3; ++j) {
+    const GemmDesc g3 = gemm_cols(T, D.I, D.d, S.n1, D.d, ws3, 3, ty);
+    const GemmEpi e3 = epi(EPI_STORE, S.qkv, 3 * D.I, ty);
+    const bool one = gemm_f32_supported(g3, e3);
+    if (one) T5_STEP("gemm_qkv", launch_gemm_f32(g3, e3, st));
+    for (int j = 0; j < 3 && !one; ++j) {
       GemmDesc g = gemm1(T, D.I, D.d, S.n1, D.d, 1, ws3[j], D.I, 0, ty);
       T5_STEP("gemm_qkv", run_gemm(g, epi(EPI_STORE, at(S.qkv, (size_t)j * D.I, es), 3 * D.I, ty), st));
     }
@@ -437,7 +449,11 @@ int fwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
     GemmDesc gq = gemm1(T, D.I, D.d, S.nx, D.d, 1, xw->xq, D.I, 0, ty);
     T5_STEP("gemm_xq", run_gemm(gq, epi(EPI_STORE, S.qx, D.I, ty), st));
     const void* ws2[2] = {xw->xk, xw->xv};
-    for (int j = 0; j < 2; ++j) {
+    const GemmDesc g2 = gemm_cols(Te, D.I, D.d, enc, D.d, ws2, 2, ty);
+    const GemmEpi e2 = epi(EPI_STORE, S.kvx, 2 * D.I, ty);
+    const bool one = gemm_f32_supported(g2, e2);
+    if (one) T5_STEP("gemm_xkv", launch_gemm_f32(g2, e2, st));
+    for (int j = 0; j < 2 && !one; ++j) {
       GemmDesc g = gemm1(Te, D.I, D.d, enc, D.d, 1, ws2[j], D.I, 0, ty);
       T5_STEP("gemm_xkv", run_gemm(g, epi(EPI_STORE, at(S.kvx, (size_t)j * D.I, es), 2 * D.I, ty), st));
     }
@@ -472,6 +488,12 @@ int fwd_mlp(const t5_block_cfg* cfg, const Dims& D, const float* hin, const t5_b
     e.out1 = S.gl; e.out2 = S.a; e.act = D.mlp; e.drop = drop_site(D, DROP_MLP_HIDDEN);
     if (!gemm_mfma_supported(g, e)) return T5_ERR_UNSUPPORTED;
     T5_STEP("gemm_wi_geglu", launch_gemm_mfma(g, e, st));
+  } else if (const void* wi[2] = {w->wi0, w->wi1};
+             gemm_f32_supported(gemm_cols(T, D.F, D.d, S.n2, D.d, wi, 2, ty), epi(EPI_GEGLU_FWD, S.gp, D.F, ty))) {
+    const GemmDesc g = gemm_cols(T, D.F, D.d, S.n2, D.d, wi, 2, ty);
+    GemmEpi e = epi(EPI_GEGLU_FWD, S.gp, D.F, ty);
+    e.out1 = S.gl; e.out2 = S.a; e.act = D.mlp; e.drop = drop_site(D, DROP_MLP_HIDDEN);
+    T5_STEP("gemm_wi_geglu", launch_gemm_f32(g, e, st));
   } else {
     GemmDesc g0 = gemm1(T, D.F, D.d, S.n2, D.d, 1, w->wi0, D.F, 0, ty);
     T5_STEP("gemm_wi", run_gemm(g0, epi(EPI_STORE, S.gp, D.F, ty), st));
@@ -527,7 +549,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.F, D.d, T, S.a, D.F, 0, dy, D.d, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dw->wo_ff, D.d, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials;
+    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
     T5_STEP("gemm_dwo_ff", run_gemm(g, e, st));
   }
   if (D.mlp == ACT_RELU) {
@@ -542,7 +564,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
       hipStream_t st = wgrad_stream(W.fork);
       GemmDesc g = gemm1(D.d, D.F, T, S.n2, D.d, 0, du_p, D.F, 0, ty);
       GemmEpi e = epi(EPI_SPLIT_F32, dw->wi0, D.F, IN_F32);
-      e.accumulate = 1; e.aux0 = W.wg_partials;
+      e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
       T5_STEP("gemm_dwi", run_gemm(g, e, st));
     }
     {  // dn2 = du Wi0^T
@@ -561,7 +583,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
       hipStream_t st = wgrad_stream(W.fork);
       GemmDesc g = gemm1(D.d, 2 * D.F, T, S.n2, D.d, 0, du_p, 2 * D.F, 0, ty);
       GemmEpi e = epi(EPI_SPLIT_F32, dw->wi0, D.F, IN_F32);
-      e.out1 = dw->wi1; e.split_n = D.F; e.accumulate = 1; e.aux0 = W.wg_partials;
+      e.out1 = dw->wi1; e.split_n = D.F; e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
       T5_STEP("gemm_dwi", run_gemm(g, e, st));
     }
     {  // dn2 = du Wi0^T + dw Wi1^T
@@ -596,7 +618,7 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.I, D.d, T, S.cx, D.I, 0, dh_op, D.d, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dxw->xo, D.d, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials;
+    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
     T5_STEP("gemm_dxo", run_gemm(g, e, st));
   }
   {  // dcx = dh2 Xo^T
@@ -615,14 +637,14 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.d, D.I, T, S.nx, D.d, 0, W.dqx, D.I, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dxw->xq, D.I, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials;
+    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
     T5_STEP("gemm_dxq", run_gemm(g, e, st));
   }
   if (!W.defer_wgrad) {  // dXk | dXv = enc^T [dk | dv]   (ordered after dXq on the side stream: no new fork point needed)
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.d, 2 * D.I, Te, enc, D.d, 0, W.dkvx, 2 * D.I, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dxw->xk, D.I, IN_F32);
-    e.out1 = dxw->xv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials;
+    e.out1 = dxw->xv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
     T5_STEP("gemm_dxkv", run_gemm(g, e, st));
   }
   {  // denc = dk Xk^T + dv Xv^T
@@ -662,7 +684,7 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.I, D.d, T, S.c, D.I, 0, dh_op, D.d, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dw->wo, D.d, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials;
+    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
     T5_STEP("gemm_dwo", run_gemm(g, e, st));
   }
   {  // dc = dh Wo^T
@@ -686,7 +708,7 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.d, 3 * D.I, T, S.n1, D.d, 0, W.dqkv, 3 * D.I, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dw->wq, D.I, IN_F32);
-    e.out1 = dw->wk; e.out2 = dw->wv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials;
+    e.out1 = dw->wk; e.out2 = dw->wv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
     T5_STEP("gemm_dwqkv", run_gemm(g, e, st));
   }
   {  // dn1 = dq Wq^T + dk Wk^T + dv Wv^T

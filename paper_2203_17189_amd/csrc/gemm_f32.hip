@@ -1,0 +1,374 @@
+// float32 GEMM on the matrix units (v_mfma_f32_32x32x2_f32: float32 operands, products and sums).
+//
+//   C[m,n] = sum_s sum_k A_s(m,k) B_s(n,k)
+//
+// Bound: the float32 matrix rate, 157 TFLOP/s nominal (a vendor GEMM of 4096^3 sustains 148 here); one MFMA of 4096
+// FLOP keeps its unit busy for 64 cycles and needs two registers of operands, so neither LDS nor the L2 is near a
+// limit from 64x64 tiles on and the operands go through registers into LDS in plain code: that is where ragged edges
+// are filled with zeros, so the kernel takes any shape, leading dimension and alignment (float4 where the alignment
+// allows it, single elements elsewhere).
+//
+// Tiles: BM x BN per workgroup, k-tiles of BK, WM x WN x WK wavefronts.  WK > 1 gives each of WK wavefronts its share
+// of every k-tile; their sums meet in LDS in a fixed order.  That is what the small problems need: at 64 tokens a
+// product has one to sixteen 64x64 tiles, and the length of one wavefront's MFMA chain is its time.
+//
+// Operand layouts in LDS (floats):
+//   k-contiguous (A[m][k])  rows of BK k, padded by 4: a lane reads 4 consecutive k of its row (ds_read_b128; 16 rows
+//                           cover the 64 banks once);
+//   m-contiguous (A[k][m])  rows of BM m, padded by 8: a lane reads its column from 4 consecutive rows (ds_read_b32;
+//                           the two lane halves read rows 4 apart, 32 banks apart).
+// MFMA e of a group of 8 k contracts k = 4*half + e of both operands: any pairing serves as long as both agree.
+//
+// Measured on the layer d 512, 6 heads, d_ff 1024, 4000 tokens (forward + backward): GEMMs 5.0 ms with the FMA kernel
+// this replaces for float32 (64x64 tiles, 4x4 products a thread, one load in flight).
+#include "kernels.h"
+#include <algorithm>
+#include <atomic>
+
+namespace t5mi {
+
+namespace {
+
+struct F32Src {  // where a thread's float4 slot of an operand comes from
+  size_t off;    // elements from (segment base + tile start)
+  int row;       // position along the contraction (m-contiguous) or first k of the slot (k-contiguous)
+  int nv;        // m-contiguous: valid elements of the slot; k-contiguous: 1 if the row exists
+};
+
+__device__ __forceinline__ f32x4 ld4(const float* p, int nv, bool vec) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (nv >= 4 && vec) return *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (q < nv) v[q] = p[q];
+  return v;
+}
+
+template <int BM, int BN, int WM, int WN, int WK, int BK, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g, GemmEpi e, int split_k, int vec_a,
+                                                                     int vec_b) {
+  constexpr int NT = WM * WN * WK * 64;
+  constexpr int TMW = BM / WM, TNW = BN / WN, MI = TMW / 32, NI = TNW / 32;
+  constexpr int A_LD = A_KC ? BK + 4 : BM + 8, B_LD = B_KC ? BK + 4 : BN + 8;
+  constexpr int A_FL = (A_KC ? BM : BK) * A_LD, B_FL = (B_KC ? BN : BK) * B_LD, STG = A_FL + B_FL;
+  constexpr int A_SL = BM * BK / 4 / NT, B_SL = BN * BK / 4 / NT;  // float4 slots per thread
+  static_assert(BM * BK % (4 * NT) == 0 && BN * BK % (4 * NT) == 0 && BK % (8 * WK) == 0, "tile vs threads");
+  static_assert(EPI != EPI_GEGLU_FWD || NI % 2 == 0, "u and w columns in one wavefront");
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+
+  const int tid = threadIdx.x, lane = tid & 63, g2 = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave / (WM * WN), wmn = wave % (WM * WN), wm = wmn / WN, wn = wmn % WN;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+
+  // this slice's run of k-tiles (several segments are never sliced)
+  int nt = 0;
+  for (int s = 0; s < g.nseg; ++s) nt += (g.seg[s].K + BK - 1) / BK;
+  const int per = (nt + split_k - 1) / split_k;
+  const int t_begin = blockIdx.z * per, t_end = t_begin + per < nt ? t_begin + per : nt;
+
+  const int lda = g.seg[0].lda, ldb = g.seg[0].ldb;
+  F32Src sa[A_SL], sb[B_SL];
+#pragma unroll
+  for (int i = 0; i < A_SL; ++i) {
+    const int q = tid + i * NT;
+    if constexpr (A_KC) {
+      const int r = q / (BK / 4), k = (q % (BK / 4)) * 4, m = m0 + r;
+      sa[i].off = (size_t)(m < g.M ? m : 0) * lda + k;
+      sa[i].row = k;
+      sa[i].nv = m < g.M;
+    } else {
+      const int k = q / (BM / 4), m = m0 + (q % (BM / 4)) * 4;
+      sa[i].off = (size_t)k * lda + m;
+      sa[i].row = k;
+      sa[i].nv = g.M - m < 0 ? 0 : g.M - m;
+    }
+  }
+  const float* b_src[B_SL];  // operand of the slot where columns come from several matrices (nsrc > 1)
+#pragma unroll
+  for (int i = 0; i < B_SL; ++i) {
+    const int q = tid + i * NT;
+    b_src[i] = nullptr;
+    if constexpr (B_KC) {
+      const int r = q / (BK / 4), k = (q % (BK / 4)) * 4, n = n0 + r;
+      sb[i].off = (size_t)(n < g.N ? n : 0) * ldb + k;
+      sb[i].row = k;
+      sb[i].nv = n < g.N;
+    } else {
+      const int k = q / (BN / 4), c = (q % (BN / 4)) * 4;
+      int n = n0 + c, lim = g.N;
+      if constexpr (EPI == EPI_GEGLU_FWD) {  // packed columns: 32 of wi0, 32 of wi1, ...
+        b_src[i] = (const float*)(c & 32 ? g.seg[1].B : g.seg[0].B);
+        n = (n0 >> 1) + ((c >> 6) << 5) + (c & 31);
+        lim = g.N >> 1;
+      } else if (g.nsrc > 1) {  // N = nsrc matrices of nsrc_cols columns side by side (a tile may straddle two)
+        int s = n / g.nsrc_cols;
+        s = s < g.nsrc ? s : g.nsrc - 1;
+        b_src[i] = (const float*)g.seg[s].B;
+        n -= s * g.nsrc_cols;
+        lim = g.nsrc_cols;
+      }
+      sb[i].off = (size_t)k * ldb + n;
+      sb[i].row = k;
+      sb[i].nv = lim - n < 0 ? 0 : lim - n;
+    }
+  }
+
+  f32x4 ra[A_SL], rb[B_SL];
+  int seg = 0, kt = t_begin;  // tile kt of segment seg comes next
+  int seg_nt = (g.seg[0].K + BK - 1) / BK;
+  auto fetch = [&]() __attribute__((always_inline)) {
+    while (kt >= seg_nt) {  // next segment
+      kt -= seg_nt;
+      ++seg;
+      seg_nt = (g.seg[seg].K + BK - 1) / BK;
+    }
+    const int k0 = kt * BK, left = g.seg[seg].K - k0;
+    const float* A = (const float*)g.seg[seg].A;
+    const float* B = (const float*)g.seg[seg].B;
+    const size_t oa = A_KC ? (size_t)k0 : (size_t)k0 * lda, ob = B_KC ? (size_t)k0 : (size_t)k0 * ldb;
+#pragma unroll
+    for (int i = 0; i < A_SL; ++i) {
+      const int nv = A_KC ? (sa[i].nv ? left - sa[i].row : 0) : (sa[i].row < left ? sa[i].nv : 0);
+      ra[i] = ld4(A + sa[i].off + oa, nv, vec_a != 0);
+    }
+#pragma unroll
+    for (int i = 0; i < B_SL; ++i) {
+      const int nv = B_KC ? (sb[i].nv ? left - sb[i].row : 0) : (sb[i].row < left ? sb[i].nv : 0);
+      rb[i] = ld4((b_src[i] ? b_src[i] : B) + sb[i].off + ob, nv, vec_b != 0);
+    }
+    ++kt;
+  };
+  auto put = [&](int st) __attribute__((always_inline)) {
+    float* pa = sm + st * STG;
+    float* pb = pa + A_FL;
+#pragma unroll
+    for (int i = 0; i < A_SL; ++i) {
+      const int q = tid + i * NT;
+      constexpr int W = (A_KC ? BK : BM) / 4;
+      *reinterpret_cast<f32x4*>(pa + (q / W) * A_LD + (q % W) * 4) = ra[i];
+    }
+#pragma unroll
+    for (int i = 0; i < B_SL; ++i) {
+      const int q = tid + i * NT;
+      constexpr int W = (B_KC ? BK : BN) / 4;
+      *reinterpret_cast<f32x4*>(pb + (q / W) * B_LD + (q % W) * 4) = rb[i];
+    }
+  };
+
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  auto compute = [&](int st) __attribute__((always_inline)) {
+    const float* pa = sm + st * STG;
+    const float* pb = pa + A_FL;
+#pragma unroll
+    for (int s = 0; s < BK / WK / 8; ++s) {
+      const int kb = wk * (BK / WK) + s * 8 + g2 * 4;
+      f32x4 fa[MI], fb[NI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int m = wm * TMW + i * 32 + l32;
+        if constexpr (A_KC) fa[i] = *reinterpret_cast<const f32x4*>(pa + m * A_LD + kb);
+        else
+#pragma unroll
+          for (int q = 0; q < 4; ++q) fa[i][q] = pa[(kb + q) * A_LD + m];
+      }
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const int n = wn * TNW + j * 32 + l32;
+        if constexpr (B_KC) fb[j] = *reinterpret_cast<const f32x4*>(pb + n * B_LD + kb);
+        else
+#pragma unroll
+          for (int q = 0; q < 4; ++q) fb[j][q] = pb[(kb + q) * B_LD + n];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+    }
+  };
+
+  // Two stages: tile t+1 travels through registers while tile t is multiplied; its stage was last read at tile t-1,
+  // before the barrier that ended it.
+  if (t_begin < t_end) {
+    fetch();
+    put(0);
+    __syncthreads();
+    for (int t = t_begin; t < t_end; ++t) {
+      const int cur = (t - t_begin) & 1;
+      if (t + 1 < t_end) fetch();
+      compute(cur);
+      if (t + 1 < t_end) put(cur ^ 1);
+      __syncthreads();
+    }
+  }
+  if constexpr (WK > 1) {  // sums of the WK shares, in order, in the wavefronts of share 0
+    constexpr int PW = MI * NI * 16 * 64;  // floats per wavefront
+    if (wk > 0) {
+      float* d = sm + ((wk - 1) * WM * WN + wmn) * PW + lane;
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) d[((i * NI + j) * 16 + r) * 64] = acc[i][j][r];
+    }
+    __syncthreads();
+    if (wk > 0) return;
+#pragma unroll
+    for (int w = 1; w < WK; ++w) {
+      const float* d = sm + ((w - 1) * WM * WN + wmn) * PW + lane;
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] += d[((i * NI + j) * 16 + r) * 64];
+    }
+  }
+
+  // ---- epilogue: register r of a 32x32 tile is row (r/4)*8 + half*4 + r%4, column lane%32: a wavefront writes
+  // 128-byte runs of two rows
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + wm * TMW + i * 32 + ((r >> 2) << 3) + (g2 << 2) + (r & 3);
+      if (m >= g.M) continue;
+      const uint32_t k1 = e.drop.on ? drop_row_key(e.drop, (uint32_t)m) : 0u;
+      if constexpr (EPI == EPI_GEGLU_FWD) {
+#pragma unroll
+        for (int j = 0; j < NI; j += 2) {
+          const int f = ((n0 + wn * TNW + j * 32) >> 1) + l32;
+          if (f >= (g.N >> 1)) continue;
+          float gl, dgl;
+          gelu_both(e.act, acc[i][j][r], gl, dgl);
+          const float w = acc[i][j + 1][r];
+          const float mk = e.drop.on ? drop_mult(e.drop, k1, (uint32_t)f) : 1.f;
+          const size_t o = (size_t)m * e.ld0 + f;
+          ((float*)e.out0)[o] = w * dgl * mk;
+          ((float*)e.out1)[o] = gl * mk;
+          ((float*)e.out2)[o] = gl * w * mk;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const int n = n0 + wn * TNW + j * 32 + l32;
+          if (n >= g.N) continue;
+          const float v = acc[i][j][r];
+          const size_t o = (size_t)m * e.ld0 + n;
+          if constexpr (EPI == EPI_STORE) {
+            const float mk = e.drop.on ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
+            ((float*)e.out0)[o] = (e.act == ACT_RELU ? fmaxf(v, 0.f) : v) * mk;
+          } else if constexpr (EPI == EPI_RESID) {
+            const float a = ((const float*)e.aux0)[(size_t)m * (e.ld_aux ? e.ld_aux : e.ld0) + n];
+            const float sc = e.drop.on ? e.drop.scale : 1.f;
+            const float mk = e.drop.on && !e.aux_mask ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
+            ((float*)e.out0)[o] = e.aux_mask ? (a > 0.f ? v * sc : 0.f) : v * mk + a;
+          } else if constexpr (EPI == EPI_GEGLU_BWD) {
+            const size_t oa = (size_t)m * (e.ld_aux ? e.ld_aux : e.ld0) + n;
+            ((float*)e.out0)[o] = v * ((const float*)e.aux0)[oa];
+            ((float*)e.out1)[o] = v * ((const float*)e.aux1)[oa];
+          } else {  // EPI_SPLIT_F32
+            const int which = n / e.split_n;
+            float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2) + (size_t)m * e.ld0 + (n - which * e.split_n);
+            if (split_k > 1) unsafeAtomicAdd(dst, v);
+            else *dst = e.accumulate ? *dst + v : v;
+          }
+        }
+      }
+    }
+  }
+}
+
+template <int BM, int BN, int WM, int WN, int WK, int BK, bool A_KC, bool B_KC, int EPI>
+hipError_t launch_tile(const GemmDesc& g, const GemmEpi& e, int split_k, int va, int vb, hipStream_t st) {
+  constexpr int a_fl = A_KC ? BM * (BK + 4) : BK * (BM + 8), b_fl = B_KC ? BN * (BK + 4) : BK * (BN + 8);
+  constexpr int red = (WK - 1) * BM * BN;  // floats of the exchange between the k shares
+  constexpr int lds = (2 * (a_fl + b_fl) > red ? 2 * (a_fl + b_fl) : red) * 4;
+  auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, BK, A_KC, B_KC, EPI>;
+  if constexpr (lds > 65536) {
+    static std::atomic<bool> attr_set{false};  // once per instantiation; setting it twice is harmless
+    if (!attr_set.load(std::memory_order_relaxed)) {
+      hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (err != hipSuccess) return err;
+      attr_set.store(true, std::memory_order_relaxed);
+    }
+  }
+  dim3 grid(ceil_div(g.N, BN), ceil_div(g.M, BM), split_k);
+  kern<<<grid, WM * WN * WK * 64, lds, st>>>(g, e, split_k, va, vb);
+  return hipGetLastError();
+}
+
+template <bool A_KC, bool B_KC, int EPI>
+hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
+  // float4 loads: every row start of the operand on a 16-byte boundary
+  auto aligned = [](const void* p, int ld) { return ld % 4 == 0 && ((uintptr_t)p & 15) == 0; };
+  int va = 1, vb = 1;
+  const int nptr = g.nsrc > 1 ? g.nsrc : g.nseg;
+  for (int s = 0; s < nptr; ++s) vb &= aligned(g.seg[s].B, g.seg[0].ldb) ? 1 : 0;
+  for (int s = 0; s < g.nseg; ++s) va &= aligned(g.seg[s].A, g.seg[0].lda) ? 1 : 0;
+  if (g.nsrc > 1 && g.nsrc_cols % 4 != 0) return hipErrorInvalidValue;  // a float4 slot has one source (gemm_f32_supported)
+  const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128);
+  const int64_t t64 = (int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64);
+  int64_t K = 0;
+  for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
+  if constexpr (EPI == EPI_SPLIT_F32) {
+    // Weight gradients: few tiles, long k.  Slices of at least 256 k until two workgroups per compute unit are busy;
+    // they meet in float32 atomics on the cleared output.  In the reproducible mode (e.ordered) there is one slice
+    // and the small tiles spread the work instead.
+    if (e.accumulate && !e.ordered && K >= 512) {
+      const bool big = t128 * (K / 256) >= 256;
+      const int64_t t = big ? t128 : t64;
+      const int sk = (int)std::max<int64_t>(1, std::min<int64_t>(K / 256, (512 + t - 1) / t));
+      if (big) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI>(g, e, sk, va, vb, st);
+      return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI>(g, e, sk, va, vb, st);
+    }
+  }
+  if (t128 >= 192) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI>(g, e, 1, va, vb, st);
+  if (t64 >= 128) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI>(g, e, 1, va, vb, st);
+  return launch_tile<32, 64, 1, 1, 4, 64, A_KC, B_KC, EPI>(g, e, 1, va, vb, st);
+}
+
+}  // namespace
+
+bool gemm_f32_supported(const GemmDesc& g, const GemmEpi& e) {
+  if (g.in_type != IN_F32 || g.nseg < 1 || g.nseg > 3 || g.ngroups > 1 || e.out_type != IN_F32) return false;
+  if (g.M < 1 || g.N < 1) return false;
+  for (int s = 0; s < g.nseg; ++s)
+    if (g.seg[s].K < 1 || g.seg[s].lda != g.seg[0].lda || g.seg[s].ldb != g.seg[0].ldb) return false;
+  if (ceil_div(g.M, 32) > 65535) return false;  // grid.y
+  if (g.nsrc > 1 && (g.nseg != 1 || g.nsrc > 3 || g.b_kc || g.nsrc_cols % 4 != 0 || g.nsrc * g.nsrc_cols != g.N)) return false;
+  switch (e.kind) {
+    case EPI_STORE: return g.a_kc != 0;
+    case EPI_RESID: return g.a_kc != 0 && e.aux_type == IN_F32;
+    case EPI_GEGLU_FWD: return g.a_kc != 0 && !g.b_kc && g.nsrc == 2 && g.nsrc_cols % 32 == 0;
+    case EPI_GEGLU_BWD: return g.a_kc != 0 && g.b_kc != 0 && e.aux_type == IN_F32;
+    case EPI_SPLIT_F32: return !g.a_kc && !g.b_kc && g.nseg == 1;
+    default: return false;
+  }
+}
+
+hipError_t launch_gemm_f32(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
+  switch (e.kind) {
+    case EPI_STORE:
+      return g.b_kc ? launch_kind<true, true, EPI_STORE>(g, e, st) : launch_kind<true, false, EPI_STORE>(g, e, st);
+    case EPI_RESID:
+      return g.b_kc ? launch_kind<true, true, EPI_RESID>(g, e, st) : launch_kind<true, false, EPI_RESID>(g, e, st);
+    case EPI_GEGLU_FWD: return launch_kind<true, false, EPI_GEGLU_FWD>(g, e, st);
+    case EPI_GEGLU_BWD: return launch_kind<true, true, EPI_GEGLU_BWD>(g, e, st);
+    case EPI_SPLIT_F32: return launch_kind<false, false, EPI_SPLIT_F32>(g, e, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace t5mi

@@ -44,7 +44,7 @@ enum EpiKind {
   EPI_RESID = 1,      // out0[m*ld0 + n] = acc + aux0[m*ld0 + n]  (aux0 of aux_type)
   // Gated GELU, a = gelu(u) * w.  The forward saves the two factors the backward needs instead of
   // u and w themselves: gp = w * gelu'(u) and gl = gelu(u), so that du = da * gp and dw = da * gl.
-  EPI_GEGLU_FWD = 2,  // MFMA path only: B rows interleave wi0/wi1 in groups of 32; out0 = gp, out1 = gl, out2 = a
+  EPI_GEGLU_FWD = 2,  // MFMA paths only: B rows (bf16) interleave wi0/wi1 in groups of 32; out0 = gp, out1 = gl, out2 = a
   EPI_GEGLU_BWD = 3,  // acc = da; reads gp = aux0, gl = aux1; out0 = du, out1 = dw   (all ld0)
   EPI_SPLIT_F32 = 4   // float32 out; column n goes to outs[n / split_n][m*ld0 + n % split_n]; += if accumulate
 };
@@ -65,6 +65,7 @@ struct GemmEpi {
   int aux_type;
   int split_n;
   int accumulate;
+  int ordered;   // EPI_SPLIT_F32, float32 kernel: no k-slices that meet in atomics (reproducible mode)
   int act;       // EPI_STORE: ACT_RELU stores max(acc, 0); EPI_GEGLU_FWD: ACT_GELU_TANH or ACT_GELU_ERF
   int aux_mask;  // EPI_RESID: != 0 stores acc where aux0 > 0 and 0 elsewhere instead of acc + aux0
   // Dropout of the GEMM's result (row = m, column = n; for EPI_GEGLU_FWD column = hidden unit), when drop.on:
@@ -83,6 +84,10 @@ struct GemmDesc {
   // seg[0].A / .B and the epilogue's outputs for the workgroups of that problem.  ngroups <= 1: one problem.
   const void* const* groups;
   int ngroups;
+  // nsrc > 1 (float32 MFMA kernel, one segment, b_kc == 0): the N columns of B are nsrc matrices of nsrc_cols columns
+  // (seg[0..nsrc-1].B, all with seg[0].ldb) side by side; for EPI_GEGLU_FWD wi0 and wi1, whose columns the kernel
+  // interleaves by itself.
+  int nsrc, nsrc_cols;
 };
 constexpr int GEMM_GROUP_PTRS = 5;
 // dst[i] = ptrs[i] for i < n: builds such a table (or any other) in device memory from host values, by kernel
@@ -90,7 +95,10 @@ constexpr int GEMM_GROUP_PTRS = 5;
 hipError_t launch_fill_ptrs(const void* const* ptrs, int n, const void** dst, hipStream_t st);
 // Simple LDS-tiled FMA kernel: any shape, float32 or bf16 inputs.  Reference-grade speed.
 hipError_t launch_gemm_simple(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
-// bf16 MFMA kernel.  Requires in_type == IN_BF16, every K % 64 == 0, lda/ldb % 8 == 0, N % 64 == 0
+// float32 MFMA kernel: any shape; gemm_f32_supported() checks orientation and epilogue.
+bool gemm_f32_supported(const GemmDesc& g, const GemmEpi& e);
+hipError_t launch_gemm_f32(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+// bf16 MFMA kernel.  Requires in_type == IN_BF16, every K % 64 == 0 (k-contiguous operands), lda/ldb % 8 == 0, N % 64 == 0
 // and 16-byte aligned pointers; gemm_mfma_supported() checks this.
 bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e);
 hipError_t launch_gemm_mfma(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
@@ -167,6 +175,11 @@ hipError_t launch_attn_fwd_simple(const AttnIO& io, int type, const float* diag,
 hipError_t launch_attn_bwd_simple(const AttnIO& io, const void* c, const void* dc, int type,
                                   const float* diag, const float* lse, float* dvec, float* ddiag,
                                   const AttnDims& a, int zero_ddiag, hipStream_t st);
+// The same in float32 on the matrix units: heads of up to 128 channels, up to 4096 queries.
+bool attn_f32_supported(const AttnDims& a);
+hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st);
+hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
+                               float* dvec, float* ddiag, const AttnDims& a, int zero_ddiag, hipStream_t st);
 bool attn_mfma_supported(const AttnDims& a);
 hipError_t launch_attn_fwd_mfma(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a,
                                 hipStream_t st);

@@ -306,6 +306,7 @@ void head_wgrad_gemm(const Head& h, const Dims& D, int tc, const void* nf_c, Gem
     e = epi(EPI_SPLIT_F32, h.d_logits_w, h.V, IN_F32);
   }
   e.accumulate = 1;
+  e.ordered = D.det;
   e.aux0 = h.wg_partials;  // null unless the reproducible mode carved it
 }
 

@@ -1,0 +1,58 @@
+"""float32 block on the float32 matrix kernels, at the sizes where they change: the three GEMM tiles (by number of
+output tiles), k-slices of the weight gradients, ragged edges and unaligned rows (element loads), fused and unfused
+gated GELU, one or two attention wavefronts, heads of 5 to 136 channels (the last on the general kernels), causal and
+dropout masks, one to many encoder positions."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import synth_inputs as SI
+from oracle import t5_oracle as O
+from parity_util import TOL_F32, make_case, make_decoder_case, rel_err, run_block_gpu, run_decoder_block_gpu
+
+pytestmark = pytest.mark.gpu
+
+C = SI.BlockConfig("f32_matrix", 70, 2, 32, 64, 4, 16, 256, dtype="f32", attn_scale=0.25)
+CASES = [replace(C, batch=1, seq=1),                                                      # one token
+         replace(C, batch=1, seq=31, d_model=65, n_heads=3, d_kv=5, d_ff=33),              # nothing aligned
+         replace(C, batch=2, seq=33, d_model=68, n_heads=2, d_kv=36, d_ff=100, causal=True),
+         replace(C, batch=9, seq=65, d_model=96, n_heads=2, d_kv=64, d_ff=160, causal=True, dropout_rate=0.125,
+                 dropout_seed=77),                                                         # k-slices (585 tokens)
+         replace(C, batch=3, seq=200, d_model=64, n_heads=1, d_kv=128, d_ff=96, mlp="geglu_erf"),
+         replace(C, batch=2, seq=40, d_model=64, n_heads=1, d_kv=136, d_ff=64),            # general attention kernels
+         replace(C, batch=21, seq=129, d_model=520, n_heads=4, d_kv=32, d_ff=1056, mlp="relu"),   # 128 x 128 tiles
+         replace(C, batch=13, seq=100, d_model=256, n_heads=4, d_kv=64, d_ff=512, deterministic=True)]
+
+
+def _check(pairs):
+    for name, got, want in pairs:
+        if name in ("wq", "wk") and not np.any(np.abs(want) > 1e-12):  # one key: no gradient through the softmax
+            assert np.abs(got).max() < 1e-5
+            continue
+        assert rel_err(got, want)[0] <= TOL_F32[0], (name, rel_err(got, want))
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: f"{c.batch}x{c.seq}_d{c.d_model}_k{c.d_kv}_f{c.d_ff}")
+def test_block_f32_matrix(cfg):
+    if cfg.dropout_rate:
+        cfg = replace(cfg, dropout_rate=float(np.float32(cfg.dropout_rate)))
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    if cfg.seq == 1:
+        g = {k: v for k, v in g.items() if k not in ("rel_table",)}
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    _check([("y", gy, y), ("dx", gdx, dx)] + [(n, gg[n], g[n]) for n in g])
+
+
+@pytest.mark.parametrize("seq,enc_seq", [(1, 2), (33, 32), (32, 97), (130, 31)])
+def test_decoder_f32_matrix(seq, enc_seq):
+    cfg = replace(C, batch=2, seq=seq, enc_seq=enc_seq, causal=seq > 1, d_model=72, d_kv=24, name="f32_matrix_dec")
+    w, x, enc, dy = make_decoder_case(cfg)
+    y, saved = O.decoder_block_fwd(cfg, x, enc, w)
+    dx, denc, g = O.decoder_block_bwd(cfg, dy, w, saved)
+    if seq == 1:
+        g = {k: v for k, v in g.items() if k not in ("rel_table",)}
+    gy, gdx, gdenc, gg = run_decoder_block_gpu(cfg, w, x, enc, dy)
+    _check([("y", gy, y), ("dx", gdx, dx), ("denc", gdenc, denc)] + [(n, gg[n], g[n]) for n in g])
