@@ -1,0 +1,446 @@
+// float32 attention on the matrix units (v_mfma_f32_32x32x2_f32), forward and backward, with the relative-position
+// bias, causal masking and dropout of the probabilities, any lengths, heads of up to 128 channels.  The scores never
+// leave registers.
+//
+// A wavefront owns 32 queries (forward, dq: lane = query, S^T = K Q^T) or 32 keys (dk/dv: lane = key, S = Q K^T).  In
+// the 32x32 result layout register r of lane half g is row 8*(r/4) + 4*g + r%4, and one float32 MFMA contracts two
+// values, one from each lane half: register r of the probabilities is therefore, as it stands, the operand of an MFMA
+// that contracts rows 8*(r/4) + r%4 and + 4, and the other operand is one column read per lane from the tile in LDS.
+//
+// Bound: the float32 matrix rate (157 TFLOP/s nominal): 32 keys x 32 queries of 64 channels are 64 MFMAs of 64 cycles in
+// the forward against some 200 vector instructions.  Tiles of 32 rows travel through registers while the previous
+// tile is used; rows past the end and channels past d_kv are zeros, so no shape needs another path.
+//
+// The bias gradient (dq) adds each ds element to its diagonal in LDS and one global atomic per diagonal and workgroup
+// follows; one global atomic per element took longer than everything else.
+#include "kernels.h"
+
+namespace t5mi {
+
+namespace {
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+
+// A tile of 32 rows x DKP channels on its way from global memory to LDS (row stride LD floats).
+template <int DKP, int NT>
+struct Tile32 {
+  static constexpr int N = 32 * DKP / 4 / NT, W = DKP / 4;
+  f32x4 v[N];
+  __device__ __forceinline__ void load(const float* src, size_t ld, int rows, int dk, bool vec, int tid) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int q = tid + i * NT, row = q / W, c = (q % W) * 4;
+      const float* p = src + (size_t)row * ld + c;
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+      if (row < rows) {
+        if (vec) {
+          if (c < dk) x = *reinterpret_cast<const f32x4*>(p);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (c + e < dk) x[e] = p[e];
+        }
+      }
+      v[i] = x;
+    }
+  }
+  template <int LD>
+  __device__ __forceinline__ void put(float* dst, int tid) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int q = tid + i * NT;
+      *reinterpret_cast<f32x4*>(dst + (q / W) * LD + (q % W) * 4) = v[i];
+    }
+  }
+};
+// One row's channels as MFMA operands: group s of 8 channels gives this lane half channels 8s + 4g .. + 3.
+template <int DKP>
+__device__ __forceinline__ void load_row(f32x4 (&f)[DKP / 8], const float* row, int dk, bool vec, int g) {
+#pragma unroll
+  for (int s = 0; s < DKP / 8; ++s) {
+    const int c = s * 8 + g * 4;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (vec) {
+      if (c < dk) x = *reinterpret_cast<const f32x4*>(row + c);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c + e < dk) x[e] = row[c + e];
+    }
+    f[s] = x;
+  }
+}
+// acc += T F^T for the 32 rows of a tile (MFMA rows) and the rows held as operands (MFMA columns)
+template <int DKP, int LD>
+__device__ __forceinline__ void mul_rows(f32x16& acc, const float* tile, const f32x4 (&f)[DKP / 8], int lane) {
+  const float* p = tile + (lane & 31) * LD + (lane >> 5) * 4;
+#pragma unroll
+  for (int s = 0; s < DKP / 8; ++s) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(p + s * 8);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], f[s][e], acc, 0, 0, 0);
+  }
+}
+// acc[ct] += T^T P for a tile (channels become MFMA rows, its 32 rows are contracted) and P in the result layout
+template <int CT, int LD>
+__device__ __forceinline__ void mul_cols(f32x16 (&acc)[CT], const float* tile, const f32x16& p, int lane) {
+  const float* t = tile + (lane >> 5) * 4 * LD + (lane & 31);
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      acc[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(t[(((r >> 2) << 3) + (r & 3)) * LD + ct * 32], p[r], acc[ct], 0, 0, 0);
+}
+__device__ __forceinline__ void clear(f32x16& a) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) a[r] = 0.f;
+}
+// Result columns of a wavefront (one row of the output per lane): channels ct*32 + 8*(r/4) + 4*g + r%4.
+template <int CT>
+__device__ __forceinline__ void store_cols(float* row, const f32x16 (&acc)[CT], float f, int dk, bool vec, int g) {
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      const int c = ct * 32 + rq * 8 + g * 4;
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = acc[ct][rq * 4 + e] * f;
+      if (vec) {
+        if (c < dk) *reinterpret_cast<f32x4*>(row + c) = o;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c + e < dk) row[c + e] = o[e];
+      }
+    }
+}
+
+// ---- forward.  One workgroup per (b, h, NW*32 queries).
+template <int DKP, int NW>
+__global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag,
+                                                               float* __restrict__ c, float* __restrict__ lse, AttnDims a,
+                                                               int n_tiles, int vec) {
+  constexpr int CT = DKP / 32, KL = DKP + 4, VL = DKP + 8, NT = NW * 64;
+  __shared__ __attribute__((aligned(16))) float Kt[32 * KL];
+  __shared__ __attribute__((aligned(16))) float Vt[32 * VL];
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, wave = tid >> 6;
+  const int S = a.S, Sk = a.Sk, I = a.H * a.dk;
+  int qt = blockIdx.x % n_tiles;
+  const int bh = blockIdx.x / n_tiles, h = bh % a.H, b = bh / a.H;
+  if (a.causal) qt = n_tiles - 1 - qt;  // long rows first
+  const int i0 = qt * NW * 32, iw = i0 + wave * 32, i = iw + (lane & 31), il = i < S ? i : S - 1;
+  const float* kb = (const float*)io.k + (size_t)b * Sk * io.ldkv + h * a.dk;
+  const float* vb = (const float*)io.v + (size_t)b * Sk * io.ldkv + h * a.dk;
+  const float* dg = a.bias ? diag + (size_t)h * (2 * S - 1) + (S - 1) - il : nullptr;  // dg[j] = bias(j - i)
+  f32x4 q[DKP / 8];
+  load_row<DKP>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, vec, g);
+  const float sc = a.scale * kLog2e;
+  uint32_t k1 = 0;
+  if (a.drop.on) k1 = drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + il));
+  f32x16 o[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) clear(o[ct]);
+  float m = -INFINITY, l = 0.f;
+  const int keys = a.causal ? (i0 + NW * 32 < S ? i0 + NW * 32 : S) : Sk;
+  const int my_keys = a.causal ? (iw + 32 < keys ? iw + 32 : keys) : Sk;  // keys this wavefront's queries see
+  Tile32<DKP, NT> tk, tv;
+  tk.load(kb, io.ldkv, Sk, a.dk, vec, tid);
+  tv.load(vb, io.ldkv, Sk, a.dk, vec, tid);
+  for (int j0 = 0; j0 < keys; j0 += 32) {
+    __syncthreads();  // the tile before this one has been used
+    tk.template put<KL>(Kt, tid);
+    tv.template put<VL>(Vt, tid);
+    __syncthreads();
+    if (j0 + 32 < keys) {
+      tk.load(kb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
+      tv.load(vb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
+    }
+    if (j0 >= my_keys) continue;  // (uniform in the wavefront; the barriers are at the top of the loop)
+    float bias[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+      bias[r] = a.bias ? dg[j < Sk ? j : Sk - 1] * kLog2e : 0.f;
+    }
+    f32x16 s;
+    clear(s);
+    mul_rows<DKP, KL>(s, Kt, q, lane);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+      float x = fmaf(s[r], sc, bias[r]);
+      if ((a.causal && j > i) || j >= Sk) x = -INFINITY;
+      s[r] = x;
+      mx = fmaxf(mx, x);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - mn);  // key 0 is visible to every query: mn is finite
+    m = mn;
+    float ls = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+      const float p = __builtin_amdgcn_exp2f(s[r] - mn);
+      ls += p;  // the normaliser is that of the undropped probabilities
+      s[r] = a.drop.on ? (mix32(k1 ^ (uint32_t)j) >= a.drop.thr ? p : 0.f) : p;
+    }
+    l = l * alpha + ls;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
+    mul_cols<CT, VL>(o, Vt, s, lane);
+  }
+  l += __shfl_xor(l, 32, 64);
+  if (i < S) {
+    store_cols<CT>(c + ((size_t)b * S + i) * I + h * a.dk, o, (a.drop.on ? a.drop.scale : 1.f) / l, a.dk, vec, g);
+    if (g == 0) lse[((size_t)b * a.H + h) * S + i] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+  }
+}
+
+// ---- dq, dvec = rowsum(dO * O) and the per-diagonal bias gradient.  Ownership as in the forward.
+// Dynamic LDS: with bias, one float per diagonal the workgroup can touch (S + NW*32 - 1).
+template <int DKP, int NW>
+__global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, const float* __restrict__ o,
+                                                                  const float* __restrict__ dout,
+                                                                  const float* __restrict__ diag,
+                                                                  const float* __restrict__ lse, float* __restrict__ dvec,
+                                                                  float* __restrict__ ddiag, AttnDims a, int n_tiles, int vec) {
+  constexpr int CT = DKP / 32, LD = DKP + 4, NT = NW * 64;
+  __shared__ __attribute__((aligned(16))) float Kt[32 * LD];
+  __shared__ __attribute__((aligned(16))) float Vt[32 * LD];
+  extern __shared__ float win[];  // diagonal j - i sits at j - i + i0 + NW*32 - 1
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, wave = tid >> 6;
+  const int S = a.S, Sk = a.Sk, I = a.H * a.dk;
+  int qt = blockIdx.x % n_tiles;
+  const int bh = blockIdx.x / n_tiles, h = bh % a.H, b = bh / a.H;
+  if (a.causal) qt = n_tiles - 1 - qt;
+  const int i0 = qt * NW * 32, iw = i0 + wave * 32, i = iw + (lane & 31), il = i < S ? i : S - 1;
+  const float* kb = (const float*)io.k + (size_t)b * Sk * io.ldkv + h * a.dk;
+  const float* vb = (const float*)io.v + (size_t)b * Sk * io.ldkv + h * a.dk;
+  const float* dg = a.bias ? diag + (size_t)h * (2 * S - 1) + (S - 1) - il : nullptr;
+  const int nwin = S + NW * 32 - 1;
+  if (a.bias)
+    for (int t = tid; t < nwin; t += NT) win[t] = 0.f;
+  const size_t srow = ((size_t)b * a.H + h) * S + il;
+  f32x4 q[DKP / 8], d[DKP / 8];
+  float dsum = 0.f;
+  {
+    f32x4 x[DKP / 8];
+    load_row<DKP>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, vec, g);
+    load_row<DKP>(d, dout + ((size_t)b * S + il) * I + h * a.dk, a.dk, vec, g);
+    load_row<DKP>(x, o + ((size_t)b * S + il) * I + h * a.dk, a.dk, vec, g);
+#pragma unroll
+    for (int s = 0; s < DKP / 8; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dsum = fmaf(d[s][e], x[s][e], dsum);
+  }
+  dsum += __shfl_xor(dsum, 32, 64);
+  if (g == 0 && i < S) dvec[srow] = dsum;
+  const float nl2 = -lse[srow] * kLog2e, sc = a.scale * kLog2e;
+  uint32_t k1 = 0;
+  if (a.drop.on) k1 = drop_row_key(a.drop, (uint32_t)srow);
+  f32x16 dq[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) clear(dq[ct]);
+  const int keys = a.causal ? (i0 + NW * 32 < S ? i0 + NW * 32 : S) : Sk;
+  const int my_keys = a.causal ? (iw + 32 < keys ? iw + 32 : keys) : Sk;
+  Tile32<DKP, NT> tk, tv;
+  tk.load(kb, io.ldkv, Sk, a.dk, vec, tid);
+  tv.load(vb, io.ldkv, Sk, a.dk, vec, tid);
+  for (int j0 = 0; j0 < keys; j0 += 32) {
+    __syncthreads();
+    tk.template put<LD>(Kt, tid);
+    tv.template put<LD>(Vt, tid);
+    __syncthreads();
+    if (j0 + 32 < keys) {
+      tk.load(kb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
+      tv.load(vb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
+    }
+    if (j0 >= my_keys) continue;
+    float bias[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+      bias[r] = a.bias ? fmaf(dg[j < Sk ? j : Sk - 1], kLog2e, nl2) : nl2;
+    }
+    f32x16 s, dp;
+    clear(s);
+    clear(dp);
+    mul_rows<DKP, LD>(s, Kt, q, lane);
+    mul_rows<DKP, LD>(dp, Vt, d, lane);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+      const float p = __builtin_amdgcn_exp2f(fmaf(s[r], sc, bias[r]));
+      float x = dp[r];
+      if (a.drop.on) x = mix32(k1 ^ (uint32_t)j) >= a.drop.thr ? x * a.drop.scale : 0.f;
+      const float ds = p * (x - dsum);
+      const bool ok = i < S && j < Sk && !(a.causal && j > i);
+      s[r] = ok ? ds : 0.f;
+      if (a.bias && ok) atomicAdd(&win[j - i + i0 + NW * 32 - 1], ds);
+    }
+    mul_cols<CT, LD>(dq, Kt, s, lane);
+  }
+  if (i < S) store_cols<CT>((float*)io.dq + ((size_t)b * S + i) * io.lddq + h * a.dk, dq, a.scale, a.dk, vec, g);
+  if (a.bias) {
+    __syncthreads();
+    float* dd = ddiag + (size_t)h * (2 * S - 1) + (S - 1) - (i0 + NW * 32 - 1);
+    for (int t = tid; t < nwin; t += NT) {
+      const float x = win[t];
+      // (slots of queries past the end lie below the first diagonal; they are zero)
+      if (t - (i0 + NW * 32 - 1) > -S && x != 0.f) unsafeAtomicAdd(dd + t, x);
+    }
+  }
+}
+
+// ---- dk and dv.  One workgroup per (b, h, NW*32 keys); lane = key.
+template <int DKP, int NW>
+__global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout,
+                                                                   const float* __restrict__ diag,
+                                                                   const float* __restrict__ lse,
+                                                                   const float* __restrict__ dvec, AttnDims a, int n_tiles,
+                                                                   int vec) {
+  constexpr int CT = DKP / 32, LD = DKP + 4, NT = NW * 64;
+  __shared__ __attribute__((aligned(16))) float Qt[32 * LD];
+  __shared__ __attribute__((aligned(16))) float Dt[32 * LD];
+  __shared__ float row_l[32], row_d[32];     // -lse * log2(e) and dvec of the tile's queries
+  __shared__ uint32_t row_k[32];             // their dropout row keys
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, wave = tid >> 6;
+  const int S = a.S, Sk = a.Sk, I = a.H * a.dk;
+  const int kt = blockIdx.x % n_tiles, bh = blockIdx.x / n_tiles, h = bh % a.H, b = bh / a.H;
+  const int jw = kt * NW * 32 + wave * 32, j = jw + (lane & 31), jl = j < Sk ? j : Sk - 1;
+  const float* qb = (const float*)io.q + (size_t)b * S * io.ldq + h * a.dk;
+  const float* db = dout + (size_t)b * S * I + h * a.dk;
+  const float* dg = a.bias ? diag + (size_t)h * (2 * S - 1) + (S - 1) + jl : nullptr;  // dg[-i] = bias(j - i)
+  const size_t srow = ((size_t)b * a.H + h) * S;
+  f32x4 k[DKP / 8], v[DKP / 8];
+  load_row<DKP>(k, (const float*)io.k + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, vec, g);
+  load_row<DKP>(v, (const float*)io.v + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, vec, g);
+  const float sc = a.scale * kLog2e;
+  f32x16 dk[CT], dv[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) { clear(dk[ct]); clear(dv[ct]); }
+  const int ibeg = a.causal ? kt * NW * 32 : 0;  // a multiple of 32
+  Tile32<DKP, NT> tq, td;
+  tq.load(qb + (size_t)ibeg * io.ldq, io.ldq, S - ibeg, a.dk, vec, tid);
+  td.load(db + (size_t)ibeg * I, I, S - ibeg, a.dk, vec, tid);
+  for (int i0 = ibeg; i0 < S; i0 += 32) {
+    __syncthreads();
+    tq.template put<LD>(Qt, tid);
+    td.template put<LD>(Dt, tid);
+    if (tid < 32) {
+      const int i = i0 + tid < S ? i0 + tid : S - 1;
+      row_l[tid] = -lse[srow + i] * kLog2e;
+      row_d[tid] = dvec[srow + i];
+      if (a.drop.on) row_k[tid] = drop_row_key(a.drop, (uint32_t)(srow + i));
+    }
+    __syncthreads();
+    if (i0 + 32 < S) {
+      tq.load(qb + (size_t)(i0 + 32) * io.ldq, io.ldq, S - i0 - 32, a.dk, vec, tid);
+      td.load(db + (size_t)(i0 + 32) * I, I, S - i0 - 32, a.dk, vec, tid);
+    }
+    if (a.causal && i0 + 31 < jw) continue;  // every query of the tile comes before this wavefront's keys
+    float bias[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int il = ((r >> 2) << 3) + (g << 2) + (r & 3), i = i0 + il;
+      bias[r] = a.bias ? fmaf(dg[-(i < S ? i : S - 1)], kLog2e, row_l[il]) : row_l[il];
+    }
+    f32x16 s, dp;
+    clear(s);
+    clear(dp);
+    mul_rows<DKP, LD>(s, Qt, k, lane);
+    mul_rows<DKP, LD>(dp, Dt, v, lane);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int il = ((r >> 2) << 3) + (g << 2) + (r & 3), i = i0 + il;
+      const bool ok = i < S && j < Sk && !(a.causal && j > i);
+      const float p = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], sc, bias[r])) : 0.f;
+      float mk = 1.f;
+      if (a.drop.on) mk = mix32(row_k[il] ^ (uint32_t)j) >= a.drop.thr ? a.drop.scale : 0.f;
+      s[r] = p * mk;
+      dp[r] = p * (dp[r] * mk - row_d[il]);
+    }
+    mul_cols<CT, LD>(dv, Dt, s, lane);
+    mul_cols<CT, LD>(dk, Qt, dp, lane);
+  }
+  if (j < Sk) {
+    store_cols<CT>((float*)io.dk + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dk, a.scale, a.dk, vec, g);
+    store_cols<CT>((float*)io.dv + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dv, 1.f, a.dk, vec, g);
+  }
+}
+
+__global__ void clear_f32_kernel(float* p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0.f;
+}
+
+bool vec_ok(const AttnIO& io, const AttnDims& a, const void* c, const void* dc) {
+  const uintptr_t all = (uintptr_t)io.q | (uintptr_t)io.k | (uintptr_t)io.v | (uintptr_t)io.dq | (uintptr_t)io.dk |
+                        (uintptr_t)io.dv | (uintptr_t)c | (uintptr_t)dc;
+  return (all & 15) == 0 && a.dk % 4 == 0 && io.ldq % 4 == 0 && io.ldkv % 4 == 0 && io.lddq % 4 == 0 && io.lddkv % 4 == 0;
+}
+
+// Wavefronts per workgroup: two share each K/V (or Q/dO) tile; one where a sequence has no more than 32 rows.
+template <int DKP>
+hipError_t launch_fwd(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
+  const int vec = vec_ok(io, a, c, nullptr);
+  if (a.S <= 32) {
+    attn_fwd_f32_kernel<DKP, 1><<<a.B * a.H, 64, 0, st>>>(io, diag, c, lse, a, 1, vec);
+  } else {
+    const int nt = ceil_div(a.S, 64);
+    attn_fwd_f32_kernel<DKP, 2><<<nt * a.B * a.H, 128, 0, st>>>(io, diag, c, lse, a, nt, vec);
+  }
+  return hipGetLastError();
+}
+template <int DKP>
+hipError_t launch_bwd(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse, float* dvec,
+                      float* ddiag, const AttnDims& a, hipStream_t st) {
+  const int vec = vec_ok(io, a, c, dc);
+  if (a.S <= 32) {
+    attn_bwd_dq_f32_kernel<DKP, 1><<<a.B * a.H, 64, a.bias ? (a.S + 31) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec, ddiag,
+                                                                                      a, 1, vec);
+  } else {
+    const int nt = ceil_div(a.S, 64);
+    attn_bwd_dq_f32_kernel<DKP, 2><<<nt * a.B * a.H, 128, a.bias ? (a.S + 63) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec,
+                                                                                            ddiag, a, nt, vec);
+  }
+  if (a.Sk <= 32) {
+    attn_bwd_dkv_f32_kernel<DKP, 1><<<a.B * a.H, 64, 0, st>>>(io, dc, diag, lse, dvec, a, 1, vec);
+  } else {
+    const int nt = ceil_div(a.Sk, 64);
+    attn_bwd_dkv_f32_kernel<DKP, 2><<<nt * a.B * a.H, 128, 0, st>>>(io, dc, diag, lse, dvec, a, nt, vec);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool attn_f32_supported(const AttnDims& a) {
+  const int64_t tiles = ceil_div(a.S > a.Sk ? a.S : a.Sk, 64);
+  // static tiles (up to 34 KB) + the diagonals of a workgroup in 64 KB of LDS
+  return a.dk <= 128 && a.S <= 4096 && tiles * a.B * a.H < ((int64_t)1 << 31);
+}
+
+hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
+  if (a.dk <= 32) return launch_fwd<32>(io, diag, c, lse, a, st);
+  if (a.dk <= 64) return launch_fwd<64>(io, diag, c, lse, a, st);
+  return launch_fwd<128>(io, diag, c, lse, a, st);
+}
+
+hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
+                               float* dvec, float* ddiag, const AttnDims& a, int zero_ddiag, hipStream_t st) {
+  if (a.bias && zero_ddiag) {
+    const int64_t nd = (int64_t)a.H * (2 * a.S - 1);
+    clear_f32_kernel<<<ceil_div(nd, 256), 256, 0, st>>>(ddiag, nd);
+  }
+  if (a.dk <= 32) return launch_bwd<32>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+  if (a.dk <= 64) return launch_bwd<64>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+  return launch_bwd<128>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+}
+
+}  // namespace t5mi

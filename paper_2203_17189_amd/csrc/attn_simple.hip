@@ -175,6 +175,7 @@ __global__ void zero_diag_kernel(float* p, int64_t n) {
 
 hipError_t launch_attn_fwd_simple(const AttnIO& io, int type, const float* diag, void* c, float* lse,
                                   const AttnDims& a, hipStream_t st) {
+  if (type == IN_F32 && attn_f32_supported(a)) return launch_attn_fwd_f32(io, diag, (float*)c, lse, a, st);
   const int64_t rows = (int64_t)a.B * a.H * a.S;
   const int grid = ceil_div(rows, AW);
   const size_t lds = sizeof(float) * AW * a.Sk;
@@ -188,6 +189,8 @@ hipError_t launch_attn_fwd_simple(const AttnIO& io, int type, const float* diag,
 hipError_t launch_attn_bwd_simple(const AttnIO& io, const void* c, const void* dc, int type,
                                   const float* diag, const float* lse, float* dvec, float* ddiag,
                                   const AttnDims& a, int zero_ddiag, hipStream_t st) {
+  if (type == IN_F32 && attn_f32_supported(a))
+    return launch_attn_bwd_f32(io, (const float*)c, (const float*)dc, diag, lse, dvec, ddiag, a, zero_ddiag, st);
   const int grid_q = ceil_div((int64_t)a.B * a.H * a.S, AW);
   const int grid_k = ceil_div((int64_t)a.B * a.H * a.Sk, AW);
   if (a.bias && zero_ddiag) {
