@@ -22,51 +22,50 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// A tile of 32 rows x DKP channels on its way from global memory to LDS (row stride LD floats).
-template <int DKP, int NT>
+// A tile of 32 rows x DKP channels on its way from global memory to LDS (row stride LD floats).  Rows past the end
+// repeat the last one (their scores are masked), channels past d_kv become zeros on the way into LDS: with VEC the
+// loads carry no branch, around which the compiler would wait for them on the spot.
+template <int DKP, int NT, bool VEC>
 struct Tile32 {
   static constexpr int N = 32 * DKP / 4 / NT, W = DKP / 4;
   f32x4 v[N];
-  __device__ __forceinline__ void load(const float* src, size_t ld, int rows, int dk, bool vec, int tid) {
+  __device__ __forceinline__ void load(const float* src, size_t ld, int rows, int dk, int tid) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int q = tid + i * NT, row = q / W, c = (q % W) * 4;
-      const float* p = src + (size_t)row * ld + c;
-      f32x4 x = {0.f, 0.f, 0.f, 0.f};
-      if (row < rows) {
-        if (vec) {
-          if (c < dk) x = *reinterpret_cast<const f32x4*>(p);
-        } else {
+      const int q = tid + i * NT, row = q / W < rows ? q / W : rows - 1, c = (q % W) * 4;
+      const float* p = src + (size_t)row * ld;
+      if constexpr (VEC) {
+        v[i] = *reinterpret_cast<const f32x4*>(p + (c < dk ? c : 0));
+      } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (c + e < dk) x[e] = p[e];
-        }
+        for (int e = 0; e < 4; ++e) v[i][e] = p[c + e < dk ? c + e : 0];
       }
-      v[i] = x;
     }
   }
   template <int LD>
-  __device__ __forceinline__ void put(float* dst, int tid) const {
+  __device__ __forceinline__ void put(float* dst, int dk, int tid) const {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int q = tid + i * NT;
-      *reinterpret_cast<f32x4*>(dst + (q / W) * LD + (q % W) * 4) = v[i];
+      const int q = tid + i * NT, c = (q % W) * 4;
+      f32x4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = c + e < dk ? v[i][e] : 0.f;
+      *reinterpret_cast<f32x4*>(dst + (q / W) * LD + c) = x;
     }
   }
 };
 // One row's channels as MFMA operands: group s of 8 channels gives this lane half channels 8s + 4g .. + 3.
-template <int DKP>
-__device__ __forceinline__ void load_row(f32x4 (&f)[DKP / 8], const float* row, int dk, bool vec, int g) {
+template <int DKP, bool VEC>
+__device__ __forceinline__ void load_row(f32x4 (&f)[DKP / 8], const float* row, int dk, int g) {
 #pragma unroll
   for (int s = 0; s < DKP / 8; ++s) {
     const int c = s * 8 + g * 4;
-    f32x4 x = {0.f, 0.f, 0.f, 0.f};
-    if (vec) {
-      if (c < dk) x = *reinterpret_cast<const f32x4*>(row + c);
-    } else {
+    f32x4 x;
+    if constexpr (VEC) x = *reinterpret_cast<const f32x4*>(row + (c < dk ? c : 0));
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (c + e < dk) x[e] = row[c + e];
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (!VEC) x[e] = row[c + e < dk ? c + e : 0];
+      x[e] = c + e < dk ? x[e] : 0.f;
     }
     f[s] = x;
   }
@@ -97,8 +96,8 @@ __device__ __forceinline__ void clear(f32x16& a) {
   for (int r = 0; r < 16; ++r) a[r] = 0.f;
 }
 // Result columns of a wavefront (one row of the output per lane): channels ct*32 + 8*(r/4) + 4*g + r%4.
-template <int CT>
-__device__ __forceinline__ void store_cols(float* row, const f32x16 (&acc)[CT], float f, int dk, bool vec, int g) {
+template <int CT, bool VEC>
+__device__ __forceinline__ void store_cols(float* row, const f32x16 (&acc)[CT], float f, int dk, int g) {
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -107,7 +106,7 @@ __device__ __forceinline__ void store_cols(float* row, const f32x16 (&acc)[CT], 
       f32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = acc[ct][rq * 4 + e] * f;
-      if (vec) {
+      if constexpr (VEC) {
         if (c < dk) *reinterpret_cast<f32x4*>(row + c) = o;
       } else {
 #pragma unroll
@@ -118,10 +117,10 @@ __device__ __forceinline__ void store_cols(float* row, const f32x16 (&acc)[CT], 
 }
 
 // ---- forward.  One workgroup per (b, h, NW*32 queries).
-template <int DKP, int NW>
+template <int DKP, int NW, bool VEC>
 __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag,
                                                                float* __restrict__ c, float* __restrict__ lse, AttnDims a,
-                                                               int n_tiles, int vec) {
+                                                               int n_tiles) {
   constexpr int CT = DKP / 32, KL = DKP + 4, VL = DKP + 8, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Kt[32 * KL];
   __shared__ __attribute__((aligned(16))) float Vt[32 * VL];
@@ -135,7 +134,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   const float* vb = (const float*)io.v + (size_t)b * Sk * io.ldkv + h * a.dk;
   const float* dg = a.bias ? diag + (size_t)h * (2 * S - 1) + (S - 1) - il : nullptr;  // dg[j] = bias(j - i)
   f32x4 q[DKP / 8];
-  load_row<DKP>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, vec, g);
+  load_row<DKP, VEC>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, g);
   const float sc = a.scale * kLog2e;
   uint32_t k1 = 0;
   if (a.drop.on) k1 = drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + il));
@@ -145,25 +144,26 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   float m = -INFINITY, l = 0.f;
   const int keys = a.causal ? (i0 + NW * 32 < S ? i0 + NW * 32 : S) : Sk;
   const int my_keys = a.causal ? (iw + 32 < keys ? iw + 32 : keys) : Sk;  // keys this wavefront's queries see
-  Tile32<DKP, NT> tk, tv;
-  tk.load(kb, io.ldkv, Sk, a.dk, vec, tid);
-  tv.load(vb, io.ldkv, Sk, a.dk, vec, tid);
+  Tile32<DKP, NT, VEC> tk, tv;
+  tk.load(kb, io.ldkv, Sk, a.dk, tid);
+  tv.load(vb, io.ldkv, Sk, a.dk, tid);
   for (int j0 = 0; j0 < keys; j0 += 32) {
     __syncthreads();  // the tile before this one has been used
-    tk.template put<KL>(Kt, tid);
-    tv.template put<VL>(Vt, tid);
+    tk.template put<KL>(Kt, a.dk, tid);
+    tv.template put<VL>(Vt, a.dk, tid);
     __syncthreads();
-    if (j0 + 32 < keys) {
-      tk.load(kb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
-      tv.load(vb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
-    }
-    if (j0 >= my_keys) continue;  // (uniform in the wavefront; the barriers are at the top of the loop)
+    // (requested before the next tile: loads return in order, and these are needed first)
     float bias[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-      bias[r] = a.bias ? dg[j < Sk ? j : Sk - 1] * kLog2e : 0.f;
+      bias[r] = a.bias ? dg[j < Sk ? j : Sk - 1] : 0.f;
     }
+    if (j0 + 32 < keys) {
+      tk.load(kb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, tid);
+      tv.load(vb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, tid);
+    }
+    if (j0 >= my_keys) continue;  // (uniform in the wavefront; the barriers are at the top of the loop)
     f32x16 s;
     clear(s);
     mul_rows<DKP, KL>(s, Kt, q, lane);
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-      float x = fmaf(s[r], sc, bias[r]);
+      float x = fmaf(s[r], sc, bias[r] * kLog2e);
       if ((a.causal && j > i) || j >= Sk) x = -INFINITY;
       s[r] = x;
       mx = fmaxf(mx, x);
@@ -196,19 +196,19 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   }
   l += __shfl_xor(l, 32, 64);
   if (i < S) {
-    store_cols<CT>(c + ((size_t)b * S + i) * I + h * a.dk, o, (a.drop.on ? a.drop.scale : 1.f) / l, a.dk, vec, g);
+    store_cols<CT, VEC>(c + ((size_t)b * S + i) * I + h * a.dk, o, (a.drop.on ? a.drop.scale : 1.f) / l, a.dk, g);
     if (g == 0) lse[((size_t)b * a.H + h) * S + i] = (m + __builtin_amdgcn_logf(l)) * kLn2;
   }
 }
 
 // ---- dq, dvec = rowsum(dO * O) and the per-diagonal bias gradient.  Ownership as in the forward.
 // Dynamic LDS: with bias, one float per diagonal the workgroup can touch (S + NW*32 - 1).
-template <int DKP, int NW>
+template <int DKP, int NW, bool VEC>
 __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, const float* __restrict__ o,
                                                                   const float* __restrict__ dout,
                                                                   const float* __restrict__ diag,
                                                                   const float* __restrict__ lse, float* __restrict__ dvec,
-                                                                  float* __restrict__ ddiag, AttnDims a, int n_tiles, int vec) {
+                                                                  float* __restrict__ ddiag, AttnDims a, int n_tiles) {
   constexpr int CT = DKP / 32, LD = DKP + 4, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Kt[32 * LD];
   __shared__ __attribute__((aligned(16))) float Vt[32 * LD];
@@ -230,9 +230,9 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
   float dsum = 0.f;
   {
     f32x4 x[DKP / 8];
-    load_row<DKP>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, vec, g);
-    load_row<DKP>(d, dout + ((size_t)b * S + il) * I + h * a.dk, a.dk, vec, g);
-    load_row<DKP>(x, o + ((size_t)b * S + il) * I + h * a.dk, a.dk, vec, g);
+    load_row<DKP, VEC>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, g);
+    load_row<DKP, VEC>(d, dout + ((size_t)b * S + il) * I + h * a.dk, a.dk, g);
+    load_row<DKP, VEC>(x, o + ((size_t)b * S + il) * I + h * a.dk, a.dk, g);
 #pragma unroll
     for (int s = 0; s < DKP / 8; ++s)
 #pragma unroll
@@ -248,25 +248,25 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
   for (int ct = 0; ct < CT; ++ct) clear(dq[ct]);
   const int keys = a.causal ? (i0 + NW * 32 < S ? i0 + NW * 32 : S) : Sk;
   const int my_keys = a.causal ? (iw + 32 < keys ? iw + 32 : keys) : Sk;
-  Tile32<DKP, NT> tk, tv;
-  tk.load(kb, io.ldkv, Sk, a.dk, vec, tid);
-  tv.load(vb, io.ldkv, Sk, a.dk, vec, tid);
+  Tile32<DKP, NT, VEC> tk, tv;
+  tk.load(kb, io.ldkv, Sk, a.dk, tid);
+  tv.load(vb, io.ldkv, Sk, a.dk, tid);
   for (int j0 = 0; j0 < keys; j0 += 32) {
     __syncthreads();
-    tk.template put<LD>(Kt, tid);
-    tv.template put<LD>(Vt, tid);
+    tk.template put<LD>(Kt, a.dk, tid);
+    tv.template put<LD>(Vt, a.dk, tid);
     __syncthreads();
-    if (j0 + 32 < keys) {
-      tk.load(kb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
-      tv.load(vb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, vec, tid);
-    }
-    if (j0 >= my_keys) continue;
-    float bias[16];
+    float bias[16];  // (requested before the next tile, as in the forward)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-      bias[r] = a.bias ? fmaf(dg[j < Sk ? j : Sk - 1], kLog2e, nl2) : nl2;
+      bias[r] = a.bias ? dg[j < Sk ? j : Sk - 1] : 0.f;
     }
+    if (j0 + 32 < keys) {
+      tk.load(kb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, tid);
+      tv.load(vb + (size_t)(j0 + 32) * io.ldkv, io.ldkv, Sk - j0 - 32, a.dk, tid);
+    }
+    if (j0 >= my_keys) continue;
     f32x16 s, dp;
     clear(s);
     clear(dp);
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-      const float p = __builtin_amdgcn_exp2f(fmaf(s[r], sc, bias[r]));
+      const float p = __builtin_amdgcn_exp2f(fmaf(s[r], sc, fmaf(bias[r], kLog2e, nl2)));
       float x = dp[r];
       if (a.drop.on) x = mix32(k1 ^ (uint32_t)j) >= a.drop.thr ? x * a.drop.scale : 0.f;
       const float ds = p * (x - dsum);
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
     }
     mul_cols<CT, LD>(dq, Kt, s, lane);
   }
-  if (i < S) store_cols<CT>((float*)io.dq + ((size_t)b * S + i) * io.lddq + h * a.dk, dq, a.scale, a.dk, vec, g);
+  if (i < S) store_cols<CT, VEC>((float*)io.dq + ((size_t)b * S + i) * io.lddq + h * a.dk, dq, a.scale, a.dk, g);
   if (a.bias) {
     __syncthreads();
     float* dd = ddiag + (size_t)h * (2 * S - 1) + (S - 1) - (i0 + NW * 32 - 1);
@@ -298,12 +298,11 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
 }
 
 // ---- dk and dv.  One workgroup per (b, h, NW*32 keys); lane = key.
-template <int DKP, int NW>
+template <int DKP, int NW, bool VEC>
 __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout,
                                                                    const float* __restrict__ diag,
                                                                    const float* __restrict__ lse,
-                                                                   const float* __restrict__ dvec, AttnDims a, int n_tiles,
-                                                                   int vec) {
+                                                                   const float* __restrict__ dvec, AttnDims a, int n_tiles) {
   constexpr int CT = DKP / 32, LD = DKP + 4, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Qt[32 * LD];
   __shared__ __attribute__((aligned(16))) float Dt[32 * LD];
@@ -318,38 +317,45 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
   const float* dg = a.bias ? diag + (size_t)h * (2 * S - 1) + (S - 1) + jl : nullptr;  // dg[-i] = bias(j - i)
   const size_t srow = ((size_t)b * a.H + h) * S;
   f32x4 k[DKP / 8], v[DKP / 8];
-  load_row<DKP>(k, (const float*)io.k + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, vec, g);
-  load_row<DKP>(v, (const float*)io.v + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, vec, g);
+  load_row<DKP, VEC>(k, (const float*)io.k + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, g);
+  load_row<DKP, VEC>(v, (const float*)io.v + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, g);
   const float sc = a.scale * kLog2e;
   f32x16 dk[CT], dv[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) { clear(dk[ct]); clear(dv[ct]); }
   const int ibeg = a.causal ? kt * NW * 32 : 0;  // a multiple of 32
-  Tile32<DKP, NT> tq, td;
-  tq.load(qb + (size_t)ibeg * io.ldq, io.ldq, S - ibeg, a.dk, vec, tid);
-  td.load(db + (size_t)ibeg * I, I, S - ibeg, a.dk, vec, tid);
+  Tile32<DKP, NT, VEC> tq, td;
+  tq.load(qb + (size_t)ibeg * io.ldq, io.ldq, S - ibeg, a.dk, tid);
+  td.load(db + (size_t)ibeg * I, I, S - ibeg, a.dk, tid);
+  float rl = 0.f, rd = 0.f;  // lse and dvec of query i0 + tid of the tile to come (first 32 threads)
+  auto load_consts = [&](int i0) __attribute__((always_inline)) {
+    const int i = i0 + (tid & 31) < S ? i0 + (tid & 31) : S - 1;
+    rl = lse[srow + i];
+    rd = dvec[srow + i];
+  };
+  load_consts(ibeg);
   for (int i0 = ibeg; i0 < S; i0 += 32) {
     __syncthreads();
-    tq.template put<LD>(Qt, tid);
-    td.template put<LD>(Dt, tid);
+    tq.template put<LD>(Qt, a.dk, tid);
+    td.template put<LD>(Dt, a.dk, tid);
+    float bias[16];  // (requested before the next tile, as in the forward)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = i0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+      bias[r] = a.bias ? dg[-(i < S ? i : S - 1)] : 0.f;
+    }
     if (tid < 32) {
-      const int i = i0 + tid < S ? i0 + tid : S - 1;
-      row_l[tid] = -lse[srow + i] * kLog2e;
-      row_d[tid] = dvec[srow + i];
-      if (a.drop.on) row_k[tid] = drop_row_key(a.drop, (uint32_t)(srow + i));
+      row_l[tid] = -rl * kLog2e;
+      row_d[tid] = rd;
+      if (a.drop.on) row_k[tid] = drop_row_key(a.drop, (uint32_t)(srow + (i0 + tid < S ? i0 + tid : S - 1)));
     }
     __syncthreads();
     if (i0 + 32 < S) {
-      tq.load(qb + (size_t)(i0 + 32) * io.ldq, io.ldq, S - i0 - 32, a.dk, vec, tid);
-      td.load(db + (size_t)(i0 + 32) * I, I, S - i0 - 32, a.dk, vec, tid);
+      tq.load(qb + (size_t)(i0 + 32) * io.ldq, io.ldq, S - i0 - 32, a.dk, tid);
+      td.load(db + (size_t)(i0 + 32) * I, I, S - i0 - 32, a.dk, tid);
+      load_consts(i0 + 32);
     }
     if (a.causal && i0 + 31 < jw) continue;  // every query of the tile comes before this wavefront's keys
-    float bias[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int il = ((r >> 2) << 3) + (g << 2) + (r & 3), i = i0 + il;
-      bias[r] = a.bias ? fmaf(dg[-(i < S ? i : S - 1)], kLog2e, row_l[il]) : row_l[il];
-    }
     f32x16 s, dp;
     clear(s);
     clear(dp);
@@ -359,7 +365,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
     for (int r = 0; r < 16; ++r) {
       const int il = ((r >> 2) << 3) + (g << 2) + (r & 3), i = i0 + il;
       const bool ok = i < S && j < Sk && !(a.causal && j > i);
-      const float p = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], sc, bias[r])) : 0.f;
+      const float p = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], sc, fmaf(bias[r], kLog2e, row_l[il]))) : 0.f;
       float mk = 1.f;
       if (a.drop.on) mk = mix32(row_k[il] ^ (uint32_t)j) >= a.drop.thr ? a.drop.scale : 0.f;
       s[r] = p * mk;
@@ -369,8 +375,8 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
     mul_cols<CT, LD>(dk, Qt, dp, lane);
   }
   if (j < Sk) {
-    store_cols<CT>((float*)io.dk + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dk, a.scale, a.dk, vec, g);
-    store_cols<CT>((float*)io.dv + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dv, 1.f, a.dk, vec, g);
+    store_cols<CT, VEC>((float*)io.dk + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dk, a.scale, a.dk, g);
+    store_cols<CT, VEC>((float*)io.dv + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dv, 1.f, a.dk, g);
   }
 }
 
@@ -386,35 +392,27 @@ bool vec_ok(const AttnIO& io, const AttnDims& a, const void* c, const void* dc) 
 }
 
 // Wavefronts per workgroup: two share each K/V (or Q/dO) tile; one where a sequence has no more than 32 rows.
-template <int DKP>
+template <int DKP, bool VEC>
 hipError_t launch_fwd(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
-  const int vec = vec_ok(io, a, c, nullptr);
   if (a.S <= 32) {
-    attn_fwd_f32_kernel<DKP, 1><<<a.B * a.H, 64, 0, st>>>(io, diag, c, lse, a, 1, vec);
+    attn_fwd_f32_kernel<DKP, 1, VEC><<<a.B * a.H, 64, 0, st>>>(io, diag, c, lse, a, 1);
   } else {
     const int nt = ceil_div(a.S, 64);
-    attn_fwd_f32_kernel<DKP, 2><<<nt * a.B * a.H, 128, 0, st>>>(io, diag, c, lse, a, nt, vec);
+    attn_fwd_f32_kernel<DKP, 2, VEC><<<nt * a.B * a.H, 128, 0, st>>>(io, diag, c, lse, a, nt);
   }
   return hipGetLastError();
 }
-template <int DKP>
+template <int DKP, bool VEC>
 hipError_t launch_bwd(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse, float* dvec,
                       float* ddiag, const AttnDims& a, hipStream_t st) {
-  const int vec = vec_ok(io, a, c, dc);
-  if (a.S <= 32) {
-    attn_bwd_dq_f32_kernel<DKP, 1><<<a.B * a.H, 64, a.bias ? (a.S + 31) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec, ddiag,
-                                                                                      a, 1, vec);
-  } else {
-    const int nt = ceil_div(a.S, 64);
-    attn_bwd_dq_f32_kernel<DKP, 2><<<nt * a.B * a.H, 128, a.bias ? (a.S + 63) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec,
-                                                                                            ddiag, a, nt, vec);
-  }
-  if (a.Sk <= 32) {
-    attn_bwd_dkv_f32_kernel<DKP, 1><<<a.B * a.H, 64, 0, st>>>(io, dc, diag, lse, dvec, a, 1, vec);
-  } else {
-    const int nt = ceil_div(a.Sk, 64);
-    attn_bwd_dkv_f32_kernel<DKP, 2><<<nt * a.B * a.H, 128, 0, st>>>(io, dc, diag, lse, dvec, a, nt, vec);
-  }
+  const int nq = ceil_div(a.S, 64), nk = ceil_div(a.Sk, 64), bh = a.B * a.H;
+  if (a.S <= 32)
+    attn_bwd_dq_f32_kernel<DKP, 1, VEC><<<bh, 64, a.bias ? (a.S + 31) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec, ddiag, a, 1);
+  else
+    attn_bwd_dq_f32_kernel<DKP, 2, VEC><<<nq * bh, 128, a.bias ? (a.S + 63) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec, ddiag,
+                                                                                        a, nq);
+  if (a.Sk <= 32) attn_bwd_dkv_f32_kernel<DKP, 1, VEC><<<bh, 64, 0, st>>>(io, dc, diag, lse, dvec, a, 1);
+  else attn_bwd_dkv_f32_kernel<DKP, 2, VEC><<<nk * bh, 128, 0, st>>>(io, dc, diag, lse, dvec, a, nk);
   return hipGetLastError();
 }
 
@@ -427,9 +425,10 @@ bool attn_f32_supported(const AttnDims& a) {
 }
 
 hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
-  if (a.dk <= 32) return launch_fwd<32>(io, diag, c, lse, a, st);
-  if (a.dk <= 64) return launch_fwd<64>(io, diag, c, lse, a, st);
-  return launch_fwd<128>(io, diag, c, lse, a, st);
+  if (!vec_ok(io, a, c, nullptr)) return launch_fwd<128, false>(io, diag, c, lse, a, st);
+  if (a.dk <= 32) return launch_fwd<32, true>(io, diag, c, lse, a, st);
+  if (a.dk <= 64) return launch_fwd<64, true>(io, diag, c, lse, a, st);
+  return launch_fwd<128, true>(io, diag, c, lse, a, st);
 }
 
 hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
@@ -438,9 +437,10 @@ hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc
     const int64_t nd = (int64_t)a.H * (2 * a.S - 1);
     clear_f32_kernel<<<ceil_div(nd, 256), 256, 0, st>>>(ddiag, nd);
   }
-  if (a.dk <= 32) return launch_bwd<32>(io, c, dc, diag, lse, dvec, ddiag, a, st);
-  if (a.dk <= 64) return launch_bwd<64>(io, c, dc, diag, lse, dvec, ddiag, a, st);
-  return launch_bwd<128>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+  if (!vec_ok(io, a, c, dc)) return launch_bwd<128, false>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+  if (a.dk <= 32) return launch_bwd<32, true>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+  if (a.dk <= 64) return launch_bwd<64, true>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+  return launch_bwd<128, true>(io, c, dc, diag, lse, dvec, ddiag, a, st);
 }
 
 }  // namespace t5mi

@@ -132,7 +132,7 @@ int t5_block_bwd(const t5_block_cfg* cfg, const void* dy, const void* x, const t
   const bool attn_mfma = D.ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad, far);
   W.fork = fork_begin(st, D.drop == 0.f && !D.det);
   ForkGuard guard(W.fork);
-  T5_SUB(bwd_zero(D, dw, nullptr, attn_mfma ? W.ddiag : nullptr, acc != 0, st));
+  T5_SUB(bwd_zero(D, dw, nullptr, W.ddiag, acc != 0, st));
   T5_SUB(bwd_mlp(D, dy, S.h, w, S, W, dw, acc, st));
   T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh, W.dh_lp, w, S, W, attn_mfma, far, dx, dw, acc, st));
   T5_TRY(guard.join());
@@ -190,7 +190,7 @@ int t5_decoder_block_bwd(const t5_block_cfg* cfg, int32_t enc_seq, const void* d
   const bool attn_mfma = D.ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad, far);
   W.fork = fork_begin(st, D.drop == 0.f && !D.det);
   ForkGuard guard(W.fork);
-  T5_SUB(bwd_zero(D, dw, dxw, attn_mfma ? W.ddiag : nullptr, acc != 0, st));
+  T5_SUB(bwd_zero(D, dw, dxw, W.ddiag, acc != 0, st));
   T5_SUB(bwd_mlp(D, dy, S.h2, w, S, W, dw, acc, st));
   T5_SUB(bwd_cross_attn(cfg, D, enc, xw, S, W, denc, dxw, acc, st));
   T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh1, W.dh1_lp, w, S, W, attn_mfma, far, dx, dw, acc, st));

@@ -35,18 +35,24 @@ struct F32Src {  // where a thread's float4 slot of an operand comes from
   int nv;        // m-contiguous: valid elements of the slot; k-contiguous: 1 if the row exists
 };
 
-__device__ __forceinline__ f32x4 ld4(const float* p, int nv, bool vec) {
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  if (nv >= 4 && vec) return *reinterpret_cast<const f32x4*>(p);
+// Slot of a thread: four elements at base + off of which the first nv exist.  VEC (every slot exists whole or not at
+// all): one load from an address that is valid either way, zeroed by the caller when it is used -- a branch around
+// the load makes the compiler wait for it on the spot.  Otherwise element by element.
+template <bool VEC>
+__device__ __forceinline__ f32x4 ld4(const float* base, size_t off, int nv) {
+  if constexpr (VEC) {
+    return *reinterpret_cast<const f32x4*>(base + (nv > 0 ? off : 0));
+  } else {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (q < nv) v[q] = p[q];
-  return v;
+    for (int q = 0; q < 4; ++q)
+      if (q < nv) v[q] = base[off + q];
+    return v;
+  }
 }
 
-template <int BM, int BN, int WM, int WN, int WK, int BK, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g, GemmEpi e, int split_k, int vec_a,
-                                                                     int vec_b) {
+template <int BM, int BN, int WM, int WN, int WK, int BK, bool A_KC, bool B_KC, int EPI, bool VEC>
+__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g, GemmEpi e, int split_k) {
   constexpr int NT = WM * WN * WK * 64;
   constexpr int TMW = BM / WM, TNW = BN / WN, MI = TMW / 32, NI = TNW / 32;
   constexpr int A_LD = A_KC ? BK + 4 : BM + 8, B_LD = B_KC ? BK + 4 : BN + 8;
@@ -115,6 +121,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
   }
 
   f32x4 ra[A_SL], rb[B_SL];
+  bool oka[A_SL], okb[B_SL];
   int seg = 0, kt = t_begin;  // tile kt of segment seg comes next
   int seg_nt = (g.seg[0].K + BK - 1) / BK;
   auto fetch = [&]() __attribute__((always_inline)) {
@@ -130,12 +137,14 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
 #pragma unroll
     for (int i = 0; i < A_SL; ++i) {
       const int nv = A_KC ? (sa[i].nv ? left - sa[i].row : 0) : (sa[i].row < left ? sa[i].nv : 0);
-      ra[i] = ld4(A + sa[i].off + oa, nv, vec_a != 0);
+      oka[i] = nv > 0;
+      ra[i] = ld4<VEC>(A, sa[i].off + oa, nv);
     }
 #pragma unroll
     for (int i = 0; i < B_SL; ++i) {
       const int nv = B_KC ? (sb[i].nv ? left - sb[i].row : 0) : (sb[i].row < left ? sb[i].nv : 0);
-      rb[i] = ld4((b_src[i] ? b_src[i] : B) + sb[i].off + ob, nv, vec_b != 0);
+      okb[i] = nv > 0;
+      rb[i] = ld4<VEC>(b_src[i] ? b_src[i] : B, sb[i].off + ob, nv);
     }
     ++kt;
   };
@@ -146,13 +155,19 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
     for (int i = 0; i < A_SL; ++i) {
       const int q = tid + i * NT;
       constexpr int W = (A_KC ? BK : BM) / 4;
-      *reinterpret_cast<f32x4*>(pa + (q / W) * A_LD + (q % W) * 4) = ra[i];
+      f32x4 v = ra[i];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) v[x] = !VEC || oka[i] ? v[x] : 0.f;
+      *reinterpret_cast<f32x4*>(pa + (q / W) * A_LD + (q % W) * 4) = v;
     }
 #pragma unroll
     for (int i = 0; i < B_SL; ++i) {
       const int q = tid + i * NT;
       constexpr int W = (B_KC ? BK : BN) / 4;
-      *reinterpret_cast<f32x4*>(pb + (q / W) * B_LD + (q % W) * 4) = rb[i];
+      f32x4 v = rb[i];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) v[x] = !VEC || okb[i] ? v[x] : 0.f;
+      *reinterpret_cast<f32x4*>(pb + (q / W) * B_LD + (q % W) * 4) = v;
     }
   };
 
@@ -237,12 +252,40 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
   }
 
   // ---- epilogue: register r of a 32x32 tile is row (r/4)*8 + half*4 + r%4, column lane%32: a wavefront writes
-  // 128-byte runs of two rows
+  // 128-byte runs of two rows.  Operands of the epilogue are fetched for a whole row of tiles before the first store:
+  // the compiler cannot move a load across a store that might alias it, and one at a time each costs a round trip
+  // (the gated-GELU backward at 64 tokens: 23 us, most of it here).
+  constexpr bool AUX = EPI == EPI_RESID || EPI == EPI_GEGLU_BWD || EPI == EPI_SPLIT_F32;
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
+    const int mb = m0 + wm * TMW + i * 32 + (g2 << 2), nb = n0 + wn * TNW + l32;
+    float xa[AUX ? 16 : 1][NI], xb[EPI == EPI_GEGLU_BWD ? 16 : 1][NI];
+    if (AUX && (EPI != EPI_SPLIT_F32 || (split_k == 1 && e.accumulate))) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const int m = mb + ((r >> 2) << 3) + (r & 3), n = nb + j * 32;
+          const int mc = m < g.M ? m : g.M - 1, nc = n < g.N ? n : g.N - 1;
+          if constexpr (EPI == EPI_SPLIT_F32) {
+            const int which = nc / e.split_n;
+            const float* d = (const float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
+            xa[r][j] = d[(size_t)mc * e.ld0 + (nc - which * e.split_n)];
+          } else if constexpr (AUX) {
+            const size_t oa = (size_t)mc * (e.ld_aux ? e.ld_aux : e.ld0) + nc;
+            xa[r][j] = ((const float*)e.aux0)[oa];
+            if constexpr (EPI == EPI_GEGLU_BWD) xb[r][j] = ((const float*)e.aux1)[oa];
+          }
+        }
+    } else if (AUX) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) xa[AUX ? r : 0][j] = 0.f;
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int m = m0 + wm * TMW + i * 32 + ((r >> 2) << 3) + (g2 << 2) + (r & 3);
+      const int m = mb + ((r >> 2) << 3) + (r & 3);
       if (m >= g.M) continue;
       const uint32_t k1 = e.drop.on ? drop_row_key(e.drop, (uint32_t)m) : 0u;
       if constexpr (EPI == EPI_GEGLU_FWD) {
@@ -262,7 +305,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
       } else {
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
-          const int n = n0 + wn * TNW + j * 32 + l32;
+          const int n = nb + j * 32;
           if (n >= g.N) continue;
           const float v = acc[i][j][r];
           const size_t o = (size_t)m * e.ld0 + n;
@@ -270,19 +313,17 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
             const float mk = e.drop.on ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
             ((float*)e.out0)[o] = (e.act == ACT_RELU ? fmaxf(v, 0.f) : v) * mk;
           } else if constexpr (EPI == EPI_RESID) {
-            const float a = ((const float*)e.aux0)[(size_t)m * (e.ld_aux ? e.ld_aux : e.ld0) + n];
-            const float sc = e.drop.on ? e.drop.scale : 1.f;
+            const float a = xa[r][j], sc = e.drop.on ? e.drop.scale : 1.f;
             const float mk = e.drop.on && !e.aux_mask ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
             ((float*)e.out0)[o] = e.aux_mask ? (a > 0.f ? v * sc : 0.f) : v * mk + a;
           } else if constexpr (EPI == EPI_GEGLU_BWD) {
-            const size_t oa = (size_t)m * (e.ld_aux ? e.ld_aux : e.ld0) + n;
-            ((float*)e.out0)[o] = v * ((const float*)e.aux0)[oa];
-            ((float*)e.out1)[o] = v * ((const float*)e.aux1)[oa];
+            ((float*)e.out0)[o] = v * xa[r][j];
+            ((float*)e.out1)[o] = v * xb[r][j];
           } else {  // EPI_SPLIT_F32
             const int which = n / e.split_n;
             float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2) + (size_t)m * e.ld0 + (n - which * e.split_n);
             if (split_k > 1) unsafeAtomicAdd(dst, v);
-            else *dst = e.accumulate ? *dst + v : v;
+            else *dst = xa[r][j] + v;
           }
         }
       }
@@ -290,12 +331,12 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
   }
 }
 
-template <int BM, int BN, int WM, int WN, int WK, int BK, bool A_KC, bool B_KC, int EPI>
-hipError_t launch_tile(const GemmDesc& g, const GemmEpi& e, int split_k, int va, int vb, hipStream_t st) {
+template <int BM, int BN, int WM, int WN, int WK, int BK, bool A_KC, bool B_KC, int EPI, bool VEC>
+hipError_t launch_tile(const GemmDesc& g, const GemmEpi& e, int split_k, hipStream_t st) {
   constexpr int a_fl = A_KC ? BM * (BK + 4) : BK * (BM + 8), b_fl = B_KC ? BN * (BK + 4) : BK * (BN + 8);
   constexpr int red = (WK - 1) * BM * BN;  // floats of the exchange between the k shares
   constexpr int lds = (2 * (a_fl + b_fl) > red ? 2 * (a_fl + b_fl) : red) * 4;
-  auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, BK, A_KC, B_KC, EPI>;
+  auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, BK, A_KC, B_KC, EPI, VEC>;
   if constexpr (lds > 65536) {
     static std::atomic<bool> attr_set{false};  // once per instantiation; setting it twice is harmless
     if (!attr_set.load(std::memory_order_relaxed)) {
@@ -305,19 +346,22 @@ hipError_t launch_tile(const GemmDesc& g, const GemmEpi& e, int split_k, int va,
     }
   }
   dim3 grid(ceil_div(g.N, BN), ceil_div(g.M, BM), split_k);
-  kern<<<grid, WM * WN * WK * 64, lds, st>>>(g, e, split_k, va, vb);
+  kern<<<grid, WM * WN * WK * 64, lds, st>>>(g, e, split_k);
   return hipGetLastError();
 }
 
 template <bool A_KC, bool B_KC, int EPI>
 hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
-  // float4 loads: every row start of the operand on a 16-byte boundary
-  auto aligned = [](const void* p, int ld) { return ld % 4 == 0 && ((uintptr_t)p & 15) == 0; };
-  int va = 1, vb = 1;
-  const int nptr = g.nsrc > 1 ? g.nsrc : g.nseg;
-  for (int s = 0; s < nptr; ++s) vb &= aligned(g.seg[s].B, g.seg[0].ldb) ? 1 : 0;
-  for (int s = 0; s < g.nseg; ++s) va &= aligned(g.seg[s].A, g.seg[0].lda) ? 1 : 0;
-  if (g.nsrc > 1 && g.nsrc_cols % 4 != 0) return hipErrorInvalidValue;  // a float4 slot has one source (gemm_f32_supported)
+  // float4 loads: every row of the operands starts on a 16-byte boundary and no slot of four lies half outside
+  bool vec = g.seg[0].lda % 4 == 0 && g.seg[0].ldb % 4 == 0;
+  for (int s = 0; s < (g.nsrc > 1 ? g.nsrc : g.nseg); ++s) vec = vec && ((uintptr_t)g.seg[s].B & 15) == 0;
+  for (int s = 0; s < g.nseg; ++s) {
+    vec = vec && ((uintptr_t)g.seg[s].A & 15) == 0;
+    if (A_KC || B_KC) vec = vec && g.seg[s].K % 4 == 0;
+  }
+  if (!A_KC) vec = vec && g.M % 4 == 0;
+  if (!B_KC) vec = vec && g.N % 4 == 0;
+  if (!vec) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, false>(g, e, 1, st);
   const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128);
   const int64_t t64 = (int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64);
   int64_t K = 0;
@@ -330,13 +374,17 @@ hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
       const bool big = t128 * (K / 256) >= 256;
       const int64_t t = big ? t128 : t64;
       const int sk = (int)std::max<int64_t>(1, std::min<int64_t>(K / 256, (512 + t - 1) / t));
-      if (big) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI>(g, e, sk, va, vb, st);
-      return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI>(g, e, sk, va, vb, st);
+      if (big) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI, true>(g, e, sk, st);
+      return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, sk, st);
     }
   }
-  if (t128 >= 192) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI>(g, e, 1, va, vb, st);
-  if (t64 >= 128) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI>(g, e, 1, va, vb, st);
-  return launch_tile<32, 64, 1, 1, 4, 64, A_KC, B_KC, EPI>(g, e, 1, va, vb, st);
+  // 128x128 tiles where their last round over the 256 compute units is about as full as that of the 64x64 tiles
+  // (4000 x 1152: 288 large tiles are one round and an eighth, at half the rate of 1134 small ones); 32x64 tiles with
+  // the reduction over four wavefronts where even the 64x64 ones leave half the chip idle.
+  auto filled = [](int64_t t) { return (double)t / (double)((t + 255) / 256 * 256); };
+  if (t128 >= 192 && filled(t128) * 1.1 >= filled(t64)) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
+  if (t64 >= 128) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
+  return launch_tile<32, 64, 1, 1, 4, 64, A_KC, B_KC, EPI, true>(g, e, 1, st);
 }
 
 }  // namespace
