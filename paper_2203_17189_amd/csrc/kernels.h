@@ -102,6 +102,13 @@ hipError_t launch_gemm_f32(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 // and 16-byte aligned pointers; gemm_mfma_supported() checks this.
 bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e);
 hipError_t launch_gemm_mfma(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+// its epilogue families
+hipError_t launch_gemm_mfma_store(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+hipError_t launch_gemm_mfma_resid(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+hipError_t launch_gemm_mfma_geglu_fwd(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+hipError_t launch_gemm_mfma_geglu_bwd(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+hipError_t launch_gemm_mfma_split(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+hipError_t launch_gemm_mfma_split_grouped(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 // Bytes of the partial-sum buffer (GemmEpi::aux0) that launch_gemm_mfma would use for this EPI_SPLIT_F32 problem (0: no split).
 size_t gemm_split_partials_bytes(const GemmDesc& g, const GemmEpi& e);
 
