@@ -5,9 +5,7 @@
 //   C[m,n] = sum_s sum_k A_s(m,k) B_s(n,k)
 //
 // Tiling: workgroup tile BM x BN, k-tiles of BK, WM x WN wavefronts, each wave owns
-// (BM/WM) x (BN/WN) as 32x32 MFMA tiles.  BK = 64 in two stages for the large k-contiguous problems (a
-// DMA request then covers a whole 128-byte line of a row; with 64-byte rows the L1 still spends a
-// line's worth of time per request), BK = 32 in three to five stages elsewhere.
+// (BM/WM) x (BN/WN) as 32x32 MFMA tiles; which tile a problem gets is decided in launch_layout.
 //
 // Data path: global -> LDS directly (global_load_lds_dwordx4: every lane fetches 16 bytes, a wave
 // fills 1 KB of contiguous LDS), NS stages deep.  Global load latency on this part is on the order
@@ -136,7 +134,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
   constexpr bool DROP = (EPI_T & EPI_DROP) != 0;
   constexpr bool GROUP = (EPI_T & EPI_GROUP) != 0;
   constexpr int NW = WM * WN;
-  constexpr bool AB32 = BK == 64 && NS == 3;  // three stages of A and two of B (see ab_loop)
+  constexpr bool AB32 = BK == 64 && NS == 3 && BM == 256;  // three stages of A and two of B (see ab_loop)
   constexpr int TMW = BM / WM, TNW = BN / WN;
   constexpr int MI = TMW / 32, NI = TNW / 32;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
@@ -850,7 +848,7 @@ bool split_partials_ok(const GemmDesc& g, const GemmEpi& e) {
 template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, int EPI, int NS = 4, int MINW = 1, int BK = 32>
 hipError_t launch_cfg(const GemmDesc& g, const GemmEpi& e, int split_k, hipStream_t st) {
   auto kern = gemm_mfma_kernel<BM, BN, WM, WN, A_KC, B_KC, EPI, NS, MINW, BK>;
-  constexpr int lds_loop = (BK == 64 && NS == 3 ? 3 * BM + 2 * BN : NS * (BM + BN)) * BK * 2;
+  constexpr int lds_loop = (BK == 64 && NS == 3 && BM == 256 ? 3 * BM + 2 * BN : NS * (BM + BN)) * BK * 2;
   constexpr int lds_epi = WM * WN * 64 * (BN / WN + 8) * 4;
   constexpr int lds = lds_loop > lds_epi ? lds_loop : lds_epi;
   // once per instantiation; setting it twice is harmless, so a relaxed flag is enough
@@ -869,77 +867,71 @@ hipError_t launch_cfg(const GemmDesc& g, const GemmEpi& e, int split_k, hipStrea
 template <bool A_KC, bool B_KC, int EPI_T>
 hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   constexpr int EPI = EPI_T & (EPI_DROP - 1);
-  int nk = 0;
-  for (int s = 0; s < g.nseg; ++s) nk += g.seg[s].K / KQ;
   // a grouped launch (weight gradients of several layers) counts the tiles of all its problems
   const int ngr = (EPI_T & EPI_GROUP) ? g.ngroups : 1;
   const int64_t t256 = (int64_t)ceil_div(g.M, 256) * ceil_div(g.N, 256) * ngr;
   const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128) * ngr;
-  bool big = t256 >= 192;
-  int split_k = 1;
-  bool two_pass = false;  // reproducible split reduction through the partial-sum buffer in GemmEpi::aux0
   if constexpr (EPI == EPI_SPLIT_F32) {
     // Partial sums of the k-slices meet in float32 atomics on a zeroed output, or, when the caller provides
     // room for them, in a second pass that adds them up in a fixed order.
+    bool big;
+    int split_k;
     wgrad_plan(g, e, ngr, big, split_k);
     if (ngr > 1 && !e.accumulate) return hipErrorInvalidValue;  // grouped outputs are cleared by the caller
-    two_pass = split_k > 1 && split_partials_ok(g, e);
+    const bool two_pass = split_k > 1 && split_partials_ok(g, e);  // through the partial-sum buffer in GemmEpi::aux0
     if (split_k > 1 && !e.accumulate && !two_pass) {
       zero_split_kernel<<<ceil_div((int64_t)g.M * g.N, 256), 256, 0, st>>>(e, g.M, g.N);
       hipError_t err = hipGetLastError();
       if (err != hipSuccess) return err;
     }
-  }
-  GemmEpi ee = e;
-  if constexpr (EPI == EPI_SPLIT_F32) {
+    GemmEpi ee = e;
     if (!two_pass) ee.aux0 = nullptr;
-  }
-  auto finish = [&](hipError_t err) {
+    const hipError_t err = big ? launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 5, 1>(g, ee, split_k, st)
+                               : launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, ee, split_k, st);
     if (err != hipSuccess || !two_pass) return err;
     splitk_reduce_kernel<<<ceil_div((int64_t)g.M * g.N / 4, 256), 256, 0, st>>>(ee, g.M, g.N, split_k);
     return hipGetLastError();
-  };
-  if constexpr (EPI == EPI_SPLIT_F32) {
-    if (big) return finish(launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 5, 1>(g, ee, split_k, st));
-    return finish(launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, ee, split_k, st));
   }
-  if (big) {
-    // short k loops: two 256x128 workgroups per compute unit hide each other's prologue/epilogue
-    // and so do the epilogue-heavy gated-GELU kernels (three outputs, or two inputs and two outputs);
-    // the gated-GELU forward goes back to one 256x256 tile once k is long enough (measured: better
-    // from K = 768, worse at K = 512) because the smaller tiles re-stream more operand data
-    // residual epilogues into a narrow output (N < 1024: T5.1.1-Small/Base widths), measured per shape:
-    // K <= 512 as below (256x128), 128x128 tiles for K up to 768 (-6..15 % at N = 768), 256x256 beyond
-    // (-4..9 %)
-    if (EPI_T == EPI_RESID && g.N < 1024 && nk > 8) {
-      if (nk <= 12) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, split_k, st);
-      if constexpr (A_KC) return launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, split_k, st);
-      else return launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 5, 1>(g, e, split_k, st);
+  if constexpr (EPI != EPI_SPLIT_F32) {
+    // k-contiguous operands, k-tiles of 64 (a DMA instruction then covers eight whole 128-byte rows instead of sixteen
+    // half rows; the L1 processes a line per request whatever part of it is used).  In the order tried:
+    //  * 256x256, one workgroup per compute unit, three A and two B stages: the fewest operand bytes per flop, so the
+    //    fastest where its last round over the 256 compute units is full (32768 x 6144 x 2048: 646 us against 770);
+    //  * 128x128, two workgroups per compute unit, two stages: a round of 512 tiles costs w of a 256x256 round, which
+    //    is four times the work for w = 0.62 (plain store and gated-GELU forward; 0.53 at K < 640), 0.56 and 0.49 (K <= 768)
+    //    with the residual epilogue, whose extra traffic the second workgroup hides; a last round of up to 256 tiles
+    //    costs 0.65 of a full one, as much as a full one from K = 1024 on.  The cheaper sum of rounds is taken
+    //    (14592 x 768 x 2304, 171 against 684 tiles: 59 us against 68; 8991 x 768 x 4096, 108 against 426: 92 against 64).
+    //    The gated-GELU backward, two tensors in and two out, always takes it (32768 x 5120 x 2048: 1149 us with 256x256,
+    //    850 with 256x128, 753 with this);
+    //  * 256x128, two workgroups, k-tiles of 32 in three stages: gated-GELU forward up to K = 704, residual up to K = 512
+    //    (32768 x 512 x 384: 31 us against 32 and 34);
+    //  * up to 256 tiles of 128x128 (one per compute unit): latency counts, so more stages (k-tiles of 32 in four) and,
+    //    while they fit one round, smaller tiles, 128x64 and 64x64 (1332 x 768 x 2048 with residual: 37 us -> 21;
+    //    1332 x 768 x 768: 25 -> 18).
+    int64_t K = 0;
+    for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
+    const double last = K >= 1024 ? 1.0 : 0.65;
+    const double w = EPI == EPI_RESID ? (K <= 768 ? 0.49 : 0.56) : K < 640 ? 0.53 : 0.62;
+    const double c256 = (double)((t256 + 255) / 256);
+    const int64_t rem = t128 % 512;
+    const double c128 = w * ((double)(t128 / 512) + (rem > 256 ? 1.0 : rem > 0 ? last : 0.0));
+    if (t128 <= 256) {
+      if constexpr (EPI != EPI_GEGLU_FWD) {  // (which needs 64 columns in a wavefront)
+        if ((int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64) <= 256)
+          return launch_cfg<64, 64, 1, 2, A_KC, B_KC, EPI_T, 4, 1, 64>(g, e, 1, st);
+        if ((int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 64) <= 256)
+          return launch_cfg<128, 64, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
+      }
+      return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
     }
-    // the residual epilogue with dropout does not fit the 256x256 tile's register budget (it would spill)
-    if (EPI_T == (EPI_RESID | EPI_DROP)) return launch_cfg<256, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 2>(g, e, split_k, st);
-    // (thresholds in units of 64 along k, measured per epilogue: plain stores and the gated-GELU forward gain
-    // 10-12 % from the 256x256 tile at K = 768 and lose 7-20 % at K = 512; the residual epilogue is indifferent
-    // up to K = 2048)
-    if (EPI != EPI_SPLIT_F32 && (((EPI == EPI_STORE || EPI == EPI_GEGLU_FWD) && nk < 12) || EPI == EPI_GEGLU_BWD ||
-                                 (EPI == EPI_RESID && nk <= 32)))
-      return launch_cfg<256, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 2>(g, e, split_k, st);
-    // k-contiguous operands: k-tiles of 64 in two stages.  A DMA instruction then covers eight whole 128-byte
-    // rows instead of sixteen half rows (the L1 processes a line per request whatever part of it is used, and
-    // at 64 bytes per row that path, not the matrix unit, sets the pace), and there is one barrier per 64 MFMAs
-    // instead of per 32.  Measured on the T5.1.1-XL GEMMs against five stages of 32: +7 to +12 %, once a tile's
-    // sixteen DMA instructions per wave are issued two per chunk over two k-steps instead of four per chunk over
-    // one (issued four at a time they stall the wave in the memory pipeline's queue and the gain is lost).
-    // The weight-gradient GEMMs (rows of 512 bytes already) and the 256x128 two-workgroup configuration lose
-    // with k-tiles of 64 (-4 % and -25 %) and keep 32.
-    if constexpr (A_KC) return launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, split_k, st);
-    else return launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 5, 1>(g, e, split_k, st);
+    if constexpr (EPI == EPI_GEGLU_FWD || EPI == EPI_RESID)
+      if (t256 >= 192 && K <= (EPI == EPI_RESID ? 512 : 704))
+        return launch_cfg<256, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 2>(g, e, 1, st);
+    if constexpr (EPI != EPI_GEGLU_BWD)
+      if (c256 <= c128) return launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
+    return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 2, 1, 64>(g, e, 1, st);
   }
-  // too few 256x256 tiles to fill the chip, but a long reduction: 256x128 tiles, two per compute unit
-  // (8192 x 768 x 32128: -11 % against 128x128)
-  if (EPI != EPI_SPLIT_F32 && t256 >= 64 && nk >= 64)
-    return launch_cfg<256, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 2>(g, e, split_k, st);
-  return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, split_k, st);
 }
 
 }  // namespace
