@@ -130,20 +130,22 @@ __global__ void geglu_fwd_kernel(T* __restrict__ u, T* __restrict__ w, T* __rest
   }
 }
 
-// dst[n][k] for a 64x64 tile staged through LDS; see launch_pack_transpose_bf16.  blockIdx.z picks the
-// job; blocks outside a job's tile range leave at once.  Each thread moves two adjacent elements, so
-// a row of the tile is one 128-byte line on the way in and on the way out.
+// dst[n][k] for a 64x64 tile staged through LDS; see launch_pack_transpose_bf16.  blockIdx.z picks the job; blocks
+// outside a job's tile range leave at once.  Bound: bytes (28 MB for the weights of a d 768 layer, 6 us at the copy
+// rate); with 4-byte accesses the kernel took 17 us there.  A thread reads 16 bytes of two rows, pairs the rows'
+// elements into words (k, k + 1) of its 8 columns, and the tile leaves LDS as 16-byte runs along k.
+// LDS: word (n, k/2) of the tile at n * 32 + ((k/2) ^ swz(n)), the 16-byte groups of a row swizzled so that the writes of
+// a wavefront (8 columns of 8 row pairs at a time) and its 16-byte reads spread over the banks.
 __global__ __launch_bounds__(256) void pack_transpose_kernel(PackJobs jobs) {
-  __shared__ bf16 tile[64][66];
+  __shared__ __attribute__((aligned(16))) uint32_t tile[64 * 32];
   const PackJob& jb = jobs.j[blockIdx.z];
   const int nsrc = jb.nsrc, K = jb.K, n_each = jb.n_each, interleave = jb.interleave;
   const int n_total = nsrc * n_each;
   const int n0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
   if (n0 >= n_total || k0 >= K) return;
-  const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;  // 32 column pairs x 8 rows
   // interleave and n_each are multiples of 32 (or interleave == 0), so each 32-wide half of the tile's packed
-  // rows comes from one source and 32 consecutive source columns; a thread's pair lies inside one half.
-  const int c = 2 * tx, nh = n0 + (c & 32);  // first packed row of this thread's half
+  // rows comes from one source and 32 consecutive source columns; a thread's 8 columns lie inside one half.
+  const int c = (threadIdx.x & 7) * 8, kp = threadIdx.x >> 3, nh = n0 + (c & 32);  // columns c .. c+7, rows 2 kp and 2 kp + 1
   int which, col0;
   if (interleave > 0) {
     which = (nh / interleave) % nsrc;
@@ -153,20 +155,43 @@ __global__ __launch_bounds__(256) void pack_transpose_kernel(PackJobs jobs) {
     col0 = nh % n_each;
   }
   const bool in_n = nh < n_total;
-  const bf16* src = (const bf16*)jb.src[in_n ? which : 0];
-  bf16* dst = (bf16*)jb.dst;
-  for (int r = ty; r < 64; r += 8) {
-    const int k = k0 + r;
-    uint32_t v = 0;
-    if (in_n && k < K) v = *reinterpret_cast<const uint32_t*>(src + (size_t)k * n_each + col0 + (c & 31));
-    *reinterpret_cast<uint32_t*>(&tile[r][c]) = v;
+  const bf16* src = (const bf16*)jb.src[in_n ? which : 0] + (in_n ? col0 + (c & 31) : 0);
+  const int k = k0 + 2 * kp;
+  u32x4 lo = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
+  if (in_n && k < K) {  // K is even: the two rows are inside or outside together
+    const bf16 *r0 = src + (size_t)k * n_each, *r1 = r0 + n_each;
+    if (((uintptr_t)src & 15) == 0) {  // (uniform over the 32 columns of a source: n_each is a multiple of 32)
+      lo = *reinterpret_cast<const u32x4*>(r0);
+      hi = *reinterpret_cast<const u32x4*>(r1);
+    } else {  // a weight that does not start on 16 bytes
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        lo[q] = __builtin_bit_cast(uint16_t, r0[2 * q]) | ((uint32_t)__builtin_bit_cast(uint16_t, r0[2 * q + 1]) << 16);
+        hi[q] = __builtin_bit_cast(uint16_t, r1[2 * q]) | ((uint32_t)__builtin_bit_cast(uint16_t, r1[2 * q + 1]) << 16);
+      }
+    }
+  }
+  auto swz = [](int n) { return ((n ^ (n >> 3)) & 7) << 2; };
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int n = c + 2 * q;
+    tile[n * 32 + (kp ^ swz(n))] = (lo[q] & 0xFFFFu) | (hi[q] << 16);
+    tile[(n + 1) * 32 + (kp ^ swz(n + 1))] = (lo[q] >> 16) | (hi[q] & 0xFFFF0000u);
   }
   __syncthreads();
-  for (int r = ty; r < 64; r += 8) {
-    const int n = n0 + r, k = k0 + c;
-    if (n < n_total && k < K) {  // K is even: the pair (k, k + 1) is inside or outside together
-      const uint32_t lo = __builtin_bit_cast(uint16_t, tile[c][r]), hi = __builtin_bit_cast(uint16_t, tile[c + 1][r]);
-      *reinterpret_cast<uint32_t*>(dst + (size_t)n * K + k) = lo | (hi << 16);
+  bf16* dst = (bf16*)jb.dst;
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const int n = it * 32 + (threadIdx.x >> 3), k8 = threadIdx.x & 7;  // 16 bytes: k0 + 8 k8 .. + 7 of packed row n0 + n
+    const u32x4 v = *reinterpret_cast<const u32x4*>(tile + n * 32 + ((k8 * 4) ^ swz(n)));
+    if (n0 + n >= n_total) continue;
+    bf16* d = dst + (size_t)(n0 + n) * K + k0 + k8 * 8;
+    if (k0 + k8 * 8 + 8 <= K && K % 8 == 0 && ((uintptr_t)dst & 15) == 0) {
+      *reinterpret_cast<u32x4*>(d) = v;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (k0 + k8 * 8 + 2 * q < K) reinterpret_cast<uint32_t*>(d)[q] = v[q];
     }
   }
 }
