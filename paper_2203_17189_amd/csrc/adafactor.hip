@@ -95,22 +95,35 @@ __device__ __forceinline__ void af_stats_tile(const AfItem& it, int bx, int by, 
   float csum[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) csum[i] = 0.f;
-  for (int rr = wave; rr < TR; rr += 4) {
-    const int64_t r = r0 + rr;
-    if (r >= R) break;
-    float rs = 0.f;
-    if (c0 < C) {
-      float v[VEC];
-      ldv<VEC>(g + r * C + c0, v);
+  // four rows at a time: their loads are in flight together and the four lane reductions interleave (one row at a time,
+  // each load waited for the reduction before it: 49 us for the 193 MB of a d 2048 layer's gradients, 4.0 TB/s)
+  for (int rr = wave; rr < TR; rr += 16) {
+    float v[4][VEC], rs[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t r = r0 + rr + 4 * q;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) v[q][i] = 0.f;
+      if (c0 < C && r < R) ldv<VEC>(g + r * C + c0, v[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      rs[q] = 0.f;
 #pragma unroll
       for (int i = 0; i < VEC; ++i) {
-        const float q = v[i] * v[i];
-        csum[i] += q;
-        rs += q;
+        const float x = v[q][i] * v[q][i];
+        csum[i] += x;
+        rs[q] += x;
       }
     }
-    rs = wave_sum(rs);
-    if (lane == 0) it.ws.rowpart[(int64_t)bx * R + r] = rs;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) rs[q] += __shfl_xor(rs[q], off, 64);
+    if (lane < 4) {
+      const int64_t r = r0 + rr + 4 * lane;
+      if (r < R) it.ws.rowpart[(int64_t)bx * R + r] = lane == 0 ? rs[0] : lane == 1 ? rs[1] : lane == 2 ? rs[2] : rs[3];
+    }
   }
 #pragma unroll
   for (int i = 0; i < VEC; ++i) colred[wave][lane * VEC + i] = csum[i];
@@ -143,11 +156,13 @@ __global__ __launch_bounds__(256) void af_finalize_kernel(AfBatch b) {
   const int64_t idx = (int64_t)(blockIdx.x - b.fin_start[ti]) * 256 + threadIdx.x;
   if (idx < R) {
     float s = 0.f;
-    for (int t = 0; t < it.ntc; ++t) s += it.ws.rowpart[(int64_t)t * R + idx];
+#pragma unroll 8
+    for (int t = 0; t < it.ntc; ++t) s += it.ws.rowpart[(int64_t)t * R + idx];  // (eight loads in flight, summed in order)
     it.v_row[idx] = beta2 * it.v_row[idx] + (1.f - beta2) * (s / (float)C + eps1);
   } else if (idx < R + C) {
     const int64_t j = idx - R;
     float s = 0.f;
+#pragma unroll 8
     for (int t = 0; t < it.ntr; ++t) s += it.ws.colpart[(int64_t)t * C + j];
     const float vc = beta2 * it.v_col[j] + (1.f - beta2) * (s / (float)R + eps1);
     it.v_col[j] = vc;
