@@ -807,7 +807,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmEpi e, int M, in
 
 // Tile size and k split of a weight-gradient GEMM (EPI_SPLIT_F32): few output tiles, very long k.
 // Small outputs take 128x128 tiles (fewer k-slices, hence fewer partial sums per output element); k is split
-// so that the workgroups fill whole rounds of the 256 compute units.
+// by the cost of the rounds over the 256 compute units and of the partial sums (measured, below).
 void wgrad_plan(const GemmDesc& g, const GemmEpi& e, int ngr, bool& big, int& split_k) {
   int nk = 0;
   for (int s = 0; s < g.nseg; ++s) nk += g.seg[s].K / KQ;
@@ -821,22 +821,27 @@ void wgrad_plan(const GemmDesc& g, const GemmEpi& e, int ngr, bool& big, int& sp
   // reduction, no split and no atomics, beats 256x256 tiles split seven ways (0.20 -> 0.17 ms at 4096 tokens)
   if (ngr > 1 && t128 <= 512) big = false;
   const int64_t tiles = big ? t256 : t128;
-  const int per_cu = big ? 1 : 2;  // concurrent workgroups per compute unit (LDS-limited)
   double best = -1.0;
   split_k = 1;
   for (int sp = 1; sp <= 32; ++sp) {
     if (sp > 1 && nk / sp < 8) break;
-    const int64_t wgs = tiles * sp, slots = 256 * per_cu;
-    const int64_t rounds = (wgs + slots - 1) / slots;
-    double eff;
+    const int64_t wgs = tiles * sp;
+    double cost;
     if (big) {
-      // time = rounds x (a workgroup's k-tiles + its epilogue); the epilogue of a 256x256 slice (65536 float
+      // rounds x (a workgroup's k-tiles + its epilogue); the epilogue of a 256x256 slice (65536 float
       // atomics beside those of 255 other workgroups) costs about as much as 12 k-tiles of 64 (measured)
-      eff = 1.0 / ((double)rounds * ((double)nk / sp + 12.0));
+      cost = (double)((wgs + 255) / 256) * ((double)nk / sp + 12.0);
     } else {
-      eff = (double)wgs / (double)(rounds * slots) - 0.012 * sp;
+      // In units of a 128x128 workgroup's k-tile of 64 when it has a compute unit to itself (0.54 us): two on one unit
+      // take 1.75 each, and the float atomics of all slices together run at 340 G/s whatever the split, 0.09 units
+      // per workgroup.  So one workgroup per unit with half the slices beats two (512 x 1024 over 32768 tokens: 8 slices
+      // 52 us, 16 slices 60; 768 x 768 over 8991: 7 slices 27, 14 slices 38) unless it leaves units idle
+      // (2048 x 768 over 14592, 96 tiles: 2 slices 80, 5 slices 64).
+      const int64_t rem = wgs % 512;
+      const double rounds = (double)(wgs / 512) * 1.75 + (rem > 256 ? 1.75 : rem > 0 ? 1.0 : 0.0);
+      cost = rounds * (double)nk / sp + (sp > 1 ? 0.09 * (double)wgs : 0.0);
     }
-    if (eff > best) { best = eff; split_k = sp; }
+    if (best < 0.0 || cost < best) { best = cost; split_k = sp; }
   }
   (void)e;
 }
