@@ -891,7 +891,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     }
     GemmEpi ee = e;
     if (!two_pass) ee.aux0 = nullptr;
-    const hipError_t err = big ? launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 5, 1>(g, ee, split_k, st)
+    const hipError_t err = big ? launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, ee, split_k, st)
                                : launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, ee, split_k, st);
     if (err != hipSuccess || !two_pass) return err;
     splitk_reduce_kernel<<<ceil_div((int64_t)g.M * g.N / 4, 256), 256, 0, st>>>(ee, g.M, g.N, split_k);
