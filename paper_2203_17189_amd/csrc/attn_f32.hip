@@ -137,7 +137,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   load_row<DKP, VEC>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, g);
   const float sc = a.scale * kLog2e;
   uint32_t k1 = 0;
-  if (a.drop.on) k1 = drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + il));
+  if (a.drop.on) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + il)));
   f32x16 o[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) clear(o[ct]);
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
       const float p = __builtin_amdgcn_exp2f(s[r] - mn);
       ls += p;  // the normaliser is that of the undropped probabilities
-      s[r] = a.drop.on ? (mix32(k1 ^ (uint32_t)j) >= a.drop.thr ? p : 0.f) : p;
+      s[r] = a.drop.on ? (drop_keep16(a.drop, k1 ^ (uint32_t)j) ? p : 0.f) : p;
     }
     l = l * alpha + ls;
 #pragma unroll
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
   if (g == 0 && i < S) dvec[srow] = dsum;
   const float nl2 = -lse[srow] * kLog2e, sc = a.scale * kLog2e;
   uint32_t k1 = 0;
-  if (a.drop.on) k1 = drop_row_key(a.drop, (uint32_t)srow);
+  if (a.drop.on) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)srow));
   f32x16 dq[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) clear(dq[ct]);
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
       const float p = __builtin_amdgcn_exp2f(fmaf(s[r], sc, fmaf(bias[r], kLog2e, nl2)));
       float x = dp[r];
-      if (a.drop.on) x = mix32(k1 ^ (uint32_t)j) >= a.drop.thr ? x * a.drop.scale : 0.f;
+      if (a.drop.on) x = drop_keep16(a.drop, k1 ^ (uint32_t)j) ? x * a.drop.scale : 0.f;
       const float ds = p * (x - dsum);
       const bool ok = i < S && j < Sk && !(a.causal && j > i);
       s[r] = ok ? ds : 0.f;
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
     if (tid < 32) {
       row_l[tid] = -rl * kLog2e;
       row_d[tid] = rd;
-      if (a.drop.on) row_k[tid] = drop_row_key(a.drop, (uint32_t)(srow + (i0 + tid < S ? i0 + tid : S - 1)));
+      if (a.drop.on) row_k[tid] = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + (i0 + tid < S ? i0 + tid : S - 1))));
     }
     __syncthreads();
     if (i0 + 32 < S) {
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
       const bool ok = i < S && j < Sk && !(a.causal && j > i);
       const float p = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], sc, fmaf(bias[r], kLog2e, row_l[il]))) : 0.f;
       float mk = 1.f;
-      if (a.drop.on) mk = mix32(row_k[il] ^ (uint32_t)j) >= a.drop.thr ? a.drop.scale : 0.f;
+      if (a.drop.on) mk = drop_keep16(a.drop, row_k[il] ^ (uint32_t)j) ? a.drop.scale : 0.f;
       s[r] = p * mk;
       dp[r] = p * (dp[r] * mk - row_d[il]);
     }

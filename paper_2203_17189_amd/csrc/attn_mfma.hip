@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
   const float sc = a.scale * kLog2e;
   const int dg_base = BR - 1 - i_loc;  // dg[dg_base + j] = bias(j - i)
   uint32_t k1 = 0;  // dropout row key of this lane's query
-  if constexpr (DROP) k1 = drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + i_ld));
+  if constexpr (DROP) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + i_ld)));
 
   f32x16 oT[CT];
 #pragma unroll
@@ -354,6 +354,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
     const float alpha = fast_exp2(m - m_new);
     m = m_new;
     float ls = 0.f;
+    uint32_t kx = 0;
+    if constexpr (DROP) kx = k1 ^ (uint32_t)(j0 | (g << 2));
 #pragma unroll
     for (int kt = 0; kt < BC / 32; ++kt)
 #pragma unroll
@@ -361,8 +363,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
         const float p = fast_exp2(sT[kt][r] - m_new);
         ls += p;  // the normaliser is that of the undropped probabilities
         if constexpr (DROP) {
-          const int j = j0 + kt * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-          sT[kt][r] = mix32(k1 ^ (uint32_t)j) >= a.drop.thr ? p : 0.f;
+          // (key index = tile start | lane half << 2 | constant of the register, disjoint bits)
+          const uint32_t c = (uint32_t)(kt * 32 + ((r >> 2) << 3) + (r & 3));
+          sT[kt][r] = drop_keep16(a.drop, kx ^ c) ? p : 0.f;
         } else {
           sT[kt][r] = p;
         }
@@ -484,10 +487,11 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
   }
   const float nlse2 = -lse_q * kLog2e, ndv = -dsum;
   uint32_t k1 = 0;  // dropout row key of this lane's query
-  if constexpr (DROP) k1 = drop_row_key(a.drop, (uint32_t)srow);
+  if constexpr (DROP) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)srow));
   // dP of a kept probability carries the factor 1/(1 - rate); that of a dropped one is zero
-  auto dp_masked = [&](float dp, int j) {
-    if constexpr (DROP) return mix32(k1 ^ (uint32_t)j) >= a.drop.thr ? dp * a.drop.scale : 0.f;
+  // (kx: row key with the sub-tile's key index and the lane half in it, r: result register)
+  auto dp_masked = [&](float dp, uint32_t kx, int r) {
+    if constexpr (DROP) return drop_keep16(a.drop, kx ^ (uint32_t)(((r >> 2) << 3) + (r & 3))) ? dp * a.drop.scale : 0.f;
     else return dp;
   };
   if constexpr (BIAS) {
@@ -572,20 +576,21 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
       __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
       // sub-tile reaches above the diagonal, past the last key, or this wave holds queries past the end
       // (all wave-uniform)
+      uint32_t kx = 0;
+      if constexpr (DROP) kx = k1 ^ (uint32_t)(j0s | (g << 2));
       if ((CAUSAL && j0s + 31 > i_w0) || j0s + 32 > Sk || i_w0 + 32 > S) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int j = j0s + ((r >> 2) << 3) + (g << 2) + (r & 3);
           float p = BIAS ? fast_exp2(fmaf(sT[r], sc, bias[r]) + nlse2) : fast_exp2(fmaf(sT[r], sc, nlse2));
           if ((CAUSAL && j > i) || j >= Sk || !q_ok) p = 0.f;
-          sT[r] = p * (dp_masked(dpT[r], j) + ndv);
+          sT[r] = p * (dp_masked(dpT[r], kx, r) + ndv);
         }
       } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int j = j0s + ((r >> 2) << 3) + (g << 2) + (r & 3);
           const float p = BIAS ? fast_exp2(fmaf(sT[r], sc, bias[r]) + nlse2) : fast_exp2(fmaf(sT[r], sc, nlse2));
-          sT[r] = p * (dp_masked(dpT[r], j) + ndv);
+          sT[r] = p * (dp_masked(dpT[r], kx, r) + ndv);
         }
       }
       // ---- bias gradient of this 32x32 sub-tile (wave-uniform branches)
@@ -815,7 +820,7 @@ __global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
   if constexpr (DROP) {
     if (tid < BQ) {
       const int qi = it_begin * BQ + tid < S ? it_begin * BQ + tid : S - 1;
-      key_all[tid] = drop_row_key(a.drop, (uint32_t)(srow + qi));
+      key_all[tid] = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + qi)));
     }
   }
   for (int it = it_begin; it < n_it; ++it) {
@@ -832,7 +837,7 @@ __global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
       if constexpr (DROP) {
         if (tid < BQ) {
           const int qi = q0 + BQ + tid < S ? q0 + BQ + tid : S - 1;
-          nkey = drop_row_key(a.drop, (uint32_t)(srow + qi));
+          nkey = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + qi)));
         }
       }
     }
@@ -904,7 +909,7 @@ __global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
                          : fast_exp2(s[r] * sc);
           if ((CAUSAL && j > i) || i >= S) p = 0.f;
           if constexpr (DROP) {
-            const bool keep = mix32(key_s[il] ^ (uint32_t)j) >= a.drop.thr;
+            const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
             s[r] = keep ? p : 0.f;
             dp[r] = p * ((keep ? dp[r] * a.drop.scale : 0.f) + dv_s[il]);
           } else {
@@ -920,7 +925,7 @@ __global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
           const float p = BIAS ? fast_exp2(fmaf(s[r], sc, HOIST ? bias[r] : bq[27 - (((r >> 2) << 3) + (r & 3))]))
                                : fast_exp2(s[r] * sc);
           if constexpr (DROP) {
-            const bool keep = mix32(key_s[il] ^ (uint32_t)j) >= a.drop.thr;
+            const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
             s[r] = keep ? p : 0.f;
             dp[r] = p * ((keep ? dp[r] * a.drop.scale : 0.f) + dv_s[il]);
           } else {

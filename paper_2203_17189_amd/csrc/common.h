@@ -125,6 +125,17 @@ enum {
   DROP_CROSS_OUT = 6, DROP_EMBED = 7, DROP_FINAL = 8, DROP_DEC_EMBED = 9, DROP_DEC_FINAL = 10
 };
 __device__ __forceinline__ uint32_t drop_row_key(const DropSite& d, uint32_t hi) { return mix32(d.k0 ^ hi ^ d.seed_hi); }
+// The same decision for lo < 65536 (attention keys, channels), a sixth of the instructions less: the generator's first
+// step, x ^= x >> 16 on x = key ^ lo, then only meets bits of the key in x >> 16, so that part is taken once per row
+// (drop_row_pre) and, lo's bits being an exclusive-or away, so may be any other part of lo that a loop holds fixed.
+__device__ __forceinline__ uint32_t drop_row_pre(uint32_t k1) { return k1 ^ (k1 >> 16); }
+__device__ __forceinline__ bool drop_keep16(const DropSite& d, uint32_t x) {  // x = drop_row_pre(k1) ^ lo
+  x *= 0x7FEB352Du;
+  x ^= x >> 15;
+  x *= 0x846CA68Bu;
+  x ^= x >> 16;
+  return x >= d.thr;
+}
 // multiplier of element lo in the row whose key is k1: scale where kept, 0 where dropped
 __device__ __forceinline__ float drop_mult(const DropSite& d, uint32_t k1, uint32_t lo) {
   return mix32(k1 ^ lo) >= d.thr ? d.scale : 0.f;
