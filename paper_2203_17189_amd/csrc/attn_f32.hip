@@ -74,22 +74,38 @@ __device__ __forceinline__ void load_row(f32x4 (&f)[DKP / 8], const float* row, 
 template <int DKP, int LD>
 __device__ __forceinline__ void mul_rows(f32x16& acc, const float* tile, const f32x4 (&f)[DKP / 8], int lane) {
   const float* p = tile + (lane & 31) * LD + (lane >> 5) * 4;
+  f32x4 a[2];  // (requested one group ahead of its products)
+  a[0] = *reinterpret_cast<const f32x4*>(p);
 #pragma unroll
   for (int s = 0; s < DKP / 8; ++s) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(p + s * 8);
+    if (s + 1 < DKP / 8) a[(s + 1) & 1] = *reinterpret_cast<const f32x4*>(p + (s + 1) * 8);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], f[s][e], acc, 0, 0, 0);
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s & 1][e], f[s][e], acc, 0, 0, 0);
   }
 }
 // acc[ct] += T^T P for a tile (channels become MFMA rows, its 32 rows are contracted) and P in the result layout
 template <int CT, int LD>
 __device__ __forceinline__ void mul_cols(f32x16 (&acc)[CT], const float* tile, const f32x16& p, int lane) {
   const float* t = tile + (lane >> 5) * 4 * LD + (lane & 31);
+  float a[2][4][CT];  // (four rows' columns, requested one group ahead of their products)
+  auto columns = [&](int rq) __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r)
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-      acc[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(t[(((r >> 2) << 3) + (r & 3)) * LD + ct * 32], p[r], acc[ct], 0, 0, 0);
+      for (int ct = 0; ct < CT; ++ct) a[rq & 1][e][ct] = t[(rq * 8 + e) * LD + ct * 32];
+  };
+  columns(0);
+#pragma unroll
+  for (int rq = 0; rq < 4; ++rq) {
+    if (rq + 1 < 4) columns(rq + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+        acc[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[rq & 1][e][ct], p[rq * 4 + e], acc[ct], 0, 0, 0);
+  }
 }
 __device__ __forceinline__ void clear(f32x16& a) {
 #pragma unroll
