@@ -105,8 +105,8 @@ int t5_block_fwd(const t5_block_cfg* cfg, const void* x, const t5_block_weights*
   FwdWs W;
   carve_fwd(D, workspace, &W);
   const bool fused = fused_fwd_ok(D);
-  if (fused) T5_SUB(fwd_pack_weights(D, w, nullptr, W, st));
-  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st));
+  if (fused) T5_SUB(fwd_pack_weights(D, w, nullptr, W, st, &lut, S.diag));
+  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st, !fused));
   T5_SUB(fwd_mlp(cfg, D, S.h, w, S, W, fused, y, st));
   return T5_OK;
 }
@@ -134,7 +134,7 @@ int t5_block_bwd(const t5_block_cfg* cfg, const void* dy, const void* x, const t
   ForkGuard guard(W.fork);
   T5_SUB(bwd_zero(D, dw, nullptr, W.ddiag, acc != 0, st));
   T5_SUB(bwd_mlp(D, dy, S.h, w, S, W, dw, acc, st));
-  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh, W.dh_lp, w, S, W, attn_mfma, far, dx, dw, acc, st));
+  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh, W.dh_lp, w, S, W, attn_mfma, far, dx, dw, nullptr, acc, st));
   T5_TRY(guard.join());
   return T5_OK;
 }
@@ -157,8 +157,8 @@ int t5_decoder_block_fwd(const t5_block_cfg* cfg, int32_t enc_seq, const void* x
   FwdWs W;
   carve_fwd(D, workspace, &W);
   const bool fused = fused_fwd_ok(D);
-  if (fused) T5_SUB(fwd_pack_weights(D, w, xw, W, st));
-  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st));
+  if (fused) T5_SUB(fwd_pack_weights(D, w, xw, W, st, &lut, S.diag));
+  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st, !fused));
   T5_SUB(fwd_cross_attn(cfg, D, enc, xw, S, W, fused, st));
   T5_SUB(fwd_mlp(cfg, D, S.h2, w, S, W, fused, y, st));
   return T5_OK;
@@ -193,7 +193,7 @@ int t5_decoder_block_bwd(const t5_block_cfg* cfg, int32_t enc_seq, const void* d
   T5_SUB(bwd_zero(D, dw, dxw, W.ddiag, acc != 0, st));
   T5_SUB(bwd_mlp(D, dy, S.h2, w, S, W, dw, acc, st));
   T5_SUB(bwd_cross_attn(cfg, D, enc, xw, S, W, denc, dxw, acc, st));
-  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh1, W.dh1_lp, w, S, W, attn_mfma, far, dx, dw, acc, st));
+  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh1, W.dh1_lp, w, S, W, attn_mfma, far, dx, dw, dxw, acc, st));
   T5_TRY(guard.join());
   return T5_OK;
 }

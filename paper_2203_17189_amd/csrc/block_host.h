@@ -199,7 +199,8 @@ struct BwdWs {
   // set by a stack that launches the weight-gradient GEMMs of all its layers together after the sweep: the
   // layer functions then skip theirs and leave the operands (duw, dh_lp / dh1_lp, dqkv, dqx, dkvx) in place
   bool defer_wgrad = false;
-  float *dn, *dh, *dvec, *ddiag, *dg_partial;
+  float *dn, *dh, *dvec, *ddiag;
+  float *dg_mlp, *dg_attn, *dg_cross;  // partial rows of the norms' scale gradients, added up at the end of the layer
   void *dh_lp, *duw, *dc, *dqkv;  // duw: [T][2F], du in columns 0..F-1, dw in F..2F-1
   // cross-attention sublayer: dh/dh_lp hold the gradient of h2, dh1/dh1_lp that of h
   float* dh1;
@@ -220,7 +221,10 @@ size_t carve_bwd(const Dims& D, void* base, BwdWs* w) {
   t.dh = cv.take<float>((size_t)D.T * D.d * 4);
   t.dvec = cv.take<float>((size_t)2 * D.B * D.H * D.S * 4);  // rowsum(dO * O), and the forward's lse rescaled, per query
   t.ddiag = cv.take<float>((size_t)D.H * (2 * D.S - 1) * 4);
-  t.dg_partial = cv.take<float>((size_t)rmsnorm_bwd_partial_rows((int)D.T) * D.d * 4);
+  const size_t dg_bytes = (size_t)rmsnorm_bwd_partial_rows((int)D.T) * D.d * 4;
+  t.dg_mlp = cv.take<float>(dg_bytes);
+  t.dg_attn = cv.take<float>(dg_bytes);
+  t.dg_cross = cv.take<float>(D.Sk > 0 ? dg_bytes : 0);
   t.dh_lp = cv.take(D.ty == IN_BF16 ? (size_t)D.T * D.d * D.es : 0);
   t.duw = cv.take((size_t)D.T * 2 * D.F * D.es);
   t.dc = cv.take((size_t)D.T * D.I * D.es);
@@ -375,8 +379,9 @@ AttnIO cross_io(const Dims& D, const Stash& S, const BwdWs* W) {
 
 // ------------------------------------------------------------------ forward sublayers
 // All weight packs (transposes to k-contiguous rows) of the layer in one launch.
+// lut: the layer owns its bias table, whose diagonals (into diag) join the launch.
 int fwd_pack_weights(const Dims& D, const t5_block_weights* w, const t5_cross_weights* xw, const FwdWs& W,
-                     hipStream_t st) {
+                     hipStream_t st, const RelposLut* lut = nullptr, float* diag = nullptr) {
   PackJobs pj;
   std::memset(&pj, 0, sizeof(pj));
   pj.j[0] = PackJob{{w->wq, w->wk, w->wv}, 3, D.d, D.I, 0, W.wqkv_t};
@@ -391,13 +396,14 @@ int fwd_pack_weights(const Dims& D, const t5_block_weights* w, const t5_cross_we
     pj.j[6] = PackJob{{xw->xo, nullptr, nullptr}, 1, D.I, D.d, 0, W.xo_t};
     pj.count = 7;
   }
+  if (lut) { pj.table = w->rel_table; pj.diag = diag; pj.S = D.S; pj.H = D.H; pj.lut = *lut; }
   T5_STEP("pack_weights", launch_pack_transpose_multi(pj, st));
   return T5_OK;
 }
 
 // S.h = x + SelfAttn(RMSNorm(x; ln1_scale))   (float32 residual stream)
 // own_table: the layer builds the bias diagonals S.diag from its table; otherwise S.diag already holds
-// them (a stack shares one table between its layers).
+// them (a stack shares one table between its layers, the weight pack of a fused layer builds them).
 int fwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, const void* x,
                   const t5_block_weights* w, const Stash& S, const FwdWs& W, bool fused, hipStream_t st,
                   bool own_table = true) {
@@ -594,7 +600,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
     }
   }
   T5_STEP("rmsnorm_bwd", launch_rmsnorm_bwd(hin, IN_F32, w->ln2_scale, ty, S.r2, W.dn, dy_in, ty, W.dh,
-                            ty == IN_BF16 ? W.dh_lp : nullptr, ty, dw->ln2_scale, W.dg_partial, acc, T, D.d,
+                            ty == IN_BF16 ? W.dh_lp : nullptr, ty, nullptr, W.dg_mlp, acc, T, D.d,
                             st));
   return T5_OK;
 }
@@ -661,16 +667,18 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   }
   // dh1 = dh2 + RMSNormBwd(h, lnx_scale, dnx)
   T5_STEP("rmsnorm_bwd", launch_rmsnorm_bwd(S.h, IN_F32, xw->lnx_scale, ty, S.rx, W.dn, W.dh, IN_F32, W.dh1,
-                            ty == IN_BF16 ? W.dh1_lp : nullptr, ty, dxw->lnx_scale, W.dg_partial, acc, T, D.d,
+                            ty == IN_BF16 ? W.dh1_lp : nullptr, ty, nullptr, W.dg_cross, acc, T, D.d,
                             st));
   return T5_OK;
 }
 
 // Given dh (float32) and dh_lp (bf16 copy, bf16 blocks) = gradient of S.h: dx and the weight
-// gradients of the self-attention sublayer.
+// gradients of the self-attention sublayer; then, as the last sublayer of the backward pass, the sums that the
+// layer's norms (dxw: also the cross-attention sublayer's) and its own bias table have left.
 int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, const void* x, const float* dh,
                   const void* dh_lp, const t5_block_weights* w, const Stash& S, const BwdWs& W, bool attn_mfma,
-                  int far, void* dx, const t5_block_grads* dw, int acc, hipStream_t st, bool own_table = true) {
+                  int far, void* dx, const t5_block_grads* dw, const t5_cross_grads* dxw, int acc, hipStream_t st,
+                  bool own_table = true) {
   const int T = (int)D.T, ty = D.ty;
   const size_t es = D.es;
   const AttnDims ad = self_dims(cfg, D);
@@ -699,9 +707,6 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   } else {
     T5_STEP("attn_bwd", launch_attn_bwd_simple(io, S.c, W.dc, ty, S.diag, S.lse, W.dvec, W.ddiag, ad, 0, st));
   }
-  // a stack with a shared table keeps adding into W.ddiag over its layers and folds it once at the end
-  if (own_table)
-    T5_STEP("relpos_diag_bwd", launch_relpos_diag_bwd(W.ddiag, dw->rel_table, D.S, D.H, cfg->num_buckets, lut, acc, st));
   if (!W.defer_wgrad) {  // dWq | dWk | dWv = n1^T dqkv
     T5_TRY(fork_sync(W.fork));
     hipStream_t st = wgrad_stream(W.fork);
@@ -719,8 +724,19 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   }
   // dx = dh + RMSNormBwd(x, g1, dn1)
   T5_STEP("rmsnorm_bwd", launch_rmsnorm_bwd(x, ty, w->ln1_scale, ty, S.r1, W.dn, dh, IN_F32,
-                            ty == IN_F32 ? (float*)dx : nullptr, ty == IN_BF16 ? dx : nullptr, ty, dw->ln1_scale,
-                            W.dg_partial, acc, T, D.d, st));
+                            ty == IN_F32 ? (float*)dx : nullptr, ty == IN_BF16 ? dx : nullptr, ty, nullptr,
+                            W.dg_attn, acc, T, D.d, st));
+  LayerTail t;
+  std::memset(&t, 0, sizeof(t));
+  auto add = [&](const float* part, float* dg) { t.part[t.ndg] = part; t.dg[t.ndg] = dg; ++t.ndg; };
+  add(W.dg_mlp, dw->ln2_scale);
+  if (dxw) add(W.dg_cross, dxw->lnx_scale);
+  add(W.dg_attn, dw->ln1_scale);
+  t.nrows = rmsnorm_bwd_partial_rows(T); t.d = D.d; t.accumulate = acc;
+  if (own_table) {  // (a stack with a shared table keeps adding into W.ddiag over its layers and folds it once at the end)
+    t.ddiag = W.ddiag; t.dtable = dw->rel_table; t.S = D.S; t.H = D.H; t.num_buckets = cfg->num_buckets; t.lut = lut;
+  }
+  T5_STEP("layer_tail", launch_layer_tail(t, st));
   return T5_OK;
 }
 

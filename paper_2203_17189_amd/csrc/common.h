@@ -167,6 +167,26 @@ __device__ __forceinline__ int relpos_bucket_dev(int rp, const RelposLut& lut) {
   return base + b;
 }
 
+// Sum of ddiag over the distances of bucket c (one head's diagonals, S of them on each side), by one wave: buckets are
+// contiguous distance ranges on each side, so the order is fixed.  Every lane gets the sum.
+__device__ __forceinline__ float relpos_fold_bucket(const float* __restrict__ ddiag_h, int c, int S, const RelposLut& lut) {
+  int side = 0, cl = c;
+  if (lut.bidirectional && c >= lut.n_side) { side = 1; cl = c - lut.n_side; }
+  int n_lo, n_hi;  // inclusive distance range of this bucket
+  if (cl < lut.max_exact) {
+    n_lo = n_hi = cl;
+  } else {
+    const int k = cl - lut.max_exact;  // logarithmic index
+    n_lo = (k == 0) ? lut.max_exact : lut.thr[k - 1];
+    n_hi = (cl == lut.n_side - 1) ? (S - 1) : (lut.thr[k] - 1);
+  }
+  if (n_hi > S - 1) n_hi = S - 1;
+  if (side == 1 && n_lo == 0) n_lo = 1;  // distance 0 belongs to the non-positive side
+  float s = 0.f;
+  for (int n = n_lo + (int)(threadIdx.x & 63); n <= n_hi; n += kWave) s += ddiag_h[(side ? n : -n) + (S - 1)];
+  return wave_sum(s);
+}
+
 typedef __attribute__((address_space(3))) char lds_char;
 
 // Streaming (non-temporal) global accesses for data this kernel touches exactly once: outputs and

@@ -138,6 +138,14 @@ __global__ void geglu_fwd_kernel(T* __restrict__ u, T* __restrict__ w, T* __rest
 // a wavefront (8 columns of 8 row pairs at a time) and its 16-byte reads spread over the banks.
 __global__ __launch_bounds__(256) void pack_transpose_kernel(PackJobs jobs) {
   __shared__ __attribute__((aligned(16))) uint32_t tile[64 * 32];
+  if ((int)blockIdx.z == jobs.count) {  // the layer's bias diagonals (see launch_relpos_diag): a launch of their own costs 4.5 us
+    const int w = 2 * jobs.S - 1;
+    for (int i = (int)(blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < w; i += (int)(gridDim.x * gridDim.y) * 256) {
+      const int b = relpos_bucket_dev(i - (jobs.S - 1), jobs.lut);
+      for (int h = 0; h < jobs.H; ++h) jobs.diag[(size_t)h * w + i] = (float)((const bf16*)jobs.table)[b * jobs.H + h];
+    }
+    return;
+  }
   const PackJob& jb = jobs.j[blockIdx.z];
   const int nsrc = jb.nsrc, K = jb.K, n_each = jb.n_each, interleave = jb.interleave;
   const int n_total = nsrc * n_each;
@@ -244,7 +252,7 @@ hipError_t launch_pack_transpose_multi(const PackJobs& jobs, hipStream_t st) {
     gx = std::max(gx, ceil_div(jb.nsrc * jb.n_each, 64));
     gy = std::max(gy, ceil_div(jb.K, 64));
   }
-  pack_transpose_kernel<<<dim3(gx, gy, jobs.count), 256, 0, st>>>(jobs);
+  pack_transpose_kernel<<<dim3(gx, gy, jobs.count + (jobs.diag ? 1 : 0)), 256, 0, st>>>(jobs);
   return hipGetLastError();
 }
 

@@ -24,12 +24,25 @@ hipError_t launch_rmsnorm_fwd(const void* x, int x_type, const void* g, void* n,
                               int T, int d, float eps, hipStream_t st);
 // dx_total = resid + r * (dn*g - xh * mean(dn*g*xh)),  xh = x*r;  dg (+)= sum_T dn*xh.
 // x of x_type; g of g_type; dn float32; resid of resid_type (nullable: no residual term); outputs: out_f32 (nullable),
-// out_lp (nullable, lp_type).  dg_partial: workspace float[rmsnorm_bwd_partial_rows(T) * d].
+// out_lp (nullable, lp_type).  dg_partial: workspace float[rmsnorm_bwd_partial_rows(T) * d]; dg == nullptr leaves the sums there.
 int rmsnorm_bwd_partial_rows(int T);
 hipError_t launch_rmsnorm_bwd(const void* x, int x_type, const void* g, int g_type, const float* r,
                               const float* dn, const void* resid, int resid_type, float* out_f32,
                               void* out_lp, int lp_type, float* dg, float* dg_partial, int accumulate,
                               int T, int d, hipStream_t st);
+
+// Sums a layer's backward leaves for its end: dg[k] (+)= sum of the nrows partial rows part[k] (calls of launch_rmsnorm_bwd
+// with dg == nullptr, nrows = rmsnorm_bwd_partial_rows(T)) and, with dtable, what launch_relpos_diag_bwd does.
+struct LayerTail {
+  const float* part[3];
+  float* dg[3];
+  int ndg, nrows, d, accumulate;
+  const float* ddiag;
+  float* dtable;  // nullable
+  int S, H, num_buckets;
+  RelposLut lut;
+};
+hipError_t launch_layer_tail(const LayerTail& t, hipStream_t st);
 
 // ------------------------------------------------------------------ GEMM
 // C[m,n] = sum over segments s, k < K_s of A_s(m,k) * B_s(n,k), float32 accumulation.
@@ -136,6 +149,11 @@ struct PackJob {
 struct PackJobs {
   PackJob j[8];
   int count;
+  // with diag: what launch_relpos_diag does for a bf16 table, in the same launch
+  const void* table;
+  float* diag;
+  int S, H;
+  RelposLut lut;
 };
 hipError_t launch_pack_transpose_multi(const PackJobs& jobs, hipStream_t st);
 

@@ -115,30 +115,11 @@ hipError_t launch_relpos_diag(const void* table, int dtype, float* diag, int S, 
   return hipGetLastError();
 }
 
-// One wave per (bucket c, head h).  Buckets are contiguous distance ranges on each side, so the
-// wave sums ddiag over its range in a fixed order (deterministic).
+// One wave per (bucket c, head h).
 __global__ void relpos_diag_bwd_kernel(const float* __restrict__ ddiag, float* __restrict__ dtable, int S,
                                        int H, int num_buckets, RelposLut lut, int accumulate) {
   const int c = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  const int w = 2 * S - 1;
-  int side = 0, cl = c;
-  if (lut.bidirectional && c >= lut.n_side) { side = 1; cl = c - lut.n_side; }
-  int n_lo, n_hi;  // inclusive distance range of this bucket
-  if (cl < lut.max_exact) {
-    n_lo = n_hi = cl;
-  } else {
-    const int k = cl - lut.max_exact;  // logarithmic index
-    n_lo = (k == 0) ? lut.max_exact : lut.thr[k - 1];
-    n_hi = (cl == lut.n_side - 1) ? (S - 1) : (lut.thr[k] - 1);
-  }
-  if (n_hi > S - 1) n_hi = S - 1;
-  if (side == 1 && n_lo == 0) n_lo = 1;  // distance 0 belongs to the non-positive side
-  float s = 0.f;
-  for (int n = n_lo + lane; n <= n_hi; n += kWave) {
-    const int delta = side ? n : -n;
-    s += ddiag[(size_t)h * w + delta + (S - 1)];
-  }
-  s = wave_sum(s);
+  const float s = relpos_fold_bucket(ddiag + (size_t)h * (2 * S - 1), c, S, lut);
   if (lane == 0) {
     float* o = dtable + c * H + h;
     *o = accumulate ? (*o + s) : s;

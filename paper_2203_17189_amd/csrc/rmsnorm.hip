@@ -182,11 +182,10 @@ __global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_bwd_kernel(
 }
 
 // 1024 threads = 32 columns x 32 row slices; the slices meet in LDS in a fixed order.
-__global__ __launch_bounds__(1024) void rmsnorm_dg_reduce_kernel(const float* __restrict__ part, int nrows, int d,
-                                                                 float* __restrict__ dg, int accumulate) {
-  __shared__ float red[32][33];
+__device__ __forceinline__ void dg_reduce_block(const float* __restrict__ part, int nrows, int d, float* __restrict__ dg,
+                                                int accumulate, int block, float (*red)[33]) {
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int c = blockIdx.x * 32 + tx;
+  const int c = block * 32 + tx;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
   if (c < d) {
     int i = ty;
@@ -206,6 +205,28 @@ __global__ __launch_bounds__(1024) void rmsnorm_dg_reduce_kernel(const float* __
     for (int k = 0; k < 32; ++k) t += red[k][tx];
     dg[c] = accumulate ? dg[c] + t : t;
   }
+}
+__global__ __launch_bounds__(1024) void rmsnorm_dg_reduce_kernel(const float* __restrict__ part, int nrows, int d,
+                                                                 float* __restrict__ dg, int accumulate) {
+  __shared__ float red[32][33];
+  dg_reduce_block(part, nrows, d, dg, accumulate, blockIdx.x, red);
+}
+// What a layer's backward has left to add up, in one launch: the scale gradients of its norms and, where the layer owns
+// its bias table, the fold of the bias-gradient diagonals into buckets.  Launched one by one each costs the 4 to 5 us
+// that any launch does.
+__global__ __launch_bounds__(1024) void layer_tail_kernel(LayerTail t) {
+  __shared__ float red[32][33];
+  const int per = (t.d + 31) / 32, nd = per * t.ndg;
+  if ((int)blockIdx.x < nd) {
+    const int k = blockIdx.x / per;
+    dg_reduce_block(t.part[k], t.nrows, t.d, t.dg[k], t.accumulate, blockIdx.x - k * per, red);
+    return;
+  }
+  const int idx = ((int)blockIdx.x - nd) * 16 + (threadIdx.x >> 6);  // one wave per (bucket, head)
+  if (idx >= t.num_buckets * t.H) return;
+  const int c = idx / t.H, h = idx - c * t.H;
+  const float s = relpos_fold_bucket(t.ddiag + (size_t)h * (2 * t.S - 1), c, t.S, t.lut);
+  if ((threadIdx.x & 63) == 0) t.dtable[idx] = t.accumulate ? t.dtable[idx] + s : s;
 }
 
 template <typename TX, typename TO>
@@ -302,8 +323,16 @@ hipError_t launch_rmsnorm_bwd(const void* x, int x_type, const void* g, int g_ty
                                                  st);
   else
     return hipErrorInvalidValue;
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !dg) return e;  // without dg the partial rows stay for launch_layer_tail
   rmsnorm_dg_reduce_kernel<<<ceil_div(d, 32), 1024, 0, st>>>(dg_partial, grid, d, dg, accumulate);
+  return hipGetLastError();
+}
+
+hipError_t launch_layer_tail(const LayerTail& t, hipStream_t st) {
+  if (t.ndg < 0 || t.ndg > 3) return hipErrorInvalidValue;
+  const int blocks = ceil_div(t.d, 32) * t.ndg + (t.dtable ? ceil_div((int64_t)t.num_buckets * t.H, 16) : 0);
+  if (blocks == 0) return hipSuccess;
+  layer_tail_kernel<<<blocks, 1024, 0, st>>>(t);
   return hipGetLastError();
 }
 

@@ -225,10 +225,10 @@ int layers_backward(const Layers& s, const void* enc_out, float* denc_acc, int a
       // the first layer processed stores its denc, the others add theirs to it
       T5_SUB(bwd_cross_attn(&bc, D, enc_out, &s.xw[l], S, BW, denc_acc, &s.xg[l], acc, st, true, l != s.L - 1));
       T5_SUB(bwd_self_attn(&bc, D, s.lut, s.x_of(l), BW.dh1, BW.dh1_lp, &s.lw[l], S, BW, attn_mfma, far, dx,
-                           &s.lg[l], acc, st, false));
+                           &s.lg[l], &s.xg[l], acc, st, false));
     } else {
       T5_SUB(bwd_self_attn(&bc, D, s.lut, s.x_of(l), BW.dh, BW.dh_lp, &s.lw[l], S, BW, attn_mfma, far, dx,
-                           &s.lg[l], acc, st, false));
+                           &s.lg[l], nullptr, acc, st, false));
     }
     // the next layer rewrites the workspace (and, with remat, the stash) the side GEMMs read
     T5_TRY(guard.join());
