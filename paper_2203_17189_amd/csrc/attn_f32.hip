@@ -132,6 +132,31 @@ __device__ __forceinline__ void store_cols(float* row, const f32x16 (&acc)[CT], 
     }
 }
 
+// mul_cols for a tile whose rows some lanes must not see (row j counts for a lane where j <= last), without multiplying
+// what they must not see: a zero probability times an infinity is not zero.  Plain multiply-adds, for the causal
+// forward's diagonal tiles that hold a value that is not finite (a padding position's, say).
+template <int CT, int LD>
+__device__ __forceinline__ void mul_cols_masked(f32x16 (&acc)[CT], const float* tile, const f32x16& p, int last, int lane) {
+  const int g = lane >> 5;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float mine = p[r], other = __shfl_xor(mine, 32, 64);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int j = ((r >> 2) << 3) + half * 4 + (r & 3);
+      const float pj = half == g ? mine : other;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const float v = tile[j * LD + ct * 32 + ((q >> 2) << 3) + g * 4 + (q & 3)];
+          acc[ct][q] = j <= last ? fmaf(pj, v, acc[ct][q]) : acc[ct][q];
+        }
+      __builtin_amdgcn_sched_barrier(0);  // (rare path: no registers for operands in advance)
+    }
+  }
+}
+
 // ---- forward.  One workgroup per (b, h, NW*32 queries).
 template <int DKP, int NW, bool VEC>
 __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag,
@@ -140,6 +165,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   constexpr int CT = DKP / 32, KL = DKP + 4, VL = DKP + 8, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Kt[32 * KL];
   __shared__ __attribute__((aligned(16))) float Vt[32 * VL];
+  __shared__ int v_bad;  // the tile holds a value that is not finite
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, wave = tid >> 6;
   const int S = a.S, Sk = a.Sk, I = a.H * a.dk;
   int qt = blockIdx.x % n_tiles;
@@ -165,9 +191,21 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   tv.load(vb, io.ldkv, Sk, a.dk, tid);
   for (int j0 = 0; j0 < keys; j0 += 32) {
     __syncthreads();  // the tile before this one has been used
+    if (tid == 0) v_bad = 0;
+    bool bad = false;
+    if (a.causal && j0 + 31 > i0) {  // (the tiles that a mask cuts through)
+#pragma unroll
+      for (int q = 0; q < Tile32<DKP, NT, VEC>::N; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad |= !(__builtin_fabsf(tv.v[q][e]) <= 3.402823466e38f);
+    }
     tk.template put<KL>(Kt, a.dk, tid);
     tv.template put<VL>(Vt, a.dk, tid);
     __syncthreads();
+    if (a.causal && j0 + 31 > i0) {
+      if (bad) v_bad = 1;
+      __syncthreads();
+    }
     // (requested before the next tile: loads return in order, and these are needed first)
     float bias[16];
 #pragma unroll
@@ -208,7 +246,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
-    mul_cols<CT, VL>(o, Vt, s, lane);
+    if (a.causal && j0 + 31 > iw && v_bad) mul_cols_masked<CT, VL>(o, Vt, s, i - j0, lane);
+    else mul_cols<CT, VL>(o, Vt, s, lane);
   }
   l += __shfl_xor(l, 32, 64);
   if (i < S) {

@@ -56,3 +56,23 @@ def test_decoder_f32_matrix(seq, enc_seq):
         g = {k: v for k, v in g.items() if k not in ("rel_table",)}
     gy, gdx, gdenc, gg = run_decoder_block_gpu(cfg, w, x, enc, dy)
     _check([("y", gy, y), ("dx", gdx, dx), ("denc", gdenc, denc)] + [(n, gg[n], g[n]) for n in g])
+
+
+@pytest.mark.parametrize("seq,d_kv", [(20, 16), (100, 64)])
+def test_causal_rows_before_a_nan_token(seq, d_kv):
+    """A token that is not finite changes no row before it (float32, causal), also inside its own tile of keys."""
+    import torch
+    import paper_2203_17189_amd as P
+    from parity_util import upload_case
+    cfg = replace(C, batch=1, seq=seq, d_kv=d_kv, causal=True, name="f32_nan")
+    w, x, dy = make_case(cfg)
+    dw, dx, _ = upload_case(cfg, w, x, dy)
+    y0, _ = P.t5_block_fwd(cfg, dx, dw)
+    bad = seq - 7
+    dx2 = dx.clone().view(seq, -1)
+    dx2[bad] = float("nan")
+    y1, _ = P.t5_block_fwd(cfg, dx2.view_as(dx), dw)
+    y0, y1 = y0.view(seq, -1), y1.view(seq, -1)
+    # the plain multiply-adds of that tile differ from the matrix unit's by float32 rounding
+    assert rel_err(y1[:bad].cpu().numpy().astype(np.float64), y0[:bad].cpu().numpy().astype(np.float64))[0] <= TOL_F32[0]
+    assert torch.isnan(y1[bad:]).any(dim=1).all()
