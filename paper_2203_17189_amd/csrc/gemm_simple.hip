@@ -1,4 +1,4 @@
-// Reference-grade GEMM for the float32 block and for bf16 shapes the MFMA kernel does not take:
+// Reference-grade GEMM for bf16 shapes the MFMA kernel does not take (and float32 problems beyond its grid):
 // 64x64 output tile, 16-deep LDS stages, float32 FMA, any shape and either operand orientation.
 // Also: the elementwise gated-GELU of the unfused path and the bf16 weight transpose-pack.
 #include "kernels.h"
