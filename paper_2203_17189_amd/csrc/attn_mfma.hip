@@ -751,15 +751,26 @@ __global__ __launch_bounds__(256) void attn_ddiag_reduce_kernel(const float* __r
 // ------------------------------------------------------------------------------------------------
 // dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
 // ------------------------------------------------------------------------------------------------
+// Waves per SIMD of the dk / dv kernel.  With 64 channels and without dropout the causal and the bias-free forms run
+// three: at 168 registers the bias values are read where they are used, which the third wave covers (12 causal layers of
+// 32 x 512 tokens, 12 heads: 853 -> 808 us; 12 cross-attention layers of 32 x 114: 332 -> 328 us).  The non-causal form
+// with bias stays at two and requests its bias values ahead: with three, 128 x 512 tokens took 372 instead of 361 us.
+// Dropout's keys do not fit beside a third wave.
+constexpr bool dkv_three_waves(int dk, bool causal, bool bias, bool drop) {
+  return dk == 64 && !drop && (causal || !bias);
+}
+
 template <int DK, bool CAUSAL, bool BIAS, bool DROP>
-__global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kernel(AttnIO io,
-                                                                const bf16* __restrict__ dout,
-                                                                const float* __restrict__ diag,
-                                                                const float* __restrict__ lse,
-                                                                const float* __restrict__ dvec,
-                                                                AttnDims a) {
+__global__ __launch_bounds__(256, DK == 64 ? (dkv_three_waves(DK, CAUSAL, BIAS, DROP) ? 3 : 2) : 1)
+void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
+                              const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
   constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
   constexpr int TILE = BQ * DK * 2, STG = 2 * TILE;  // a stage holds a Q tile then a dO tile
+  // How the queries past the end of a ragged last tile come to probability zero: by a masked copy of the element loop,
+  // or from the accumulator seeds.  The copy costs registers, which the three-wave forms do not have, and time elsewhere
+  // (128 channels, causal, 16 x 2048: 971 -> 960 us without it).  The non-causal 64-channel form with bias keeps it: without
+  // it 32 x 1024 tokens with 32 heads gain (630 -> 602 us) but 128 x 512 with 12 heads lose (361 -> 371 us).
+  constexpr bool TAIL_MASK = DK == 64 && BIAS && !CAUSAL;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // The score and dP accumulators start from -lse/scale and -dvec, so that the MFMA results are
   // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
@@ -854,6 +865,11 @@ __global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     const int q0 = it * BQ;
     const int st = (it - it_begin) & 1;
     dma_wait_barrier();  // tile `it` and its lse / dvec slices landed; other stage is free
+    if (!TAIL_MASK && q0 + BQ > S) {
+      // queries past the end: their score accumulators start from the infinity that makes their probabilities zero
+      if (tid < BQ && q0 + tid >= S) lse_all[st * BQ + tid] = sc > 0.f ? -INFINITY : INFINITY;
+      __syncthreads();
+    }
     uint32_t nkey = 0;
     const bool more = it + 1 < n_it;
     if (more) {
@@ -880,7 +896,7 @@ __global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
       // is hidden behind the matrix work instead of stalling the softmax arithmetic (read at first use they
       // put an LDS round trip on every sub-tile's dependent chain: 651 -> 635 us at 64 channels, the sixteen
       // registers are there at two waves per SIMD)
-      constexpr bool HOIST = BIAS;
+      constexpr bool HOIST = BIAS && !dkv_three_waves(DK, CAUSAL, BIAS, DROP);
       float bias[16];
       // Bias of (query i, key j) sits at dg[j_loc + S - 1 - i].  Where every query of the tile exists the sixteen
       // values of a lane are one pointer and constant offsets: register r belongs to query
@@ -927,14 +943,14 @@ __global__ __launch_bounds__(256, DK == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
       }
       // with 64 channels the second copy of the loop costs a wave per SIMD in registers: mask always
       // some key here lies after some query, or the tile reaches past the last query (both wave-uniform)
-      if ((CAUSAL && (DK == 64 || j0 + wave * 32 + 31 > q0 + qb * 32)) || q0 + BQ > S) {
+      if ((TAIL_MASK && q0 + BQ > S) || (CAUSAL && (DK == 64 || j0 + wave * 32 + 31 > q0 + qb * 32))) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
           const int i = q0 + il;
           float p = BIAS ? fast_exp2(fmaf(s[r], sc, HOIST ? bias[r] : bq[27 - (((r >> 2) << 3) + (r & 3))]))
                          : fast_exp2(s[r] * sc);
-          if ((CAUSAL && j > i) || i >= S) p = 0.f;
+          if ((CAUSAL && j > i) || (TAIL_MASK && i >= S)) p = 0.f;
           if constexpr (DROP) {
             const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
             s[r] = keep ? p : 0.f;
