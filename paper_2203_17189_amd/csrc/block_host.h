@@ -242,8 +242,8 @@ size_t carve_bwd(const Dims& D, void* base, BwdWs* w) {
     t.wg_partials = cv.take<float>(wgrad_partials_bytes(D));
     AttnDims ad;
     std::memset(&ad, 0, sizeof(ad));
-    ad.B = D.B; ad.S = D.S; ad.H = D.H;
-    t.ddiag_part = cv.take<float>(D.S % 128 == 0 ? attn_ddiag_part_bytes(ad) : 0);
+    ad.B = D.B; ad.S = ad.Sk = D.S; ad.H = D.H; ad.dk = D.dk; ad.bias = 1;
+    if (attn_mfma_supported(ad)) t.ddiag_part = cv.take<float>(attn_ddiag_part_bytes(ad));  // (only these kernels use it)
   }
   if (w) *w = t;
   return cv.off;

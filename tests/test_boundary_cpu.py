@@ -3,6 +3,7 @@ and rejects bad arguments before touching the GPU (so these run on a machine wit
 import ctypes as C
 import os
 import re
+from dataclasses import replace
 
 import pytest
 
@@ -40,6 +41,21 @@ def test_size_queries():
     assert P.t5_block_stash_bytes(bad) == 0 and P.t5_block_workspace_bytes(bad) == 0
     assert P.adafactor_workspace_bytes(0, 5, True) == 0
     assert P.adafactor_workspace_bytes(64, 64, True) > 0
+
+
+@pytest.mark.parametrize("seq", [33, 100, 127, 128, 129, 333, 500])
+@pytest.mark.parametrize("d_kv", [64, 128])
+def test_reproducible_workspace_holds_the_bias_windows(seq, d_kv):
+    """The dq kernel of the reproducible mode writes one row per (batch, head, 128 queries): a window of up to 64 *
+    ceil(seq / 32) diagonals, 4 more for its upper lane half and two sums.  With fewer than 1024 tokens no weight
+    gradient is split, so that buffer is all the mode adds to the workspace, whatever the length is a multiple of."""
+    cfg = replace(SI.CONFIGS["c3_base"], batch=1000 // seq, seq=seq, d_model=64, n_heads=2, d_kv=d_kv, d_ff=64)
+    rows = cfg.batch * cfg.n_heads * -(-seq // 128)
+    need = 4 * (rows - 1) * (64 * -(-seq // 32) + 8) + 4 * (64 * -(-seq // 32) + 6)
+    for size, c in ((P.t5_block_workspace_bytes, cfg),
+                    (P.t5_decoder_block_workspace_bytes, replace(cfg, causal=True, enc_seq=77))):
+        assert P.t5_block_kernel_path(c) & P.PATH_MFMA_ATTN_BWD
+        assert size(replace(c, deterministic=True)) >= size(c) + need
 
 
 def test_relpos_validation():

@@ -48,3 +48,19 @@ def test_stack_ragged_tokens_grouped():
         for n, a in out[0]["layers"][l].items():
             # K = 185 products of float32-accumulated bf16 pairs: reordering moves a sum by a few ulps of its largest term
             assert rel_err(to_np(a), to_np(out[1]["layers"][l][n]))[0] <= 2e-5, (l, n)
+
+
+@pytest.mark.parametrize("batch,seq", [(3, 43), (7, 331)])
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_backward_stays_inside_its_workspace(batch, seq, deterministic):
+    """Bytes behind the workspace keep their values."""
+    import torch
+    import paper_2203_17189_amd as P
+    from parity_util import upload_case
+    cfg = replace(BASE, batch=batch, seq=seq, deterministic=deterministic, name="ragged_guard")
+    dw, dx, ddy = upload_case(cfg, *make_case(cfg))
+    _, stash = P.t5_block_fwd(cfg, dx, dw)
+    n = P.t5_block_workspace_bytes(cfg)
+    buf = torch.full((n + (4 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+    P.t5_block_bwd(cfg, ddy, dx, dw, stash, workspace=buf[:n])
+    assert bool((buf[n:] == 0xA5).all())
