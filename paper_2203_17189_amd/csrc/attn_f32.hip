@@ -11,6 +11,11 @@
 // the forward against some 200 vector instructions.  Tiles of 32 rows travel through registers while the previous
 // tile is used; rows past the end and channels past d_kv are zeros, so no shape needs another path.
 //
+// A bias table masks with -inf or with the lowest float32, which times log2(e) overflows to -inf, and a whole tile may be
+// masked so: the forward keeps its scores in natural units until the maximum has been taken off them, and that maximum
+// may be -inf.  The backward scales first, an instruction less per element (masked ones are zero either way), so the
+// log-sum it reads is kept where it stays finite in log2 units.
+//
 // The bias gradient (dq) adds each ds element to its diagonal in LDS and one global atomic per diagonal and workgroup
 // follows; one global atomic per element took longer than everything else.
 #include "kernels.h"
@@ -177,7 +182,6 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   const float* dg = a.bias ? diag + (size_t)h * (2 * S - 1) + (S - 1) - il : nullptr;  // dg[j] = bias(j - i)
   f32x4 q[DKP / 8];
   load_row<DKP, VEC>(q, (const float*)io.q + ((size_t)b * S + il) * io.ldq + h * a.dk, a.dk, g);
-  const float sc = a.scale * kLog2e;
   uint32_t k1 = 0;
   if (a.drop.on) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + il)));
   f32x16 o[CT];
@@ -225,19 +229,20 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-      float x = fmaf(s[r], sc, bias[r] * kLog2e);
+      float x = fmaf(s[r], a.scale, bias[r]);
       if ((a.causal && j > i) || j >= Sk) x = -INFINITY;
       s[r] = x;
       mx = fmaxf(mx, x);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - mn);  // key 0 is visible to every query: mn is finite
+    const float mn = fmaxf(m, mx), base = mn == -INFINITY ? 0.f : mn;  // (no visible key so far: every p and l are zero)
+    const float alpha = __builtin_amdgcn_exp2f((m - base) * kLog2e);
     m = mn;
     float ls = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-      const float p = __builtin_amdgcn_exp2f(s[r] - mn);
+      const float p = __builtin_amdgcn_exp2f((s[r] - base) * kLog2e);
       ls += p;  // the normaliser is that of the undropped probabilities
       s[r] = a.drop.on ? (drop_keep16(a.drop, k1 ^ (uint32_t)j) ? p : 0.f) : p;
     }
@@ -252,7 +257,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   l += __shfl_xor(l, 32, 64);
   if (i < S) {
     store_cols<CT, VEC>(c + ((size_t)b * S + i) * I + h * a.dk, o, (a.drop.on ? a.drop.scale : 1.f) / l, a.dk, g);
-    if (g == 0) lse[((size_t)b * a.H + h) * S + i] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+    const float ls = fmaf(__builtin_amdgcn_logf(l), kLn2, m);
+    if (g == 0) lse[((size_t)b * a.H + h) * S + i] = ls < -2.35e38f ? -2.35e38f : ls;
   }
 }
 

@@ -76,3 +76,38 @@ def test_causal_rows_before_a_nan_token(seq, d_kv):
     # the plain multiply-adds of that tile differ from the matrix unit's by float32 rounding
     assert rel_err(y1[:bad].cpu().numpy().astype(np.float64), y0[:bad].cpu().numpy().astype(np.float64))[0] <= TOL_F32[0]
     assert torch.isnan(y1[bad:]).any(dim=1).all()
+
+
+FAR = {"-inf": -np.inf, "lowest": np.finfo(np.float32).min}
+
+
+@pytest.mark.parametrize("value", sorted(FAR))
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("seq,d_kv", [(200, 16), (130, 64), (70, 18)])
+def test_local_attention_by_the_bias_table(seq, d_kv, causal, value):
+    """Far buckets of -inf, or of the lowest float32 (which times log2 e is -inf): whole key tiles without a visible key,
+    before (causal) or around the tiles that have some."""
+    cfg = replace(C, batch=2, seq=seq, d_kv=d_kv, causal=causal, attn_scale=d_kv ** -0.5, name="f32_local")
+    w, x, dy = make_case(cfg)
+    w = dict(w, rel_table=w["rel_table"].copy())
+    near = 20 if causal else 12  # buckets of distances below about 25 (causal) and 12
+    side = 32 if causal else 16
+    far = np.arange(32) % side >= near
+    w["rel_table"][far] = FAR[value]
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    assert np.all(gg["rel_table"][far] == 0)
+    _check([("y", gy, y), ("dx", gdx, dx)] + [(n, gg[n], g[n]) for n in g])
+
+
+def test_every_bucket_at_the_lowest_value():
+    """Scores that all round to the same number: uniform attention, as the maximum of the whole row gives it."""
+    cfg = replace(C, batch=1, seq=40, name="f32_lowest")
+    w, x, dy = make_case(cfg)
+    w = dict(w, rel_table=np.full_like(w["rel_table"], FAR["lowest"]))
+    y, _ = O.block_fwd(cfg, x, w)
+    import paper_2203_17189_amd as P
+    from parity_util import to_np, upload_case
+    dw, dx, _ = upload_case(cfg, w, x, dy)
+    _check([("y", to_np(P.t5_block_fwd(cfg, dx, dw)[0]), y)])
