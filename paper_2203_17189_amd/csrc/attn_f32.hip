@@ -139,34 +139,33 @@ __device__ __forceinline__ void store_cols(float* row, const f32x16 (&acc)[CT], 
 
 // mul_cols for a tile whose rows some lanes must not see (row j counts for a lane where j <= last), without multiplying
 // what they must not see: a zero probability times an infinity is not zero.  Plain multiply-adds, for the causal
-// forward's diagonal tiles that hold a value that is not finite (a padding position's, say).
+// forward's diagonal tiles that hold a value that is not finite (a padding position's, say).  Rolled, so that it holds
+// one row's operands: unrolled it took the whole kernel from two wavefronts per SIMD to one.
 template <int CT, int LD>
 __device__ __forceinline__ void mul_cols_masked(f32x16 (&acc)[CT], const float* tile, const f32x16& p, int last, int lane) {
   const int g = lane >> 5;
+#pragma unroll 1
+  for (int j = 0; j < 32; ++j) {
+    const float mine = p[(j >> 3) * 4 + (j & 3)], other = __shfl_xor(mine, 32, 64);
+    const float pj = ((j >> 2) & 1) == g ? mine : other;
+    const float* t = tile + j * LD + g * 4;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float mine = p[r], other = __shfl_xor(mine, 32, 64);
+    for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int j = ((r >> 2) << 3) + half * 4 + (r & 3);
-      const float pj = half == g ? mine : other;
+      for (int rq = 0; rq < 4; ++rq) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(t + ct * 32 + rq * 8);
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const float v = tile[j * LD + ct * 32 + ((q >> 2) << 3) + g * 4 + (q & 3)];
-          acc[ct][q] = j <= last ? fmaf(pj, v, acc[ct][q]) : acc[ct][q];
-        }
-      __builtin_amdgcn_sched_barrier(0);  // (rare path: no registers for operands in advance)
-    }
+        for (int e = 0; e < 4; ++e) acc[ct][rq * 4 + e] = j <= last ? fmaf(pj, v[e], acc[ct][rq * 4 + e]) : acc[ct][rq * 4 + e];
+      }
   }
 }
 
-// ---- forward.  One workgroup per (b, h, NW*32 queries).
-template <int DKP, int NW, bool VEC>
-__global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag,
-                                                               float* __restrict__ c, float* __restrict__ lse, AttnDims a,
-                                                               int n_tiles) {
+// ---- forward.  One workgroup per (b, h, NW*32 queries).  Up to 64 channels two wavefronts share a SIMD (three up to 32):
+// one hides the other's softmax arithmetic and the barriers around the tiles.
+template <int DKP, int NW, bool VEC, bool CAUSAL>
+__global__ __launch_bounds__(NW * 64, DKP == 32 ? 3 : DKP == 64 ? 2 : 1)
+void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag, float* __restrict__ c, float* __restrict__ lse,
+                         AttnDims a, int n_tiles) {
   constexpr int CT = DKP / 32, KL = DKP + 4, VL = DKP + 8, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Kt[32 * KL];
   __shared__ __attribute__((aligned(16))) float Vt[32 * VL];
@@ -175,7 +174,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
   const int S = a.S, Sk = a.Sk, I = a.H * a.dk;
   int qt = blockIdx.x % n_tiles;
   const int bh = blockIdx.x / n_tiles, h = bh % a.H, b = bh / a.H;
-  if (a.causal) qt = n_tiles - 1 - qt;  // long rows first
+  if (CAUSAL) qt = n_tiles - 1 - qt;  // long rows first
   const int i0 = qt * NW * 32, iw = i0 + wave * 32, i = iw + (lane & 31), il = i < S ? i : S - 1;
   const float* kb = (const float*)io.k + (size_t)b * Sk * io.ldkv + h * a.dk;
   const float* vb = (const float*)io.v + (size_t)b * Sk * io.ldkv + h * a.dk;
@@ -188,16 +187,16 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) clear(o[ct]);
   float m = -INFINITY, l = 0.f;
-  const int keys = a.causal ? (i0 + NW * 32 < S ? i0 + NW * 32 : S) : Sk;
-  const int my_keys = a.causal ? (iw + 32 < keys ? iw + 32 : keys) : Sk;  // keys this wavefront's queries see
+  const int keys = CAUSAL ? (i0 + NW * 32 < S ? i0 + NW * 32 : S) : Sk;
+  const int my_keys = CAUSAL ? (iw + 32 < keys ? iw + 32 : keys) : Sk;  // keys this wavefront's queries see
   Tile32<DKP, NT, VEC> tk, tv;
   tk.load(kb, io.ldkv, Sk, a.dk, tid);
   tv.load(vb, io.ldkv, Sk, a.dk, tid);
   for (int j0 = 0; j0 < keys; j0 += 32) {
     __syncthreads();  // the tile before this one has been used
-    if (tid == 0) v_bad = 0;
     bool bad = false;
-    if (a.causal && j0 + 31 > i0) {  // (the tiles that a mask cuts through)
+    if (CAUSAL && j0 + 31 > i0) {  // (the tiles that a mask cuts through)
+      if (tid == 0) v_bad = 0;
 #pragma unroll
       for (int q = 0; q < Tile32<DKP, NT, VEC>::N; ++q)
 #pragma unroll
@@ -206,7 +205,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
     tk.template put<KL>(Kt, a.dk, tid);
     tv.template put<VL>(Vt, a.dk, tid);
     __syncthreads();
-    if (a.causal && j0 + 31 > i0) {
+    if (CAUSAL && j0 + 31 > i0) {
       if (bad) v_bad = 1;
       __syncthreads();
     }
@@ -230,7 +229,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
       float x = fmaf(s[r], a.scale, bias[r]);
-      if ((a.causal && j > i) || j >= Sk) x = -INFINITY;
+      if ((CAUSAL && j > i) || j >= Sk) x = -INFINITY;
       s[r] = x;
       mx = fmaxf(mx, x);
     }
@@ -251,8 +250,13 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnIO io, const 
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
-    if (a.causal && j0 + 31 > iw && v_bad) mul_cols_masked<CT, VL>(o, Vt, s, i - j0, lane);
-    else mul_cols<CT, VL>(o, Vt, s, lane);
+    if constexpr (CAUSAL) {
+      if (j0 + 31 > iw && v_bad) {
+        mul_cols_masked<CT, VL>(o, Vt, s, i - j0, lane);
+        continue;
+      }
+    }
+    mul_cols<CT, VL>(o, Vt, s, lane);
   }
   l += __shfl_xor(l, 32, 64);
   if (i < S) {
@@ -452,16 +456,21 @@ bool vec_ok(const AttnIO& io, const AttnDims& a, const void* c, const void* dc) 
   return (all & 15) == 0 && a.dk % 4 == 0 && io.ldq % 4 == 0 && io.ldkv % 4 == 0 && io.lddq % 4 == 0 && io.lddkv % 4 == 0;
 }
 
-// Wavefronts per workgroup: two share each K/V (or Q/dO) tile; one where a sequence has no more than 32 rows.
+// Wavefronts per workgroup: two share each K/V (or Q/dO) tile; one where a sequence has no more than 32 rows.  In the
+// forward four, beyond 64 rows: the second workgroup of two wavefronts on a compute unit lands on the SIMDs of the first
+// and leaves the other two idle (16 x 250 tokens, 6 heads of 64: 48 us with two, 32 with four; 12 heads 53 and 51).
+template <int DKP, bool VEC, bool CAUSAL>
+hipError_t launch_fwd_form(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
+  const int bh = a.B * a.H, nt = ceil_div(a.S, 128);
+  if (a.S <= 32) attn_fwd_f32_kernel<DKP, 1, VEC, CAUSAL><<<bh, 64, 0, st>>>(io, diag, c, lse, a, 1);
+  else if (a.S <= 64) attn_fwd_f32_kernel<DKP, 2, VEC, CAUSAL><<<bh, 128, 0, st>>>(io, diag, c, lse, a, 1);
+  else attn_fwd_f32_kernel<DKP, 4, VEC, CAUSAL><<<nt * bh, 256, 0, st>>>(io, diag, c, lse, a, nt);
+  return hipGetLastError();
+}
 template <int DKP, bool VEC>
 hipError_t launch_fwd(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
-  if (a.S <= 32) {
-    attn_fwd_f32_kernel<DKP, 1, VEC><<<a.B * a.H, 64, 0, st>>>(io, diag, c, lse, a, 1);
-  } else {
-    const int nt = ceil_div(a.S, 64);
-    attn_fwd_f32_kernel<DKP, 2, VEC><<<nt * a.B * a.H, 128, 0, st>>>(io, diag, c, lse, a, nt);
-  }
-  return hipGetLastError();
+  return a.causal ? launch_fwd_form<DKP, VEC, true>(io, diag, c, lse, a, st)
+                  : launch_fwd_form<DKP, VEC, false>(io, diag, c, lse, a, st);
 }
 template <int DKP, bool VEC>
 hipError_t launch_bwd(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse, float* dvec,

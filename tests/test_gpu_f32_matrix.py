@@ -58,7 +58,7 @@ def test_decoder_f32_matrix(seq, enc_seq):
     _check([("y", gy, y), ("dx", gdx, dx), ("denc", gdenc, denc)] + [(n, gg[n], g[n]) for n in g])
 
 
-@pytest.mark.parametrize("seq,d_kv", [(20, 16), (100, 64)])
+@pytest.mark.parametrize("seq,d_kv", [(20, 16), (50, 16), (100, 64), (140, 128)])
 def test_causal_rows_before_a_nan_token(seq, d_kv):
     """A token that is not finite changes no row before it (float32, causal), also inside its own tile of keys."""
     import torch
