@@ -9,7 +9,13 @@
 //
 // Bound: the float32 matrix rate (157 TFLOP/s nominal): 32 keys x 32 queries of 64 channels are 64 MFMAs of 64 cycles in
 // the forward against some 200 vector instructions.  Tiles of 32 rows travel through registers while the previous
-// tile is used; rows past the end and channels past d_kv are zeros, so no shape needs another path.
+// tile is used; rows past the end repeat the last one with probability zero (where that row is not finite, what it
+// contributes to is not either) and channels past d_kv are zeros, so no shape needs another path.
+//
+// Causal rows and values that are not finite: a masked element's zero times an infinity is not zero, so the tiles that the
+// mask cuts through are looked over.  A value row that is not finite reaches only the queries at or after it; a query row
+// (or its output gradient) only the keys at or before it, whose dk and dv are NaN then.  dq needs no such care: a key that
+// is not finite makes dk of every earlier position not finite, and with it their dx.
 //
 // A bias table masks with -inf or with the lowest float32, which times log2(e) overflows to -inf, and a whole tile may be
 // masked so: the forward keeps its scores in natural units until the maximum has been taken off them, and that maximum
@@ -57,6 +63,27 @@ struct Tile32 {
       for (int e = 0; e < 4; ++e) x[e] = c + e < dk ? v[i][e] : 0.f;
       *reinterpret_cast<f32x4*>(dst + (q / W) * LD + c) = x;
     }
+  }
+  __device__ __forceinline__ bool finite(int i) const {  // slot i of this thread
+    bool ok = true;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ok &= __builtin_fabsf(v[i][e]) <= 3.402823466e38f;
+    return ok;
+  }
+  // 1 in bad[row] for every row of the tile that holds a value that is not finite
+  __device__ __forceinline__ void mark(int* bad, int tid) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (!finite(i)) bad[(tid + i * NT) / W] = 1;
+  }
+  // clears the rows of `bad` in LDS
+  template <int LD>
+  static __device__ __forceinline__ void clear_rows(float* dst, uint32_t bad, int tid) {
+#pragma unroll 1
+    for (int q = tid; q < 32 * W; q += NT)
+      if ((bad >> (q / W)) & 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[(q / W) * LD + (q % W) * 4 + e] = 0.f;
   }
 };
 // One row's channels as MFMA operands: group s of 8 channels gives this lane half channels 8s + 4g .. + 3.
@@ -198,9 +225,7 @@ void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag, float* __res
     if (CAUSAL && j0 + 31 > i0) {  // (the tiles that a mask cuts through)
       if (tid == 0) v_bad = 0;
 #pragma unroll
-      for (int q = 0; q < Tile32<DKP, NT, VEC>::N; ++q)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bad |= !(__builtin_fabsf(tv.v[q][e]) <= 3.402823466e38f);
+      for (int q = 0; q < Tile32<DKP, NT, VEC>::N; ++q) bad |= !tv.finite(q);
     }
     tk.template put<KL>(Kt, a.dk, tid);
     tv.template put<VL>(Vt, a.dk, tid);
@@ -363,16 +388,19 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
 }
 
 // ---- dk and dv.  One workgroup per (b, h, NW*32 keys); lane = key.
-template <int DKP, int NW, bool VEC>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout,
-                                                                   const float* __restrict__ diag,
-                                                                   const float* __restrict__ lse,
-                                                                   const float* __restrict__ dvec, AttnDims a, int n_tiles) {
+template <int DKP, int NW, bool VEC, bool CAUSAL>
+__global__ __launch_bounds__(NW * 64)
+void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout, const float* __restrict__ diag,
+                             const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a, int n_tiles) {
   constexpr int CT = DKP / 32, LD = DKP + 4, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Qt[32 * LD];
   __shared__ __attribute__((aligned(16))) float Dt[32 * LD];
   __shared__ float row_l[32], row_d[32];     // -lse * log2(e) and dvec of the tile's queries
   __shared__ uint32_t row_k[32];             // their dropout row keys
+  // tiles that the mask cuts through: not zero where q or dO of the query is not finite, and the last such query
+  __shared__ int row_bad[NW * 32];
+  int last_bad = -1;
+  typedef Tile32<DKP, NT, VEC> Tile;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, wave = tid >> 6;
   const int S = a.S, Sk = a.Sk, I = a.H * a.dk;
   const int kt = blockIdx.x % n_tiles, bh = blockIdx.x / n_tiles, h = bh % a.H, b = bh / a.H;
@@ -388,8 +416,8 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
   f32x16 dk[CT], dv[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) { clear(dk[ct]); clear(dv[ct]); }
-  const int ibeg = a.causal ? kt * NW * 32 : 0;  // a multiple of 32
-  Tile32<DKP, NT, VEC> tq, td;
+  const int ibeg = CAUSAL ? kt * NW * 32 : 0;  // a multiple of 32
+  Tile tq, td;
   tq.load(qb + (size_t)ibeg * io.ldq, io.ldq, S - ibeg, a.dk, tid);
   td.load(db + (size_t)ibeg * I, I, S - ibeg, a.dk, tid);
   float rl = 0.f, rd = 0.f;  // lse and dvec of query i0 + tid of the tile to come (first 32 threads)
@@ -399,8 +427,15 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
     rd = dvec[srow + i];
   };
   load_consts(ibeg);
+  if (CAUSAL && tid < NW * 32) row_bad[tid] = 0;
   for (int i0 = ibeg; i0 < S; i0 += 32) {
     __syncthreads();
+    const bool cut = CAUSAL && i0 < ibeg + NW * 32;  // some key of the workgroup comes after some query
+    int* bad_row = row_bad + (i0 - ibeg);
+    if (cut) {
+      tq.mark(bad_row, tid);
+      td.mark(bad_row, tid);
+    }
     tq.template put<LD>(Qt, a.dk, tid);
     td.template put<LD>(Dt, a.dk, tid);
     float bias[16];  // (requested before the next tile, as in the forward)
@@ -415,12 +450,25 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
       if (a.drop.on) row_k[tid] = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + (i0 + tid < S ? i0 + tid : S - 1))));
     }
     __syncthreads();
+    if (cut) {
+      const uint32_t bad = (uint32_t)__ballot(bad_row[lane & 31] != 0);  // (the same in every wavefront)
+      if (bad) {  // such a query takes no part in the products; the keys that see it are marked
+        Tile::template clear_rows<LD>(Qt, bad, tid);
+        Tile::template clear_rows<LD>(Dt, bad, tid);
+        if (tid < 32 && bad_row[tid]) {
+          row_l[tid] = -INFINITY;
+          row_d[tid] = 0.f;
+        }
+        last_bad = i0 + 31 - __builtin_clz(bad);
+        __syncthreads();
+      }
+    }
     if (i0 + 32 < S) {
       tq.load(qb + (size_t)(i0 + 32) * io.ldq, io.ldq, S - i0 - 32, a.dk, tid);
       td.load(db + (size_t)(i0 + 32) * I, I, S - i0 - 32, a.dk, tid);
       load_consts(i0 + 32);
     }
-    if (a.causal && i0 + 31 < jw) continue;  // every query of the tile comes before this wavefront's keys
+    if (CAUSAL && i0 + 31 < jw) continue;  // every query of the tile comes before this wavefront's keys
     f32x16 s, dp;
     clear(s);
     clear(dp);
@@ -429,19 +477,20 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnIO io, co
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int il = ((r >> 2) << 3) + (g << 2) + (r & 3), i = i0 + il;
-      const bool ok = i < S && j < Sk && !(a.causal && j > i);
+      const bool ok = i < S && j < Sk && !(CAUSAL && j > i);
       const float p = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], sc, fmaf(bias[r], kLog2e, row_l[il]))) : 0.f;
       float mk = 1.f;
       if (a.drop.on) mk = drop_keep16(a.drop, row_k[il] ^ (uint32_t)j) ? a.drop.scale : 0.f;
       s[r] = p * mk;
-      dp[r] = p * (dp[r] * mk - row_d[il]);
+      dp[r] = ok ? p * (dp[r] * mk - row_d[il]) : 0.f;
     }
     mul_cols<CT, LD>(dv, Dt, s, lane);
     mul_cols<CT, LD>(dk, Qt, dp, lane);
   }
   if (j < Sk) {
-    store_cols<CT, VEC>((float*)io.dk + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dk, a.scale, a.dk, g);
-    store_cols<CT, VEC>((float*)io.dv + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dv, 1.f, a.dk, g);
+    const float f = CAUSAL && j <= last_bad ? __builtin_nanf("") : 1.f;
+    store_cols<CT, VEC>((float*)io.dk + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dk, a.scale * f, a.dk, g);
+    store_cols<CT, VEC>((float*)io.dv + ((size_t)b * Sk + j) * io.lddkv + h * a.dk, dv, f, a.dk, g);
   }
 }
 
@@ -481,8 +530,13 @@ hipError_t launch_bwd(const AttnIO& io, const float* c, const float* dc, const f
   else
     attn_bwd_dq_f32_kernel<DKP, 2, VEC><<<nq * bh, 128, a.bias ? (a.S + 63) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec, ddiag,
                                                                                         a, nq);
-  if (a.Sk <= 32) attn_bwd_dkv_f32_kernel<DKP, 1, VEC><<<bh, 64, 0, st>>>(io, dc, diag, lse, dvec, a, 1);
-  else attn_bwd_dkv_f32_kernel<DKP, 2, VEC><<<nk * bh, 128, 0, st>>>(io, dc, diag, lse, dvec, a, nk);
+  if (a.Sk <= 32) {
+    auto kern = a.causal ? attn_bwd_dkv_f32_kernel<DKP, 1, VEC, true> : attn_bwd_dkv_f32_kernel<DKP, 1, VEC, false>;
+    kern<<<bh, 64, 0, st>>>(io, dc, diag, lse, dvec, a, 1);
+  } else {
+    auto kern = a.causal ? attn_bwd_dkv_f32_kernel<DKP, 2, VEC, true> : attn_bwd_dkv_f32_kernel<DKP, 2, VEC, false>;
+    kern<<<nk * bh, 128, 0, st>>>(io, dc, diag, lse, dvec, a, nk);
+  }
   return hipGetLastError();
 }
 

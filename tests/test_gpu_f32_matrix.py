@@ -111,3 +111,26 @@ def test_every_bucket_at_the_lowest_value():
     from parity_util import to_np, upload_case
     dw, dx, _ = upload_case(cfg, w, x, dy)
     _check([("y", to_np(P.t5_block_fwd(cfg, dx, dw)[0]), y)])
+
+
+@pytest.mark.parametrize("seq,d_kv", [(20, 16), (50, 16), (100, 64), (140, 128), (45, 18)])
+def test_causal_gradients_after_a_nan_gradient(seq, d_kv):
+    """An output gradient that is not finite reaches the keys its query sees, none after it, also inside its own tile of
+    queries: dx of the later rows is that of the clean gradient (float32, causal)."""
+    import torch
+    import paper_2203_17189_amd as P
+    from parity_util import upload_case
+    cfg = replace(C, batch=1, seq=seq, d_kv=d_kv, causal=True, name="f32_nan_grad")
+    w, x, dy = make_case(cfg)
+    dw, dx, ddy = upload_case(cfg, w, x, dy)
+    _, stash = P.t5_block_fwd(cfg, dx, dw)
+    g0, _ = P.t5_block_bwd(cfg, ddy, dx, dw, stash)
+    bad = seq - 12
+    ddy = ddy.clone().view(seq, -1)
+    ddy[bad] = float("nan")
+    g1, _ = P.t5_block_bwd(cfg, ddy.view_as(dx), dx, dw, stash)
+    g0, g1 = g0.view(seq, -1), g1.view(seq, -1)
+    assert torch.isnan(g1[:bad + 1]).any(dim=1).all()
+    # the plain multiply-adds of that tile differ from the matrix unit's by float32 rounding
+    assert rel_err(g1[bad + 1:].cpu().numpy().astype(np.float64),
+                   g0[bad + 1:].cpu().numpy().astype(np.float64))[0] <= TOL_F32[0]
