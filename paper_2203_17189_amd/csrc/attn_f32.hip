@@ -188,9 +188,10 @@ __device__ __forceinline__ void mul_cols_masked(f32x16 (&acc)[CT], const float* 
 }
 
 // ---- forward.  One workgroup per (b, h, NW*32 queries).  Up to 64 channels two wavefronts share a SIMD (three up to 32):
-// one hides the other's softmax arithmetic and the barriers around the tiles.
+// one hides the other's softmax arithmetic and the barriers around the tiles (one less where a single wavefront loads whole
+// tiles element by element, which would spill).
 template <int DKP, int NW, bool VEC, bool CAUSAL>
-__global__ __launch_bounds__(NW * 64, DKP == 32 ? 3 : DKP == 64 ? 2 : 1)
+__global__ __launch_bounds__(NW * 64, DKP == 128 ? 1 : (DKP == 32 ? 3 : 2) - (NW == 1 && !VEC))
 void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag, float* __restrict__ c, float* __restrict__ lse,
                          AttnDims a, int n_tiles) {
   constexpr int CT = DKP / 32, KL = DKP + 4, VL = DKP + 8, NT = NW * 64;
@@ -505,6 +506,11 @@ bool vec_ok(const AttnIO& io, const AttnDims& a, const void* c, const void* dc) 
   return (all & 15) == 0 && a.dk % 4 == 0 && io.ldq % 4 == 0 && io.ldkv % 4 == 0 && io.lddq % 4 == 0 && io.lddkv % 4 == 0;
 }
 
+// Channels are rounded up to 32, 64 or 128, with float4 loads (VEC) or element loads.  Against the row-at-a-time kernels,
+// forward + backward at 12 x 250 tokens, 6 heads: 5 channels 373 -> 147 us, 18 836 -> 150, 50 2003 -> 197, 66 2743 -> 332 (5
+// channels in the 128-channel tiles: 438).  Those kernels stay ahead only below some 100 rows of 5 to 18 channels in all,
+// by up to 5 us in the backward.
+//
 // Wavefronts per workgroup: two share each K/V (or Q/dO) tile; one where a sequence has no more than 32 rows.  In the
 // forward four, beyond 64 rows: the second workgroup of two wavefronts on a compute unit lands on the SIMDs of the first
 // and leaves the other two idle (16 x 250 tokens, 6 heads of 64: 48 us with two, 32 with four; 12 heads 53 and 51).
@@ -549,10 +555,10 @@ bool attn_f32_supported(const AttnDims& a) {
 }
 
 hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
-  if (!vec_ok(io, a, c, nullptr)) return launch_fwd<128, false>(io, diag, c, lse, a, st);
-  if (a.dk <= 32) return launch_fwd<32, true>(io, diag, c, lse, a, st);
-  if (a.dk <= 64) return launch_fwd<64, true>(io, diag, c, lse, a, st);
-  return launch_fwd<128, true>(io, diag, c, lse, a, st);
+  const bool vec = vec_ok(io, a, c, nullptr);
+  if (a.dk <= 32) return vec ? launch_fwd<32, true>(io, diag, c, lse, a, st) : launch_fwd<32, false>(io, diag, c, lse, a, st);
+  if (a.dk <= 64) return vec ? launch_fwd<64, true>(io, diag, c, lse, a, st) : launch_fwd<64, false>(io, diag, c, lse, a, st);
+  return vec ? launch_fwd<128, true>(io, diag, c, lse, a, st) : launch_fwd<128, false>(io, diag, c, lse, a, st);
 }
 
 hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
@@ -561,10 +567,11 @@ hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc
     const int64_t nd = (int64_t)a.H * (2 * a.S - 1);
     clear_f32_kernel<<<ceil_div(nd, 256), 256, 0, st>>>(ddiag, nd);
   }
-  if (!vec_ok(io, a, c, dc)) return launch_bwd<128, false>(io, c, dc, diag, lse, dvec, ddiag, a, st);
-  if (a.dk <= 32) return launch_bwd<32, true>(io, c, dc, diag, lse, dvec, ddiag, a, st);
-  if (a.dk <= 64) return launch_bwd<64, true>(io, c, dc, diag, lse, dvec, ddiag, a, st);
-  return launch_bwd<128, true>(io, c, dc, diag, lse, dvec, ddiag, a, st);
+  const bool vec = vec_ok(io, a, c, dc);
+  auto run = [&](auto fn) { return fn(io, c, dc, diag, lse, dvec, ddiag, a, st); };
+  if (a.dk <= 32) return run(vec ? launch_bwd<32, true> : launch_bwd<32, false>);
+  if (a.dk <= 64) return run(vec ? launch_bwd<64, true> : launch_bwd<64, false>);
+  return run(vec ? launch_bwd<128, true> : launch_bwd<128, false>);
 }
 
 }  // namespace t5mi
