@@ -83,8 +83,8 @@ typedef struct {
                             by a second pass: every output of the backward pass is bit-reproducible, for a larger
                             workspace (the *_workspace_bytes() queries account for it) and a few percent of time.
                             Applies to the bf16 matrix-unit kernels; y, dx (and denc) are bit-reproducible either way.
-                            float32: the weight gradients are bit-reproducible with 1, the bias-table gradient meets in
-                            float32 atomics either way.
+                            float32: the weight gradients and the output-matrix gradient are bit-reproducible with 0
+                            too, the bias-table gradient meets in float32 atomics either way.
                             In a stack it also covers the output-matrix gradient and the embedding gradient (formed
                             per vocabulary row in position order instead of with atomics). */
 } t5_block_cfg;

@@ -212,8 +212,13 @@ struct BwdWs {
   // layer (the GEMMs run one after the other and share it), and for the bias-gradient windows of the
   // attention backward's workgroups
   float *wg_partials, *ddiag_part;
+  // float32: the k-slices of all the layer's weight gradients, which one launch adds up at its end
+  float* wg_slices;
+  mutable SplitJobs split;       // those that have been left there so far
+  mutable size_t wg_slices_off;  // floats in use
 };
 size_t wgrad_partials_bytes(const Dims& D);  // defined below, after the GEMM descriptor helpers
+size_t wgrad_slices_bytes(const Dims& D);
 size_t carve_bwd(const Dims& D, void* base, BwdWs* w) {
   Carver cv(base);
   BwdWs t = {};
@@ -245,6 +250,7 @@ size_t carve_bwd(const Dims& D, void* base, BwdWs* w) {
     ad.B = D.B; ad.S = ad.Sk = D.S; ad.H = D.H; ad.dk = D.dk; ad.bias = 1;
     if (attn_mfma_supported(ad)) t.ddiag_part = cv.take<float>(attn_ddiag_part_bytes(ad));  // (only these kernels use it)
   }
+  if (D.ty == IN_F32) t.wg_slices = cv.take<float>(wgrad_slices_bytes(D));
   if (w) *w = t;
   return cv.off;
 }
@@ -275,31 +281,70 @@ GemmEpi epi(int kind, void* out0, int ld0, int out_type) {
   return e;
 }
 
-// Room for the partial sums of the layer's largest split weight-gradient GEMM (reproducible mode).
-size_t wgrad_partials_bytes(const Dims& D) {
-  alignas(16) static const long long dummy[4] = {0, 0, 0, 0};
+// Shapes (M, N, K) of a layer's weight gradients, C[M, N] = A[K, M]^T B[K, N].
+template <typename F>
+void each_wgrad(const Dims& D, F probe) {
   const int T = (int)D.T, Te = (int)D.Te;
-  size_t need = 0;
-  auto probe = [&](int M, int N, int K) {
-    GemmDesc g = gemm1(M, N, K, dummy, M, 0, dummy, N, 0, IN_BF16);
-    const size_t b = gemm_split_partials_bytes(g, epi(EPI_SPLIT_F32, (void*)dummy, N, IN_F32));
-    need = b > need ? b : need;
-  };
   probe(D.F, D.d, T);                                   // dWo_ff
   probe(D.d, D.mlp == ACT_RELU ? D.F : 2 * D.F, T);     // dWi0 | dWi1
-  probe(D.I, D.d, T);                                   // dWo (and dXo)
+  probe(D.I, D.d, T);                                   // dWo
   probe(D.d, 3 * D.I, T);                               // dWq | dWk | dWv
   if (D.Sk > 0) {
+    probe(D.I, D.d, T);                                 // dXo
     probe(D.d, D.I, T);                                 // dXq
     probe(D.d, 2 * D.I, Te);                            // dXk | dXv
   }
+}
+alignas(16) const long long kAligned16[4] = {0, 0, 0, 0};  // placeholder operand of a size query
+// Room for the partial sums of the layer's largest split weight-gradient GEMM (reproducible mode).
+size_t wgrad_partials_bytes(const Dims& D) {
+  size_t need = 0;
+  each_wgrad(D, [&](int M, int N, int K) {
+    GemmDesc g = gemm1(M, N, K, kAligned16, M, 0, kAligned16, N, 0, IN_BF16);
+    const size_t b = gemm_split_partials_bytes(g, epi(EPI_SPLIT_F32, (void*)kAligned16, N, IN_F32));
+    need = b > need ? b : need;
+  });
   return need;
+}
+// Floats that the k-slices of a float32 weight gradient take (a multiple of four, 0: not sliced).
+size_t slice_floats(const GemmDesc& g, const GemmEpi& e) {
+  const int n = gemm_f32_slices(g, e);
+  return n > 1 ? (size_t)n * (size_t)g.M * (size_t)g.N : 0;
+}
+size_t wgrad_slices_bytes(const Dims& D) {
+  size_t need = 0;
+  each_wgrad(D, [&](int M, int N, int K) {
+    GemmEpi e = epi(EPI_SPLIT_F32, (void*)kAligned16, N, IN_F32);
+    e.accumulate = 1;
+    need += slice_floats(gemm1(M, N, K, kAligned16, M, 0, kAligned16, N, 0, IN_F32), e) * 4;
+  });
+  return need;
+}
+SplitJob split_job(const GemmDesc& g, const GemmEpi& e, const float* part) {
+  return SplitJob{part, {(float*)e.out0, (float*)e.out1, (float*)e.out2}, g.M, g.N, gemm_f32_slices(g, e), e.ld0, e.split_n};
 }
 
 hipError_t run_gemm(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   if (gemm_mfma_supported(g, e)) return launch_gemm_mfma(g, e, st);
   if (gemm_f32_supported(g, e)) return launch_gemm_f32(g, e, st);
   return launch_gemm_simple(g, e, st);
+}
+// A weight gradient of a layer; the slices of a float32 one wait for wgrad_finish.
+hipError_t wgrad_gemm(const BwdWs& W, const GemmDesc& g, GemmEpi e, hipStream_t st) {
+  const size_t n = W.wg_slices ? slice_floats(g, e) : 0;
+  if (n > 0) {
+    float* part = W.wg_slices + W.wg_slices_off;
+    e.aux0 = part;
+    W.wg_slices_off += n;
+    W.split.j[W.split.count++] = split_job(g, e, part);
+  }
+  return run_gemm(g, e, st);
+}
+hipError_t wgrad_finish(const BwdWs& W, hipStream_t st) {
+  const hipError_t err = W.split.count > 0 ? launch_split_reduce(W.split, st) : hipSuccess;
+  W.split.count = 0;
+  W.wg_slices_off = 0;
+  return err;
 }
 
 #define T5_TRY(expr)                          \
@@ -555,8 +600,8 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.F, D.d, T, S.a, D.F, 0, dy, D.d, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dw->wo_ff, D.d, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-    T5_STEP("gemm_dwo_ff", run_gemm(g, e, st));
+    e.accumulate = 1; e.aux0 = W.wg_partials;
+    T5_STEP("gemm_dwo_ff", wgrad_gemm(W, g, e, st));
   }
   if (D.mlp == ACT_RELU) {
     {  // du = (dy Wo_ff^T) where a > 0
@@ -570,8 +615,8 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
       hipStream_t st = wgrad_stream(W.fork);
       GemmDesc g = gemm1(D.d, D.F, T, S.n2, D.d, 0, du_p, D.F, 0, ty);
       GemmEpi e = epi(EPI_SPLIT_F32, dw->wi0, D.F, IN_F32);
-      e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-      T5_STEP("gemm_dwi", run_gemm(g, e, st));
+      e.accumulate = 1; e.aux0 = W.wg_partials;
+      T5_STEP("gemm_dwi", wgrad_gemm(W, g, e, st));
     }
     {  // dn2 = du Wi0^T
       GemmDesc g = gemm1(T, D.d, D.F, du_p, D.F, 1, w->wi0, D.F, 1, ty);
@@ -589,8 +634,8 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
       hipStream_t st = wgrad_stream(W.fork);
       GemmDesc g = gemm1(D.d, 2 * D.F, T, S.n2, D.d, 0, du_p, 2 * D.F, 0, ty);
       GemmEpi e = epi(EPI_SPLIT_F32, dw->wi0, D.F, IN_F32);
-      e.out1 = dw->wi1; e.split_n = D.F; e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-      T5_STEP("gemm_dwi", run_gemm(g, e, st));
+      e.out1 = dw->wi1; e.split_n = D.F; e.accumulate = 1; e.aux0 = W.wg_partials;
+      T5_STEP("gemm_dwi", wgrad_gemm(W, g, e, st));
     }
     {  // dn2 = du Wi0^T + dw Wi1^T
       GemmDesc g = gemm1(T, D.d, D.F, du_p, 2 * D.F, 1, w->wi0, D.F, 1, ty);
@@ -624,8 +669,8 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.I, D.d, T, S.cx, D.I, 0, dh_op, D.d, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dxw->xo, D.d, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-    T5_STEP("gemm_dxo", run_gemm(g, e, st));
+    e.accumulate = 1; e.aux0 = W.wg_partials;
+    T5_STEP("gemm_dxo", wgrad_gemm(W, g, e, st));
   }
   {  // dcx = dh2 Xo^T
     GemmDesc g = gemm1(T, D.I, D.d, dh_op, D.d, 1, xw->xo, D.d, 1, ty);
@@ -643,15 +688,15 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.d, D.I, T, S.nx, D.d, 0, W.dqx, D.I, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dxw->xq, D.I, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-    T5_STEP("gemm_dxq", run_gemm(g, e, st));
+    e.accumulate = 1; e.aux0 = W.wg_partials;
+    T5_STEP("gemm_dxq", wgrad_gemm(W, g, e, st));
   }
   if (!W.defer_wgrad) {  // dXk | dXv = enc^T [dk | dv]   (ordered after dXq on the side stream: no new fork point needed)
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.d, 2 * D.I, Te, enc, D.d, 0, W.dkvx, 2 * D.I, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dxw->xk, D.I, IN_F32);
-    e.out1 = dxw->xv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-    T5_STEP("gemm_dxkv", run_gemm(g, e, st));
+    e.out1 = dxw->xv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials;
+    T5_STEP("gemm_dxkv", wgrad_gemm(W, g, e, st));
   }
   {  // denc = dk Xk^T + dv Xv^T
     GemmDesc g = gemm1(Te, D.d, D.I, W.dkvx, 2 * D.I, 1, xw->xk, D.I, 1, ty);
@@ -692,8 +737,8 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.I, D.d, T, S.c, D.I, 0, dh_op, D.d, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dw->wo, D.d, IN_F32);
-    e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-    T5_STEP("gemm_dwo", run_gemm(g, e, st));
+    e.accumulate = 1; e.aux0 = W.wg_partials;
+    T5_STEP("gemm_dwo", wgrad_gemm(W, g, e, st));
   }
   {  // dc = dh Wo^T
     GemmDesc g = gemm1(T, D.I, D.d, dh_op, D.d, 1, w->wo, D.d, 1, ty);
@@ -712,8 +757,9 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
     hipStream_t st = wgrad_stream(W.fork);
     GemmDesc g = gemm1(D.d, 3 * D.I, T, S.n1, D.d, 0, W.dqkv, 3 * D.I, 0, ty);
     GemmEpi e = epi(EPI_SPLIT_F32, dw->wq, D.I, IN_F32);
-    e.out1 = dw->wk; e.out2 = dw->wv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials; e.ordered = D.det;
-    T5_STEP("gemm_dwqkv", run_gemm(g, e, st));
+    e.out1 = dw->wk; e.out2 = dw->wv; e.split_n = D.I; e.accumulate = 1; e.aux0 = W.wg_partials;
+    T5_STEP("gemm_dwqkv", wgrad_gemm(W, g, e, st));  // (the layer's last weight gradient)
+    if (W.split.count > 0) T5_STEP("wgrad_slices", wgrad_finish(W, st));
   }
   {  // dn1 = dq Wq^T + dk Wk^T + dv Wv^T
     GemmDesc g = gemm1(T, D.d, D.I, W.dqkv, 3 * D.I, 1, w->wq, D.I, 1, ty);

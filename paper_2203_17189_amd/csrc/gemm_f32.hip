@@ -268,7 +268,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
           const int m = mb + ((r >> 2) << 3) + (r & 3), n = nb + j * 32;
           const int mc = m < g.M ? m : g.M - 1, nc = n < g.N ? n : g.N - 1;
           if constexpr (EPI == EPI_SPLIT_F32) {
-            const int which = nc / e.split_n;
+            const int which = nc / e.split_n;  // (one slice)
             const float* d = (const float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
             xa[r][j] = d[(size_t)mc * e.ld0 + (nc - which * e.split_n)];
           } else if constexpr (AUX) {
@@ -320,14 +320,59 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
             ((float*)e.out0)[o] = v * xa[r][j];
             ((float*)e.out1)[o] = v * xb[r][j];
           } else {  // EPI_SPLIT_F32
-            const int which = n / e.split_n;
-            float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2) + (size_t)m * e.ld0 + (n - which * e.split_n);
-            if (split_k > 1) unsafeAtomicAdd(dst, v);
-            else *dst = xa[r][j] + v;
+            if (split_k > 1) {  // this slice's sums, for launch_split_reduce
+              ((float*)const_cast<void*>(e.aux0))[((size_t)blockIdx.z * g.M + m) * g.N + n] = v;
+            } else {
+              const int which = n / e.split_n;
+              float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
+              dst[(size_t)m * e.ld0 + (n - which * e.split_n)] = xa[r][j] + v;
+            }
           }
         }
       }
     }
+  }
+}
+
+// All sliced weight gradients of a layer in one launch: a thread adds four columns of one row over the slices, in their
+// order.  Bound: bytes, the slices once, the outputs twice.  (Float atomics of the slices on the outputs took longer, and
+// their order varied from run to run: layer of d 512 over 4000 tokens 893 us, 880 with this.)
+struct SplitArgs {
+  SplitJobs jobs;
+  int first[SPLIT_JOBS];  // first block of each job
+};
+__global__ __launch_bounds__(256) void split_reduce_kernel(SplitArgs s) {
+  int i = 0;
+  while (i + 1 < s.jobs.count && (int)blockIdx.x >= s.first[i + 1]) ++i;
+  const SplitJob& j = s.jobs.j[i];
+  const uint32_t idx = ((blockIdx.x - (uint32_t)s.first[i]) * 256 + threadIdx.x) * 4, mn = (uint32_t)j.M * (uint32_t)j.N;
+  if (idx >= mn) return;
+  const uint32_t m = idx / (uint32_t)j.N, n = idx - m * (uint32_t)j.N;
+  const float* p = j.part + idx;
+  f32x4 acc = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll 8
+  for (int k = 1; k < j.slices; ++k) {
+    p += mn;
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] += v[q];
+  }
+  uint32_t which = n / (uint32_t)j.split_n, col = n - which * (uint32_t)j.split_n;
+  if (col + 4 <= (uint32_t)j.split_n) {
+    typedef f32x4 __attribute__((aligned(4))) f32x4_any;  // (an output may start anywhere)
+    float* o = (which == 0 ? j.out[0] : which == 1 ? j.out[1] : j.out[2]) + (size_t)m * j.ld0 + col;
+    f32x4 v = *reinterpret_cast<const f32x4_any*>(o);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] += acc[q];
+    *reinterpret_cast<f32x4_any*>(o) = v;
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {  // the four columns belong to two outputs
+    if (col == (uint32_t)j.split_n) { ++which; col = 0; }
+    float* o = which == 0 ? j.out[0] : which == 1 ? j.out[1] : j.out[2];
+    o[(size_t)m * j.ld0 + col] += acc[q];
+    ++col;
   }
 }
 
@@ -350,30 +395,38 @@ hipError_t launch_tile(const GemmDesc& g, const GemmEpi& e, int split_k, hipStre
   return hipGetLastError();
 }
 
-template <bool A_KC, bool B_KC, int EPI>
-hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
-  // float4 loads: every row of the operands starts on a 16-byte boundary and no slot of four lies half outside
+// float4 loads: every row of the operands starts on a 16-byte boundary and no slot of four lies half outside
+bool vec_ok(const GemmDesc& g) {
   bool vec = g.seg[0].lda % 4 == 0 && g.seg[0].ldb % 4 == 0;
   for (int s = 0; s < (g.nsrc > 1 ? g.nsrc : g.nseg); ++s) vec = vec && ((uintptr_t)g.seg[s].B & 15) == 0;
   for (int s = 0; s < g.nseg; ++s) {
     vec = vec && ((uintptr_t)g.seg[s].A & 15) == 0;
-    if (A_KC || B_KC) vec = vec && g.seg[s].K % 4 == 0;
+    if (g.a_kc || g.b_kc) vec = vec && g.seg[s].K % 4 == 0;
   }
-  if (!A_KC) vec = vec && g.M % 4 == 0;
-  if (!B_KC) vec = vec && g.N % 4 == 0;
-  if (!vec) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, false>(g, e, 1, st);
+  if (!g.a_kc) vec = vec && g.M % 4 == 0;
+  if (!g.b_kc) vec = vec && g.N % 4 == 0;
+  return vec;
+}
+// Weight gradients: few tiles, long k.  Slices of at least 256 k until two workgroups per compute unit are busy.
+int wgrad_slices(const GemmDesc& g, bool& big) {
+  const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128);
+  const int64_t t64 = (int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64), K = g.seg[0].K;
+  big = t128 * (K / 256) >= 256;
+  const int64_t t = big ? t128 : t64;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(K / 256, (512 + t - 1) / t));
+}
+
+template <bool A_KC, bool B_KC, int EPI>
+hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
+  if (!vec_ok(g)) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, false>(g, e, 1, st);
   const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128);
   const int64_t t64 = (int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64);
   int64_t K = 0;
   for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
   if constexpr (EPI == EPI_SPLIT_F32) {
-    // Weight gradients: few tiles, long k.  Slices of at least 256 k until two workgroups per compute unit are busy;
-    // they meet in float32 atomics on the cleared output.  In the reproducible mode (e.ordered) there is one slice
-    // and the small tiles spread the work instead.
-    if (e.accumulate && !e.ordered && K >= 512) {
-      const bool big = t128 * (K / 256) >= 256;
-      const int64_t t = big ? t128 : t64;
-      const int sk = (int)std::max<int64_t>(1, std::min<int64_t>(K / 256, (512 + t - 1) / t));
+    if (e.aux0 && e.accumulate && K >= 512) {
+      bool big;
+      const int sk = wgrad_slices(g, big);
       if (big) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI, true>(g, e, sk, st);
       return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, sk, st);
     }
@@ -388,6 +441,26 @@ hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
 }
 
 }  // namespace
+
+int gemm_f32_slices(const GemmDesc& g, const GemmEpi& e) {
+  if (!gemm_f32_supported(g, e) || e.kind != EPI_SPLIT_F32 || !e.accumulate || g.seg[0].K < 512 || !vec_ok(g)) return 1;
+  bool big;
+  return wgrad_slices(g, big);
+}
+
+hipError_t launch_split_reduce(const SplitJobs& jobs, hipStream_t st) {
+  int blocks = 0;
+  SplitArgs s;
+  for (int i = 0; i < jobs.count; ++i) {
+    if (jobs.j[i].N % 4 != 0 || (int64_t)jobs.j[i].M * jobs.j[i].N >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    s.first[i] = blocks;
+    blocks += ceil_div((int64_t)jobs.j[i].M * jobs.j[i].N / 4, 256);
+  }
+  if (blocks == 0) return hipSuccess;
+  s.jobs = jobs;
+  split_reduce_kernel<<<blocks, 256, 0, st>>>(s);
+  return hipGetLastError();
+}
 
 bool gemm_f32_supported(const GemmDesc& g, const GemmEpi& e) {
   if (g.in_type != IN_F32 || g.nseg < 1 || g.nseg > 3 || g.ngroups > 1 || e.out_type != IN_F32) return false;

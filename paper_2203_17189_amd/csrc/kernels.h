@@ -78,7 +78,6 @@ struct GemmEpi {
   int aux_type;
   int split_n;
   int accumulate;
-  int ordered;   // EPI_SPLIT_F32, float32 kernel: no k-slices that meet in atomics (reproducible mode)
   int act;       // EPI_STORE: ACT_RELU stores max(acc, 0); EPI_GEGLU_FWD: ACT_GELU_TANH or ACT_GELU_ERF
   int aux_mask;  // EPI_RESID: != 0 stores acc where aux0 > 0 and 0 elsewhere instead of acc + aux0
   // Dropout of the GEMM's result (row = m, column = n; for EPI_GEGLU_FWD column = hidden unit), when drop.on:
@@ -110,7 +109,22 @@ hipError_t launch_fill_ptrs(const void* const* ptrs, int n, const void** dst, hi
 hipError_t launch_gemm_simple(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 // float32 MFMA kernel: any shape; gemm_f32_supported() checks orientation and epilogue.
 bool gemm_f32_supported(const GemmDesc& g, const GemmEpi& e);
+// k-slices of a weight gradient (EPI_SPLIT_F32, accumulate).  With GemmEpi::aux0 (gemm_f32_slices() * M * N floats) the
+// slices are left there and launch_split_reduce adds them to the outputs; without it, or with one, there is none.
+int gemm_f32_slices(const GemmDesc& g, const GemmEpi& e);
 hipError_t launch_gemm_f32(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+// out (as in EPI_SPLIT_F32) += part[0] + part[1] + ..., M x N floats each, in that order, for every job (N % 4 == 0).
+struct SplitJob {
+  const float* part;
+  float* out[3];
+  int M, N, slices, ld0, split_n;
+};
+constexpr int SPLIT_JOBS = 7;
+struct SplitJobs {
+  SplitJob j[SPLIT_JOBS];
+  int count;
+};
+hipError_t launch_split_reduce(const SplitJobs& jobs, hipStream_t st);
 // bf16 MFMA kernel.  Requires in_type == IN_BF16, every K % 64 == 0 (k-contiguous operands), lda/ldb % 8 == 0, N % 64 == 0
 // and 16-byte aligned pointers; gemm_mfma_supported() checks this.
 bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e);

@@ -293,7 +293,7 @@ struct Head {
   void *nf = nullptr, *logits = nullptr, *wout_t = nullptr, *scale_s = nullptr;
   float *rf = nullptr, *loss_rows = nullptr, *n_valid = nullptr, *dnf = nullptr, *dg_tmp = nullptr,
         *dg_partial = nullptr;
-  float* wg_partials = nullptr;  // reproducible mode: partial sums of the output-matrix gradient's k-slices
+  float* wg_partials = nullptr;  // float32, or reproducible mode: partial sums of the output-matrix gradient's k-slices
 };
 
 // The gradient GEMM of the output matrix (or of the tied embedding) for one chunk of tokens.
@@ -306,8 +306,7 @@ void head_wgrad_gemm(const Head& h, const Dims& D, int tc, const void* nf_c, Gem
     e = epi(EPI_SPLIT_F32, h.d_logits_w, h.V, IN_F32);
   }
   e.accumulate = 1;
-  e.ordered = D.det;
-  e.aux0 = h.wg_partials;  // null unless the reproducible mode carved it
+  e.aux0 = h.wg_partials;  // null unless carve_head took room for it
 }
 
 void carve_head(Carver& cv, Head& h, const Dims& D) {
@@ -327,6 +326,13 @@ void carve_head(Carver& cv, Head& h, const Dims& D) {
     GemmEpi e;
     head_wgrad_gemm(h, D, h.chunk, h.nf, g, e);
     h.wg_partials = cv.take<float>(gemm_split_partials_bytes(g, e));
+  } else if (D.ty == IN_F32) {
+    GemmDesc g;
+    GemmEpi e;
+    head_wgrad_gemm(h, D, h.chunk, kAligned16, g, e);
+    g.seg[0].A = g.seg[0].B = kAligned16;
+    const size_t n = slice_floats(g, e) * 4;  // (a shorter last chunk has no more slices)
+    if (n > 0) h.wg_partials = cv.take<float>(n);
   }
 }
 
@@ -382,6 +388,12 @@ int head_loss_and_grad(const Head& h, const Dims& D, float rms_eps, const void* 
       GemmEpi e;
       head_wgrad_gemm(h, D, tc, nf_c, g, e);
       T5_STEP("gemm_dlogits_w", run_gemm(g, e, st));
+      if (ty == IN_F32 && h.wg_partials && slice_floats(g, e) > 0) {
+        SplitJobs jobs;
+        jobs.j[0] = split_job(g, e, h.wg_partials);
+        jobs.count = 1;
+        T5_STEP("wgrad_slices", launch_split_reduce(jobs, st));
+      }
     }
   }
   T5_STEP("loss_reduce", launch_loss_reduce(h.loss_rows, D.T, h.n_valid, loss, st));
