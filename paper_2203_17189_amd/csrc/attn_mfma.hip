@@ -384,7 +384,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
     }
     mx = max_across_halves(mx);
     const float m_new = fmaxf(m, mx);
-    const float alpha = fast_exp2(m - m_new);
+    // (a bias table may mask all keys so far, with -inf or with the lowest number: then there is no maximum yet)
+    const float base = BIAS && m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = fast_exp2(m - base);
     m = m_new;
     float ls = 0.f;
     uint32_t kx = 0;
@@ -393,7 +395,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
     for (int kt = 0; kt < BC / 32; ++kt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = fast_exp2(sT[kt][r] - m_new);
+        const float p = fast_exp2(sT[kt][r] - base);
         ls += p;  // the normaliser is that of the undropped probabilities
         if constexpr (DROP) {
           // (key index = tile start | lane half << 2 | constant of the register, disjoint bits)
