@@ -753,26 +753,21 @@ __global__ __launch_bounds__(256) void attn_ddiag_reduce_kernel(const float* __r
 // ------------------------------------------------------------------------------------------------
 // dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
 // ------------------------------------------------------------------------------------------------
-// Waves per SIMD of the dk / dv kernel.  With 64 channels and without dropout the causal and the bias-free forms run
-// three: at 168 registers the bias values are read where they are used, which the third wave covers (12 causal layers of
-// 32 x 512 tokens, 12 heads: 853 -> 808 us; 12 cross-attention layers of 32 x 114: 332 -> 328 us).  The non-causal form
-// with bias stays at two and requests its bias values ahead: with three, 128 x 512 tokens took 372 instead of 361 us.
-// Dropout's keys do not fit beside a third wave.
-constexpr bool dkv_three_waves(int dk, bool causal, bool bias, bool drop) {
-  return dk == 64 && !drop && (causal || !bias);
-}
-
-template <int DK, bool CAUSAL, bool BIAS, bool DROP>
-__global__ __launch_bounds__(256, DK == 64 ? (dkv_three_waves(DK, CAUSAL, BIAS, DROP) ? 3 : 2) : 1)
+// With 64 channels two workgroups share a compute unit and the bias values are requested ahead.  THREE: the bias-free form
+// without dropout has registers for a third (164), see bwd_launch.
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool THREE>
+__global__ __launch_bounds__(256, DK == 64 ? (THREE ? 3 : 2) : 1)
 void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
                               const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
   constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
   constexpr int TILE = BQ * DK * 2, STG = 2 * TILE;  // a stage holds a Q tile then a dO tile
   // How the queries past the end of a ragged last tile come to probability zero: by a masked copy of the element loop,
-  // or from the accumulator seeds.  The copy costs registers, which the three-wave forms do not have, and time elsewhere
-  // (128 channels, causal, 16 x 2048: 971 -> 960 us without it).  The non-causal 64-channel form with bias keeps it: without
-  // it 32 x 1024 tokens with 32 heads gain (630 -> 602 us) but 128 x 512 with 12 heads lose (361 -> 371 us).
-  constexpr bool TAIL_MASK = DK == 64 && BIAS && !CAUSAL;
+  // or from the accumulator seeds.  Without the copy (and its branch) an iteration is one block that the compiler
+  // schedules whole.  Causal, 64 channels: 8 x 2048 tokens, 12 heads 181 -> 156 us, 1 x 1024 35 -> 29, 32 x 512 65 -> 62
+  // (three waves per SIMD without bias values ahead: 190, 44, 66); 128 channels, 16 x 2048 971 -> 960.  The non-causal
+  // 64-channel form with bias keeps it: without it 32 x 1024 tokens with 32 heads gain (630 -> 602 us) but 128 x 512 with
+  // 12 heads lose (361 -> 371 us).  The bias-free form has both, see bwd_launch.
+  constexpr bool TAIL_MASK = DK == 64 && !CAUSAL && (BIAS || (!DROP && !THREE));
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // The score and dP accumulators start from -lse/scale and -dvec, so that the MFMA results are
   // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
@@ -898,14 +893,13 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
       // is hidden behind the matrix work instead of stalling the softmax arithmetic (read at first use they
       // put an LDS round trip on every sub-tile's dependent chain: 651 -> 635 us at 64 channels, the sixteen
       // registers are there at two waves per SIMD)
-      constexpr bool HOIST = BIAS && !dkv_three_waves(DK, CAUSAL, BIAS, DROP);
       float bias[16];
       // Bias of (query i, key j) sits at dg[j_loc + S - 1 - i].  Where every query of the tile exists the sixteen
       // values of a lane are one pointer and constant offsets: register r belongs to query
       // q0 + qb*32 + 4g + c_r with c_r = 8*(r/4) + r%4 <= 27, so bq[27 - c_r] with bq 27 below the first.
       // (a query past the end of a ragged tile reads at most BQ - 1 entries below dg[0]: the padding)
       const float* bq = dg + (j_loc + S - 1 - q0 - qb * 32 - (g << 2) - 27);
-      if constexpr (HOIST) {
+      if constexpr (BIAS) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) bias[r] = bq[27 - (((r >> 2) << 3) + (r & 3))];
       }
@@ -921,7 +915,7 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
         // with dropout dP is rescaled before dvec is subtracted: it starts from zero
         for (int e = 0; e < 4; ++e) { s[rq * 4 + e] = l4[e]; dp[rq * 4 + e] = DROP ? 0.f : d4[e]; }
       }
-      if constexpr (HOIST) __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);  // 8 bias + 4 seed reads first
+      if constexpr (BIAS) __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);  // 8 bias + 4 seed reads first
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         const bool pre = ROWS_AHEAD && qb == 1;
@@ -943,14 +937,14 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
             qtr[mm][ct] = frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane);
           }
       }
-      // with 64 channels the second copy of the loop costs a wave per SIMD in registers: mask always
-      // some key here lies after some query, or the tile reaches past the last query (both wave-uniform)
+      // some key here lies after some query (with 64 channels the causal form masks always: see above), or the tile
+      // reaches past the last query and is not seeded (both wave-uniform)
       if ((TAIL_MASK && q0 + BQ > S) || (CAUSAL && (DK == 64 || j0 + wave * 32 + 31 > q0 + qb * 32))) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
           const int i = q0 + il;
-          float p = BIAS ? fast_exp2(fmaf(s[r], sc, HOIST ? bias[r] : bq[27 - (((r >> 2) << 3) + (r & 3))]))
+          float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r]))
                          : fast_exp2(s[r] * sc);
           if ((CAUSAL && j > i) || (TAIL_MASK && i >= S)) p = 0.f;
           if constexpr (DROP) {
@@ -967,7 +961,7 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
         for (int r = 0; r < 16; ++r) {
           const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
           const int i = q0 + il;
-          const float p = BIAS ? fast_exp2(fmaf(s[r], sc, HOIST ? bias[r] : bq[27 - (((r >> 2) << 3) + (r & 3))]))
+          const float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r]))
                                : fast_exp2(s[r] * sc);
           if constexpr (DROP) {
             const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
@@ -1056,10 +1050,16 @@ hipError_t bwd_launch(const AttnIO& io, const void* c, const void* dc, const flo
     }
   }
   if (phase == 2) {
-    auto kern = attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP>;
     const size_t lds = 4 * 64 * DK * 2 + sizeof(float) * (256 + (DROP ? 128 : 0) + (BIAS ? 64 + a.S + 127 : 0));
+    const int wgs = ((a.Sk + 127) / 128) * a.H * a.B;
+    // Bias-free with 64 channels: beyond two workgroups per compute unit the form that lets a third in, up to there the
+    // one whose single workgroup is faster (1 x 1024 queries over 100 keys, 12 heads, 12 workgroups: 27 against 23 us;
+    // 384 workgroups 39 and 38; 768 61 and 65; 128 x 114 over 512, 6144 workgroups: 103 and 106).
+    constexpr bool CAN_THREE = DK == 64 && !BIAS && !DROP;
+    auto kern = CAN_THREE && wgs > 512 ? attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, CAN_THREE>
+                                       : attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, false>;
     if ((e = set_lds(kern, lds)) != hipSuccess) return e;
-    kern<<<dim3(((a.Sk + 127) / 128) * a.H * a.B), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+    kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;

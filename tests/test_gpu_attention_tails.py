@@ -28,3 +28,30 @@ def test_ragged_last_query_tile(d_kv, causal, seq):
     gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
     errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
     check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
+
+
+@pytest.mark.parametrize("batch", [3, 66])   # 24 and 528 workgroups: the two forms of the bias-free dk/dv kernel
+@pytest.mark.parametrize("seq", [33, 64])
+def test_cross_attention_forms(batch, seq):
+    import paper_2203_17189_amd as P
+    from parity_util import decoder_floors, make_decoder_case, run_decoder_block_gpu
+    cfg = replace(BASE, batch=batch, seq=seq, causal=True, enc_seq=500, name=f"cross_forms_{batch}_{seq}")
+    assert P.t5_block_kernel_path(cfg) & P.PATH_MFMA_ATTN_BWD
+    w, x, enc, dy = make_decoder_case(cfg)
+    y, saved = O.decoder_block_fwd(cfg, x, enc, w)
+    dx, denc, g = O.decoder_block_bwd(cfg, dy, w, saved)
+    gy, gdx, gdenc, gg = run_decoder_block_gpu(cfg, w, x, enc, dy)
+    errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), "denc": rel_err(gdenc, denc),
+            **{n: rel_err(gg[n], g[n]) for n in g}}
+    check_bf16(cfg.name, errs, decoder_floors(cfg, w, x, enc, dy, (y, dx, denc, g)))
+
+
+def test_long_causal_sequence():
+    """5100 positions: the bias slice in LDS no longer leaves room for three workgroups on a compute unit."""
+    cfg = replace(BASE, batch=1, seq=5100, causal=True, d_model=64, n_heads=1, d_ff=64, name="attention_tails_long")
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
+    check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
