@@ -29,13 +29,30 @@ def test_256_tiles_every_loop_remainder(nk):
     _check_gemm(8192, 2048, 64 * nk, True)
 
 
-@pytest.mark.parametrize("M,N,K", [(1332, 768, 768),      # 64x64, one round
-                                   (1020, 1032, 128),     # 64x64, 272 tiles: 128x64
-                                   (3648, 768, 192),      # 128x128, one per unit
-                                   (5000, 1024, 256),     # 128x128, two per unit
-                                   (8991, 776, 320),      # the same, ragged
-                                   (8200, 2040, 192)])    # 256x256, ragged
-def test_tile_families_k_contiguous(M, N, K):
+def _tile(M, N, K):
+    """The tile that a plain store of these sizes gets (rounds over the 256 compute units, as launch_layout counts them)."""
+    def tiles(bm, bn):
+        return -(-M // bm) * -(-N // bn)
+    t128 = tiles(128, 128)
+    if t128 <= 256:
+        return "64x64" if tiles(64, 64) <= 256 else "128x64" if tiles(128, 64) <= 256 else "128x128"
+    rem = t128 % 512
+    c128 = (0.53 if K < 640 else 0.62) * (t128 // 512 + (1.0 if rem > 256 else 1.0 if rem and K >= 1024 else 0.65 if rem else 0.0))
+    return "256x256" if -(-tiles(256, 256) // 256) <= c128 else "128x128, two per unit"
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(1332, 768, 768, "64x64"),
+                                        (1020, 1000, 128, "64x64"),
+                                        (1020, 1032, 128, "128x64"),
+                                        (3648, 768, 192, "128x128"),
+                                        (5000, 1024, 256, "128x128, two per unit"),
+                                        (8991, 776, 320, "128x128, two per unit"),
+                                        (8200, 2040, 192, "128x128, two per unit"),
+                                        (8190, 2040, 192, "256x256"),       # clamped rows of both operands
+                                        (8185, 2041, 448, "256x256"),       # ... and six loop rounds and one
+                                        (8192, 2048, 64, "256x256")])
+def test_tile_families_k_contiguous(M, N, K, tile):
+    assert _tile(M, N, K) == tile
     _check_gemm(M, N, K, True)
 
 
@@ -61,15 +78,21 @@ def test_weights_off_16_bytes():
     assert torch.equal(got, want)
 
 
-@pytest.mark.parametrize("d_model", [128, 72])
-def test_masked_gradient_copy(d_model):
-    """dWo_ff of a layer is a^T (dy o M): with one token it is the outer product, zero exactly where the mask is."""
+@pytest.mark.parametrize("dtype,d_model", [("f32", 128), ("f32", 72), ("f32", 70),      # pieces of 4 elements; one by one
+                                           ("bf16", 128), ("bf16", 72), ("bf16", 76)])  # pieces of 8; one by one
+def test_masked_gradient_copy(dtype, d_model):
+    """dWo_ff of a layer is a^T (dy o M): with one token the outer product of the hidden row and the masked, rescaled
+    gradient, whose elements are those that the general generator keeps."""
     import paper_2203_17189_amd as P
-    cfg = SI.BlockConfig("maskcopy", 81, 1, 1, d_model, 2, 8, 64, dtype="f32", dropout_rate=0.25, dropout_seed=99)
+    cfg = SI.BlockConfig("maskcopy", 81, 1, 1, d_model, 2, 8, 64, dtype=dtype, dropout_rate=0.25, dropout_seed=99)
     w, x, dy = make_case(cfg)
     dw, dx, ddy = upload_case(cfg, w, x, dy)
     _, stash = P.t5_block_fwd(cfg, dx, dw)
     _, g = P.t5_block_bwd(cfg, ddy, dx, dw, stash)
     keep = P.t5_dropout_keep(99, 4, 0.25, 1, d_model).bool()[0]
-    cols = (g["wo_ff"] != 0).any(0)
-    assert torch.equal(cols, keep)
+    assert torch.equal((g["wo_ff"] != 0).any(0), keep)
+    masked = torch.where(keep, ddy.flatten().float() * torch.tensor(4 / 3, device="cuda"), 0.0).to(ddy.dtype).double()
+    ref = int(masked.abs().argmax())
+    a = g["wo_ff"].double()[:, ref:ref + 1] / masked[ref]
+    # one product per element, in float32: two roundings of 2^-24 each, in the element and in a
+    assert float((g["wo_ff"].double() - a * masked).abs().max()) <= 4 * 2.0 ** -24 * float((a * masked).abs().max())
