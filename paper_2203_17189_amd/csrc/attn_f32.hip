@@ -495,11 +495,6 @@ void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout, const fl
   }
 }
 
-__global__ void clear_f32_kernel(float* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.f;
-}
-
 bool vec_ok(const AttnIO& io, const AttnDims& a, const void* c, const void* dc) {
   const uintptr_t all = (uintptr_t)io.q | (uintptr_t)io.k | (uintptr_t)io.v | (uintptr_t)io.dq | (uintptr_t)io.dk |
                         (uintptr_t)io.dv | (uintptr_t)c | (uintptr_t)dc;
@@ -562,11 +557,7 @@ hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, fl
 }
 
 hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
-                               float* dvec, float* ddiag, const AttnDims& a, int zero_ddiag, hipStream_t st) {
-  if (a.bias && zero_ddiag) {
-    const int64_t nd = (int64_t)a.H * (2 * a.S - 1);
-    clear_f32_kernel<<<ceil_div(nd, 256), 256, 0, st>>>(ddiag, nd);
-  }
+                               float* dvec, float* ddiag, const AttnDims& a, hipStream_t st) {
   const bool vec = vec_ok(io, a, c, dc);
   auto run = [&](auto fn) { return fn(io, c, dc, diag, lse, dvec, ddiag, a, st); };
   if (a.dk <= 32) return run(vec ? launch_bwd<32, true> : launch_bwd<32, false>);

@@ -166,11 +166,6 @@ __global__ __launch_bounds__(AW * 64) void attn_bwd_dkv_simple_kernel(
   }
 }
 
-__global__ void zero_diag_kernel(float* p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.f;
-}
-
 }  // namespace
 
 hipError_t launch_attn_fwd_simple(const AttnIO& io, int type, const float* diag, void* c, float* lse,
@@ -188,15 +183,11 @@ hipError_t launch_attn_fwd_simple(const AttnIO& io, int type, const float* diag,
 
 hipError_t launch_attn_bwd_simple(const AttnIO& io, const void* c, const void* dc, int type,
                                   const float* diag, const float* lse, float* dvec, float* ddiag,
-                                  const AttnDims& a, int zero_ddiag, hipStream_t st) {
+                                  const AttnDims& a, hipStream_t st) {
   if (type == IN_F32 && attn_f32_supported(a))
-    return launch_attn_bwd_f32(io, (const float*)c, (const float*)dc, diag, lse, dvec, ddiag, a, zero_ddiag, st);
+    return launch_attn_bwd_f32(io, (const float*)c, (const float*)dc, diag, lse, dvec, ddiag, a, st);
   const int grid_q = ceil_div((int64_t)a.B * a.H * a.S, AW);
   const int grid_k = ceil_div((int64_t)a.B * a.H * a.Sk, AW);
-  if (a.bias && zero_ddiag) {
-    const int64_t nd = (int64_t)a.H * (2 * a.S - 1);
-    zero_diag_kernel<<<ceil_div(nd, 256), 256, 0, st>>>(ddiag, nd);
-  }
   const size_t lds_q = sizeof(float) * AW * a.Sk, lds_k = sizeof(float) * AW * 2 * a.S;
   if (type == IN_BF16) {
     attn_bwd_dq_simple_kernel<bf16><<<grid_q, AW * 64, lds_q, st>>>(io, (const bf16*)c, (const bf16*)dc, diag, lse,

@@ -681,7 +681,7 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
     T5_STEP("xattn_bwd_dq", launch_attn_bwd_mfma(io, S.cx, W.dc, nullptr, S.lse_x, W.dvec, nullptr, ad, 1, 1, st));
     T5_STEP("xattn_bwd_dkv", launch_attn_bwd_mfma(io, S.cx, W.dc, nullptr, S.lse_x, W.dvec, nullptr, ad, 1, 2, st));
   } else {
-    T5_STEP("xattn_bwd", launch_attn_bwd_simple(io, S.cx, W.dc, ty, nullptr, S.lse_x, W.dvec, nullptr, ad, 0, st));
+    T5_STEP("xattn_bwd", launch_attn_bwd_simple(io, S.cx, W.dc, ty, nullptr, S.lse_x, W.dvec, nullptr, ad, st));
   }
   if (!W.defer_wgrad) {  // dXq = nx^T dq
     T5_TRY(fork_sync(W.fork));
@@ -750,7 +750,7 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
                                                 W.ddiag_part));
     T5_STEP("attn_bwd_dkv", launch_attn_bwd_mfma(io, S.c, W.dc, S.diag, S.lse, W.dvec, W.ddiag, ad, far, 2, st));
   } else {
-    T5_STEP("attn_bwd", launch_attn_bwd_simple(io, S.c, W.dc, ty, S.diag, S.lse, W.dvec, W.ddiag, ad, 0, st));
+    T5_STEP("attn_bwd", launch_attn_bwd_simple(io, S.c, W.dc, ty, S.diag, S.lse, W.dvec, W.ddiag, ad, st));
   }
   if (!W.defer_wgrad) {  // dWq | dWk | dWv = n1^T dqkv
     T5_TRY(fork_sync(W.fork));

@@ -29,6 +29,10 @@
 
 namespace t5mi {
 
+// Ends of a split reduction (gemm_mfma.hip): clears the outputs, or adds the slices in GemmEpi::aux0 up in order.
+hipError_t launch_zero_split(const GemmEpi& e, int M, int N, hipStream_t st);
+hipError_t launch_splitk_reduce(const GemmEpi& e, int M, int N, int slices, hipStream_t st);
+
 namespace {
 
 constexpr int KQ = 64;   // every segment's K must be a multiple of this (m-contiguous operands: any K)
@@ -773,38 +777,6 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
   }
 }
 
-__global__ void zero_split_kernel(GemmEpi e, int M, int N) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)M * N) return;
-  const int m = (int)(idx / N), n = (int)(idx % N);
-  const int which = n / e.split_n, nn = n - which * e.split_n;
-  float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
-  dst[(size_t)m * e.ld0 + nn] = 0.f;
-}
-
-// out[m][n] (+)= partials[0][m][n] + partials[1][m][n] + ... in that order; out as in EPI_SPLIT_F32.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmEpi e, int M, int N, int slices) {
-  const int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;  // N % 4 == 0 (checked by the launcher)
-  if (idx >= (int64_t)M * N) return;
-  const size_t mn = (size_t)M * N;
-  const float* partials = (const float*)e.aux0;
-  f32x4 acc = *reinterpret_cast<const f32x4*>(partials + idx);
-  for (int s = 1; s < slices; ++s) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(partials + (size_t)s * mn + idx);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] += v[q];
-  }
-  const int m = (int)(idx / N), n = (int)(idx % N);
-  const int which = n / e.split_n, nn = n - which * e.split_n;  // split_n % 4 == 0: the four columns share an output
-  float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2) + (size_t)m * e.ld0 + nn;
-  if (e.accumulate) {
-    const f32x4 old = *reinterpret_cast<const f32x4*>(dst);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] += old[q];
-  }
-  *reinterpret_cast<f32x4*>(dst) = acc;
-}
-
 // Tile size and k split of a weight-gradient GEMM (EPI_SPLIT_F32): few output tiles, very long k.
 // Small outputs take 128x128 tiles (fewer k-slices, hence fewer partial sums per output element); k is split
 // by the cost of the rounds over the 256 compute units and of the partial sums (measured, below).
@@ -885,8 +857,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     if (ngr > 1 && !e.accumulate) return hipErrorInvalidValue;  // grouped outputs are cleared by the caller
     const bool two_pass = split_k > 1 && split_partials_ok(g, e);  // through the partial-sum buffer in GemmEpi::aux0
     if (split_k > 1 && !e.accumulate && !two_pass) {
-      zero_split_kernel<<<ceil_div((int64_t)g.M * g.N, 256), 256, 0, st>>>(e, g.M, g.N);
-      hipError_t err = hipGetLastError();
+      hipError_t err = launch_zero_split(e, g.M, g.N, st);
       if (err != hipSuccess) return err;
     }
     GemmEpi ee = e;
@@ -894,8 +865,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     const hipError_t err = big ? launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, ee, split_k, st)
                                : launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, ee, split_k, st);
     if (err != hipSuccess || !two_pass) return err;
-    splitk_reduce_kernel<<<ceil_div((int64_t)g.M * g.N / 4, 256), 256, 0, st>>>(ee, g.M, g.N, split_k);
-    return hipGetLastError();
+    return launch_splitk_reduce(ee, g.M, g.N, split_k, st);
   }
   if constexpr (EPI != EPI_SPLIT_F32) {
     // k-contiguous operands, k-tiles of 64 (a DMA instruction then covers eight whole 128-byte rows instead of sixteen

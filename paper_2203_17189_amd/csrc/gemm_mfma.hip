@@ -11,7 +11,48 @@ __global__ void fill_ptrs_kernel(PtrChunk c, int n, const void** dst) {
   if ((int)threadIdx.x < n) dst[threadIdx.x] = c.p[threadIdx.x];
 }
 
+__global__ void zero_split_kernel(GemmEpi e, int M, int N) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (int64_t)M * N) return;
+  const int m = (int)(idx / N), n = (int)(idx % N);
+  const int which = n / e.split_n, nn = n - which * e.split_n;
+  float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
+  dst[(size_t)m * e.ld0 + nn] = 0.f;
+}
+
+// out[m][n] (+)= partials[0][m][n] + partials[1][m][n] + ... in that order; out as in EPI_SPLIT_F32.
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmEpi e, int M, int N, int slices) {
+  const int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;  // N % 4 == 0 (checked by the launcher)
+  if (idx >= (int64_t)M * N) return;
+  const size_t mn = (size_t)M * N;
+  const float* partials = (const float*)e.aux0;
+  f32x4 acc = *reinterpret_cast<const f32x4*>(partials + idx);
+  for (int s = 1; s < slices; ++s) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(partials + (size_t)s * mn + idx);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] += v[q];
+  }
+  const int m = (int)(idx / N), n = (int)(idx % N);
+  const int which = n / e.split_n, nn = n - which * e.split_n;  // split_n % 4 == 0: the four columns share an output
+  float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2) + (size_t)m * e.ld0 + nn;
+  if (e.accumulate) {
+    const f32x4 old = *reinterpret_cast<const f32x4*>(dst);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] += old[q];
+  }
+  *reinterpret_cast<f32x4*>(dst) = acc;
+}
+
 }  // namespace
+
+hipError_t launch_zero_split(const GemmEpi& e, int M, int N, hipStream_t st) {
+  zero_split_kernel<<<ceil_div((int64_t)M * N, 256), 256, 0, st>>>(e, M, N);
+  return hipGetLastError();
+}
+hipError_t launch_splitk_reduce(const GemmEpi& e, int M, int N, int slices, hipStream_t st) {
+  splitk_reduce_kernel<<<ceil_div((int64_t)M * N / 4, 256), 256, 0, st>>>(e, M, N, slices);
+  return hipGetLastError();
+}
 
 bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e) {
   if (g.in_type != IN_BF16) return false;

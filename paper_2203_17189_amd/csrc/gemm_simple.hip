@@ -3,7 +3,6 @@
 // Also: the elementwise gated-GELU of the unfused path and the bf16 weight transpose-pack.
 #include "kernels.h"
 #include <algorithm>
-#include <cstring>
 
 namespace t5mi {
 
@@ -130,7 +129,7 @@ __global__ void geglu_fwd_kernel(T* __restrict__ u, T* __restrict__ w, T* __rest
   }
 }
 
-// dst[n][k] for a 64x64 tile staged through LDS; see launch_pack_transpose_bf16.  blockIdx.z picks the job; blocks
+// dst[n][k] for a 64x64 tile staged through LDS; see launch_pack_transpose_multi.  blockIdx.z picks the job; blocks
 // outside a job's tile range leave at once.  Bound: bytes (28 MB for the weights of a d 768 layer, 6 us at the copy
 // rate); with 4-byte accesses the kernel took 17 us there.  A thread reads 16 bytes of two rows, pairs the rows'
 // elements into words (k, k + 1) of its 8 columns, and the tile leaves LDS as 16-byte runs along k.
@@ -254,18 +253,6 @@ hipError_t launch_pack_transpose_multi(const PackJobs& jobs, hipStream_t st) {
   }
   pack_transpose_kernel<<<dim3(gx, gy, jobs.count + (jobs.diag ? 1 : 0)), 256, 0, st>>>(jobs);
   return hipGetLastError();
-}
-
-hipError_t launch_pack_transpose_bf16(const void* const* srcs, int nsrc, int K, int n_each, void* dst,
-                                      int interleave, hipStream_t st) {
-  if (nsrc < 1 || nsrc > 3) return hipErrorInvalidValue;
-  PackJobs jobs;
-  std::memset(&jobs, 0, sizeof(jobs));
-  for (int i = 0; i < nsrc; ++i) jobs.j[0].src[i] = srcs[i];
-  jobs.j[0].nsrc = nsrc; jobs.j[0].K = K; jobs.j[0].n_each = n_each; jobs.j[0].interleave = interleave;
-  jobs.j[0].dst = dst;
-  jobs.count = 1;
-  return launch_pack_transpose_multi(jobs, st);
 }
 
 }  // namespace t5mi

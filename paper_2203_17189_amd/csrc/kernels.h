@@ -152,8 +152,6 @@ hipError_t launch_zero_f32(const ZeroList& z, hipStream_t st);
 // Transpose-pack for the forward weights (bf16): dst[n][k] = src_j[k][n'] for the concatenation of
 // nsrc matrices [K, n_each] along n.  interleave > 0: packed row n maps to source
 // (n / interleave) % nsrc and column (n / (interleave*nsrc)) * interleave + n % interleave.
-hipError_t launch_pack_transpose_bf16(const void* const* srcs, int nsrc, int K, int n_each, void* dst,
-                                      int interleave, hipStream_t st);
 // Up to eight such packs in one launch.
 struct PackJob {
   const void* src[3];
@@ -210,15 +208,15 @@ inline AttnIO attn_io_packed(const void* qkv, void* dqkv, int I, size_t es) {
 hipError_t launch_attn_fwd_simple(const AttnIO& io, int type, const float* diag, void* c, float* lse,
                                   const AttnDims& a, hipStream_t st);
 // dc: [B*S, H*dk] gradient of c.  Writes dq, dk, dv, dvec [B,H,S] (scratch) and, with bias, adds the
-// bias gradient into ddiag [H, 2S-1] float32 (cleared first when zero_ddiag is set).
+// bias gradient into ddiag [H, 2S-1] float32, which the caller clears.
 hipError_t launch_attn_bwd_simple(const AttnIO& io, const void* c, const void* dc, int type,
                                   const float* diag, const float* lse, float* dvec, float* ddiag,
-                                  const AttnDims& a, int zero_ddiag, hipStream_t st);
+                                  const AttnDims& a, hipStream_t st);
 // The same in float32 on the matrix units: heads of up to 128 channels, up to 4096 queries.
 bool attn_f32_supported(const AttnDims& a);
 hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st);
 hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
-                               float* dvec, float* ddiag, const AttnDims& a, int zero_ddiag, hipStream_t st);
+                               float* dvec, float* ddiag, const AttnDims& a, hipStream_t st);
 bool attn_mfma_supported(const AttnDims& a);
 hipError_t launch_attn_fwd_mfma(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a,
                                 hipStream_t st);
