@@ -18,9 +18,8 @@
 // is not finite makes dk of every earlier position not finite, and with it their dx.
 //
 // A bias table masks with -inf or with the lowest float32, which times log2(e) overflows to -inf, and a whole tile may be
-// masked so: the forward keeps its scores in natural units until the maximum has been taken off them, and that maximum
-// may be -inf.  The backward scales first, an instruction less per element (masked ones are zero either way), so the
-// log-sum it reads is kept where it stays finite in log2 units.
+// masked so: scores stay in natural units until the maximum (forward) or the log-sum (backward) has been taken off them,
+// and the running maximum may be -inf.
 //
 // The bias gradient (dq) adds each ds element to its diagonal in LDS and one global atomic per diagonal and workgroup
 // follows; one global atomic per element took longer than everything else.
@@ -287,19 +286,17 @@ void attn_fwd_f32_kernel(AttnIO io, const float* __restrict__ diag, float* __res
   l += __shfl_xor(l, 32, 64);
   if (i < S) {
     store_cols<CT, VEC>(c + ((size_t)b * S + i) * I + h * a.dk, o, (a.drop.on ? a.drop.scale : 1.f) / l, a.dk, g);
-    const float ls = fmaf(__builtin_amdgcn_logf(l), kLn2, m);
-    if (g == 0) lse[((size_t)b * a.H + h) * S + i] = ls < -2.35e38f ? -2.35e38f : ls;
+    if (g == 0) lse[((size_t)b * a.H + h) * S + i] = fmaf(__builtin_amdgcn_logf(l), kLn2, m);
   }
 }
 
 // ---- dq, dvec = rowsum(dO * O) and the per-diagonal bias gradient.  Ownership as in the forward.
 // Dynamic LDS: with bias, one float per diagonal the workgroup can touch (S + NW*32 - 1).
 template <int DKP, int NW, bool VEC>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, const float* __restrict__ o,
-                                                                  const float* __restrict__ dout,
-                                                                  const float* __restrict__ diag,
-                                                                  const float* __restrict__ lse, float* __restrict__ dvec,
-                                                                  float* __restrict__ ddiag, AttnDims a, int n_tiles) {
+__global__ __launch_bounds__(NW * 64, DKP == 32 || (DKP == 64 && NW > 1) ? 2 : 1)
+void attn_bwd_dq_f32_kernel(AttnIO io, const float* __restrict__ o, const float* __restrict__ dout,
+                            const float* __restrict__ diag, const float* __restrict__ lse, float* __restrict__ dvec,
+                            float* __restrict__ ddiag, AttnDims a, int n_tiles) {
   constexpr int CT = DKP / 32, LD = DKP + 4, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Kt[32 * LD];
   __shared__ __attribute__((aligned(16))) float Vt[32 * LD];
@@ -331,7 +328,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
   }
   dsum += __shfl_xor(dsum, 32, 64);
   if (g == 0 && i < S) dvec[srow] = dsum;
-  const float nl2 = -lse[srow] * kLog2e, sc = a.scale * kLog2e;
+  const float lse_q = lse[srow];
   uint32_t k1 = 0;
   if (a.drop.on) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)srow));
   f32x16 dq[CT];
@@ -366,7 +363,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-      const float p = __builtin_amdgcn_exp2f(fmaf(s[r], sc, fmaf(bias[r], kLog2e, nl2)));
+      const float p = __builtin_amdgcn_exp2f((fmaf(s[r], a.scale, bias[r]) - lse_q) * kLog2e);
       float x = dp[r];
       if (a.drop.on) x = drop_keep16(a.drop, k1 ^ (uint32_t)j) ? x * a.drop.scale : 0.f;
       const float ds = p * (x - dsum);
@@ -390,13 +387,13 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnIO io, con
 
 // ---- dk and dv.  One workgroup per (b, h, NW*32 keys); lane = key.
 template <int DKP, int NW, bool VEC, bool CAUSAL>
-__global__ __launch_bounds__(NW * 64)
+__global__ __launch_bounds__(NW * 64, DKP == 32 || (DKP == 64 && NW == 4) ? 2 : 1)
 void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout, const float* __restrict__ diag,
                              const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a, int n_tiles) {
   constexpr int CT = DKP / 32, LD = DKP + 4, NT = NW * 64;
   __shared__ __attribute__((aligned(16))) float Qt[32 * LD];
   __shared__ __attribute__((aligned(16))) float Dt[32 * LD];
-  __shared__ float row_l[32], row_d[32];     // -lse * log2(e) and dvec of the tile's queries
+  __shared__ float row_l[32], row_d[32];     // lse and dvec of the tile's queries
   __shared__ uint32_t row_k[32];             // their dropout row keys
   // tiles that the mask cuts through: not zero where q or dO of the query is not finite, and the last such query
   __shared__ int row_bad[NW * 32];
@@ -413,7 +410,6 @@ void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout, const fl
   f32x4 k[DKP / 8], v[DKP / 8];
   load_row<DKP, VEC>(k, (const float*)io.k + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, g);
   load_row<DKP, VEC>(v, (const float*)io.v + ((size_t)b * Sk + jl) * io.ldkv + h * a.dk, a.dk, g);
-  const float sc = a.scale * kLog2e;
   f32x16 dk[CT], dv[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) { clear(dk[ct]); clear(dv[ct]); }
@@ -446,7 +442,7 @@ void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout, const fl
       bias[r] = a.bias ? dg[-(i < S ? i : S - 1)] : 0.f;
     }
     if (tid < 32) {
-      row_l[tid] = -rl * kLog2e;
+      row_l[tid] = rl;
       row_d[tid] = rd;
       if (a.drop.on) row_k[tid] = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + (i0 + tid < S ? i0 + tid : S - 1))));
     }
@@ -457,7 +453,7 @@ void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout, const fl
         Tile::template clear_rows<LD>(Qt, bad, tid);
         Tile::template clear_rows<LD>(Dt, bad, tid);
         if (tid < 32 && bad_row[tid]) {
-          row_l[tid] = -INFINITY;
+          row_l[tid] = INFINITY;
           row_d[tid] = 0.f;
         }
         last_bad = i0 + 31 - __builtin_clz(bad);
@@ -479,7 +475,7 @@ void attn_bwd_dkv_f32_kernel(AttnIO io, const float* __restrict__ dout, const fl
     for (int r = 0; r < 16; ++r) {
       const int il = ((r >> 2) << 3) + (g << 2) + (r & 3), i = i0 + il;
       const bool ok = i < S && j < Sk && !(CAUSAL && j > i);
-      const float p = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], sc, fmaf(bias[r], kLog2e, row_l[il]))) : 0.f;
+      const float p = ok ? __builtin_amdgcn_exp2f((fmaf(s[r], a.scale, bias[r]) - row_l[il]) * kLog2e) : 0.f;
       float mk = 1.f;
       if (a.drop.on) mk = drop_keep16(a.drop, row_k[il] ^ (uint32_t)j) ? a.drop.scale : 0.f;
       s[r] = p * mk;
@@ -506,9 +502,15 @@ bool vec_ok(const AttnIO& io, const AttnDims& a, const void* c, const void* dc) 
 // channels in the 128-channel tiles: 438).  Those kernels stay ahead only below some 100 rows of 5 to 18 channels in all,
 // by up to 5 us in the backward.
 //
-// Wavefronts per workgroup: two share each K/V (or Q/dO) tile; one where a sequence has no more than 32 rows.  In the
-// forward four, beyond 64 rows: the second workgroup of two wavefronts on a compute unit lands on the SIMDs of the first
-// and leaves the other two idle (16 x 250 tokens, 6 heads of 64: 48 us with two, 32 with four; 12 heads 53 and 51).
+// Wavefronts per workgroup, which share each K/V (or Q/dO) tile: one where a sequence has no more than 32 rows, two up to
+// 64, then four: the second workgroup of two wavefronts on a compute unit may land on the SIMDs of the first and leave the
+// other two idle.  Forward, 16 x 250 tokens, 6 heads of 64: 48 us with two, 32 with four; 12 heads 53 and 51; with
+// dk/dv of four the backward at 8 x 500, 12 heads 421 and 380.  dq adds into one window in LDS, where four wavefronts get into each other's way
+// (1 x 250, 6 heads: backward 109 us with two, 130 with four; 8 x 500, 12 heads 375 and 417), so it takes four only where
+// two would make between one and two workgroups a unit (16 x 250, 6 heads: 151 and 135; 8 heads 153 and 137).
+//
+// Registers: with two wavefronts per SIMD asked for, the accumulators stay out of the accumulation registers, from which
+// the element loops would copy them (8 x 500, causal: backward 398 -> 344 us).
 template <int DKP, bool VEC, bool CAUSAL>
 hipError_t launch_fwd_form(const AttnIO& io, const float* diag, float* c, float* lse, const AttnDims& a, hipStream_t st) {
   const int bh = a.B * a.H, nt = ceil_div(a.S, 128);
@@ -522,23 +524,30 @@ hipError_t launch_fwd(const AttnIO& io, const float* diag, float* c, float* lse,
   return a.causal ? launch_fwd_form<DKP, VEC, true>(io, diag, c, lse, a, st)
                   : launch_fwd_form<DKP, VEC, false>(io, diag, c, lse, a, st);
 }
+template <int DKP, bool VEC, bool CAUSAL>
+hipError_t launch_dkv_form(const AttnIO& io, const float* dc, const float* diag, const float* lse, const float* dvec,
+                           const AttnDims& a, hipStream_t st) {
+  const int bh = a.B * a.H, nt = ceil_div(a.Sk, 128);
+  if (a.Sk <= 32) attn_bwd_dkv_f32_kernel<DKP, 1, VEC, CAUSAL><<<bh, 64, 0, st>>>(io, dc, diag, lse, dvec, a, 1);
+  else if (a.Sk <= 64) attn_bwd_dkv_f32_kernel<DKP, 2, VEC, CAUSAL><<<bh, 128, 0, st>>>(io, dc, diag, lse, dvec, a, 1);
+  else attn_bwd_dkv_f32_kernel<DKP, 4, VEC, CAUSAL><<<nt * bh, 256, 0, st>>>(io, dc, diag, lse, dvec, a, nt);
+  return hipGetLastError();
+}
 template <int DKP, bool VEC>
 hipError_t launch_bwd(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse, float* dvec,
                       float* ddiag, const AttnDims& a, hipStream_t st) {
-  const int nq = ceil_div(a.S, 64), nk = ceil_div(a.Sk, 64), bh = a.B * a.H;
-  if (a.S <= 32)
-    attn_bwd_dq_f32_kernel<DKP, 1, VEC><<<bh, 64, a.bias ? (a.S + 31) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec, ddiag, a, 1);
-  else
-    attn_bwd_dq_f32_kernel<DKP, 2, VEC><<<nq * bh, 128, a.bias ? (a.S + 63) * 4 : 0, st>>>(io, c, dc, diag, lse, dvec, ddiag,
-                                                                                        a, nq);
-  if (a.Sk <= 32) {
-    auto kern = a.causal ? attn_bwd_dkv_f32_kernel<DKP, 1, VEC, true> : attn_bwd_dkv_f32_kernel<DKP, 1, VEC, false>;
-    kern<<<bh, 64, 0, st>>>(io, dc, diag, lse, dvec, a, 1);
-  } else {
-    auto kern = a.causal ? attn_bwd_dkv_f32_kernel<DKP, 2, VEC, true> : attn_bwd_dkv_f32_kernel<DKP, 2, VEC, false>;
-    kern<<<nk * bh, 128, 0, st>>>(io, dc, diag, lse, dvec, a, nk);
-  }
-  return hipGetLastError();
+  const int bh = a.B * a.H, nt = ceil_div(a.S, 64);
+  auto dq = [&](auto kern, int tiles, int waves) {
+    const int lds = a.bias ? (a.S + waves * 32 - 1) * 4 : 0;
+    kern<<<tiles * bh, waves * 64, lds, st>>>(io, c, dc, diag, lse, dvec, ddiag, a, tiles);
+  };
+  if (a.S <= 32) dq(attn_bwd_dq_f32_kernel<DKP, 1, VEC>, 1, 1);
+  else if (a.S > 64 && nt * bh > 256 && nt * bh <= 512) dq(attn_bwd_dq_f32_kernel<DKP, 4, VEC>, ceil_div(a.S, 128), 4);
+  else dq(attn_bwd_dq_f32_kernel<DKP, 2, VEC>, nt, 2);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  return a.causal ? launch_dkv_form<DKP, VEC, true>(io, dc, diag, lse, dvec, a, st)
+                  : launch_dkv_form<DKP, VEC, false>(io, dc, diag, lse, dvec, a, st);
 }
 
 }  // namespace

@@ -23,6 +23,7 @@ CASES = [replace(C, batch=1, seq=1),                                            
          replace(C, batch=2, seq=70, d_model=60, n_heads=3, d_kv=50, d_ff=64, causal=True),  # 64-channel tiles, element loads
          replace(C, batch=2, seq=40, d_model=60, n_heads=1, d_kv=66, d_ff=64, dropout_rate=0.25, dropout_seed=5),  # 128
          replace(C, batch=2, seq=20, d_model=60, n_heads=1, d_kv=33, d_ff=64),             # one wavefront, element loads
+         replace(C, batch=75, seq=130, d_model=64, n_heads=2, d_kv=16, d_ff=64, causal=True),  # dq: 450 workgroups, four wavefronts
          replace(C, batch=2, seq=40, d_model=64, n_heads=1, d_kv=136, d_ff=64),            # general attention kernels
          replace(C, batch=21, seq=129, d_model=520, n_heads=4, d_kv=32, d_ff=1056, mlp="relu"),   # 128 x 128 tiles
          replace(C, batch=13, seq=100, d_model=256, n_heads=4, d_kv=64, d_ff=512, deterministic=True)]
