@@ -499,15 +499,16 @@ bool vec_ok(const AttnIO& io, const AttnDims& a, const void* c, const void* dc) 
 
 // Channels are rounded up to 32, 64 or 128, with float4 loads (VEC) or element loads.  Against the row-at-a-time kernels,
 // forward + backward at 12 x 250 tokens, 6 heads: 5 channels 373 -> 147 us, 18 836 -> 150, 50 2003 -> 197, 66 2743 -> 332 (5
-// channels in the 128-channel tiles: 438).  Those kernels stay ahead only below some 100 rows of 5 to 18 channels in all,
-// by up to 5 us in the backward.
+// channels in the 128-channel tiles: 438).  Those kernels stay ahead only with 5 to 18 channels and some 100 rows in all
+// (2 x 33 tokens), by up to 5 us in the backward.
 //
 // Wavefronts per workgroup, which share each K/V (or Q/dO) tile: one where a sequence has no more than 32 rows, two up to
 // 64, then four: the second workgroup of two wavefronts on a compute unit may land on the SIMDs of the first and leave the
-// other two idle.  Forward, 16 x 250 tokens, 6 heads of 64: 48 us with two, 32 with four; 12 heads 53 and 51; with
-// dk/dv of four the backward at 8 x 500, 12 heads 421 and 380.  dq adds into one window in LDS, where four wavefronts get into each other's way
-// (1 x 250, 6 heads: backward 109 us with two, 130 with four; 8 x 500, 12 heads 375 and 417), so it takes four only where
-// two would make between one and two workgroups a unit (16 x 250, 6 heads: 151 and 135; 8 heads 153 and 137).
+// other two idle.  Forward, 16 x 250 tokens, 6 heads of 64: 48 us with two, 32 with four; 12 heads 53 and 51.  Backward at
+// 8 x 500, 12 heads: 421 us with two in dk/dv, 380 with four.  dq adds into one window in LDS, where four wavefronts get
+// into each other's way (1 x 250, 6 heads: backward 109 us with two in dq, 130 with four; 8 x 500, 12 heads 375 and 417),
+// so it takes four only where two would make between one and two workgroups a unit (16 x 250, 6 heads: 151 and 135;
+// 8 heads 153 and 137).
 //
 // Registers: with two wavefronts per SIMD asked for, the accumulators stay out of the accumulation registers, from which
 // the element loops would copy them (8 x 500, causal: backward 398 -> 344 us).

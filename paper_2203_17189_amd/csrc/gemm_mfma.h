@@ -871,7 +871,9 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     // k-contiguous operands, k-tiles of 64 (a DMA instruction then covers eight whole 128-byte rows instead of sixteen
     // half rows; the L1 processes a line per request whatever part of it is used).  In the order tried:
     //  * 256x256, one workgroup per compute unit, three A and two B stages: the fewest operand bytes per flop, so the
-    //    fastest where its last round over the 256 compute units is full (32768 x 6144 x 2048: 646 us against 770);
+    //    fastest where its last round over the 256 compute units is full (32768 x 6144 x 2048: 646 us against 770); also
+    //    for the residual epilogue with dropout, which spills 33 registers outside the loop there (32768 x 2048 x 5120 557 us
+    //    against 675 with 128x128 and 736 with 256x128; 65536 x 768 x 2048 209, 231, 242);
     //  * 128x128, two workgroups per compute unit, two stages: a round of 512 tiles costs w of a 256x256 round, which
     //    is four times the work for w = 0.62 (plain store and gated-GELU forward; 0.53 at K < 640), 0.56 and 0.49 (K <= 768)
     //    with the residual epilogue, whose extra traffic the second workgroup hides; a last round of up to 256 tiles

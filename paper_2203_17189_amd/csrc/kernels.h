@@ -125,8 +125,9 @@ struct SplitJobs {
   int count;
 };
 hipError_t launch_split_reduce(const SplitJobs& jobs, hipStream_t st);
-// bf16 MFMA kernel.  Requires in_type == IN_BF16, every K % 64 == 0 (k-contiguous operands), lda/ldb % 8 == 0, N % 64 == 0
-// and 16-byte aligned pointers; gemm_mfma_supported() checks this.
+// bf16 MFMA kernel.  Requires in_type == IN_BF16, M and N >= 8, every K % 64 == 0 (k-contiguous operands) or M and N
+// multiples of 8 (m-contiguous ones, any K), N % 64 == 0 for the gated-GELU forward, lda/ldb % 8 == 0 and 16-byte aligned
+// pointers; gemm_mfma_supported() checks this.
 bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e);
 hipError_t launch_gemm_mfma(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 // its epilogue families
