@@ -94,3 +94,64 @@ def test_side_stream():
             _same(g1, g2)
     finally:
         P.t5_wgrad_overlap_enable(False)
+
+
+def _buffers(P, cfg, dw, tx, guard):
+    from paper_2203_17189_amd import binding as B
+    n = P.t5_decoder_block_workspace_bytes(cfg) if cfg.enc_seq else P.t5_block_workspace_bytes(cfg)
+    ws = torch.full((n + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    return n, ws, (B.alloc_decoder_grads if cfg.enc_seq else B.alloc_grads)(cfg, dw), torch.empty_like(tx)
+
+
+@pytest.mark.parametrize("enc_seq", [0, 130])
+@pytest.mark.parametrize("d_model,d_ff", [(128, 256), (126, 250), (132, 66)])  # sliced; not aligned: whole; some of each
+def test_slices_stay_inside_the_workspace(enc_seq, d_model, d_ff):
+    import paper_2203_17189_amd as P
+    cfg = replace(C, d_model=d_model, d_ff=d_ff, causal=bool(enc_seq), enc_seq=enc_seq, name="f32_guard")
+    w, x, enc, dy = make_decoder_case(cfg) if enc_seq else (*make_case(cfg)[:2], None, make_case(cfg)[2])
+    dw = {k: to_dev(v, "f32") for k, v in w.items()}
+    tx, tdy = to_dev(x, "f32"), to_dev(dy, "f32")
+    n, ws, grads, dx = _buffers(P, cfg, dw, tx, 8 << 20)
+    if enc_seq:
+        te = to_dev(enc, "f32")
+        _, stash = P.t5_decoder_block_fwd(cfg, tx, te, dw)
+        P.t5_decoder_block_bwd(cfg, tdy, tx, te, dw, stash, dx=dx, grads=grads, workspace=ws[:n])
+    else:
+        _, stash = P.t5_block_fwd(cfg, tx, dw)
+        P.t5_block_bwd(cfg, tdy, tx, dw, stash, dx=dx, grads=grads, workspace=ws[:n])
+    assert bool((ws[n:] == 0xA5).all())
+
+
+def test_captured_step():
+    """The step recorded into a graph gives the eager bits on every replay, with other inputs and eager work between."""
+    import paper_2203_17189_amd as P
+    w, x, dy = make_case(C)
+    dw = {k: to_dev(v, "f32") for k, v in w.items()}
+    tx, tdy = to_dev(x, "f32"), to_dev(dy, "f32")
+    y, stash = P.t5_block_fwd(C, tx, dw)
+    sets = [_buffers(P, C, dw, tx, 0) for _ in range(2)]
+
+    def step(n, ws, grads, dx):
+        P.t5_block_fwd(C, tx, dw, y=y, stash=stash)
+        P.t5_block_bwd(C, tdy, tx, dw, stash, dx=dx, grads=grads, workspace=ws)
+
+    fwd_ws = torch.empty(P.t5_block_workspace_bytes(C), dtype=torch.uint8, device="cuda")
+
+    def captured(n, ws, grads, dx):
+        P.t5_block_fwd(C, tx, dw, y=y, stash=stash, workspace=fwd_ws)
+        P.t5_block_bwd(C, tdy, tx, dw, stash, dx=dx, grads=grads, workspace=ws)
+
+    captured(*sets[0])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        captured(*sets[0])
+    for rep in range(4):
+        _, x2, dy2 = make_case(C, seed_offset=rep + 1)
+        tx.copy_(to_dev(x2, "f32"))
+        tdy.copy_(to_dev(dy2, "f32"))
+        g.replay()
+        step(*sets[1])
+        torch.cuda.synchronize()
+        assert torch.equal(sets[0][3], sets[1][3]), rep
+        _same(sets[1][2], sets[0][2])
