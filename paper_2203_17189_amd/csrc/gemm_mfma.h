@@ -558,6 +558,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
         return;
       }
     }
+#define T5MI_EPI_EDGE 0
     if (interior) {
       float* stg = reinterpret_cast<float*>(smem) + wave * (64 * EP_LD);
       const int cl = lane & 31, rl = (lane >> 5) << 2;
@@ -717,6 +718,26 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
       }
       return;
     }
+#undef T5MI_EPI_EDGE
+    // A last tile of rows that is not full takes the row-wise path too, its missing rows left out.  Element by element,
+    // with the residual read one value at a time, it took longer than the rest of the launch: 18668 x 512 x 1024 with
+    // residual, 146 tiles of 256x256, 106 -> 45 us (18432 rows: 36); 31713 x 2048 x 5120 614 -> 545.
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_GEGLU_BWD) {
+      if (mw < g.M && nw + TNW <= g.N && ep_ld0 % 8 == 0 && e.ld_aux % 8 == 0) {
+        float* stg = reinterpret_cast<float*>(smem) + wave * (64 * EP_LD);
+        const int cl = lane & 31, rl = (lane >> 5) << 2;
+#define T5MI_EPI_EDGE 1
+#define T5MI_EPI_AF 2
+#define T5MI_EPI_OB 2
+#define T5MI_EPI_SP 2
+#include "gemm_epilogue_rows.inc"
+#undef T5MI_EPI_EDGE
+#undef T5MI_EPI_AF
+#undef T5MI_EPI_OB
+#undef T5MI_EPI_SP
+        return;
+      }
+    }
   }
   // ---- edge tiles: per-element bounds checks
   const int col_l = lane & 31, row_l = (lane >> 5) << 2;
@@ -872,8 +893,8 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     // half rows; the L1 processes a line per request whatever part of it is used).  In the order tried:
     //  * 256x256, one workgroup per compute unit, three A and two B stages: the fewest operand bytes per flop, so the
     //    fastest where its last round over the 256 compute units is full (32768 x 6144 x 2048: 646 us against 770); also
-    //    for the residual epilogue with dropout, which spills 33 registers outside the loop there (32768 x 2048 x 5120 557 us
-    //    against 675 with 128x128 and 736 with 256x128; 65536 x 768 x 2048 209, 231, 242);
+    //    for the residual epilogue with dropout (32768 x 2048 x 5120 557 us against 675 with 128x128 and 736 with 256x128;
+    //    65536 x 768 x 2048 209, 231, 242);
     //  * 128x128, two workgroups per compute unit, two stages: a round of 512 tiles costs w of a 256x256 round, which
     //    is four times the work for w = 0.62 (plain store and gated-GELU forward; 0.53 at K < 640), 0.56 and 0.49 (K <= 768)
     //    with the residual epilogue, whose extra traffic the second workgroup hides; a last round of up to 256 tiles

@@ -96,3 +96,21 @@ def test_masked_gradient_copy(dtype, d_model):
     a = g["wo_ff"].double()[:, ref:ref + 1] / masked[ref]
     # one product per element, in float32: two roundings of 2^-24 each, in the element and in a
     assert float((g["wo_ff"].double() - a * masked).abs().max()) <= 4 * 2.0 ** -24 * float((a * masked).abs().max())
+
+
+@pytest.mark.parametrize("full,ragged,seq", [(292, 291, 64), (96, 95, 64), (8, 7, 64)])  # 256x256, 128x128, small tiles
+@pytest.mark.parametrize("mlp,rate", [("geglu_tanh", 0.0), ("geglu_tanh", 0.125), ("relu", 0.0)])
+def test_rows_do_not_depend_on_the_last_tile(full, ragged, seq, mlp, rate):
+    """y and dx of a batch are, bit for bit, those of the same sequences in a larger batch that fills its last tile of rows."""
+    import paper_2203_17189_amd as P
+    cfg = SI.BlockConfig("last_rows", 82, full, seq, 512, 6, 64, 1024, attn_scale=0.125, mlp=mlp, dropout_rate=rate,
+                         dropout_seed=5)
+    w, x, dy = make_case(cfg)
+    out = []
+    for b in (full, ragged):
+        c = replace(cfg, batch=b)
+        dw, tx, tdy = upload_case(c, w, x[:b], dy[:b])
+        y, stash = P.t5_block_fwd(c, tx, dw)
+        dx, _ = P.t5_block_bwd(c, tdy, tx, dw, stash)
+        out.append((y.view(b, seq, -1)[:ragged].clone(), dx.view(b, seq, -1)[:ragged].clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
