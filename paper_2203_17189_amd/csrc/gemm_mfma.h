@@ -896,7 +896,9 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    for the residual epilogue with dropout (32768 x 2048 x 5120 557 us against 675 with 128x128 and 736 with 256x128;
     //    65536 x 768 x 2048 209, 231, 242);
     //  * 128x128, two workgroups per compute unit, two stages: a round of 512 tiles costs w of a 256x256 round, which
-    //    is four times the work for w = 0.62 (plain store and gated-GELU forward; 0.53 at K < 640), 0.56 and 0.49 (K <= 768)
+    //    is four times the work for w = 0.62 (plain store and gated-GELU forward; 0.53 at K < 640, 0.40 for a plain store
+    //    whose last 256 columns are not all there: 12800 x 1152 x 512 40 us with 256x256, 25 with this, 25600 rows 59 and
+    //    43), 0.56 and 0.49 (K <= 768)
     //    with the residual epilogue, whose extra traffic the second workgroup hides; a last round of up to 256 tiles
     //    costs 0.65 of a full one, as much as a full one from K = 1024 on.  The cheaper sum of rounds is taken
     //    (14592 x 768 x 2304, 171 against 684 tiles: 59 us against 68; 8991 x 768 x 4096, 108 against 426: 92 against 64).
@@ -910,7 +912,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     int64_t K = 0;
     for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
     const double last = K >= 1024 ? 1.0 : 0.65;
-    const double w = EPI == EPI_RESID ? (K <= 768 ? 0.49 : 0.56) : K < 640 ? 0.53 : 0.62;
+    const double w = EPI == EPI_RESID ? (K <= 768 ? 0.49 : 0.56) : K < 640 ? (EPI == EPI_STORE && g.N % 256 != 0 ? 0.40 : 0.53) : 0.62;
     const double c256 = (double)((t256 + 255) / 256);
     const int64_t rem = t128 % 512;
     const double c128 = w * ((double)(t128 / 512) + (rem > 256 ? 1.0 : rem > 0 ? last : 0.0));

@@ -37,7 +37,7 @@ def _tile(M, N, K):
     if t128 <= 256:
         return "64x64" if tiles(64, 64) <= 256 else "128x64" if tiles(128, 64) <= 256 else "128x128"
     rem = t128 % 512
-    c128 = (0.53 if K < 640 else 0.62) * (t128 // 512 + (1.0 if rem > 256 else 1.0 if rem and K >= 1024 else 0.65 if rem else 0.0))
+    c128 = ((0.40 if N % 256 else 0.53) if K < 640 else 0.62) * (t128 // 512 + (1.0 if rem > 256 else 1.0 if rem and K >= 1024 else 0.65 if rem else 0.0))
     return "256x256" if -(-tiles(256, 256) // 256) <= c128 else "128x128, two per unit"
 
 
@@ -48,8 +48,10 @@ def _tile(M, N, K):
                                         (5000, 1024, 256, "128x128, two per unit"),
                                         (8991, 776, 320, "128x128, two per unit"),
                                         (8200, 2040, 192, "128x128, two per unit"),
-                                        (8190, 2040, 192, "256x256"),       # clamped rows of both operands
-                                        (8185, 2041, 448, "256x256"),       # ... and six loop rounds and one
+                                        (8190, 2040, 192, "128x128, two per unit"),
+                                        (8190, 2048, 192, "256x256"),       # clamped rows of the first operand
+                                        (8190, 2040, 704, "256x256"),       # ... of both
+                                        (8185, 2041, 832, "256x256"),
                                         (8192, 2048, 64, "256x256")])
 def test_tile_families_k_contiguous(M, N, K, tile):
     assert _tile(M, N, K) == tile
