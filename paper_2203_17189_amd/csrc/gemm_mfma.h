@@ -722,6 +722,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
     // A last tile of rows that is not full takes the row-wise path too, its missing rows left out.  Element by element,
     // with the residual read one value at a time, it took longer than the rest of the launch: 18668 x 512 x 1024 with
     // residual, 146 tiles of 256x256, 106 -> 45 us (18432 rows: 36); 31713 x 2048 x 5120 614 -> 545.
+    // A wave whose tile lies wholly outside ends here (no barrier follows) instead of stepping over its elements one by
+    // one: 9344 x 1024 x 1024 52 -> 41 us.  Plain stores and gated-GELU backward keep the walk: with a return at the
+    // top of the epilogue for every kind, 25600 x 3072 x 1024 went from 155 to 190 us.
+    if constexpr (EPI == EPI_RESID)
+      if (mw >= g.M || nw >= g.N) return;
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_GEGLU_BWD) {
       if (mw < g.M && nw + TNW <= g.N && ep_ld0 % 8 == 0 && e.ld_aux % 8 == 0) {
         float* stg = reinterpret_cast<float*>(smem) + wave * (64 * EP_LD);
