@@ -334,6 +334,176 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
   }
 }
 
+// ------------------------------------------------------------------ few tiles
+// 32x32 results (32x32 pairs of u and w columns for the gated inputs) per workgroup of WK wavefronts, float32 matrix
+// instructions.  At 64 tokens a product is one round trip to memory and a short chain of products, and the code of the
+// launch is read for the first time as often as not, so: every wavefront takes its own batches of 32 k straight into registers
+// in the order of the instruction's operands, the next batch on its way (no staging, no barrier), the operands of the
+// epilogue are requested before the products, the wavefronts' sums meet in LDS once, in their order, and all of them
+// share the epilogue.  (The kernel it replaced staged through LDS and left the epilogue, a branch an element, to one of
+// four wavefronts.)  Layer of d 64, 64 tokens: its 12 products 132 -> 86 us, 140 -> 104 us in all; dn2 of d 768, 200 tokens
+// (k 4096) 66 -> 42 us.  Eight wavefronts from 128 k on: with fewer k some of them would have nothing to do.
+template <int WK, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(WK * 64) void gemm_f32_small_kernel(GemmDesc g, GemmEpi e) {
+  constexpr bool GF = EPI == EPI_GEGLU_FWD;
+  constexpr int NJ = GF ? 2 : 1, U = 4;  // column tiles; steps of 8 k in a batch
+  __shared__ float part[WK][NJ][32][32];
+  const int tid = threadIdx.x, lane = tid & 63, g2 = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;  // (GF: n0 counts hidden units)
+  const int lda = g.seg[0].lda, ldb = g.seg[0].ldb, N = GF ? g.N >> 1 : g.N;
+
+  // epilogue: thread -> column tid % 32, rows tid / 32 + (threads / 32) * i
+  constexpr int RS = WK * 2, NE = 32 / RS;
+  const int en = n0 + (tid & 31), er = m0 + (tid >> 5);
+  const bool add = EPI == EPI_SPLIT_F32 && e.accumulate;
+  float xa[NE], xb[NE];
+  size_t eo[NE];
+  float* out0 = (float*)e.out0;
+  if constexpr (EPI == EPI_SPLIT_F32) {
+    const int which = en / e.split_n;
+    out0 = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
+    for (int i = 0; i < NE; ++i) eo[i] = (size_t)(er + RS * i) * e.ld0 + (en - which * e.split_n);
+  } else {
+    for (int i = 0; i < NE; ++i) eo[i] = (size_t)(er + RS * i) * e.ld0 + en;
+  }
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    const bool ok = er + RS * i < g.M && en < N;
+    xa[i] = xb[i] = 0.f;
+    if constexpr (EPI == EPI_RESID || EPI == EPI_GEGLU_BWD) {
+      const size_t o = ok ? (size_t)(er + RS * i) * (e.ld_aux ? e.ld_aux : e.ld0) + en : 0;
+      xa[i] = ((const float*)e.aux0)[o];
+      if constexpr (EPI == EPI_GEGLU_BWD) xb[i] = ((const float*)e.aux1)[o];
+    } else if constexpr (EPI == EPI_SPLIT_F32) {
+      if (add && ok) xa[i] = out0[eo[i]];
+    }
+  }
+
+  // this lane's row of A and columns of B (past the end: the last one, its results are not stored)
+  const int m = m0 + l32 < g.M ? m0 + l32 : g.M - 1;
+  int n[NJ];
+  const float* bsrc = nullptr;  // columns from several matrices
+  n[0] = n0 + l32 < N ? n0 + l32 : N - 1;
+  if constexpr (GF) n[NJ - 1] = n[0];
+  if constexpr (!GF && !B_KC) {
+    if (g.nsrc > 1) {
+      const int q = n[0] / g.nsrc_cols;
+      bsrc = (const float*)(q == 0 ? g.seg[0].B : q == 1 ? g.seg[1].B : g.seg[2].B);
+      n[0] -= q * g.nsrc_cols;
+    }
+  }
+  f32x16 acc[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+
+  f32x4 va[2][U], vb[2][NJ][U];
+  auto load = [&](const float* A, const float* B, const float* B1, int K, int b, f32x4 (&a)[U], f32x4 (&bb)[NJ][U])
+                  __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = b * (8 * U) + u * 8 + g2 * 4;
+      if constexpr (A_KC) {
+        a[u] = ld4<true>(A, (size_t)m * lda + k, K - k);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[u][q] = A[(size_t)(k + q < K ? k + q : K - 1) * lda + m];
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const float* Bj = j ? B1 : B;
+        if constexpr (B_KC) {
+          bb[j][u] = ld4<true>(Bj, (size_t)n[j] * ldb + k, K - k);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) bb[j][u][q] = Bj[(size_t)(k + q < K ? k + q : K - 1) * ldb + n[j]];
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[u][q] = k + q < K ? a[u][q] : 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) bb[j][u][q] = k + q < K ? bb[j][u][q] : 0.f;
+      }
+    }
+  };
+  auto mul = [&](const f32x4 (&a)[U], const f32x4 (&bb)[NJ][U]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][q], bb[j][u][q], acc[j], 0, 0, 0);
+  };
+  int b0 = wave;  // batches wave, wave + WK, ... over all segments
+  for (int s = 0; s < g.nseg; ++s) {
+    const int K = g.seg[s].K, nb = (K + 8 * U - 1) / (8 * U);
+    const float* A = (const float*)g.seg[s].A;
+    const float* B = bsrc ? bsrc : (const float*)g.seg[s].B;
+    const float* B1 = (const float*)g.seg[GF ? 1 : 0].B;
+    int b = b0;
+    if (b < nb) {
+      load(A, B, B1, K, b, va[0], vb[0]);
+      for (;;) {
+        if (b + WK < nb) load(A, B, B1, K, b + WK, va[1], vb[1]);
+        mul(va[0], vb[0]);
+        b += WK;
+        if (b >= nb) break;
+        if (b + WK < nb) load(A, B, B1, K, b + WK, va[0], vb[0]);
+        mul(va[1], vb[1]);
+        b += WK;
+        if (b >= nb) break;
+      }
+    }
+    b0 = b - nb;
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[wave][j][((r >> 2) << 3) + (g2 << 2) + (r & 3)][l32] = acc[j][r];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    const int row = er + RS * i;
+    float v = part[0][0][row - m0][tid & 31], w = 0.f;
+    if constexpr (GF) w = part[0][NJ - 1][row - m0][tid & 31];
+#pragma unroll
+    for (int k = 1; k < WK; ++k) {
+      v += part[k][0][row - m0][tid & 31];
+      if constexpr (GF) w += part[k][NJ - 1][row - m0][tid & 31];
+    }
+    if (row >= g.M || en >= N) continue;
+    const float mk = e.drop.on && !(EPI == EPI_RESID && e.aux_mask) ? drop_mult(e.drop, drop_row_key(e.drop, (uint32_t)row), (uint32_t)en) : 1.f;
+    if constexpr (GF) {
+      float gl, dgl;
+      gelu_both(e.act, v, gl, dgl);
+      out0[eo[i]] = w * dgl * mk;
+      ((float*)e.out1)[eo[i]] = gl * mk;
+      ((float*)e.out2)[eo[i]] = gl * w * mk;
+    } else if constexpr (EPI == EPI_STORE) {
+      out0[eo[i]] = (e.act == ACT_RELU ? fmaxf(v, 0.f) : v) * mk;
+    } else if constexpr (EPI == EPI_RESID) {
+      out0[eo[i]] = e.aux_mask ? (xa[i] > 0.f ? v * (e.drop.on ? e.drop.scale : 1.f) : 0.f) : v * mk + xa[i];
+    } else if constexpr (EPI == EPI_GEGLU_BWD) {
+      out0[eo[i]] = v * xa[i];
+      ((float*)e.out1)[eo[i]] = v * xb[i];
+    } else {
+      out0[eo[i]] = xa[i] + v;
+    }
+  }
+}
+template <bool A_KC, bool B_KC, int EPI>
+hipError_t launch_small(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
+  dim3 grid(ceil_div(EPI == EPI_GEGLU_FWD ? g.N / 2 : g.N, 32), ceil_div(g.M, 32));
+  int K = 0;
+  for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
+  if (K > 128) gemm_f32_small_kernel<8, A_KC, B_KC, EPI><<<grid, 512, 0, st>>>(g, e);
+  else gemm_f32_small_kernel<4, A_KC, B_KC, EPI><<<grid, 256, 0, st>>>(g, e);
+  return hipGetLastError();
+}
+
 // All sliced weight gradients of a layer in one launch: a thread adds four columns of one row over the slices, in their
 // order.  Bound: bytes, the slices once, the outputs twice.  (Float atomics of the slices on the outputs took longer, and
 // their order varied from run to run: layer of d 512 over 4000 tokens 893 us, 880 with this.)
@@ -437,7 +607,7 @@ hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   auto filled = [](int64_t t) { return (double)t / (double)((t + 255) / 256 * 256); };
   if (t128 >= 192 && filled(t128) * 1.1 >= filled(t64)) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
   if (t64 >= 128) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
-  return launch_tile<32, 64, 1, 1, 4, 64, A_KC, B_KC, EPI, true>(g, e, 1, st);
+  return launch_small<A_KC, B_KC, EPI>(g, e, st);
 }
 
 }  // namespace

@@ -29,6 +29,14 @@ CASES = [replace(C, batch=1, seq=1),                                            
          replace(C, batch=13, seq=100, d_model=256, n_heads=4, d_kv=64, d_ff=512, deterministic=True)]
 
 
+# Few tiles: one to three batches of 32 k for four or eight wavefronts, batches that run over a segment's end, k not a
+# multiple of 4, 8 or 32, columns from several matrices, results narrower than a tile
+SMALL_CASES = [replace(C, batch=1, seq=33, d_model=36, n_heads=1, d_kv=20, d_ff=68, num_buckets=32),
+               replace(C, batch=3, seq=43, d_model=132, n_heads=3, d_kv=12, d_ff=164, mlp="geglu_erf", dropout_rate=0.25, dropout_seed=9),
+               replace(C, batch=1, seq=97, d_model=260, n_heads=2, d_kv=64, d_ff=1060, causal=True),
+               replace(C, batch=2, seq=40, d_model=96, n_heads=3, d_kv=32, d_ff=36, mlp="relu", dropout_rate=0.125, dropout_seed=4)]
+
+
 def _check(pairs):
     for name, got, want in pairs:
         if name in ("wq", "wk") and not np.any(np.abs(want) > 1e-12):  # one key: no gradient through the softmax
@@ -37,7 +45,7 @@ def _check(pairs):
         assert rel_err(got, want)[0] <= TOL_F32[0], (name, rel_err(got, want))
 
 
-@pytest.mark.parametrize("cfg", CASES, ids=lambda c: f"{c.batch}x{c.seq}_d{c.d_model}_k{c.d_kv}_f{c.d_ff}")
+@pytest.mark.parametrize("cfg", CASES + SMALL_CASES, ids=lambda c: f"{c.batch}x{c.seq}_d{c.d_model}_k{c.d_kv}_f{c.d_ff}")
 def test_block_f32_matrix(cfg):
     if cfg.dropout_rate:
         cfg = replace(cfg, dropout_rate=float(np.float32(cfg.dropout_rate)))
