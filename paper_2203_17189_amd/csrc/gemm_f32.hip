@@ -1,4 +1,5 @@
-// float32 GEMM on the matrix units (v_mfma_f32_32x32x2_f32: float32 operands, products and sums).
+// float32 GEMM on the matrix units.  Small problems run on v_mfma_f32_32x32x2_f32 (float32 operands, products and sums),
+// larger ones on the bf16 units with every operand in three parts (second kernel below).
 //
 //   C[m,n] = sum_s sum_k A_s(m,k) B_s(n,k)
 //
@@ -20,7 +21,8 @@
 // MFMA e of a group of 8 k contracts k = 4*half + e of both operands: any pairing serves as long as both agree.
 //
 // Measured on the layer d 512, 6 heads, d_ff 1024, 4000 tokens (forward + backward): GEMMs 5.0 ms with the FMA kernel
-// this replaces for float32 (64x64 tiles, 4x4 products a thread, one load in flight).
+// this replaced for float32 (64x64 tiles, 4x4 products a thread, one load in flight), 650 us with float32 instructions
+// everywhere, 560 us now.
 #include "kernels.h"
 #include <algorithm>
 #include <atomic>
@@ -28,6 +30,22 @@
 namespace t5mi {
 
 namespace {
+
+// Workgroup -> (n tile, m tile, k-slice).  Consecutive workgroups go to different XCDs, so each XCD takes a contiguous run of
+// the tiles in the order n, m, slice: the tiles that share rows of A (or a slice's k range) meet in one L2.
+struct TilePos {
+  int x, y, z;
+};
+__device__ __forceinline__ TilePos tile_pos(int gx, int gy) {
+  const uint32_t n = gridDim.x, id = blockIdx.x, q = n / 8, r = n % 8, xcd = id % 8;
+  uint32_t t = xcd * q + (xcd < r ? xcd : r) + id / 8;
+  TilePos p;
+  p.x = (int)(t % (uint32_t)gx);
+  t /= (uint32_t)gx;
+  p.y = (int)(t % (uint32_t)gy);
+  p.z = (int)(t / (uint32_t)gy);
+  return p;
+}
 
 struct F32Src {  // where a thread's float4 slot of an operand comes from
   size_t off;    // elements from (segment base + tile start)
@@ -49,6 +67,101 @@ __device__ __forceinline__ f32x4 ld4(const float* base, size_t off, int nv) {
       if (q < nv) v[q] = base[off + q];
     return v;
   }
+}
+
+// Epilogue of a wavefront's MI x NI tiles from (mw, nw) on: register r of a 32x32 tile is row (r/4)*8 + half*4 + r%4, column lane%32: a wavefront writes
+// 128-byte runs of two rows.  Operands of the epilogue are fetched for a whole row of tiles before the first store:
+// the compiler cannot move a load across a store that might alias it, and one at a time each costs a round trip
+// (the gated-GELU backward at 64 tokens: 23 us, most of it here).
+template <bool FULL, int MI, int NI, int EPI>
+__device__ __forceinline__ void f32_epilogue_part(const GemmDesc& g, const GemmEpi& e, int split_k, const f32x16 (&acc)[MI][NI],
+                                             int mw, int nw, int slice, int lane) {
+  const int g2 = lane >> 5, l32 = lane & 31;
+  constexpr bool AUX = EPI == EPI_RESID || EPI == EPI_GEGLU_BWD || EPI == EPI_SPLIT_F32;
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int mb = mw + i * 32 + (g2 << 2), nb = nw + l32;
+    float xa[AUX ? 16 : 1][NI], xb[EPI == EPI_GEGLU_BWD ? 16 : 1][NI];
+    if (AUX && (EPI != EPI_SPLIT_F32 || (split_k == 1 && e.accumulate))) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const int m = mb + ((r >> 2) << 3) + (r & 3), n = nb + j * 32;
+          const int mc = FULL || m < g.M ? m : g.M - 1, nc = FULL || n < g.N ? n : g.N - 1;
+          if constexpr (EPI == EPI_SPLIT_F32) {
+            const int which = nc / e.split_n;  // (one slice)
+            const float* d = (const float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
+            xa[r][j] = d[(size_t)mc * e.ld0 + (nc - which * e.split_n)];
+          } else if constexpr (AUX) {
+            const size_t oa = (size_t)mc * (e.ld_aux ? e.ld_aux : e.ld0) + nc;
+            xa[r][j] = ((const float*)e.aux0)[oa];
+            if constexpr (EPI == EPI_GEGLU_BWD) xb[r][j] = ((const float*)e.aux1)[oa];
+          }
+        }
+    } else if (AUX) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) xa[AUX ? r : 0][j] = 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = mb + ((r >> 2) << 3) + (r & 3);
+      if (!FULL && m >= g.M) continue;
+      const uint32_t k1 = e.drop.on ? drop_row_key(e.drop, (uint32_t)m) : 0u;
+      if constexpr (EPI == EPI_GEGLU_FWD) {
+#pragma unroll
+        for (int j = 0; j < NI; j += 2) {
+          const int f = ((nw + j * 32) >> 1) + l32;
+          if (!FULL && f >= (g.N >> 1)) continue;
+          float gl, dgl;
+          gelu_both(e.act, acc[i][j][r], gl, dgl);
+          const float w = acc[i][j + 1][r];
+          const float mk = e.drop.on ? drop_mult(e.drop, k1, (uint32_t)f) : 1.f;
+          const size_t o = (size_t)m * e.ld0 + f;
+          ((float*)e.out0)[o] = w * dgl * mk;
+          ((float*)e.out1)[o] = gl * mk;
+          ((float*)e.out2)[o] = gl * w * mk;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const int n = nb + j * 32;
+          if (!FULL && n >= g.N) continue;
+          const float v = acc[i][j][r];
+          const size_t o = (size_t)m * e.ld0 + n;
+          if constexpr (EPI == EPI_STORE) {
+            const float mk = e.drop.on ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
+            ((float*)e.out0)[o] = (e.act == ACT_RELU ? fmaxf(v, 0.f) : v) * mk;
+          } else if constexpr (EPI == EPI_RESID) {
+            const float a = xa[r][j], sc = e.drop.on ? e.drop.scale : 1.f;
+            const float mk = e.drop.on && !e.aux_mask ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
+            ((float*)e.out0)[o] = e.aux_mask ? (a > 0.f ? v * sc : 0.f) : v * mk + a;
+          } else if constexpr (EPI == EPI_GEGLU_BWD) {
+            ((float*)e.out0)[o] = v * xa[r][j];
+            ((float*)e.out1)[o] = v * xb[r][j];
+          } else {  // EPI_SPLIT_F32
+            if (split_k > 1) {  // this slice's sums, for launch_split_reduce
+              ((float*)const_cast<void*>(e.aux0))[((size_t)slice * g.M + m) * g.N + n] = v;
+            } else {
+              const int which = n / e.split_n;
+              float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
+              dst[(size_t)m * e.ld0 + (n - which * e.split_n)] = xa[r][j] + v;
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
+// FULL: every element of the wavefront's tiles exists, no test and no branch per element.
+template <int MI, int NI, int EPI>
+__device__ __forceinline__ void f32_epilogue(const GemmDesc& g, const GemmEpi& e, int split_k, const f32x16 (&acc)[MI][NI],
+                                             int mw, int nw, int slice, int lane) {
+  if (mw + MI * 32 <= g.M && nw + NI * 32 <= g.N) f32_epilogue_part<true, MI, NI, EPI>(g, e, split_k, acc, mw, nw, slice, lane);
+  else f32_epilogue_part<false, MI, NI, EPI>(g, e, split_k, acc, mw, nw, slice, lane);
 }
 
 template <int BM, int BN, int WM, int WN, int WK, int BK, bool A_KC, bool B_KC, int EPI, bool VEC>
@@ -251,87 +364,335 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
     }
   }
 
-  // ---- epilogue: register r of a 32x32 tile is row (r/4)*8 + half*4 + r%4, column lane%32: a wavefront writes
-  // 128-byte runs of two rows.  Operands of the epilogue are fetched for a whole row of tiles before the first store:
-  // the compiler cannot move a load across a store that might alias it, and one at a time each costs a round trip
-  // (the gated-GELU backward at 64 tokens: 23 us, most of it here).
-  constexpr bool AUX = EPI == EPI_RESID || EPI == EPI_GEGLU_BWD || EPI == EPI_SPLIT_F32;
+  f32_epilogue_part<false, MI, NI, EPI>(g, e, split_k, acc, m0 + wm * TMW, n0 + wn * TNW, blockIdx.z, lane);
+}
+
+// ------------------------------------------------------------------ the same on the bf16 matrix units
+// Every operand as three bf16 parts, a = a0 + a1 + a2 exactly, and six of the nine products of parts:
+//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),  what is left out is 2^-26 of it.
+// Six bf16 products of 32x32x16 take 192 cycles where the float32 instructions take 512 for the same k, and the sums lose less:
+// a0 b0 meets in one accumulator (one rounding in 16 k; float32 instructions round every two), the five small
+// products in another, whose roundings are 2^-8 of the first one's.  Error of a layer's results against 64 bits, d 512,
+// 16 x 250 tokens: y 4.2e-7 -> 1.8e-7, weight gradients 7.0e-7..1.04e-6 -> 2.7e-7..6.5e-7; with one accumulator 4.1e-7 and 6e-7..1.2e-6.
+// Bound: the vector instructions of the conversion (5.5 a value) and the LDS round trips between the barriers, beside the matrix
+// unit; d 768, 4000 tokens: products of a layer 1807 -> 1409 us (152 TFLOP/s with 1024 tiles), d 512: 650 -> 557.
+// A tile is requested D k-tiles ahead into registers, converted once and written to one of two LDS stages (rows of
+// BK k of each part, padded by 16 bytes: 16 rows cover the banks once) while the other one is multiplied.
+// Measured and left: parts by truncation instead of rounding (same time, y 2.0e-7); fragments read one k-tile ahead
+// (dn2 of d 512 92 -> 83 us, but one wavefront a SIMD: weight gradients a fifth slower); k-tiles of 32 at 128x128.
+
+// Four float32 values as three bf16 parts each (two 32-bit words per part), x = p0 + p1 + p2 exactly: every part is the
+// rounded remainder of the ones before it, eight significant bits at a time.
+struct Split3 {
+  u32x2 p[3];
+};
+__device__ __forceinline__ Split3 split3(f32x4 v) {
+  Split3 s;
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    const int mb = m0 + wm * TMW + i * 32 + (g2 << 2), nb = n0 + wn * TNW + l32;
-    float xa[AUX ? 16 : 1][NI], xb[EPI == EPI_GEGLU_BWD ? 16 : 1][NI];
-    if (AUX && (EPI != EPI_SPLIT_F32 || (split_k == 1 && e.accumulate))) {
+  for (int p = 0; p < 3; ++p) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-          const int m = mb + ((r >> 2) << 3) + (r & 3), n = nb + j * 32;
-          const int mc = m < g.M ? m : g.M - 1, nc = n < g.N ? n : g.N - 1;
-          if constexpr (EPI == EPI_SPLIT_F32) {
-            const int which = nc / e.split_n;  // (one slice)
-            const float* d = (const float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
-            xa[r][j] = d[(size_t)mc * e.ld0 + (nc - which * e.split_n)];
-          } else if constexpr (AUX) {
-            const size_t oa = (size_t)mc * (e.ld_aux ? e.ld_aux : e.ld0) + nc;
-            xa[r][j] = ((const float*)e.aux0)[oa];
-            if constexpr (EPI == EPI_GEGLU_BWD) xb[r][j] = ((const float*)e.aux1)[oa];
-          }
-        }
-    } else if (AUX) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-#pragma unroll
-        for (int j = 0; j < NI; ++j) xa[AUX ? r : 0][j] = 0.f;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = mb + ((r >> 2) << 3) + (r & 3);
-      if (m >= g.M) continue;
-      const uint32_t k1 = e.drop.on ? drop_row_key(e.drop, (uint32_t)m) : 0u;
-      if constexpr (EPI == EPI_GEGLU_FWD) {
-#pragma unroll
-        for (int j = 0; j < NI; j += 2) {
-          const int f = ((n0 + wn * TNW + j * 32) >> 1) + l32;
-          if (f >= (g.N >> 1)) continue;
-          float gl, dgl;
-          gelu_both(e.act, acc[i][j][r], gl, dgl);
-          const float w = acc[i][j + 1][r];
-          const float mk = e.drop.on ? drop_mult(e.drop, k1, (uint32_t)f) : 1.f;
-          const size_t o = (size_t)m * e.ld0 + f;
-          ((float*)e.out0)[o] = w * dgl * mk;
-          ((float*)e.out1)[o] = gl * mk;
-          ((float*)e.out2)[o] = gl * w * mk;
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-          const int n = nb + j * 32;
-          if (n >= g.N) continue;
-          const float v = acc[i][j][r];
-          const size_t o = (size_t)m * e.ld0 + n;
-          if constexpr (EPI == EPI_STORE) {
-            const float mk = e.drop.on ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
-            ((float*)e.out0)[o] = (e.act == ACT_RELU ? fmaxf(v, 0.f) : v) * mk;
-          } else if constexpr (EPI == EPI_RESID) {
-            const float a = xa[r][j], sc = e.drop.on ? e.drop.scale : 1.f;
-            const float mk = e.drop.on && !e.aux_mask ? drop_mult(e.drop, k1, (uint32_t)n) : 1.f;
-            ((float*)e.out0)[o] = e.aux_mask ? (a > 0.f ? v * sc : 0.f) : v * mk + a;
-          } else if constexpr (EPI == EPI_GEGLU_BWD) {
-            ((float*)e.out0)[o] = v * xa[r][j];
-            ((float*)e.out1)[o] = v * xb[r][j];
-          } else {  // EPI_SPLIT_F32
-            if (split_k > 1) {  // this slice's sums, for launch_split_reduce
-              ((float*)const_cast<void*>(e.aux0))[((size_t)blockIdx.z * g.M + m) * g.N + n] = v;
-            } else {
-              const int which = n / e.split_n;
-              float* dst = (float*)(which == 0 ? e.out0 : which == 1 ? e.out1 : e.out2);
-              dst[(size_t)m * e.ld0 + (n - which * e.split_n)] = xa[r][j] + v;
-            }
-          }
-        }
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t u = pack_bf16x2(v[2 * h], v[2 * h + 1]);
+      s.p[p][h] = u;
+      if (p < 2) {
+        v[2 * h] -= __builtin_bit_cast(float, u << 16);
+        v[2 * h + 1] -= __builtin_bit_cast(float, u & 0xFFFF0000u);
       }
     }
   }
+  return s;
+}
+
+// MANY: the columns of B come from several matrices
+template <int BM, int BN, int WM, int WN, int BK, int D, bool A_KC, bool B_KC, int EPI, bool MANY>
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g, GemmEpi e, int split_k) {
+  constexpr int NT = WM * WN * 64;
+  constexpr int TMW = BM / WM, TNW = BN / WN, MI = TMW / 32, NI = TNW / 32;
+  constexpr int LD = BK * 2 + 16;                        // bytes of a row of one part in LDS
+  constexpr int A_PL = BM * LD, B_PL = BN * LD;          // one part of a tile
+  constexpr int STG = 3 * (A_PL + B_PL);
+  constexpr int A_SL = BM * BK / 4 / NT, B_SL = BN * BK / 4 / NT;  // slots of four k per thread
+  static_assert(NT % BM == 0 && NT % BN == 0 && BM >= 64 && BN >= 64, "a wavefront's slots share their four k");
+  static_assert(EPI != EPI_GEGLU_FWD || NI % 2 == 0, "u and w columns in one wavefront");
+  extern __shared__ __attribute__((aligned(16))) char smx[];
+
+  const int tid = threadIdx.x, lane = tid & 63, g2 = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const TilePos pos = tile_pos((g.N + BN - 1) / BN, (g.M + BM - 1) / BM);
+  const int m0 = pos.y * BM, n0 = pos.x * BN;
+
+  int nt = 0;
+  for (int s = 0; s < g.nseg; ++s) nt += (g.seg[s].K + BK - 1) / BK;
+  const int per = (nt + split_k - 1) / split_k;
+  const int t_begin = pos.z * per, t_end = t_begin + per < nt ? t_begin + per : nt;
+  const int lda = g.seg[0].lda, ldb = g.seg[0].ldb;
+
+  // Column c of this tile of B: its matrix (MANY) and its column there.  Rows and columns past the end repeat the last
+  // one: their results are not stored.
+  auto b_col = [&](int c, const float*& src) __attribute__((always_inline)) {
+    int n = n0 + c, lim = g.N;
+    if constexpr (EPI == EPI_GEGLU_FWD) {  // packed columns: 32 of wi0, 32 of wi1, ...
+      src = (const float*)(c & 32 ? g.seg[1].B : g.seg[0].B);
+      n = (n0 >> 1) + ((c >> 6) << 5) + (c & 31);
+      lim = g.N >> 1;
+    } else if constexpr (MANY) {  // N = nsrc matrices of nsrc_cols columns side by side (a tile may straddle two)
+      int s = n / g.nsrc_cols;
+      s = s < g.nsrc ? s : g.nsrc - 1;
+      src = (const float*)(s == 0 ? g.seg[0].B : s == 1 ? g.seg[1].B : g.seg[2].B);
+      n -= s * g.nsrc_cols;
+      lim = g.nsrc_cols;
+    }
+    return n < lim ? n : lim - 1;
+  };
+
+  // Slot i of a thread: row r, k = 4 * (...) of a k-contiguous operand, offset from the tile's first row; or column c
+  // and wavefront-uniform rows of an m-contiguous one.
+  uint32_t oa[A_KC ? A_SL : 1], ob[B_KC ? B_SL : 1];
+  const float* b_src = nullptr;
+  const int wka = (wave * 64) / BM, wkb = (wave * 64) / BN;  // m-contiguous: first group of four k of the wavefront
+  if constexpr (A_KC) {
+#pragma unroll
+    for (int i = 0; i < A_SL; ++i) {
+      const int q = tid + i * NT, r = q / (BK / 4), k = (q % (BK / 4)) * 4;
+      oa[i] = (uint32_t)((m0 + r < g.M ? r : g.M - 1 - m0) * lda + k);
+    }
+  } else {
+    const int c = tid % BM;
+    oa[0] = (uint32_t)(m0 + c < g.M ? c : g.M - 1 - m0);
+  }
+  if constexpr (B_KC) {
+#pragma unroll
+    for (int i = 0; i < B_SL; ++i) {
+      const int q = tid + i * NT, r = q / (BK / 4), k = (q % (BK / 4)) * 4;
+      ob[i] = (uint32_t)((n0 + r < g.N ? r : g.N - 1 - n0) * ldb + k);
+    }
+  } else {
+    const float* src = nullptr;
+    const int n = b_col(tid % BN, src);
+    ob[0] = MANY ? 0u : (uint32_t)(n - n0);
+    if (MANY) b_src = src + n;
+  }
+
+  f32x4 raw_a[D][A_SL], raw_b[D][B_SL];  // tiles on their way
+  int left[D];                           // k from the start of each on
+  // The tile that is requested next: its segment (in scalar registers, chosen without a branch) and number.
+  int seg = 0, kt = t_begin;
+  const int K0 = g.seg[0].K, K1 = g.seg[1].K, K2 = g.seg[2].K, nseg = g.nseg;
+  const float *A0 = (const float*)g.seg[0].A, *A1 = (const float*)g.seg[1].A, *A2 = (const float*)g.seg[2].A;
+  const float *B0 = (const float*)g.seg[0].B, *B1 = (const float*)g.seg[1].B, *B2 = (const float*)g.seg[2].B;
+  auto pick = [&](auto x0, auto x1, auto x2) __attribute__((always_inline)) { return seg == 0 ? x0 : seg == 1 ? x1 : x2; };
+  while (seg + 1 < nseg && kt >= (pick(K0, K1, K2) + BK - 1) / BK) kt -= (pick(K0, K1, K2) + BK - 1) / BK, ++seg;
+  auto advance = [&]() __attribute__((always_inline)) {  // stays on the last tile
+    const bool same = (kt + 1) * BK < pick(K0, K1, K2), next = !same && seg + 1 < nseg;
+    kt = next ? 0 : same ? kt + 1 : kt;
+    seg = next ? seg + 1 : seg;
+  };
+  auto fetch = [&](f32x4 (&ra)[A_SL], f32x4 (&rb)[B_SL], int& left) __attribute__((always_inline)) {
+    const int k0 = kt * BK;
+    left = pick(K0, K1, K2) - k0;
+    const float* A = pick(A0, A1, A2) + (A_KC ? (size_t)m0 * lda + k0 : (size_t)k0 * lda + m0);
+    const float* B = pick(B0, B1, B2) + (B_KC ? (size_t)n0 * ldb + k0 : (size_t)k0 * ldb + n0);
+    if constexpr (A_KC) {
+      const int k = (tid % (BK / 4)) * 4;
+#pragma unroll
+      for (int i = 0; i < A_SL; ++i) {
+        ra[i] = *reinterpret_cast<const f32x4*>(A + (k < left ? oa[i] : oa[i] - k));
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < A_SL; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int k = (wka + i * (NT / BM)) * 4 + q;
+          ra[i][q] = (A + (size_t)(k < left ? k : left - 1) * lda)[oa[0]];
+        }
+    }
+    if constexpr (B_KC) {
+      const int k = (tid % (BK / 4)) * 4;
+#pragma unroll
+      for (int i = 0; i < B_SL; ++i) {
+        rb[i] = *reinterpret_cast<const f32x4*>(B + (k < left ? ob[i] : ob[i] - k));
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < B_SL; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int k = (wkb + i * (NT / BN)) * 4 + q;
+          const size_t o = (size_t)(k < left ? k : left - 1) * ldb;
+          rb[i][q] = MANY ? b_src[(size_t)k0 * ldb + o] : (B + o)[ob[0]];
+        }
+    }
+    advance();
+  };
+  // Rows of A past the end of k become zeros; those of B repeat its last one (where that is not finite, the check
+  // behind the loop sees it).
+  auto put = [&](char* st, f32x4 (&ra)[A_SL], const f32x4 (&rb)[B_SL], int left) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < A_SL; ++i) {
+      const int q = tid + i * NT;
+      const int r = A_KC ? q / (BK / 4) : tid % BM, k = A_KC ? (q % (BK / 4)) * 4 : (wka + i * (NT / BM)) * 4;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) ra[i][x] = k + x < left ? ra[i][x] : 0.f;
+      const Split3 s = split3(ra[i]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(st + p * A_PL + r * LD + k * 2) = s.p[p];
+    }
+#pragma unroll
+    for (int i = 0; i < B_SL; ++i) {
+      const int q = tid + i * NT;
+      const int r = B_KC ? q / (BK / 4) : tid % BN, k = B_KC ? (q % (BK / 4)) * 4 : (wkb + i * (NT / BN)) * 4;
+      const Split3 s = split3(rb[i]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(st + 3 * A_PL + p * B_PL + r * LD + k * 2) = s.p[p];
+    }
+  };
+
+  f32x16 acc[MI][NI], lo[MI][NI];  // products of the first parts; the five that are 2^-8 of them and less
+  auto clear = [&](f32x16 (&c)[MI][NI]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) c[i][j][r] = 0.f;
+  };
+  clear(acc);
+  clear(lo);
+
+  if (t_begin < t_end) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) fetch(raw_a[u], raw_b[u], left[u]);
+    put(smx, raw_a[0], raw_b[0], left[0]);
+    fetch(raw_a[0], raw_b[0], left[0]);
+    for (int t0 = t_begin; t0 < t_end; t0 += D)
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      const int t = t0 + u, v = (u + 1) % D;
+      if (t >= t_end) break;
+      char* cur = smx + ((t - t_begin) & 1) * STG;
+      char* nxt = smx + STG - ((t - t_begin) & 1) * STG;
+      __syncthreads();
+      constexpr int NS = BK / 16;
+      bf16x8 fa[NS][MI][3], fb[NS][NI][3];
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+            fa[s][i][p] = *reinterpret_cast<const bf16x8*>(cur + p * A_PL + (wm * TMW + i * 32 + l32) * LD + s * 32 + g2 * 16);
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            fb[s][j][p] = *reinterpret_cast<const bf16x8*>(cur + 3 * A_PL + p * B_PL + (wn * TNW + j * 32 + l32) * LD + s * 32 + g2 * 16);
+        }
+      put(nxt, raw_a[v], raw_b[v], left[v]);  // tile t + 1 (behind the last one: that one again, unread)
+      fetch(raw_a[v], raw_b[v], left[v]);     // tile t + 1 + D
+      constexpr int PA[6] = {0, 2, 0, 1, 1, 0}, PB[6] = {0, 0, 2, 1, 0, 1};
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int p = 0; p < 6; ++p)
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+              f32x16& c = p == 0 ? acc[i][j] : lo[i][j];
+              c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][i][PA[p]], fb[s][j][PB[p]], c, 0, 0, 0);
+            }
+      // one product, then its share of the next tile's conversion: a matrix instruction keeps its unit busy for 32 cycles,
+      // in which the wavefront issues eight others
+      constexpr int NMF = NS * 6 * MI * NI, VAL = ((A_SL + B_SL) * 24 + NMF - 1) / NMF + 1;
+      __builtin_amdgcn_sched_group_barrier(0x100, NS * 3 * (MI + NI), 0);
+#pragma unroll
+      for (int x = 0; x < NMF; ++x) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, VAL, 0);
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
+
+  // A sum that is not finite: the parts of an infinite or nearly infinite operand are not finite together with their
+  // remainders.  Sums that are all minute: the matrix unit takes parts below 2^-126 for zero.  Either way the wavefront forms
+  // its tiles again from the float32 values themselves (rare; operands from global memory).
+  float chk = 0.f, top = 0.f;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        chk = fmaf(acc[i][j][r], 0.f, chk);
+        top = fmaxf(top, fabsf(acc[i][j][r]));
+      }
+  if (__builtin_expect(__any(chk != 0.f) || (!__any(top >= 0x1p-90f) && __any(top > 0.f)), 0)) {
+    clear(acc);
+    seg = 0;
+    kt = t_begin;
+    while (seg + 1 < nseg && kt >= (pick(K0, K1, K2) + BK - 1) / BK) kt -= (pick(K0, K1, K2) + BK - 1) / BK, ++seg;
+    for (int t = t_begin; t < t_end; ++t) {
+      const int K = pick(K0, K1, K2);
+      const float* A = pick(A0, A1, A2);
+      const float* B = pick(B0, B1, B2);
+      for (int k0 = kt * BK; k0 < (kt + 1) * BK && k0 < K; k0 += 2) {
+        const int k = k0 + g2, kc = k < K ? k : K - 1;
+        float va[MI], vb[NI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          int m = m0 + wm * TMW + i * 32 + l32;
+          m = m < g.M ? m : g.M - 1;
+          const float v = A_KC ? A[(size_t)m * lda + kc] : A[(size_t)kc * lda + m];
+          va[i] = k < K ? v : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const float* src = B;
+          const int n = b_col(wn * TNW + j * 32 + l32, src);
+          const float v = B_KC ? src[(size_t)n * ldb + kc] : src[(size_t)kc * ldb + n];
+          vb[j] = k < K ? v : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[j], acc[i][j], 0, 0, 0);
+      }
+      advance();
+    }
+  }
+  f32_epilogue<MI, NI, EPI>(g, e, split_k, acc, m0 + wm * TMW, n0 + wn * TNW, pos.z, lane);
+}
+
+template <int BM, int BN, int BK, int D, bool A_KC, bool B_KC, int EPI, bool MANY>
+hipError_t launch_x3_cols(const GemmDesc& g, const GemmEpi& e, int split_k, hipStream_t st) {
+  constexpr int lds = 6 * (BM + BN) * (BK * 2 + 16);
+  auto kern = gemm_f32x3_kernel<BM, BN, 2, 2, BK, D, A_KC, B_KC, EPI, MANY>;
+  if constexpr (lds > 65536) {
+    static std::atomic<bool> attr_set{false};  // once per instantiation; setting it twice is harmless
+    if (!attr_set.load(std::memory_order_relaxed)) {
+      hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (err != hipSuccess) return err;
+      attr_set.store(true, std::memory_order_relaxed);
+    }
+  }
+  const unsigned grid = (unsigned)ceil_div(g.N, BN) * ceil_div(g.M, BM) * split_k;
+  kern<<<grid, 256, lds, st>>>(g, e, split_k);
+  return hipGetLastError();
+}
+template <int BM, int BN, int BK, int D, bool A_KC, bool B_KC, int EPI>
+hipError_t launch_x3(const GemmDesc& g, const GemmEpi& e, int split_k, hipStream_t st) {
+  if constexpr (EPI == EPI_GEGLU_FWD) return launch_x3_cols<BM, BN, BK, D, A_KC, B_KC, EPI, true>(g, e, split_k, st);
+  if constexpr (EPI == EPI_STORE && !B_KC)
+    if (g.nsrc > 1) return launch_x3_cols<BM, BN, BK, D, A_KC, B_KC, EPI, true>(g, e, split_k, st);
+  if constexpr (EPI != EPI_GEGLU_FWD) return launch_x3_cols<BM, BN, BK, D, A_KC, B_KC, EPI, false>(g, e, split_k, st);
 }
 
 // ------------------------------------------------------------------ few tiles
@@ -577,13 +938,15 @@ bool vec_ok(const GemmDesc& g) {
   if (!g.b_kc) vec = vec && g.N % 4 == 0;
   return vec;
 }
-// Weight gradients: few tiles, long k.  Slices of at least 256 k until two workgroups per compute unit are busy.
+// Weight gradients: few tiles, long k.  Slices of at least 256 k until one workgroup of 128x128 tiles, or two of 64x64,
+// per compute unit are busy (two of 128x128: their products 5 % less, the sum of their slices half as long again; layer of
+// d 768, 4000 tokens 1757 against 1729 us).
 int wgrad_slices(const GemmDesc& g, bool& big) {
   const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128);
   const int64_t t64 = (int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64), K = g.seg[0].K;
   big = t128 * (K / 256) >= 256;
   const int64_t t = big ? t128 : t64;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(K / 256, (512 + t - 1) / t));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(K / 256, ((big ? 256 : 512) + t - 1) / t));
 }
 
 template <bool A_KC, bool B_KC, int EPI>
@@ -591,22 +954,27 @@ hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   if (!vec_ok(g)) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, false>(g, e, 1, st);
   const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128);
   const int64_t t64 = (int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64);
-  int64_t K = 0;
-  for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
   if constexpr (EPI == EPI_SPLIT_F32) {
-    if (e.aux0 && e.accumulate && K >= 512) {
+    if (e.aux0 && e.accumulate && g.seg[0].K >= 512) {
       bool big;
       const int sk = wgrad_slices(g, big);
-      if (big) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI, true>(g, e, sk, st);
+      if (big) return launch_x3<128, 128, 16, 2, A_KC, B_KC, EPI>(g, e, sk, st);
       return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, sk, st);
     }
   }
-  // 128x128 tiles where their last round over the 256 compute units is about as full as that of the 64x64 tiles
-  // (4000 x 1152: 288 large tiles are one round and an eighth, at half the rate of 1134 small ones); 32x64 tiles with
-  // the reduction over four wavefronts where even the 64x64 ones leave half the chip idle.
-  auto filled = [](int64_t t) { return (double)t / (double)((t + 255) / 256 * 256); };
-  if (t128 >= 192 && filled(t128) * 1.1 >= filled(t64)) return launch_tile<128, 128, 2, 2, 1, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
-  if (t64 >= 128) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
+  int64_t K = 0;
+  for (int i = 0; i < g.nseg; ++i) K += g.seg[i].K;
+  // Split operands from about as many tiles as keep the conversion off the critical path; us for native / split:
+  //   128x128, 4000 tokens: qkv of d 512 (288 tiles) 61 / 52, dn2 of d 768 (192) 246 / 189, wi of d 768 (1024) 231 / 165;
+  //            with 128 tiles (4000 x 512 x 2048) 84 / 92, but 71 on 64x64 ones, as 768 x 4096 over 200 tokens (192) 32 / 41 / 29;
+  //   64x64:   1024 x 512 x 2048 (128 tiles) 57 / 44, 1024 x 512 x 512 (128) 15 / 16, 200 x 2048 x 768 (128) 27 / 22.
+  // The gated inputs need 64 columns a wavefront, which 64x64 tiles of four do not have.  32x32 tiles with the
+  // reduction over the wavefronts where even the 64x64 ones leave half the chip idle.
+  if (t128 >= 192 && K >= 384) return launch_x3<128, 128, 16, 2, A_KC, B_KC, EPI>(g, e, 1, st);
+  if (t64 >= 128) {
+    if constexpr (EPI == EPI_GEGLU_FWD) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
+    else return launch_x3<64, 64, 32, 3, A_KC, B_KC, EPI>(g, e, 1, st);
+  }
   return launch_small<A_KC, B_KC, EPI>(g, e, st);
 }
 

@@ -37,6 +37,14 @@ SMALL_CASES = [replace(C, batch=1, seq=33, d_model=36, n_heads=1, d_kv=20, d_ff=
                replace(C, batch=2, seq=40, d_model=96, n_heads=3, d_kv=32, d_ff=36, mlp="relu", dropout_rate=0.125, dropout_seed=4)]
 
 
+# Products with operands in three bf16 parts: 64 x 64 and 128 x 128 tiles, k not a multiple of their k-tiles, several
+# segments, columns from several matrices, sliced and whole weight gradients (540 and 400 tokens)
+SPLIT_CASES = [replace(C, batch=32, seq=130, d_model=132, n_heads=3, d_kv=20, d_ff=260),
+               replace(C, batch=32, seq=130, d_model=388, n_heads=5, d_kv=52, d_ff=772, causal=True),
+               replace(C, batch=4, seq=135, d_model=772, n_heads=12, d_kv=64, d_ff=1028, mlp="relu"),
+               replace(C, batch=4, seq=100, d_model=516, n_heads=8, d_kv=64, d_ff=1540, dropout_rate=0.125, dropout_seed=3)]
+
+
 def _check(pairs):
     for name, got, want in pairs:
         if name in ("wq", "wk") and not np.any(np.abs(want) > 1e-12):  # one key: no gradient through the softmax
@@ -45,7 +53,7 @@ def _check(pairs):
         assert rel_err(got, want)[0] <= TOL_F32[0], (name, rel_err(got, want))
 
 
-@pytest.mark.parametrize("cfg", CASES + SMALL_CASES, ids=lambda c: f"{c.batch}x{c.seq}_d{c.d_model}_k{c.d_kv}_f{c.d_ff}")
+@pytest.mark.parametrize("cfg", CASES + SMALL_CASES + SPLIT_CASES, ids=lambda c: f"{c.batch}x{c.seq}_d{c.d_model}_k{c.d_kv}_f{c.d_ff}")
 def test_block_f32_matrix(cfg):
     if cfg.dropout_rate:
         cfg = replace(cfg, dropout_rate=float(np.float32(cfg.dropout_rate)))
@@ -146,3 +154,35 @@ def test_causal_gradients_after_a_nan_gradient(seq, d_kv):
     # the plain multiply-adds of that tile differ from the matrix unit's by float32 rounding
     assert rel_err(g1[bad + 1:].cpu().numpy().astype(np.float64),
                    g0[bad + 1:].cpu().numpy().astype(np.float64))[0] <= TOL_F32[0]
+
+
+@pytest.mark.parametrize("value", [np.inf, 3.4e38, -np.inf])
+@pytest.mark.parametrize("d", [132, 772])
+def test_split_products_of_an_infinite_weight(d, value):
+    """One weight that is infinite, or rounds to infinity in bf16: its column of y as float32 products give it (0 times
+    infinity is not a number), the others untouched."""
+    import paper_2203_17189_amd as P
+    from parity_util import to_np, upload_case
+    cfg = replace(C, batch=32, seq=130, d_model=d, n_heads=3, d_kv=20, d_ff=260, mlp="relu", name="f32_inf")
+    w, x, dy = make_case(cfg)
+    dw, dx, _ = upload_case(cfg, w, x, dy)
+    y0 = to_np(P.t5_block_fwd(cfg, dx, dw)[0]).reshape(-1, d)
+    dw["wo_ff"] = dw["wo_ff"].clone()
+    dw["wo_ff"][7, 5] = value
+    y1, _ = P.t5_block_fwd(cfg, dx, dw)
+    y1 = to_np(y1).reshape(-1, d)
+    _, saved = O.block_fwd(cfg, x, w)
+    a = np.float32(saved["a"].reshape(-1, 260)[:, 7])
+    sure = np.abs(a) > 1e-6  # (elsewhere the device's own sum may have the other sign)
+    with np.errstate(all="ignore"):
+        want = a * np.float32(value)
+    far = np.isinf(want) & sure
+    assert far.sum() > 100 and np.all(y1[far, 5] == want[far])
+    if np.isinf(value):
+        assert np.all(np.isnan(y1[~sure & (a == 0), 5]) | np.isinf(y1[~sure & (a == 0), 5]))
+    else:
+        near = np.isfinite(want) & sure
+        # an error of the activations is one of their scale, not of each value: relative to the column's RMS as everywhere
+        assert rel_err(y1[near, 5], np.float64(want[near]))[0] <= TOL_F32[0]
+    keep = np.arange(d) != 5
+    assert rel_err(y1[:, keep], y0[:, keep])[0] <= TOL_F32[0]
