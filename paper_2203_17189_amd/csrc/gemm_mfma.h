@@ -25,6 +25,7 @@
 #pragma once
 #include "kernels.h"
 #include <atomic>
+
 #include <type_traits>
 
 namespace t5mi {
@@ -444,10 +445,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
     }
     // tile t in A stage sa and B stage sb; an: A of tile t+2, bn: B of tile t+1
     auto ktile = [&](int sa, int sb) __attribute__((always_inline)) {
-      constexpr int QA = A_DMA / 2 / MI, QB = B_DMA / 2 / MI;  // DMA instructions per group of MFMAs
-      static_assert(QA * 2 * MI == A_DMA && QB * 2 * MI == B_DMA, "one share per group");
+      constexpr int QA = A_DMA / 2 / MI;  // A's DMA instructions per group of MFMAs
+      constexpr int HB = B_DMA / 2;       // B's: half in each of two k-steps, over the groups (256x192 tiles: 0 1 1 1)
+      static_assert(QA * 2 * MI == A_DMA && HB * 2 == B_DMA, "shares of the groups");
       const char *a2 = an, *b2 = bn;
-      step(0, sa, sb, 1, [&](int i) __attribute__((always_inline)) { dma_b(bn, sb ^ 1, B_DMA / 2 + i * QB, B_DMA / 2 + (i + 1) * QB); },
+      step(0, sa, sb, 1, [&](int i) __attribute__((always_inline)) { dma_b(bn, sb ^ 1, HB + i * HB / MI, HB + (i + 1) * HB / MI); },
            [&](int i) __attribute__((always_inline)) { if (i == 1) cursor_bases<MULTI>(kb, skip, b2); if (i == 2) cursor_counts<MULTI>(kb); });
       step(1, sa, sb, 2, [&](int i) __attribute__((always_inline)) { dma_a(an, (sa + 2) % 3, i * QA, (i + 1) * QA); }, no_gap);
       step(0, sa, sb, 3, [&](int i) __attribute__((always_inline)) { dma_a(an, (sa + 2) % 3, A_DMA / 2 + i * QA, A_DMA / 2 + (i + 1) * QA); },
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
       // tile t+1 has landed but for nothing (only A of tile t+2, requested last, may be in flight), and this
       // wavefront's reads of tile t are done
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(A_DMA) : "memory");
-      step(1, (sa + 1) % 3, sb ^ 1, 0, [&](int i) __attribute__((always_inline)) { dma_b(bn, sb, i * QB, (i + 1) * QB); }, no_gap);
+      step(1, (sa + 1) % 3, sb ^ 1, 0, [&](int i) __attribute__((always_inline)) { dma_b(bn, sb, i * HB / MI, (i + 1) * HB / MI); }, no_gap);
     };
     int t = 0;
     for (; t + 6 <= nk; t += 6) {
@@ -909,6 +911,10 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    (14592 x 768 x 2304, 171 against 684 tiles: 59 us against 68; 8991 x 768 x 4096, 108 against 426: 92 against 64).
     //    The gated-GELU backward, two tensors in and two out, always takes it (32768 x 5120 x 2048: 1149 us with 256x256,
     //    850 with 256x128, 753 with this);
+    //  * 256x192, the same loop with three quarters of the columns, where that fills rounds that 256x256 leaves part empty
+    //    (widths of 768: 16384 x 768 is 192 tiles of 256x256 and 256 of these).  A round costs 0.88 of a 256x256 one, not
+    //    0.75: more units share the power and the L2.  k 4096 98 -> 92 us, 2048 62 -> 57, 768 30 -> 26; 16384 x 2304 x 768,
+    //    three rounds of each: 73 -> 69; 8991 x 2304 x 768, two rounds against 2.5 of 128x128: 42 with those, 50 with this;
     //  * 256x128, two workgroups, k-tiles of 32 in three stages: gated-GELU forward up to K = 704, residual up to K = 512
     //    (32768 x 512 x 384: 31 us against 32 and 34);
     //  * up to 256 tiles of 128x128 (one per compute unit): latency counts, so more stages (k-tiles of 32 in four) and,
@@ -929,6 +935,12 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
           return launch_cfg<128, 64, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
       }
       return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
+    }
+    if constexpr (EPI_T == EPI_STORE || EPI_T == EPI_RESID) {  // (with dropout it would spill)
+      if (g.N % 192 == 0) {
+        const double c192 = 0.88 * (double)(((int64_t)ceil_div(g.M, 256) * (g.N / 192) + 255) / 256);
+        if (c192 < c256 && c192 < c128) return launch_cfg<256, 192, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
+      }
     }
     if constexpr (EPI == EPI_GEGLU_FWD || EPI == EPI_RESID)
       if (t256 >= 192 && K <= (EPI == EPI_RESID ? 512 : 704))

@@ -116,3 +116,32 @@ def test_rows_do_not_depend_on_the_last_tile(full, ragged, seq, mlp, rate):
         dx, _ = P.t5_block_bwd(c, tdy, tx, dw, stash)
         out.append((y.view(b, seq, -1)[:ragged].clone(), dx.view(b, seq, -1)[:ragged].clone()))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("nk", [10, 11, 12, 13, 14, 15])
+def test_256x192_tiles_every_loop_remainder(nk):
+    _check_gemm(14500, 768, 64 * nk, True)  # 57 x 3 tiles of 256x256 in one round, 57 x 4 of 256x192 too; a last row tile of 164
+
+
+def test_256x192_tiles_with_residual():
+    """A layer of 114 sequences (256x192 tiles in every product of 768 columns) against its two halves (128x128 tiles): the
+    same sums in another order, so what differs are single bf16 roundings: the bar of a result against the exact one."""
+    import numpy as np
+    import paper_2203_17189_amd as P
+    from parity_util import STATED_BF16, rel_err
+    cfg = SI.BlockConfig("tiles_192", 95, 114, 128, 768, 12, 64, 1024, attn_scale=0.125)
+    w, x, dy = make_case(replace(cfg, batch=2))
+    dw, dx, ddy = upload_case(replace(cfg, batch=2), w, x, dy)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    dx, ddy = [torch.randn((114, 128, 768), generator=gen, device="cuda").bfloat16() for _ in range(2)]
+
+    def run(c, x, dy):
+        y, stash = P.t5_block_fwd(c, x, dw)
+        g, _ = P.t5_block_bwd(c, dy, x, dw, stash)
+        return [v.float().cpu().numpy().astype(np.float64) for v in (y, g)]
+    whole = run(cfg, dx, ddy)
+    halves = [run(replace(cfg, batch=57), dx[b:b + 57].contiguous(), ddy[b:b + 57].contiguous()) for b in (0, 57)]
+    for i in range(2):
+        e = rel_err(whole[i], np.concatenate([h[i] for h in halves]))
+        assert e[0] <= STATED_BF16[0] and e[1] <= STATED_BF16[1], e
