@@ -129,27 +129,35 @@ __global__ void geglu_fwd_kernel(T* __restrict__ u, T* __restrict__ w, T* __rest
   }
 }
 
-// dst[n][k] for a 64x64 tile staged through LDS; see launch_pack_transpose_multi.  blockIdx.z picks the job; blocks
-// outside a job's tile range leave at once.  Bound: bytes (28 MB for the weights of a d 768 layer, 6 us at the copy
-// rate); with 4-byte accesses the kernel took 17 us there.  A thread reads 16 bytes of two rows, pairs the rows'
+// dst[n][k] for a 64x64 tile staged through LDS; see launch_pack_transpose_multi.  A workgroup finds its job and tile in the
+// jobs' first workgroups.  (With one grid plane per job, each as large as the largest, five of six workgroups found nothing
+// to do: 13.4 us at d 768, 46.3 at d 2048 against 11.7 and 45.1 like this.)
+// Bound: bytes (28 MB for the weights of a d 768 layer, 6 us at the copy rate).  A thread reads 16 bytes of two rows, pairs the rows'
 // elements into words (k, k + 1) of its 8 columns, and the tile leaves LDS as 16-byte runs along k.
 // LDS: word (n, k/2) of the tile at n * 32 + ((k/2) ^ swz(n)), the 16-byte groups of a row swizzled so that the writes of
 // a wavefront (8 columns of 8 row pairs at a time) and its 16-byte reads spread over the banks.
-__global__ __launch_bounds__(256) void pack_transpose_kernel(PackJobs jobs) {
+struct PackArgs {
+  PackJobs jobs;
+  int first[9];  // first workgroup of each job, then that of the bias diagonals
+};
+__global__ __launch_bounds__(256) void pack_transpose_kernel(PackArgs args) {
   __shared__ __attribute__((aligned(16))) uint32_t tile[64 * 32];
-  if ((int)blockIdx.z == jobs.count) {  // the layer's bias diagonals (see launch_relpos_diag): a launch of their own costs 4.5 us
-    const int w = 2 * jobs.S - 1;
-    for (int i = (int)(blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < w; i += (int)(gridDim.x * gridDim.y) * 256) {
-      const int b = relpos_bucket_dev(i - (jobs.S - 1), jobs.lut);
-      for (int h = 0; h < jobs.H; ++h) jobs.diag[(size_t)h * w + i] = (float)((const bf16*)jobs.table)[b * jobs.H + h];
-    }
+  const PackJobs& jobs = args.jobs;
+  int job = 0;
+  while (job < jobs.count && (int)blockIdx.x >= args.first[job + 1]) ++job;
+  const int blk = (int)blockIdx.x - args.first[job];
+  if (job == jobs.count) {  // the layer's bias diagonals (see launch_relpos_diag): a launch of their own costs 4.5 us
+    const int w = 2 * jobs.S - 1, i = blk * 256 + (int)threadIdx.x;
+    if (i >= w) return;
+    const int b = relpos_bucket_dev(i - (jobs.S - 1), jobs.lut);
+    for (int h = 0; h < jobs.H; ++h) jobs.diag[(size_t)h * w + i] = (float)((const bf16*)jobs.table)[b * jobs.H + h];
     return;
   }
-  const PackJob& jb = jobs.j[blockIdx.z];
+  const PackJob& jb = jobs.j[job];
   const int nsrc = jb.nsrc, K = jb.K, n_each = jb.n_each, interleave = jb.interleave;
   const int n_total = nsrc * n_each;
-  const int n0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
-  if (n0 >= n_total || k0 >= K) return;
+  const int tiles_n = (n_total + 63) / 64;
+  const int n0 = blk % tiles_n * 64, k0 = blk / tiles_n * 64;
   // interleave and n_each are multiples of 32 (or interleave == 0), so each 32-wide half of the tile's packed
   // rows comes from one source and 32 consecutive source columns; a thread's 8 columns lie inside one half.
   const int c = (threadIdx.x & 7) * 8, kp = threadIdx.x >> 3, nh = n0 + (c & 32);  // columns c .. c+7, rows 2 kp and 2 kp + 1
@@ -242,16 +250,21 @@ hipError_t launch_geglu_fwd(void* u, void* w, void* a, int type, int64_t n, int 
 
 hipError_t launch_pack_transpose_multi(const PackJobs& jobs, hipStream_t st) {
   if (jobs.count < 1 || jobs.count > 8) return hipErrorInvalidValue;
-  int gx = 0, gy = 0;
+  PackArgs args;
+  args.jobs = jobs;
+  int blocks = 0;
+  for (int q = 0; q < 9; ++q) args.first[q] = 0;
   for (int q = 0; q < jobs.count; ++q) {
     const PackJob& jb = jobs.j[q];
     if (jb.nsrc < 1 || jb.nsrc > 3 || jb.n_each % 32 != 0 || (jb.interleave > 0 && jb.interleave % 32 != 0) ||
         jb.K % 2 != 0)
       return hipErrorInvalidValue;
-    gx = std::max(gx, ceil_div(jb.nsrc * jb.n_each, 64));
-    gy = std::max(gy, ceil_div(jb.K, 64));
+    args.first[q] = blocks;
+    blocks += ceil_div((int64_t)jb.nsrc * jb.n_each, 64) * ceil_div(jb.K, 64);
   }
-  pack_transpose_kernel<<<dim3(gx, gy, jobs.count + (jobs.diag ? 1 : 0)), 256, 0, st>>>(jobs);
+  args.first[jobs.count] = blocks;
+  if (jobs.diag) blocks += ceil_div(2 * (int64_t)jobs.S - 1, 256);
+  pack_transpose_kernel<<<blocks, 256, 0, st>>>(args);
   return hipGetLastError();
 }
 
