@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libt5mi.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["relpos.hip", "rmsnorm.hip", "gemm_simple.hip", "gemm_mfma.hip", "gemm_mfma_store.hip",
            "gemm_mfma_resid.hip", "gemm_mfma_geglu_fwd.hip", "gemm_mfma_geglu_bwd.hip", "gemm_mfma_split.hip",
-           "gemm_mfma_split_grouped.hip", "gemm_f32.hip", "attn_simple.hip",
+           "gemm_mfma_split_grouped.hip", "gemm_mfma_direct.hip", "gemm_f32.hip", "attn_simple.hip",
            "attn_mfma.hip", "attn_f32.hip", "adafactor.hip", "probe.hip", "embed_xent.hip", "block.hip", "stack.hip"]
 # -packed-fp32-ops is switched off: hand-written and compiler-made packed float32 math is avoided on
 # this target.

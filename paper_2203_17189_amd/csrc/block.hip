@@ -106,7 +106,7 @@ int t5_block_fwd(const t5_block_cfg* cfg, const void* x, const t5_block_weights*
   carve_fwd(D, workspace, &W);
   const bool fused = fused_fwd_ok(D);
   if (fused) T5_SUB(fwd_pack_weights(D, w, nullptr, W, st, &lut, S.diag));
-  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st, !fused));
+  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st, !fused || W.direct));
   T5_SUB(fwd_mlp(cfg, D, S.h, w, S, W, fused, y, st));
   return T5_OK;
 }
@@ -158,7 +158,7 @@ int t5_decoder_block_fwd(const t5_block_cfg* cfg, int32_t enc_seq, const void* x
   carve_fwd(D, workspace, &W);
   const bool fused = fused_fwd_ok(D);
   if (fused) T5_SUB(fwd_pack_weights(D, w, xw, W, st, &lut, S.diag));
-  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st, !fused));
+  T5_SUB(fwd_self_attn(cfg, D, lut, x, w, S, W, fused, st, !fused || W.direct));
   T5_SUB(fwd_cross_attn(cfg, D, enc, xw, S, W, fused, st));
   T5_SUB(fwd_mlp(cfg, D, S.h2, w, S, W, fused, y, st));
   return T5_OK;

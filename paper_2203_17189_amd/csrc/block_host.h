@@ -2,6 +2,7 @@
 // the caller's stash and workspace, and the sublayer sequences of the T5.1.1 block.  Everything here
 // has internal linkage except the step-timing state, which lives in block.hip.
 #pragma once
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -133,6 +134,7 @@ size_t carve_stash(const Dims& D, void* base, Stash* s) {
 struct FwdWs {
   void *wqkv_t, *wo_t, *wi_t, *woff_t;  // packed transposed weights (bf16 MFMA path)
   void *xq_t, *xkv_t, *xo_t;            // the same for the cross-attention projections
+  bool direct;                          // few tokens: the products read the weights as they are stored, nothing is packed
 };
 size_t carve_fwd(const Dims& D, void* base, FwdWs* w) {
   Carver cv(base);
@@ -423,10 +425,53 @@ AttnIO cross_io(const Dims& D, const Stash& S, const BwdWs* W) {
 }
 
 // ------------------------------------------------------------------ forward sublayers
+// Forward product with the columns of nsrc stored weights, n_each each (W.direct).  A caller's buffers may start where the
+// kernel cannot read them: one weight after the other on the general-shape kernel then, as run_gemm does it.
+hipError_t run_direct(int T, int n_each, int K, const void* A, const void* const* Bs, int nsrc, const GemmEpi& e, hipStream_t st) {
+  const GemmDesc g = gemm_cols(T, n_each, K, A, K, Bs, nsrc, IN_BF16);
+  if (gemm_direct_supported(g, e)) return launch_gemm_direct(g, e, st);
+  if (e.kind == EPI_GEGLU_FWD) return hipErrorInvalidValue;
+  for (int s = 0; s < nsrc; ++s) {
+    GemmEpi es = e;
+    es.out0 = (char*)e.out0 + (size_t)s * n_each * (e.out_type == IN_BF16 ? 2 : 4);
+    const hipError_t err = run_gemm(gemm1(T, n_each, K, A, K, 1, Bs[s], n_each, 0, IN_BF16), es, st);
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
+}
+// Whether the layer's forward reads its weights as they are stored: every product at most two rounds of 128x128 tiles (two
+// on a compute unit), where the copies cost more than larger tiles give; forward packed / direct, us: d 768 over 128 tokens
+// 57 / 47, 1332 76 / 69, 4096 (1024 tiles) 127 / 124, 8192 198 / 201; d 2048 over 128 117 / 89, 768 172 / 136, 4096 (2560)
+// 478 / 479; d 512 over 8192 (1024) 104 / 104.  Not with dropout (that would double the kernels), nor with a weight that
+// does not start on 16 bytes.
+bool fwd_direct_ok(const Dims& D, const t5_block_weights* w, const t5_cross_weights* xw) {
+  if (D.drop > 0.f) return false;
+  const int T = (int)D.T;
+  const int widest = std::max(D.mlp == ACT_RELU ? D.F : 2 * D.F, std::max(3 * D.I, D.d));
+  if ((int64_t)ceil_div(T, 128) * ceil_div(widest, 128) > 1024) return false;
+  if (xw && (int64_t)ceil_div(D.Te, 128) * ceil_div(2 * D.I, 128) > 1024) return false;
+  const GemmEpi store = epi(EPI_STORE, (void*)kAligned16, 8, IN_BF16);
+  auto ok = [&](int M, int n_each, int K, const void* const* Bs, int nsrc, const GemmEpi& e) {
+    return gemm_direct_supported(gemm_cols(M, n_each, K, kAligned16, K, Bs, nsrc, IN_BF16), e);
+  };
+  const void* qkv[3] = {w->wq, w->wk, w->wv};
+  const void* wi[2] = {w->wi0, w->wi1};
+  bool all = ok(T, D.I, D.d, qkv, 3, store) && ok(T, D.d, D.I, &w->wo, 1, store) && ok(T, D.d, D.F, &w->wo_ff, 1, store) &&
+             (D.mlp == ACT_RELU ? ok(T, D.F, D.d, wi, 1, store) : ok(T, D.F, D.d, wi, 2, epi(EPI_GEGLU_FWD, (void*)kAligned16, D.F, IN_BF16)));
+  if (xw) {
+    const void* kv[2] = {xw->xk, xw->xv};
+    all = all && ok(T, D.I, D.d, &xw->xq, 1, store) && ok((int)D.Te, D.I, D.d, kv, 2, store) && ok(T, D.d, D.I, &xw->xo, 1, store);
+  }
+  return all;
+}
+
 // All weight packs (transposes to k-contiguous rows) of the layer in one launch.
 // lut: the layer owns its bias table, whose diagonals (into diag) join the launch.
-int fwd_pack_weights(const Dims& D, const t5_block_weights* w, const t5_cross_weights* xw, const FwdWs& W,
+// Nothing where the products take the weights as they are (W.direct).
+int fwd_pack_weights(const Dims& D, const t5_block_weights* w, const t5_cross_weights* xw, FwdWs& W,
                      hipStream_t st, const RelposLut* lut = nullptr, float* diag = nullptr) {
+  W.direct = fwd_direct_ok(D, w, xw);
+  if (W.direct) return T5_OK;
   PackJobs pj;
   std::memset(&pj, 0, sizeof(pj));
   pj.j[0] = PackJob{{w->wq, w->wk, w->wv}, 3, D.d, D.I, 0, W.wqkv_t};
@@ -455,9 +500,17 @@ int fwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   const int T = (int)D.T, ty = D.ty;
   const size_t es = D.es;
   const AttnDims ad = self_dims(cfg, D);
-  if (own_table) T5_STEP("relpos_diag", launch_relpos_diag(w->rel_table, cfg->dtype, S.diag, D.S, D.H, lut, st));
-  T5_STEP("rmsnorm_fwd", launch_rmsnorm_fwd(x, ty, w->ln1_scale, S.n1, ty, S.r1, T, D.d, cfg->rms_eps, st));
-  if (fused) {
+  if (own_table && W.direct) {
+    T5_STEP("rmsnorm_fwd", launch_rmsnorm_fwd_diag(x, w->ln1_scale, S.n1, S.r1, T, D.d, cfg->rms_eps, w->rel_table, S.diag, D.S,
+                                                   D.H, lut, st));
+  } else {
+    if (own_table) T5_STEP("relpos_diag", launch_relpos_diag(w->rel_table, cfg->dtype, S.diag, D.S, D.H, lut, st));
+    T5_STEP("rmsnorm_fwd", launch_rmsnorm_fwd(x, ty, w->ln1_scale, S.n1, ty, S.r1, T, D.d, cfg->rms_eps, st));
+  }
+  if (W.direct) {
+    const void* ws3[3] = {w->wq, w->wk, w->wv};
+    T5_STEP("gemm_qkv", run_direct(T, D.I, D.d, S.n1, ws3, 3, epi(EPI_STORE, S.qkv, 3 * D.I, ty), st));
+  } else if (fused) {
     GemmDesc g = gemm1(T, 3 * D.I, D.d, S.n1, D.d, 1, W.wqkv_t, D.d, 1, ty);
     T5_STEP("gemm_qkv", run_gemm(g, epi(EPI_STORE, S.qkv, 3 * D.I, ty), st));
   } else {
@@ -480,7 +533,7 @@ int fwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
                      : gemm1(T, D.d, D.I, S.c, D.I, 1, w->wo, D.d, 0, ty);
   GemmEpi e = epi(EPI_RESID, S.h, D.d, IN_F32);
   e.aux0 = x; e.aux_type = ty; e.drop = drop_site(D, DROP_ATTN_OUT);
-  T5_STEP("gemm_o", run_gemm(g, e, st));
+  T5_STEP("gemm_o", W.direct ? run_direct(T, D.d, D.I, S.c, &w->wo, 1, e, st) : run_gemm(g, e, st));
   return T5_OK;
 }
 
@@ -491,7 +544,11 @@ int fwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   const size_t es = D.es;
   const AttnDims ad = cross_dims(cfg, D);
   T5_STEP("rmsnorm_fwd", launch_rmsnorm_fwd(S.h, IN_F32, xw->lnx_scale, S.nx, ty, S.rx, T, D.d, cfg->rms_eps, st));
-  if (fused) {
+  if (W.direct) {
+    T5_STEP("gemm_xq", run_direct(T, D.I, D.d, S.nx, &xw->xq, 1, epi(EPI_STORE, S.qx, D.I, ty), st));
+    const void* kv[2] = {xw->xk, xw->xv};
+    T5_STEP("gemm_xkv", run_direct(Te, D.I, D.d, enc, kv, 2, epi(EPI_STORE, S.kvx, 2 * D.I, ty), st));
+  } else if (fused) {
     GemmDesc gq = gemm1(T, D.I, D.d, S.nx, D.d, 1, W.xq_t, D.d, 1, ty);
     T5_STEP("gemm_xq", run_gemm(gq, epi(EPI_STORE, S.qx, D.I, ty), st));
     GemmDesc gkv = gemm1(Te, 2 * D.I, D.d, enc, D.d, 1, W.xkv_t, D.d, 1, ty);
@@ -518,7 +575,7 @@ int fwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
                      : gemm1(T, D.d, D.I, S.cx, D.I, 1, xw->xo, D.d, 0, ty);
   GemmEpi e = epi(EPI_RESID, S.h2, D.d, IN_F32);
   e.aux0 = S.h; e.aux_type = IN_F32; e.drop = drop_site(D, DROP_CROSS_OUT);
-  T5_STEP("gemm_xo", run_gemm(g, e, st));
+  T5_STEP("gemm_xo", W.direct ? run_direct(T, D.d, D.I, S.cx, &xw->xo, 1, e, st) : run_gemm(g, e, st));
   return T5_OK;
 }
 
@@ -532,7 +589,13 @@ int fwd_mlp(const t5_block_cfg* cfg, const Dims& D, const float* hin, const t5_b
                        : gemm1(T, D.F, D.d, S.n2, D.d, 1, w->wi0, D.F, 0, ty);
     GemmEpi e = epi(EPI_STORE, S.a, D.F, ty);
     e.act = ACT_RELU; e.drop = drop_site(D, DROP_MLP_HIDDEN);
-    T5_STEP("gemm_wi_relu", run_gemm(g, e, st));
+    T5_STEP("gemm_wi_relu", W.direct ? run_direct(T, D.F, D.d, S.n2, &w->wi0, 1, e, st) : run_gemm(g, e, st));
+  } else if (W.direct) {
+    const void* wi2[2] = {w->wi0, w->wi1};
+    GemmEpi e = epi(EPI_GEGLU_FWD, S.gp, D.F, ty);
+    e.out1 = S.gl; e.out2 = S.a; e.act = D.mlp;
+    if (!gemm_direct_supported(gemm_cols(T, D.F, D.d, S.n2, D.d, wi2, 2, ty), e)) return T5_ERR_UNSUPPORTED;
+    T5_STEP("gemm_wi_geglu", run_direct(T, D.F, D.d, S.n2, wi2, 2, e, st));
   } else if (fused) {
     GemmDesc g = gemm1(T, 2 * D.F, D.d, S.n2, D.d, 1, W.wi_t, D.d, 1, ty);
     GemmEpi e = epi(EPI_GEGLU_FWD, S.gp, D.F, ty);
@@ -557,7 +620,7 @@ int fwd_mlp(const t5_block_cfg* cfg, const Dims& D, const float* hin, const t5_b
                      : gemm1(T, D.d, D.F, S.a, D.F, 1, w->wo_ff, D.d, 0, ty);
   GemmEpi e = epi(EPI_RESID, y, D.d, ty);
   e.aux0 = hin; e.aux_type = IN_F32; e.drop = drop_site(D, DROP_MLP_OUT);
-  T5_STEP("gemm_wo", run_gemm(g, e, st));
+  T5_STEP("gemm_wo", W.direct ? run_direct(T, D.d, D.F, S.a, &w->wo_ff, 1, e, st) : run_gemm(g, e, st));
   return T5_OK;
 }
 

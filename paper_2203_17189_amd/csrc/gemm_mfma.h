@@ -15,6 +15,7 @@
 // lane that owns LDS slot (row, physical chunk) fetches the logical chunk that belongs there.
 // Two operand layouts:
 //   k-contiguous (A[m][k]):  LDS rows of BK k (64 or 128 B: 4 or 8 chunks), read with ds_read_b128;
+//   (the weights of gemm_mfma_direct.hip: A k-contiguous, B n-contiguous, its columns from up to three matrices)
 //   m-contiguous (A[k][m]):  LDS rows of BM m, 32-byte granules swizzled by k, read with the LDS
 //                            transpose load ds_read_b64_tr_b16 (two per MFMA operand).
 // The compiler does not see these DMA writes; ordering is explicit: s_waitcnt vmcnt(n) + s_barrier
@@ -47,6 +48,12 @@ __device__ __forceinline__ int kc_swz(int row) {
   else return (row ^ (row >> 3)) & 7;
 }
 
+// m-contiguous stage of ROWS m: 32-byte granule g of row k lies at granule g ^ mc_swz(k).
+template <int ROWS>
+__device__ __forceinline__ int mc_swz(int krow) {
+  return ((krow & 3) << 1) & (ROWS / 16 - 1);
+}
+
 // One MFMA operand (8 bf16 of k for row base + lane%32) for k-step kk of a stage.
 template <int ROWS, bool KC, int BK>
 __device__ __forceinline__ bf16x8 load_frag(const char* stage, int base, int kk, int lane) {
@@ -61,7 +68,7 @@ __device__ __forceinline__ bf16x8 load_frag(const char* stage, int base, int kk,
     const int m_e = base + (((lane >> 4) & 1) << 4) + ((i16 & 3) << 2);
     const int krow = kk * 16 + ((lane >> 5) << 3) + (i16 >> 2);
     const int g = m_e >> 4;
-    const int off0 = krow * (ROWS * 2) + ((g ^ ((krow & 3) << 1)) << 5) + ((m_e & 15) << 1);
+    const int off0 = krow * (ROWS * 2) + ((g ^ mc_swz<ROWS>(krow)) << 5) + ((m_e & 15) << 1);
     const int off1 = off0 + 4 * (ROWS * 2);  // krow + 4 keeps (krow & 3)
     short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(stage + off0));
     short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(stage + off1));
@@ -182,6 +189,9 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
       so0 = const_cast<void*>(t[2]); so1 = const_cast<void*>(t[3]); so2 = const_cast<void*>(t[4]);
     }
   }
+  if constexpr (A_KC && !B_KC) {  // columns from several matrices: offsets count from the lowest
+    for (int s = 1; s < g.nsrc; ++s) seg_b = (uint64_t)g.seg[s].B < (uint64_t)seg_b ? g.seg[s].B : seg_b;
+  }
   const int ks = L / nb;  // split-k slice
   L -= ks * nb;
   constexpr int GM = 8;
@@ -216,7 +226,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
       constexpr int CPR = BM / 8;  // 16-byte chunks per k-row
       const int slot = q * 64 + lane;
       const int krow = slot / CPR, pch = slot % CPR;
-      const int gch = (((pch >> 1) ^ ((krow & 3) << 1)) << 1) | (pch & 1);
+      const int gch = (((pch >> 1) ^ mc_swz<BM>(krow)) << 1) | (pch & 1);
       int mm = m0 + gch * 8;
       mm = mm < g.M ? mm : g.M - 8;
       a_off[i] = (uint32_t)krow * (uint32_t)lda * 2u + (uint32_t)mm * 2u;
@@ -235,10 +245,22 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
       constexpr int CPR = BN / 8;
       const int slot = q * 64 + lane;
       const int krow = slot / CPR, pch = slot % CPR;
-      const int gch = (((pch >> 1) ^ ((krow & 3) << 1)) << 1) | (pch & 1);
+      const int gch = (((pch >> 1) ^ mc_swz<BN>(krow)) << 1) | (pch & 1);
       int nn = n0 + gch * 8;
       nn = nn < g.N ? nn : g.N - 8;
-      b_off[i] = (uint32_t)krow * (uint32_t)ldb * 2u + (uint32_t)nn * 2u;
+      b_off[i] = (uint32_t)krow * (uint32_t)ldb * 2u;
+      if constexpr (A_KC) {  // weights as they are stored: the column's matrix, and its column there
+        int src = 0;
+        if constexpr (EPI == EPI_GEGLU_FWD) {  // packed columns: 32 of wi0, 32 of wi1, ...
+          src = (nn >> 5) & 1;
+          nn = ((nn >> 6) << 5) + (nn & 31);
+        } else if (g.nsrc > 1) {
+          src = nn / g.nsrc_cols;
+          nn -= src * g.nsrc_cols;
+        }
+        b_off[i] += (uint32_t)((uint64_t)(src == 0 ? g.seg[0].B : src == 1 ? g.seg[1].B : g.seg[2].B) - (uint64_t)seg_b);
+      }
+      b_off[i] += (uint32_t)nn * 2u;
     }
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;

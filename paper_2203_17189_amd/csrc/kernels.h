@@ -22,6 +22,9 @@ enum { IN_F32 = 0, IN_BF16 = 1 };
 // n = x * r * g, r = rsqrt(mean(x^2) + eps).  x: [T,d] of x_type; g, n of out_type; r: [T] float32.
 hipError_t launch_rmsnorm_fwd(const void* x, int x_type, const void* g, void* n, int out_type, float* r,
                               int T, int d, float eps, hipStream_t st);
+// The same of a bf16 x, and what launch_relpos_diag does for a bf16 table, in one launch (d % 8 == 0).
+hipError_t launch_rmsnorm_fwd_diag(const void* x, const void* g, void* n, float* r, int T, int d, float eps, const void* table,
+                                   float* diag, int S, int H, const RelposLut& lut, hipStream_t st);
 // dx_total = resid + r * (dn*g - xh * mean(dn*g*xh)),  xh = x*r;  dg (+)= sum_T dn*xh.
 // x of x_type; g of g_type; dn float32; resid of resid_type (nullable: no residual term); outputs: out_f32 (nullable),
 // out_lp (nullable, lp_type).  dg_partial: workspace float[rmsnorm_bwd_partial_rows(T) * d]; dg == nullptr leaves the sums there.
@@ -96,7 +99,7 @@ struct GemmDesc {
   // seg[0].A / .B and the epilogue's outputs for the workgroups of that problem.  ngroups <= 1: one problem.
   const void* const* groups;
   int ngroups;
-  // nsrc > 1 (float32 MFMA kernel, one segment, b_kc == 0): the N columns of B are nsrc matrices of nsrc_cols columns
+  // nsrc > 1 (float32 MFMA kernel and gemm_direct, one segment, b_kc == 0): the N columns of B are nsrc matrices of nsrc_cols columns
   // (seg[0..nsrc-1].B, all with seg[0].ldb) side by side; for EPI_GEGLU_FWD wi0 and wi1, whose columns the kernel
   // interleaves by itself.
   int nsrc, nsrc_cols;
@@ -131,6 +134,9 @@ hipError_t launch_split_reduce(const SplitJobs& jobs, hipStream_t st);
 bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e);
 hipError_t launch_gemm_mfma(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 // its epilogue families
+// ... and with the weights as they are stored (a_kc, !b_kc, one segment, nsrc as below), for problems of a few hundred rows
+bool gemm_direct_supported(const GemmDesc& g, const GemmEpi& e);
+hipError_t launch_gemm_direct(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_store(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_resid(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_geglu_fwd(const GemmDesc& g, const GemmEpi& e, hipStream_t st);

@@ -1,6 +1,7 @@
 // T5 layer norm (scale-only RMS norm, the norm of the models in paper Sec. 4): forward and backward.
 // HBM-bound: one wavefront per token row, 16-byte loads, float32 statistics, wave reductions.
 #include "kernels.h"
+#include <algorithm>
 
 namespace t5mi {
 
@@ -46,13 +47,12 @@ constexpr int kNormWaves = 4;
 // squares and the scaling, so that it is read once; read a second time it came from the fabric again (the counters
 // showed twice the algorithmic bytes).  NV == 0: any width, two passes over the row.
 template <typename TX, typename TO, int VEC, int NV>
-__global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_fwd_kernel(
-    const TX* __restrict__ x, const TO* __restrict__ g, TO* __restrict__ n, float* __restrict__ r, int T,
-    int d, float eps) {
+__device__ __forceinline__ void rmsnorm_fwd_rows(const TX* __restrict__ x, const TO* __restrict__ g, TO* __restrict__ n,
+                                                 float* __restrict__ r, int T, int d, float eps, int blocks) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const float inv_d = 1.f / (float)d;
-  for (int row = blockIdx.x * kNormWaves + wave; row < T; row += gridDim.x * kNormWaves) {
+  for (int row = blockIdx.x * kNormWaves + wave; row < T; row += blocks * kNormWaves) {
     const TX* xr = x + (size_t)row * d;
     TO* nr = n + (size_t)row * d;
     float ss = 0.f;
@@ -101,6 +101,34 @@ __global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_fwd_kernel(
       }
     }
   }
+}
+
+template <typename TX, typename TO, int VEC, int NV>
+__global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_fwd_kernel(
+    const TX* __restrict__ x, const TO* __restrict__ g, TO* __restrict__ n, float* __restrict__ r, int T,
+    int d, float eps) {
+  rmsnorm_fwd_rows<TX, TO, VEC, NV>(x, g, n, r, T, d, eps, gridDim.x);
+}
+
+// The forward of a few hundred rows and the layer's bias diagonals behind them (a launch of their own costs 4.5 us).
+struct DiagArgs {
+  const bf16* table;
+  float* diag;
+  int S, H, norm_blocks;
+  RelposLut lut;
+};
+template <int NV>
+__global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_fwd_diag_kernel(const bf16* __restrict__ x, const bf16* __restrict__ g,
+                                                                         bf16* __restrict__ n, float* __restrict__ r, int T,
+                                                                         int d, float eps, DiagArgs a) {
+  if ((int)blockIdx.x >= a.norm_blocks) {
+    const int w = 2 * a.S - 1, i = ((int)blockIdx.x - a.norm_blocks) * (kNormWaves * 64) + (int)threadIdx.x;
+    if (i >= w) return;
+    const int b = relpos_bucket_dev(i - (a.S - 1), a.lut);
+    for (int h = 0; h < a.H; ++h) a.diag[(size_t)h * w + i] = (float)a.table[b * a.H + h];
+    return;
+  }
+  rmsnorm_fwd_rows<bf16, bf16, 8, NV>(x, g, n, r, T, d, eps, a.norm_blocks);
 }
 
 // Backward.  Each wave walks rows; lane keeps float32 partial sums of dg for its columns
@@ -292,6 +320,22 @@ hipError_t launch_rmsnorm_fwd(const void* x, int x_type, const void* g, void* n,
   }
   if (x_type == IN_BF16) return hipErrorInvalidValue;
   return fwd_dispatch<float, float>(x, g, n, r, T, d, eps, st);
+}
+
+hipError_t launch_rmsnorm_fwd_diag(const void* x, const void* g, void* n, float* r, int T, int d, float eps, const void* table,
+                                   float* diag, int S, int H, const RelposLut& lut, hipStream_t st) {
+  if (d % 8 != 0) return hipErrorInvalidValue;
+  DiagArgs a{(const bf16*)table, diag, S, H, std::min(ceil_div(T, kNormWaves), 8192), lut};
+  const int grid = a.norm_blocks + ceil_div(2 * (int64_t)S - 1, kNormWaves * 64), nv = ceil_div(d, 512);
+#define T5MI_FWD(NV) \
+  rmsnorm_fwd_diag_kernel<NV><<<grid, kNormWaves * 64, 0, st>>>((const bf16*)x, (const bf16*)g, (bf16*)n, r, T, d, eps, a)
+  if (nv <= 1) T5MI_FWD(1);
+  else if (nv <= 2) T5MI_FWD(2);
+  else if (nv <= 4) T5MI_FWD(4);
+  else if (nv <= 8) T5MI_FWD(8);
+  else T5MI_FWD(0);
+#undef T5MI_FWD
+  return hipGetLastError();
 }
 
 int rmsnorm_bwd_partial_rows(int T) {

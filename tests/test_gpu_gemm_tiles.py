@@ -145,3 +145,37 @@ def test_256x192_tiles_with_residual():
     for i in range(2):
         e = rel_err(whole[i], np.concatenate([h[i] for h in halves]))
         assert e[0] <= STATED_BF16[0] and e[1] <= STATED_BF16[1], e
+
+
+@pytest.mark.parametrize("d,heads,dk,f,batch,seq,enc,mlp", [(128, 2, 64, 192, 1, 40, 0, "geglu_tanh"),   # 64x64 tiles
+                                                            (512, 6, 64, 1024, 3, 333, 0, "geglu_erf"),
+                                                            (768, 12, 64, 2048, 4, 333, 0, "geglu_tanh"),  # 128x64, 128x128
+                                                            (768, 12, 64, 2048, 13, 200, 77, "geglu_tanh"),
+                                                            (1024, 3, 128, 2880, 9, 250, 0, "relu"),       # two per unit
+                                                            (1088, 5, 64, 2816, 1, 300, 130, "relu")])
+def test_stored_and_packed_weights_give_the_same_layer(d, heads, dk, f, batch, seq, enc, mlp):
+    """Few tokens read the weights as they are stored; a weight that does not start on 16 bytes sends the layer back to the
+    packed copies.  Every sum runs over k in the same order: the same bits."""
+    import paper_2203_17189_amd as P
+    cfg = SI.BlockConfig("direct", 96, batch, seq, d, heads, dk, f, attn_scale=0.125, mlp=mlp, enc_seq=enc, causal=enc > 0)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + f)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").bfloat16()  # noqa: E731
+    i = heads * dk
+    shapes = dict(ln1_scale=(d,), wq=(d, i), wk=(d, i), wv=(d, i), wo=(i, d), rel_table=(32, heads), ln2_scale=(d,),
+                  wi0=(d, f), wi1=(d, f), wo_ff=(f, d))
+    if mlp == "relu":
+        del shapes["wi1"]
+    if enc:
+        shapes.update(lnx_scale=(d,), xq=(d, i), xk=(d, i), xv=(d, i), xo=(i, d))
+    w = {k: rnd(*s) * (1.0 if len(s) == 1 else s[0] ** -0.5) for k, s in shapes.items()}
+    x = rnd(batch, seq, d)
+    e = rnd(batch, enc, d) if enc else None
+    off = torch.empty(w["wo"].numel() + 4, device="cuda", dtype=torch.bfloat16)[4:].view_as(w["wo"]).copy_(w["wo"])
+    assert off.data_ptr() % 16 == 8
+    for n in range(2):
+        ww = dict(w, wo=off) if n else w
+        y = P.t5_decoder_block_fwd(cfg, x, e, ww)[0] if enc else P.t5_block_fwd(cfg, x, ww)[0]
+        if n == 0:
+            y0 = y.clone()
+    assert torch.isfinite(y0.float()).all() and torch.equal(y0, y)
