@@ -25,6 +25,7 @@
 // compact block of output tiles and shares operand tiles through its own L2.
 #pragma once
 #include "kernels.h"
+#include <algorithm>
 #include <atomic>
 
 #include <type_traits>
@@ -827,43 +828,32 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
   }
 }
 
-// Tile size and k split of a weight-gradient GEMM (EPI_SPLIT_F32): few output tiles, very long k.
-// Small outputs take 128x128 tiles (fewer k-slices, hence fewer partial sums per output element); k is split
-// by the cost of the rounds over the 256 compute units and of the partial sums (measured, below).
+// Tile size and k split of a weight-gradient GEMM (EPI_SPLIT_F32): the cheapest of both tiles with up to 32 slices.  In
+// microseconds: a workgroup's k-tile of 64 takes 0.54 with 128x128 tiles and a compute unit to itself (1.75 times that with two
+// on one) and 1.45 with 256x256, and the float atomics of all slices run at 340 G/s whatever the split; without slices the
+// tiles leave by plain stores.  Model / measured: 768 x 4096 over 8991 tokens 256x256 in five slices 96 / 98, 128x128 unsliced
+// 79 / 82; over 512 tokens 256x256 25 / 43, 128x128 7 / 13; 2048 x 768 over 65536, 256x256 in ten 199 / 198; 512 x 1024 over
+// 32768, 128x128 in eight 50 / 52, in sixteen 58 / 60; 768 x 768 over 8991 in seven 26 / 27.
+// Grouped launches run many rounds: the atomics hide behind the products of the rounds that follow, but for 17 us each, and
+// 128x128 tiles take 0.62 a k-tile (12 x 768 x 4096 over 16384: 1260 us with those, 1080 with 256x256).
 void wgrad_plan(const GemmDesc& g, const GemmEpi& e, int ngr, bool& big, int& split_k) {
   int nk = 0;
   for (int s = 0; s < g.nseg; ++s) nk += g.seg[s].K / KQ;
   const int64_t t256 = (int64_t)ceil_div(g.M, 256) * ceil_div(g.N, 256) * ngr;
   const int64_t t128 = (int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 128) * ngr;
-  // 256x256 tiles from 48 output tiles on, and from 24 when the reduction is long (measured at d_model 768:
-  // dWi 3x16 tiles -18 % at 65536 and -10 % at 16384 tokens; dWo_ff 8x3 and dWqkv 3x9 tiles -14 % at 65536
-  // tokens but +10..18 % at 16384, where a workgroup's share of k no longer pays for the larger epilogue)
-  big = t256 >= 48 || (t256 >= 24 && nk * KQ >= 49152);
-  // grouped small outputs (12 x 768 x 768: 432 tiles of 128x128): one round of small tiles over the whole
-  // reduction, no split and no atomics, beats 256x256 tiles split seven ways (0.20 -> 0.17 ms at 4096 tokens)
-  if (ngr > 1 && t128 <= 512) big = false;
-  const int64_t tiles = big ? t256 : t128;
   double best = -1.0;
+  big = false;
   split_k = 1;
   for (int sp = 1; sp <= 32; ++sp) {
     if (sp > 1 && nk / sp < 8) break;
-    const int64_t wgs = tiles * sp;
-    double cost;
-    if (big) {
-      // rounds x (a workgroup's k-tiles + its epilogue); the epilogue of a 256x256 slice (65536 float
-      // atomics beside those of 255 other workgroups) costs about as much as 12 k-tiles of 64 (measured)
-      cost = (double)((wgs + 255) / 256) * ((double)nk / sp + 12.0);
-    } else {
-      // In units of a 128x128 workgroup's k-tile of 64 when it has a compute unit to itself (0.54 us): two on one unit
-      // take 1.75 each, and the float atomics of all slices together run at 340 G/s whatever the split, 0.09 units
-      // per workgroup.  So one workgroup per unit with half the slices beats two (512 x 1024 over 32768 tokens: 8 slices
-      // 52 us, 16 slices 60; 768 x 768 over 8991: 7 slices 27, 14 slices 38) unless it leaves units idle
-      // (2048 x 768 over 14592, 96 tiles: 2 slices 80, 5 slices 64).
-      const int64_t rem = wgs % 512;
-      const double rounds = (double)(wgs / 512) * 1.75 + (rem > 256 ? 1.75 : rem > 0 ? 1.0 : 0.0);
-      cost = rounds * (double)nk / sp + (sp > 1 ? 0.09 * (double)wgs : 0.0);
-    }
-    if (best < 0.0 || cost < best) { best = cost; split_k = sp; }
+    const int64_t w256 = t256 * sp, w128 = t128 * sp, rem = w128 % 512;
+    const double r256 = (double)((w256 + 255) / 256);
+    const double k256 = 1.45 * r256 * nk / sp, atomics = sp > 1 ? 0.193 * (double)w256 : 8.0;
+    const double c256 = k256 + 5.0 + (ngr > 1 ? std::max(17.4 * (r256 - 1.0), atomics - k256 * (r256 - 1.0) / r256) : atomics);
+    const double rounds = (double)(w128 / 512) * 1.75 + (rem > 256 ? 1.75 : rem > 0 ? 1.0 : 0.0);
+    const double c128 = (ngr > 1 && w128 > 512 ? 0.62 : 0.54) * rounds * nk / sp + (sp > 1 ? 0.048 * (double)w128 : 0.0) + 3.0;
+    if (best < 0.0 || c128 < best) { best = c128; big = false; split_k = sp; }
+    if (c256 < best) { best = c256; big = true; split_k = sp; }
   }
   (void)e;
 }

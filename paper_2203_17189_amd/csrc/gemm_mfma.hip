@@ -83,6 +83,13 @@ bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e) {
   }
 }
 
+int gemm_wgrad_slices(const GemmDesc& g, const GemmEpi& e) {
+  bool big;
+  int split_k;
+  wgrad_plan(g, e, 1, big, split_k);
+  return split_k;
+}
+
 size_t gemm_split_partials_bytes(const GemmDesc& g, const GemmEpi& e) {
   if (e.kind != EPI_SPLIT_F32 || g.ngroups > 1) return 0;
   bool big;

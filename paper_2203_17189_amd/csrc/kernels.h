@@ -143,6 +143,8 @@ hipError_t launch_gemm_mfma_geglu_fwd(const GemmDesc& g, const GemmEpi& e, hipSt
 hipError_t launch_gemm_mfma_geglu_bwd(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_split(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_split_grouped(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+// k-slices of a weight gradient (EPI_SPLIT_F32) on that kernel; one slice without accumulate needs no cleared output.
+int gemm_wgrad_slices(const GemmDesc& g, const GemmEpi& e);
 // Bytes of the partial-sum buffer (GemmEpi::aux0) that launch_gemm_mfma would use for this EPI_SPLIT_F32 problem (0: no split).
 size_t gemm_split_partials_bytes(const GemmDesc& g, const GemmEpi& e);
 

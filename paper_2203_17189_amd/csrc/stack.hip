@@ -219,7 +219,7 @@ int layers_backward(const Layers& s, const void* enc_out, float* denc_acc, int a
     Stash S;
     carve_stash(D, s.stash_of(l), &S);
     S.diag = s.diag;
-    T5_SUB(bwd_zero(D, &s.lg[l], dec ? &s.xg[l] : nullptr, nullptr, acc != 0, st));
+    T5_SUB(bwd_zero(D, &s.lg[l], dec ? &s.xg[l] : nullptr, nullptr, acc != 0, st, BW.defer_wgrad));
     T5_SUB(bwd_mlp(D, dy, dec ? S.h2 : S.h, &s.lw[l], S, BW, &s.lg[l], acc, st));
     if (dec) {
       // the first layer processed stores its denc, the others add theirs to it

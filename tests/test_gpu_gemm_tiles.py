@@ -179,3 +179,30 @@ def test_stored_and_packed_weights_give_the_same_layer(d, heads, dk, f, batch, s
         if n == 0:
             y0 = y.clone()
     assert torch.isfinite(y0.float()).all() and torch.equal(y0, y)
+
+
+@pytest.mark.parametrize("d,f,batch,seq", [(768, 2048, 1, 40), (768, 2048, 4, 128), (512, 1024, 9, 333), (2048, 2560, 2, 150),
+                                           (768, 2048, 40, 333)])
+def test_weight_gradients_overwrite_what_the_buffers_hold(d, f, batch, seq):
+    """Gradients that one slice stores whole are not cleared first, sliced ones are: either way nothing of what the buffers
+    held is left, and with accumulate it stays.  (float32 atomics: sums in another order, 1e-6 of the largest value.)"""
+    import paper_2203_17189_amd as P
+    from paper_2203_17189_amd import binding as B
+    cfg = SI.BlockConfig("overwrite", 97, batch, seq, d, 4, 64, f, attn_scale=0.125)
+    w, x, dy = make_case(replace(cfg, batch=1, seq=32))
+    dw, _, _ = upload_case(replace(cfg, batch=1, seq=32), w, x, dy)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(batch)
+    dx, ddy = [torch.randn((batch, seq, d), generator=gen, device="cuda").bfloat16() for _ in range(2)]
+    _, stash = P.t5_block_fwd(cfg, dx, dw)
+    out = []
+    for fill, acc in ((0.0, False), (float("nan"), False), (3.0, True)):
+        g = B.alloc_grads(cfg, dw)
+        for v in g.values():
+            v.fill_(fill)
+        P.t5_block_bwd(cfg, ddy, dx, dw, stash, grads=g, accumulate=acc)
+        out.append(g)
+    for k, v in out[0].items():
+        tol = 4e-6 * float(v.abs().max()) + 4e-6
+        assert float((out[1][k] - v).abs().max()) <= tol, k
+        assert float((out[2][k] - 3.0 - v).abs().max()) <= tol + 4e-6, k  # (one rounding at 3 more)
