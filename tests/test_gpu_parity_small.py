@@ -327,3 +327,16 @@ def test_block_bf16_small(cfg):
     gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
     errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{k: rel_err(gg[k], g[k]) for k in g}}
     check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)), relu=is_relu(cfg))
+
+
+def test_bucket_tables_of_alternating_parameters():
+    """A thread keeps its last two bucket tables: three sets of parameters in turn, refused ones between them."""
+    import paper_2203_17189_amd as P
+    rp = np.arange(-300, 301, dtype=np.int32)
+    dev = torch.from_numpy(rp).cuda()
+    for _ in range(2):
+        for bi, nb, dist in ((True, 32, 128), (False, 32, 128), (True, 16, 64), (True, 32, 128), (False, 16, 64)):
+            got = P.t5_relpos_bucket(dev, bi, nb, dist).cpu().numpy()
+            assert np.array_equal(got, O.relpos_bucket(rp, bi, nb, dist)), (bi, nb, dist)
+            with pytest.raises(P.T5Error):
+                P.t5_relpos_bucket(dev, True, 31, 128)
