@@ -829,9 +829,9 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
 }
 
 // Tile size and k split of a weight-gradient GEMM (EPI_SPLIT_F32): the cheapest of both tiles with up to 32 slices.  In
-// microseconds: a workgroup's k-tile of 64 takes 0.54 with 128x128 tiles and a compute unit to itself (1.75 times that with two
-// on one) and 1.45 with 256x256, and the float atomics of all slices run at 340 G/s whatever the split; without slices the
-// tiles leave by plain stores.  Model / measured: 768 x 4096 over 8991 tokens 256x256 in five slices 96 / 98, 128x128 unsliced
+// microseconds: a workgroup's k-tile of 64 takes 0.54 to 0.6 with 128x128 tiles and a compute unit to itself (1.75 times that
+// with two on one) and 1.45 with 256x256, and the float atomics of all slices run at 340 G/s whatever the split, a quarter of
+// them behind the products of four and more rounds; without slices the tiles leave by plain stores.  Model / measured: 768 x 4096 over 8991 tokens 256x256 in five slices 96 / 98, 128x128 unsliced
 // 79 / 82; over 512 tokens 256x256 25 / 43, 128x128 7 / 13; 2048 x 768 over 65536, 256x256 in ten 199 / 198; 512 x 1024 over
 // 32768, 128x128 in eight 50 / 52, in sixteen 58 / 60; 768 x 768 over 8991 in seven 26 / 27.
 // Grouped launches run many rounds: the atomics hide behind the products of the rounds that follow, but for 17 us each, and
@@ -848,10 +848,10 @@ void wgrad_plan(const GemmDesc& g, const GemmEpi& e, int ngr, bool& big, int& sp
     if (sp > 1 && nk / sp < 8) break;
     const int64_t w256 = t256 * sp, w128 = t128 * sp, rem = w128 % 512;
     const double r256 = (double)((w256 + 255) / 256);
-    const double k256 = 1.45 * r256 * nk / sp, atomics = sp > 1 ? 0.193 * (double)w256 : 8.0;
+    const double k256 = 1.45 * r256 * nk / sp, atomics = sp > 1 ? (ngr <= 1 && r256 >= 4.0 ? 0.145 : 0.193) * (double)w256 : 8.0;
     const double c256 = k256 + 5.0 + (ngr > 1 ? std::max(17.4 * (r256 - 1.0), atomics - k256 * (r256 - 1.0) / r256) : atomics);
     const double rounds = (double)(w128 / 512) * 1.75 + (rem > 256 ? 1.75 : rem > 0 ? 1.0 : 0.0);
-    const double c128 = (ngr > 1 && w128 > 512 ? 0.62 : 0.54) * rounds * nk / sp + (sp > 1 ? 0.048 * (double)w128 : 0.0) + 3.0;
+    const double c128 = (ngr > 1 && w128 > 512 ? 0.62 : 0.58) * rounds * nk / sp + (sp > 1 ? 0.048 * (double)w128 : 0.0) + 3.0;
     if (best < 0.0 || c128 < best) { best = c128; big = false; split_k = sp; }
     if (c256 < best) { best = c256; big = true; split_k = sp; }
   }
