@@ -22,7 +22,7 @@
 //
 // Measured on the layer d 512, 6 heads, d_ff 1024, 4000 tokens (forward + backward): GEMMs 5.0 ms with the FMA kernel
 // this replaced for float32 (64x64 tiles, 4x4 products a thread, one load in flight), 650 us with float32 instructions
-// everywhere, 560 us now.
+// everywhere, 610 us now.
 #include "kernels.h"
 #include <algorithm>
 #include <atomic>
@@ -368,18 +368,28 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmDesc g,
 }
 
 // ------------------------------------------------------------------ the same on the bf16 matrix units
-// Every operand as three bf16 parts, a = a0 + a1 + a2 exactly, and six of the nine products of parts:
-//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),  what is left out is 2^-26 of it.
-// Six bf16 products of 32x32x16 take 192 cycles where the float32 instructions take 512 for the same k, and the sums lose less:
-// a0 b0 meets in one accumulator (one rounding in 16 k; float32 instructions round every two), the five small
-// products in another, whose roundings are 2^-8 of the first one's.  Error of a layer's results against 64 bits, d 512,
-// 16 x 250 tokens: y 4.2e-7 -> 1.8e-7, weight gradients 7.0e-7..1.04e-6 -> 2.7e-7..6.5e-7; with one accumulator 4.1e-7 and 6e-7..1.2e-6.
-// Bound: the vector instructions of the conversion (5.5 a value) and the LDS round trips between the barriers, beside the matrix
-// unit; d 768, 4000 tokens: products of a layer 1807 -> 1409 us (152 TFLOP/s with 1024 tiles), d 512: 650 -> 557.
+// Every operand as three bf16 parts, a = a0 + a1 + a2 exactly, and eight of the nine products of parts:
+//   a b = a0 b0 + (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0 + a1 b2 + a2 b1),  what is left out is 2^-34 of it and less.
+// (|a1| is up to 2^-8 of |a| and |a2| up to 2^-17: a1 b2 + a2 b1 reaches 2^-24, as much as the rounding of a float32 product, and
+// a sum with one term in it shows that.)  The parts are those of 2^16 a: the last bit of any float32 number, 2^-149, is then
+// 2^-133, the last of bf16, and the matrix unit keeps subnormal numbers; at the other end, from 2^112 on, the parts are
+// not finite, which shows in the sum.
+// Eight bf16 products of 32x32x16 take 256 cycles where the float32 instructions take 512 for the same k, and the sums lose less:
+// a0 b0 meets in one accumulator (one rounding in 16 k; float32 instructions round every two), the seven small
+// products in another, whose roundings are 2^-7 of the first one's.  Error of a layer's results against 64 bits, d 512,
+// 16 x 250 tokens: y 4.2e-7 -> 1.8e-7, weight gradients 7.0e-7..1.04e-6 -> 2.9e-7..6.6e-7; one term alone: 2^-24, as before.
+// Bound: the vector instructions of the conversion (6 a value) and the LDS round trips between the barriers, beside the matrix
+// unit; d 768, 4000 tokens: products of a layer 1828 -> 1501 us (134 TFLOP/s with 1024 tiles), d 512: 665 -> 611.  With six
+// products (without a1 b2 and a2 b1) and unscaled parts 1402 and 562, at up to 1.7 times the error for one term and
+// fewer than 24 bits of values below 2^-110.
+// Results that are formed again: a layer of 16 x 250 tokens, d 512, takes 2.1 ms instead of 0.83 with one token that is not
+// finite (all its weight gradients are not) and 2.4 with all of them.
 // A tile is requested D k-tiles ahead into registers, converted once and written to one of two LDS stages (rows of
 // BK k of each part, padded by 16 bytes: 16 rows cover the banks once) while the other one is multiplied.
 // Measured and left: parts by truncation instead of rounding (same time, y 2.0e-7); fragments read one k-tile ahead
 // (dn2 of d 512 92 -> 83 us, but one wavefront a SIMD: weight gradients a fifth slower); k-tiles of 32 at 128x128.
+
+constexpr float kUp = 65536.f;  // the parts are those of this times the operand (above)
 
 // Four float32 values as three bf16 parts each (two 32-bit words per part), x = p0 + p1 + p2 exactly: every part is the
 // rounded remainder of the ones before it, eight significant bits at a time.
@@ -526,15 +536,15 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
     }
     advance();
   };
-  // Rows of A past the end of k become zeros; those of B repeat its last one (where that is not finite, the check
-  // behind the loop sees it).
+  // Values times kUp, so that the parts of the smallest of them are bf16 numbers too.  Rows of A past the end of k become
+  // zeros; those of B repeat its last one (where that is not finite, the check behind the loop sees it).
   auto put = [&](char* st, f32x4 (&ra)[A_SL], const f32x4 (&rb)[B_SL], int left) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < A_SL; ++i) {
       const int q = tid + i * NT;
       const int r = A_KC ? q / (BK / 4) : tid % BM, k = A_KC ? (q % (BK / 4)) * 4 : (wka + i * (NT / BM)) * 4;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) ra[i][x] = k + x < left ? ra[i][x] : 0.f;
+      for (int x = 0; x < 4; ++x) ra[i][x] *= k + x < left ? kUp : 0.f;
       const Split3 s = split3(ra[i]);
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(st + p * A_PL + r * LD + k * 2) = s.p[p];
@@ -543,7 +553,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
     for (int i = 0; i < B_SL; ++i) {
       const int q = tid + i * NT;
       const int r = B_KC ? q / (BK / 4) : tid % BN, k = B_KC ? (q % (BK / 4)) * 4 : (wkb + i * (NT / BN)) * 4;
-      const Split3 s = split3(rb[i]);
+      const Split3 s = split3(rb[i] * kUp);
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(st + 3 * A_PL + p * B_PL + r * LD + k * 2) = s.p[p];
     }
@@ -574,7 +584,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
       char* cur = smx + ((t - t_begin) & 1) * STG;
       char* nxt = smx + STG - ((t - t_begin) & 1) * STG;
       __syncthreads();
-      constexpr int NS = BK / 16;
+      constexpr int NS = BK / 16, NP = 8;  // steps of 16 k; products of parts
       bf16x8 fa[NS][MI][3], fb[NS][NI][3];
 #pragma unroll
       for (int s = 0; s < NS; ++s)
@@ -589,11 +599,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
         }
       put(nxt, raw_a[v], raw_b[v], left[v]);  // tile t + 1 (behind the last one: that one again, unread)
       fetch(raw_a[v], raw_b[v], left[v]);     // tile t + 1 + D
-      constexpr int PA[6] = {0, 2, 0, 1, 1, 0}, PB[6] = {0, 0, 2, 1, 0, 1};
+      constexpr int PA[NP] = {0, 1, 2, 2, 0, 1, 1, 0}, PB[NP] = {0, 2, 1, 0, 2, 1, 0, 1};
 #pragma unroll
       for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int p = 0; p < 6; ++p)
+        for (int p = 0; p < NP; ++p)
 #pragma unroll
           for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -603,7 +613,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
             }
       // one product, then its share of the next tile's conversion: a matrix instruction keeps its unit busy for 32 cycles,
       // in which the wavefront issues eight others
-      constexpr int NMF = NS * 6 * MI * NI, VAL = ((A_SL + B_SL) * 24 + NMF - 1) / NMF + 1;
+      constexpr int NMF = NS * NP * MI * NI, VAL = ((A_SL + B_SL) * 28 + NMF - 1) / NMF + 1;
       __builtin_amdgcn_sched_group_barrier(0x100, NS * 3 * (MI + NI), 0);
 #pragma unroll
       for (int x = 0; x < NMF; ++x) {
@@ -619,23 +629,20 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * (1.f / kUp / kUp);
 
-  // A sum that is not finite: the parts of an infinite or nearly infinite operand are not finite together with their
-  // remainders.  Sums that are all minute: the matrix unit takes parts below 2^-126 for zero.  Either way the wavefront forms
-  // its tiles again from the float32 values themselves (rare; operands from global memory).
-  float chk = 0.f, top = 0.f;
+  // A result that is not finite: infinite operands and those from 2^112 on have no parts, products from 2^96 on no sum.  The
+  // wavefront forms its tiles again from the float32 values themselves (rare; operands from global memory) and takes
+  // those results for these elements and no others: its row and its column alone decide the bits of a result.
+  float chk = 0.f;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        chk = fmaf(acc[i][j][r], 0.f, chk);
-        top = fmaxf(top, fabsf(acc[i][j][r]));
-      }
-  if (__builtin_expect(__any(chk != 0.f) || (!__any(top >= 0x1p-90f) && __any(top > 0.f)), 0)) {
-    clear(acc);
+      for (int r = 0; r < 16; ++r) chk = fmaf(acc[i][j][r], 0.f, chk);
+  if (__builtin_expect(__any(chk != 0.f), 0)) {
+    clear(lo);
     seg = 0;
     kt = t_begin;
     while (seg + 1 < nseg && kt >= (pick(K0, K1, K2) + BK - 1) / BK) kt -= (pick(K0, K1, K2) + BK - 1) / BK, ++seg;
@@ -663,10 +670,16 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < NI; ++j) lo[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[j], lo[i][j], 0, 0, 0);
       }
       advance();
     }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = fabsf(acc[i][j][r]) < INFINITY ? acc[i][j][r] : lo[i][j][r];
   }
   f32_epilogue<MI, NI, EPI>(g, e, split_k, acc, m0 + wm * TMW, n0 + wn * TNW, pos.z, lane);
 }
@@ -965,9 +978,11 @@ hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   int64_t K = 0;
   for (int i = 0; i < g.nseg; ++i) K += g.seg[i].K;
   // Split operands from about as many tiles as keep the conversion off the critical path; us for native / split:
-  //   128x128, 4000 tokens: qkv of d 512 (288 tiles) 61 / 52, dn2 of d 768 (192) 246 / 189, wi of d 768 (1024) 231 / 165;
-  //            with 128 tiles (4000 x 512 x 2048) 84 / 92, but 71 on 64x64 ones, as 768 x 4096 over 200 tokens (192) 32 / 41 / 29;
-  //   64x64:   1024 x 512 x 2048 (128 tiles) 57 / 44, 1024 x 512 x 512 (128) 15 / 16, 200 x 2048 x 768 (128) 27 / 22.
+  //   128x128, 4000 tokens: qkv of d 512 (288 tiles) 62 / 57, dn2 of d 768 (192) 247 / 201, wi of d 768 (1024) 231 / 187;
+  //            with 128 tiles (4000 x 512 x 2048) 85 / 104, but 80 on 64x64 ones;
+  //   64x64:   1024 x 512 x 2048 (128 tiles) 57 / 46, 200 x 2048 x 768 (128) 27 / 23; with n-contiguous weights no faster
+  //            (800 x 768 x 2048 61 / 61, 1200 x 2304 x 768 54 / 60) nor over few tokens (gradient of 768 x 4096 over 200 32 / 35): their
+  //            sums lose half as much.
   // The gated inputs need 64 columns a wavefront, which 64x64 tiles of four do not have.  32x32 tiles with the
   // reduction over the wavefronts where even the 64x64 ones leave half the chip idle.
   if (t128 >= 192 && K >= 384) return launch_x3<128, 128, 16, 2, A_KC, B_KC, EPI>(g, e, 1, st);

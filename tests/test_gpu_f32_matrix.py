@@ -186,3 +186,97 @@ def test_split_products_of_an_infinite_weight(d, value):
         assert rel_err(y1[near, 5], np.float64(want[near]))[0] <= TOL_F32[0]
     keep = np.arange(d) != 5
     assert rel_err(y1[:, keep], y0[:, keep])[0] <= TOL_F32[0]
+
+
+# As SPLIT_CASES, at lengths that put several sequences into every tile of rows: (the ungated form's products are one
+# matrix wide, one segment), 64 x 64 and 128 x 128 tiles, weight gradients whole and in slices that start inside k
+MIXED_CASES = [replace(C, batch=208, seq=20, d_model=132, n_heads=3, d_kv=20, d_ff=260, mlp="relu", name="f32_mixed"),
+               replace(C, batch=208, seq=20, d_model=388, n_heads=6, d_kv=52, d_ff=772, causal=True, name="f32_mixed"),
+               replace(C, batch=20, seq=20, d_model=516, n_heads=9, d_kv=64, d_ff=1536, name="f32_mixed")]
+MIXED_IDS = ["64x64", "128x128_slices", "64x64_whole"]
+# 2-norm error of a tensor against 64 bits: 2e-7 to 1.4e-6 over this file's cases with ordinary values
+TOL_NORM = 2e-6
+
+
+def _norm_err(got, want):
+    return float(np.linalg.norm(got - want) / np.linalg.norm(want))
+
+
+@pytest.mark.parametrize("power", [-100, -118])
+@pytest.mark.parametrize("cfg", MIXED_CASES, ids=MIXED_IDS)
+def test_small_gradients_beside_ordinary_ones(cfg, power):
+    """Sequences whose output gradient is 2^-118 of the others' keep every bit that float32 has: their dx is the scaled dx
+    of the ordinary gradient (all of it normal numbers)."""
+    w, x, dy = make_case(cfg)
+    _, saved = O.block_fwd(cfg, x, w)
+    dx, _ = O.block_bwd(cfg, dy, w, saved)
+    small = np.arange(cfg.batch) % 3 == 1
+    scale = np.where(small, 2.0 ** power, 1.0)[:, None, None]
+    shape = (cfg.batch, cfg.seq, cfg.d_model)
+    _, gdx, _ = run_block_gpu(cfg, w, x, dy.reshape(shape) * scale)
+    gdx = gdx.reshape(shape) / scale
+    for rows in (small, ~small):
+        assert _norm_err(gdx[rows], dx.reshape(shape)[rows]) <= TOL_NORM
+
+
+@pytest.mark.parametrize("cfg", MIXED_CASES, ids=MIXED_IDS)
+def test_weights_of_mixed_magnitude(cfg):
+    """Channels of q, v and hidden units times 2^114 or 2^-114, undone by k, wo and wo_ff: y and dx are those of the plain
+    weights, every gradient that of its weight over the factor."""
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+
+    def factors(n):
+        return np.ldexp(1.0, np.array([0, -114, 114])[np.arange(n) // 5 % 3])
+    fi, ff = factors(cfg.n_heads * cfg.d_kv), factors(cfg.d_ff)
+    gate = "wi0" if cfg.mlp == "relu" else "wi1"
+    by = {"wq": fi, "wk": 1 / fi, "wv": fi, "wo": 1 / fi[:, None], gate: ff, "wo_ff": 1 / ff[:, None]}
+    gy, gdx, gg = run_block_gpu(cfg, {k: v * by.get(k, 1.0) for k, v in w.items()}, x, dy)
+    for name, got, want in [("y", gy, y), ("dx", gdx, dx)] + [(n, gg[n] * by.get(n, 1.0), g[n]) for n in g]:
+        assert _norm_err(got.reshape(want.shape), want) <= TOL_NORM, (name, _norm_err(got.reshape(want.shape), want))
+
+
+@pytest.mark.parametrize("cfg", MIXED_CASES, ids=MIXED_IDS)
+@pytest.mark.parametrize("where", ["x", "dy"])
+def test_other_sequences_keep_their_bits(cfg, where):
+    """A token, or an output gradient, that is not finite: y and dx of the other sequences are the same bits as without it."""
+    import torch
+    import paper_2203_17189_amd as P
+    from parity_util import upload_case
+    w, x, dy = make_case(cfg)
+    dw, dx, ddy = upload_case(cfg, w, x, dy)
+    bad = cfg.batch // 2 + 1
+    out = []
+    for value in (0.5, float("nan"), float("inf")):
+        (dx if where == "x" else ddy).view(cfg.batch, cfg.seq, -1)[bad, 11, 7] = value
+        y, stash = P.t5_block_fwd(cfg, dx, dw)
+        gx, g = P.t5_block_bwd(cfg, ddy, dx, dw, stash)
+        out.append((y.view(cfg.batch, cfg.seq, -1).clone(), gx.view(cfg.batch, cfg.seq, -1).clone(), g["wo_ff"].clone()))
+    keep = torch.arange(cfg.batch, device="cuda") != bad
+    for y, gx, gw in out[1:]:
+        assert torch.equal(y[keep], out[0][0][keep]) and torch.equal(gx[keep], out[0][1][keep])
+        assert not torch.isfinite(gx[bad]).all()
+        if where == "dy":  # dWo_ff = a^T dy: one column (of a late k-slice), its other columns the same bits
+            cols = torch.arange(cfg.d_model, device="cuda") != 7
+            assert torch.equal(gw[:, cols], out[0][2][:, cols]) and not torch.isfinite(gw[:, 7]).any()
+
+
+def test_gradient_of_one_token_is_its_rounded_products():
+    """A sum with one term: dWo_ff[f] = a_f dy, every element within a rounding of it as float32 products are."""
+    import torch
+    import paper_2203_17189_amd as P
+    from parity_util import upload_case
+    cfg = MIXED_CASES[2]
+    w, x, dy = make_case(cfg)
+    dw, dx, ddy = upload_case(cfg, w, x, dy)
+    ddy.view(-1, cfg.d_model)[torch.arange(cfg.batch * cfg.seq, device="cuda") != 123] = 0.0
+    _, stash = P.t5_block_fwd(cfg, dx, dw)
+    _, g = P.t5_block_bwd(cfg, ddy, dx, dw, stash)
+    ratio = g["wo_ff"].double() / ddy.view(-1, cfg.d_model)[123].double()  # a_f (1 + rounding)
+    lo, hi = ratio.abs().min(1).values, ratio.abs().max(1).values
+    # 2^-24 for the rounded sum of the parts' products; seven roundings of the small ones, 2^-7 of it in all; what the
+    # product of the two last parts adds, 2^-34
+    bound = 2.0 ** -24 * (1 + 7 * 2.0 ** -7 + 2.0 ** -10)
+    some = hi > 1e-30
+    assert some.sum() > 1000 and float(((hi - lo) / lo)[some].max()) <= 2 * bound * (1 + 1e-6)
