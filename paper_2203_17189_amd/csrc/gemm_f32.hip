@@ -713,12 +713,15 @@ hipError_t launch_x3(const GemmDesc& g, const GemmEpi& e, int split_k, hipStream
 // instructions.  At 64 tokens a product is one round trip to memory and a short chain of products, and the code of the
 // launch is read for the first time as often as not, so: every wavefront takes its own batches of 32 k straight into registers
 // in the order of the instruction's operands, the next batch on its way (no staging, no barrier), the operands of the
-// epilogue are requested before the products, the wavefronts' sums meet in LDS once, in their order, and all of them
-// share the epilogue.  (The kernel it replaced staged through LDS and left the epilogue, a branch an element, to one of
+// epilogue are requested before the products, the wavefronts' sums meet in LDS once, in pairs, and all of them
+// share the epilogue.  A wavefront keeps the two halves of its batches apart, so that no more than 16 k of a batch follow one
+// another in a sum: with one accumulator the weight gradients over 64 tokens had 2.5e-7 of error, now 2.2e-7.  (The kernel it replaced staged through LDS and left the epilogue, a branch an element, to one of
 // four wavefronts.)  Layer of d 64, 64 tokens: its 12 products 132 -> 86 us, 140 -> 104 us in all; dn2 of d 768, 200 tokens
 // (k 4096) 66 -> 42 us.  Eight wavefronts from 128 k on: with fewer k some of them would have nothing to do.
+// One workgroup has a compute unit, hence two wavefronts a SIMD: left to aim at four, the compiler holds back the loads (200 x 768 x 2048
+// with residual 26 us, 22 like this).
 template <int WK, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(WK * 64) void gemm_f32_small_kernel(GemmDesc g, GemmEpi e) {
+__global__ __launch_bounds__(WK * 64) __attribute__((amdgpu_waves_per_eu(WK / 4, 2))) void gemm_f32_small_kernel(GemmDesc g, GemmEpi e) {
   constexpr bool GF = EPI == EPI_GEGLU_FWD;
   constexpr int NJ = GF ? 2 : 1, U = 4;  // column tiles; steps of 8 k in a batch
   __shared__ float part[WK][NJ][32][32];
@@ -767,11 +770,13 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_small_kernel(GemmDesc g, Gem
       n[0] -= q * g.nsrc_cols;
     }
   }
-  f32x16 acc[NJ];
+  f32x16 acc[2][NJ];  // the two halves of every batch
 #pragma unroll
-  for (int j = 0; j < NJ; ++j)
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[h][j][r] = 0.f;
 
   f32x4 va[2][U], vb[2][NJ][U];
   auto load = [&](const float* A, const float* B, const float* B1, int K, int b, f32x4 (&a)[U], f32x4 (&bb)[NJ][U])
@@ -809,7 +814,10 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_small_kernel(GemmDesc g, Gem
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][q], bb[j][u][q], acc[j], 0, 0, 0);
+        for (int j = 0; j < NJ; ++j) {
+          f32x16& c = acc[u / (U / 2)][j];
+          c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][q], bb[j][u][q], c, 0, 0, 0);
+        }
   };
   int b0 = wave;  // batches wave, wave + WK, ... over all segments
   for (int s = 0; s < g.nseg; ++s) {
@@ -836,18 +844,22 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_small_kernel(GemmDesc g, Gem
 #pragma unroll
   for (int j = 0; j < NJ; ++j)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) part[wave][j][((r >> 2) << 3) + (g2 << 2) + (r & 3)][l32] = acc[j][r];
+    for (int r = 0; r < 16; ++r) part[wave][j][((r >> 2) << 3) + (g2 << 2) + (r & 3)][l32] = acc[0][j][r] + acc[1][j][r];
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < NE; ++i) {
     const int row = er + RS * i;
-    float v = part[0][0][row - m0][tid & 31], w = 0.f;
-    if constexpr (GF) w = part[0][NJ - 1][row - m0][tid & 31];
+    auto sum = [&](int j) __attribute__((always_inline)) {
+      float t[WK];
 #pragma unroll
-    for (int k = 1; k < WK; ++k) {
-      v += part[k][0][row - m0][tid & 31];
-      if constexpr (GF) w += part[k][NJ - 1][row - m0][tid & 31];
-    }
+      for (int k = 0; k < WK; ++k) t[k] = part[k][j][row - m0][tid & 31];
+#pragma unroll
+      for (int n = WK / 2; n > 0; n /= 2)
+#pragma unroll
+        for (int k = 0; k < n; ++k) t[k] += t[k + n];
+      return t[0];
+    };
+    const float v = sum(0), w = GF ? sum(NJ - 1) : 0.f;
     if (row >= g.M || en >= N) continue;
     const float mk = e.drop.on && !(EPI == EPI_RESID && e.aux_mask) ? drop_mult(e.drop, drop_row_key(e.drop, (uint32_t)row), (uint32_t)en) : 1.f;
     if constexpr (GF) {

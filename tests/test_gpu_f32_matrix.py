@@ -280,3 +280,29 @@ def test_gradient_of_one_token_is_its_rounded_products():
     bound = 2.0 ** -24 * (1 + 7 * 2.0 ** -7 + 2.0 ** -10)
     some = hi > 1e-30
     assert some.sum() > 1000 and float(((hi - lo) / lo)[some].max()) <= 2 * bound * (1 + 1e-6)
+
+
+def test_small_products_add_no_more_than_16_terms_in_a_row():
+    """64 equal tokens of which the first has an output gradient of 1 and the others just under half a rounding of that: what
+    stands in one run of sums with the first is lost, the rest is not."""
+    import torch
+    import paper_2203_17189_amd as P
+    from parity_util import upload_case
+    cfg = replace(C, batch=2, seq=32, mlp="relu", name="f32_runs")
+    w, x, dy = make_case(cfg)
+    w = dict(w, rel_table=np.zeros_like(w["rel_table"]))
+    x = np.broadcast_to(x.reshape(64, -1)[:1], (64, cfg.d_model)).reshape(x.shape)
+    tiny = np.float32(2.0 ** -25 * 0.999)
+    dy = np.full_like(dy, tiny)
+    dy.reshape(64, -1)[0] = 1.0
+    dw, dx, ddy = upload_case(cfg, w, x, dy)
+    _, stash = P.t5_block_fwd(cfg, dx, dw)
+    g = P.t5_block_bwd(cfg, ddy, dx, dw, stash)[1]["wo_ff"].double()
+    ddy.zero_()
+    ddy.view(64, -1)[0] = 1.0
+    a = P.t5_block_bwd(cfg, ddy, dx, dw, stash)[1]["wo_ff"].double()  # one term each: the activation itself
+    assert (a > 0).any()
+    want = a * (1.0 + 63 * float(tiny))
+    # 15 terms beside the first; the sums of accumulators and wavefronts, and of the terms that are kept, in four roundings
+    assert float((g - want).abs().max() / want.abs().max()) <= 15 * 2.0 ** -25 + 4 * 2.0 ** -24
+    assert torch.equal(g == 0, a == 0)
