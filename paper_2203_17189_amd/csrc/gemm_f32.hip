@@ -10,8 +10,8 @@
 // allows it, single elements elsewhere).
 //
 // Tiles: BM x BN per workgroup, k-tiles of BK, WM x WN x WK wavefronts.  WK > 1 gives each of WK wavefronts its share
-// of every k-tile; their sums meet in LDS in a fixed order.  That is what the small problems need: at 64 tokens a
-// product has one to sixteen 64x64 tiles, and the length of one wavefront's MFMA chain is its time.
+// of every k-tile; their sums meet in LDS in a fixed order: two wavefronts with 64x64 tiles, eight with 32x64.  (Problems of few
+// tiles have a kernel of their own, below.)
 //
 // Operand layouts in LDS (floats):
 //   k-contiguous (A[m][k])  rows of BK k, padded by 4: a lane reads 4 consecutive k of its row (ds_read_b128; 16 rows
@@ -993,15 +993,21 @@ hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   //   128x128, 4000 tokens: qkv of d 512 (288 tiles) 62 / 57, dn2 of d 768 (192) 247 / 201, wi of d 768 (1024) 231 / 187;
   //            with 128 tiles (4000 x 512 x 2048) 85 / 104, but 80 on 64x64 ones;
   //   64x64:   1024 x 512 x 2048 (128 tiles) 57 / 46, 200 x 2048 x 768 (128) 27 / 23; with n-contiguous weights no faster
-  //            (800 x 768 x 2048 61 / 61, 1200 x 2304 x 768 54 / 60) nor over few tokens (gradient of 768 x 4096 over 200 32 / 35): their
+  //            (800 x 768 x 2048 61 / 61, 1200 x 2304 x 768 54 / 60) nor over few tokens (gradient of 768 x 4096 over 200 32 / 35, over 400 42 / 52): their
   //            sums lose half as much.
   // The gated inputs need 64 columns a wavefront, which 64x64 tiles of four do not have.  32x32 tiles with the
-  // reduction over the wavefronts where even the 64x64 ones leave half the chip idle.
+  // reduction over the wavefronts where even the 64x64 ones leave half the chip idle.  From 64 of those on the 32x32 ones are two
+  // rounds of workgroups: products with k-contiguous weights (gradients of the norms' outputs) take 32x64 tiles instead, one
+  // round, staged, every k-tile shared by eight wavefronts: 400 x 768, k 4096 80 -> 63 us, k 2304 47 -> 40, 300 x 1024, k 8192
+  // 150 -> 116, 640 x 512, k 2048 46 -> 36; one round of 32x32: 320 x 768, k 4096 42, with 32x64 66.  The others are as fast either
+  // way, and gated-GELU backward loses (300 x 1024, k 512: 16 and 29): one of the eight wavefronts does the epilogue.
   if (t128 >= 192 && K >= 384) return launch_x3<128, 128, 16, 2, A_KC, B_KC, EPI>(g, e, 1, st);
   if (t64 >= 128) {
     if constexpr (EPI == EPI_GEGLU_FWD) return launch_tile<64, 64, 2, 1, 2, 32, A_KC, B_KC, EPI, true>(g, e, 1, st);
     else return launch_x3<64, 64, 32, 3, A_KC, B_KC, EPI>(g, e, 1, st);
   }
+  if constexpr (EPI == EPI_STORE && B_KC)
+    if (t64 > 64) return launch_tile<32, 64, 1, 1, 8, 64, A_KC, B_KC, EPI, true>(g, e, 1, st);
   return launch_small<A_KC, B_KC, EPI>(g, e, st);
 }
 

@@ -37,6 +37,12 @@ SMALL_CASES = [replace(C, batch=1, seq=33, d_model=36, n_heads=1, d_kv=20, d_ff=
                replace(C, batch=2, seq=40, d_model=96, n_heads=3, d_kv=32, d_ff=36, mlp="relu", dropout_rate=0.125, dropout_seed=4)]
 
 
+# 64 x 64 tiles by the dozen, short of 128: 32 x 64 tiles and eight wavefronts for one to three k-contiguous segments that are not a
+# multiple of their k-tiles, 32 x 32 ones for the others; a last row tile of 9, a last column tile of 4
+STAGED_CASES = [replace(C, batch=3, seq=131, d_model=772, n_heads=3, d_kv=20, d_ff=100),
+                replace(C, batch=1, seq=361, d_model=836, n_heads=5, d_kv=52, d_ff=68, mlp="relu", causal=True)]
+
+
 # Products with operands in three bf16 parts: 64 x 64 and 128 x 128 tiles, k not a multiple of their k-tiles, several
 # segments, columns from several matrices, sliced and whole weight gradients (540 and 400 tokens)
 SPLIT_CASES = [replace(C, batch=32, seq=130, d_model=132, n_heads=3, d_kv=20, d_ff=260),
@@ -53,7 +59,7 @@ def _check(pairs):
         assert rel_err(got, want)[0] <= TOL_F32[0], (name, rel_err(got, want))
 
 
-@pytest.mark.parametrize("cfg", CASES + SMALL_CASES + SPLIT_CASES, ids=lambda c: f"{c.batch}x{c.seq}_d{c.d_model}_k{c.d_kv}_f{c.d_ff}")
+@pytest.mark.parametrize("cfg", CASES + SMALL_CASES + STAGED_CASES + SPLIT_CASES, ids=lambda c: f"{c.batch}x{c.seq}_d{c.d_model}_k{c.d_kv}_f{c.d_ff}")
 def test_block_f32_matrix(cfg):
     if cfg.dropout_rate:
         cfg = replace(cfg, dropout_rate=float(np.float32(cfg.dropout_rate)))
