@@ -283,37 +283,60 @@ GemmEpi epi(int kind, void* out0, int ld0, int out_type) {
   return e;
 }
 
-// Shapes (M, N, K) of a layer's weight gradients, C[M, N] = A[K, M]^T B[K, N].
-template <typename F>
-void each_wgrad(const Dims& D, F probe) {
-  const int T = (int)D.T, Te = (int)D.Te;
-  probe(D.F, D.d, T);                                   // dWo_ff
-  probe(D.d, D.mlp == ACT_RELU ? D.F : 2 * D.F, T);     // dWi0 | dWi1
-  probe(D.I, D.d, T);                                   // dWo
-  probe(D.d, 3 * D.I, T);                               // dWq | dWk | dWv
-  if (D.Sk > 0) {
-    probe(D.I, D.d, T);                                 // dXo
-    probe(D.d, D.I, T);                                 // dXq
-    probe(D.d, 2 * D.I, Te);                            // dXk | dXv
+// A layer's weight gradients, C[M, N] = A[K, M]^T B[K, N]: what is cleared, sized, launched one by one or grouped
+// over the layers of a stack goes by these.
+enum { WG_WO_FF, WG_WI, WG_WO, WG_QKV, WG_XO, WG_XQ, WG_XKV, WG_KINDS };
+inline int wgrad_kinds(const Dims& D) { return D.Sk > 0 ? WG_KINDS : WG_XO; }
+GemmDesc wgrad_desc(const Dims& D, int kind, const void* A, const void* B) {
+  const int T = (int)D.T, Te = (int)D.Te, nf = D.mlp == ACT_RELU ? 1 : 2;
+  switch (kind) {
+    case WG_WO_FF: return gemm1(D.F, D.d, T, A, D.F, 0, B, D.d, 0, D.ty);         // dWo_ff = a^T dy
+    case WG_WI: return gemm1(D.d, nf * D.F, T, A, D.d, 0, B, nf * D.F, 0, D.ty);  // dWi0 | dWi1 = n2^T [du | dw]
+    case WG_WO: return gemm1(D.I, D.d, T, A, D.I, 0, B, D.d, 0, D.ty);            // dWo = c^T dh
+    case WG_QKV: return gemm1(D.d, 3 * D.I, T, A, D.d, 0, B, 3 * D.I, 0, D.ty);   // dWq | dWk | dWv = n1^T dqkv
+    case WG_XO: return gemm1(D.I, D.d, T, A, D.I, 0, B, D.d, 0, D.ty);            // dXo = cx^T dh2
+    case WG_XQ: return gemm1(D.d, D.I, T, A, D.d, 0, B, D.I, 0, D.ty);            // dXq = nx^T dq
+    default: return gemm1(D.d, 2 * D.I, Te, A, D.d, 0, B, 2 * D.I, 0, D.ty);      // dXk | dXv = enc^T [dk | dv]
   }
 }
+struct WgradOut {
+  float* p[3];  // the matrices that the columns of C belong to
+};
+WgradOut wgrad_out(const Dims& D, int kind, const t5_block_grads* g, const t5_cross_grads* x) {
+  switch (kind) {
+    case WG_WO_FF: return {{g->wo_ff, nullptr, nullptr}};
+    case WG_WI: return {{g->wi0, D.mlp == ACT_RELU ? nullptr : g->wi1, nullptr}};
+    case WG_WO: return {{g->wo, nullptr, nullptr}};
+    case WG_QKV: return {{g->wq, g->wk, g->wv}};
+    case WG_XO: return {{x->xo, nullptr, nullptr}};
+    case WG_XQ: return {{x->xq, nullptr, nullptr}};
+    default: return {{x->xk, x->xv, nullptr}};
+  }
+}
+GemmEpi wgrad_epi(const Dims& D, int kind, const WgradOut& o) {
+  const int ld = kind == WG_WO_FF || kind == WG_WO || kind == WG_XO ? D.d : kind == WG_WI ? D.F : D.I;
+  GemmEpi e = epi(EPI_SPLIT_F32, o.p[0], ld, IN_F32);
+  e.out1 = o.p[1]; e.out2 = o.p[2]; e.accumulate = 1;
+  if (o.p[1]) e.split_n = ld;
+  return e;
+}
 alignas(16) const long long kAligned16[4] = {0, 0, 0, 0};  // placeholder operand of a size query
+const WgradOut kNowhere = {{(float*)kAligned16, (float*)kAligned16, (float*)kAligned16}};
 // Room for the partial sums of the layer's largest split weight-gradient GEMM (reproducible mode).
 size_t wgrad_partials_bytes(const Dims& D) {
   size_t need = 0;
-  each_wgrad(D, [&](int M, int N, int K) {
-    GemmDesc g = gemm1(M, N, K, kAligned16, M, 0, kAligned16, N, 0, IN_BF16);
-    const size_t b = gemm_split_partials_bytes(g, epi(EPI_SPLIT_F32, (void*)kAligned16, N, IN_F32));
+  for (int kind = 0; kind < wgrad_kinds(D); ++kind) {
+    const size_t b = gemm_split_partials_bytes(wgrad_desc(D, kind, kAligned16, kAligned16), wgrad_epi(D, kind, kNowhere));
     need = b > need ? b : need;
-  });
+  }
   return need;
 }
-// Whether a weight gradient of this shape adds into an output that was cleared before (k-slices that meet in atomics, the
+// Whether a weight gradient adds into an output that was cleared before (k-slices that meet in atomics, the
 // float32 slices' last launch) rather than storing it whole.
-bool wgrad_adds(const Dims& D, int M, int N, int K) {
+bool wgrad_adds(const Dims& D, int kind) {
   if (D.ty != IN_BF16) return true;
-  const GemmDesc g = gemm1(M, N, K, kAligned16, M, 0, kAligned16, N, 0, IN_BF16);
-  const GemmEpi e = epi(EPI_SPLIT_F32, (void*)kAligned16, N, IN_F32);
+  const GemmDesc g = wgrad_desc(D, kind, kAligned16, kAligned16);
+  const GemmEpi e = wgrad_epi(D, kind, kNowhere);
   return !gemm_mfma_supported(g, e) || gemm_wgrad_slices(g, e) > 1;
 }
 // Floats that the k-slices of a float32 weight gradient take (a multiple of four, 0: not sliced).
@@ -323,11 +346,8 @@ size_t slice_floats(const GemmDesc& g, const GemmEpi& e) {
 }
 size_t wgrad_slices_bytes(const Dims& D) {
   size_t need = 0;
-  each_wgrad(D, [&](int M, int N, int K) {
-    GemmEpi e = epi(EPI_SPLIT_F32, (void*)kAligned16, N, IN_F32);
-    e.accumulate = 1;
-    need += slice_floats(gemm1(M, N, K, kAligned16, M, 0, kAligned16, N, 0, IN_F32), e) * 4;
-  });
+  for (int kind = 0; kind < wgrad_kinds(D); ++kind)
+    need += slice_floats(wgrad_desc(D, kind, kAligned16, kAligned16), wgrad_epi(D, kind, kNowhere)) * 4;
   return need;
 }
 SplitJob split_job(const GemmDesc& g, const GemmEpi& e, const float* part) {
@@ -349,6 +369,14 @@ hipError_t wgrad_gemm(const BwdWs& W, const GemmDesc& g, GemmEpi e, hipStream_t 
     W.split.j[W.split.count++] = split_job(g, e, part);
   }
   return run_gemm(g, e, st);
+}
+// One of a layer's weight gradients: added to the output where the caller accumulates or bwd_zero has cleared it.
+hipError_t layer_wgrad(const BwdWs& W, const Dims& D, int kind, const void* A, const void* B, const t5_block_grads* dw,
+                       const t5_cross_grads* dxw, int acc, hipStream_t st) {
+  GemmEpi e = wgrad_epi(D, kind, wgrad_out(D, kind, dw, dxw));
+  e.accumulate = acc || wgrad_adds(D, kind);
+  e.aux0 = W.wg_partials;
+  return wgrad_gemm(W, wgrad_desc(D, kind, A, B), e, st);
 }
 hipError_t wgrad_finish(const BwdWs& W, hipStream_t st) {
   const hipError_t err = W.split.count > 0 ? launch_split_reduce(W.split, st) : hipSuccess;
@@ -643,22 +671,13 @@ int bwd_zero(const Dims& D, const t5_block_grads* dw, const t5_cross_grads* dxw,
   std::memset(&z, 0, sizeof(z));
   auto add = [&](float* p, int64_t n) { z.p[z.count] = p; z.n[z.count] = n; ++z.count; };
   if (ddiag) add(ddiag, (int64_t)D.H * (2 * D.S - 1));
-  if (!acc) {
-    const int64_t dI = (int64_t)D.d * D.I, dF = (int64_t)D.d * D.F;
-    const int T = (int)D.T, Te = (int)D.Te;
-    auto adds = [&](int M, int N, int K) { return deferred || wgrad_adds(D, M, N, K); };
-    if (adds(D.d, 3 * D.I, T)) { add(dw->wq, dI); add(dw->wk, dI); add(dw->wv, dI); }
-    if (adds(D.I, D.d, T)) add(dw->wo, dI);
-    if (adds(D.d, D.mlp == ACT_RELU ? D.F : 2 * D.F, T)) {
-      add(dw->wi0, dF);
-      if (D.mlp != ACT_RELU) add(dw->wi1, dF);
-    }
-    if (adds(D.F, D.d, T)) add(dw->wo_ff, dF);
-    if (dxw) {
-      if (adds(D.d, D.I, T)) add(dxw->xq, dI);
-      if (adds(D.d, 2 * D.I, Te)) { add(dxw->xk, dI); add(dxw->xv, dI); }
-      if (adds(D.I, D.d, T)) add(dxw->xo, dI);
-    }
+  for (int kind = 0; !acc && kind < wgrad_kinds(D); ++kind) {
+    if (!deferred && !wgrad_adds(D, kind)) continue;
+    const GemmDesc g = wgrad_desc(D, kind, nullptr, nullptr);
+    const WgradOut o = wgrad_out(D, kind, dw, dxw);
+    const int64_t n = (int64_t)g.M * wgrad_epi(D, kind, o).ld0;
+    for (float* p : o.p)
+      if (p) add(p, n);
   }
   static_assert(ZERO_MAX >= 12, "ddiag + 7 block gradients + 4 cross-attention gradients");
   if (z.count > 0) T5_STEP("zero_grads", launch_zero_f32(z, st));
@@ -681,10 +700,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
   if (!W.defer_wgrad) {  // dWo_ff = a^T dy
     T5_TRY(fork_sync(W.fork));
     hipStream_t st = wgrad_stream(W.fork);
-    GemmDesc g = gemm1(D.F, D.d, T, S.a, D.F, 0, dy, D.d, 0, ty);
-    GemmEpi e = epi(EPI_SPLIT_F32, dw->wo_ff, D.d, IN_F32);
-    e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-    T5_STEP("gemm_dwo_ff", wgrad_gemm(W, g, e, st));
+    T5_STEP("gemm_dwo_ff", layer_wgrad(W, D, WG_WO_FF, S.a, dy, dw, nullptr, acc, st));
   }
   if (D.mlp == ACT_RELU) {
     {  // du = (dy Wo_ff^T) where a > 0
@@ -696,10 +712,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
     if (!W.defer_wgrad) {  // dWi0 = n2^T du
       T5_TRY(fork_sync(W.fork));
       hipStream_t st = wgrad_stream(W.fork);
-      GemmDesc g = gemm1(D.d, D.F, T, S.n2, D.d, 0, du_p, D.F, 0, ty);
-      GemmEpi e = epi(EPI_SPLIT_F32, dw->wi0, D.F, IN_F32);
-      e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-      T5_STEP("gemm_dwi", wgrad_gemm(W, g, e, st));
+      T5_STEP("gemm_dwi", layer_wgrad(W, D, WG_WI, S.n2, du_p, dw, nullptr, acc, st));
     }
     {  // dn2 = du Wi0^T
       GemmDesc g = gemm1(T, D.d, D.F, du_p, D.F, 1, w->wi0, D.F, 1, ty);
@@ -715,10 +728,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
     if (!W.defer_wgrad) {  // dWi0 | dWi1 = n2^T [du | dw]
       T5_TRY(fork_sync(W.fork));
       hipStream_t st = wgrad_stream(W.fork);
-      GemmDesc g = gemm1(D.d, 2 * D.F, T, S.n2, D.d, 0, du_p, 2 * D.F, 0, ty);
-      GemmEpi e = epi(EPI_SPLIT_F32, dw->wi0, D.F, IN_F32);
-      e.out1 = dw->wi1; e.split_n = D.F; e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-      T5_STEP("gemm_dwi", wgrad_gemm(W, g, e, st));
+      T5_STEP("gemm_dwi", layer_wgrad(W, D, WG_WI, S.n2, du_p, dw, nullptr, acc, st));
     }
     {  // dn2 = du Wi0^T + dw Wi1^T
       GemmDesc g = gemm1(T, D.d, D.F, du_p, 2 * D.F, 1, w->wi0, D.F, 1, ty);
@@ -750,10 +760,7 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   if (!W.defer_wgrad) {  // dXo = cx^T dh2
     T5_TRY(fork_sync(W.fork));
     hipStream_t st = wgrad_stream(W.fork);
-    GemmDesc g = gemm1(D.I, D.d, T, S.cx, D.I, 0, dh_op, D.d, 0, ty);
-    GemmEpi e = epi(EPI_SPLIT_F32, dxw->xo, D.d, IN_F32);
-    e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-    T5_STEP("gemm_dxo", wgrad_gemm(W, g, e, st));
+    T5_STEP("gemm_dxo", layer_wgrad(W, D, WG_XO, S.cx, dh_op, nullptr, dxw, acc, st));
   }
   {  // dcx = dh2 Xo^T
     GemmDesc g = gemm1(T, D.I, D.d, dh_op, D.d, 1, xw->xo, D.d, 1, ty);
@@ -769,17 +776,11 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   if (!W.defer_wgrad) {  // dXq = nx^T dq
     T5_TRY(fork_sync(W.fork));
     hipStream_t st = wgrad_stream(W.fork);
-    GemmDesc g = gemm1(D.d, D.I, T, S.nx, D.d, 0, W.dqx, D.I, 0, ty);
-    GemmEpi e = epi(EPI_SPLIT_F32, dxw->xq, D.I, IN_F32);
-    e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-    T5_STEP("gemm_dxq", wgrad_gemm(W, g, e, st));
+    T5_STEP("gemm_dxq", layer_wgrad(W, D, WG_XQ, S.nx, W.dqx, nullptr, dxw, acc, st));
   }
   if (!W.defer_wgrad) {  // dXk | dXv = enc^T [dk | dv]   (ordered after dXq on the side stream: no new fork point needed)
     hipStream_t st = wgrad_stream(W.fork);
-    GemmDesc g = gemm1(D.d, 2 * D.I, Te, enc, D.d, 0, W.dkvx, 2 * D.I, 0, ty);
-    GemmEpi e = epi(EPI_SPLIT_F32, dxw->xk, D.I, IN_F32);
-    e.out1 = dxw->xv; e.split_n = D.I; e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-    T5_STEP("gemm_dxkv", wgrad_gemm(W, g, e, st));
+    T5_STEP("gemm_dxkv", layer_wgrad(W, D, WG_XKV, enc, W.dkvx, nullptr, dxw, acc, st));
   }
   {  // denc = dk Xk^T + dv Xv^T
     GemmDesc g = gemm1(Te, D.d, D.I, W.dkvx, 2 * D.I, 1, xw->xk, D.I, 1, ty);
@@ -818,10 +819,7 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   if (!W.defer_wgrad) {  // dWo = c^T dh
     T5_TRY(fork_sync(W.fork));
     hipStream_t st = wgrad_stream(W.fork);
-    GemmDesc g = gemm1(D.I, D.d, T, S.c, D.I, 0, dh_op, D.d, 0, ty);
-    GemmEpi e = epi(EPI_SPLIT_F32, dw->wo, D.d, IN_F32);
-    e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-    T5_STEP("gemm_dwo", wgrad_gemm(W, g, e, st));
+    T5_STEP("gemm_dwo", layer_wgrad(W, D, WG_WO, S.c, dh_op, dw, dxw, acc, st));
   }
   {  // dc = dh Wo^T
     GemmDesc g = gemm1(T, D.I, D.d, dh_op, D.d, 1, w->wo, D.d, 1, ty);
@@ -838,10 +836,7 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   if (!W.defer_wgrad) {  // dWq | dWk | dWv = n1^T dqkv
     T5_TRY(fork_sync(W.fork));
     hipStream_t st = wgrad_stream(W.fork);
-    GemmDesc g = gemm1(D.d, 3 * D.I, T, S.n1, D.d, 0, W.dqkv, 3 * D.I, 0, ty);
-    GemmEpi e = epi(EPI_SPLIT_F32, dw->wq, D.I, IN_F32);
-    e.out1 = dw->wk; e.out2 = dw->wv; e.split_n = D.I; e.accumulate = acc || wgrad_adds(D, g.M, g.N, g.seg[0].K); e.aux0 = W.wg_partials;
-    T5_STEP("gemm_dwqkv", wgrad_gemm(W, g, e, st));  // (the layer's last weight gradient)
+    T5_STEP("gemm_dwqkv", layer_wgrad(W, D, WG_QKV, S.n1, W.dqkv, dw, dxw, acc, st));  // (the layer's last weight gradient)
     if (W.split.count > 0) T5_STEP("wgrad_slices", wgrad_finish(W, st));
   }
   {  // dn1 = dq Wq^T + dk Wk^T + dv Wv^T

@@ -50,35 +50,13 @@ struct Layers {
 // are short split-k problems that leave the chip half idle.  Launched for all layers at once (same shapes,
 // a pointer table per problem) they fill it without splitting.  That needs every layer's operands alive
 // until the end of the sweep: its saved activations (so: no remat) and its backward workspace.
-constexpr int kWgradKinds = 7;  // wo_ff, wi, wo, wqkv; decoder layers: xo, xq, xkv
-GemmDesc wgrad_desc(const Dims& D, int kind, const void* A, const void* B) {
-  const int T = (int)D.T, Te = (int)D.Te, nf = D.mlp == ACT_RELU ? 1 : 2;
-  switch (kind) {
-    case 0: return gemm1(D.F, D.d, T, A, D.F, 0, B, D.d, 0, D.ty);            // dWo_ff = a^T dy
-    case 1: return gemm1(D.d, nf * D.F, T, A, D.d, 0, B, nf * D.F, 0, D.ty);  // dWi0 | dWi1 = n2^T [du | dw]
-    case 2: return gemm1(D.I, D.d, T, A, D.I, 0, B, D.d, 0, D.ty);            // dWo = c^T dh
-    case 3: return gemm1(D.d, 3 * D.I, T, A, D.d, 0, B, 3 * D.I, 0, D.ty);    // dWq | dWk | dWv = n1^T dqkv
-    case 4: return gemm1(D.I, D.d, T, A, D.I, 0, B, D.d, 0, D.ty);            // dXo = cx^T dh2
-    case 5: return gemm1(D.d, D.I, T, A, D.d, 0, B, D.I, 0, D.ty);            // dXq = nx^T dq
-    default: return gemm1(D.d, 2 * D.I, Te, A, D.d, 0, B, 2 * D.I, 0, D.ty);  // dXk | dXv = enc^T [dk | dv]
-  }
-}
-GemmEpi wgrad_epi(const Dims& D, int kind, float* o0, float* o1, float* o2) {
-  const int ld = kind == 0 || kind == 2 || kind == 4 ? D.d : kind == 1 ? D.F : D.I;
-  GemmEpi e = epi(EPI_SPLIT_F32, o0, ld, IN_F32);
-  e.out1 = o1; e.out2 = o2; e.accumulate = 1;
-  if (kind == 1 && D.mlp != ACT_RELU) e.split_n = D.F;
-  if (kind == 3 || kind == 6) e.split_n = D.I;
-  return e;
-}
 bool wgrads_grouped_ok(const Dims& D, int L, bool remat) {
   // (the reproducible mode keeps the per-layer launches: their split reductions go through the two-pass form)
   if (D.ty != IN_BF16 || remat || L < 2 || L > 256 || D.det) return false;
-  alignas(16) static const long long dummy[4] = {0, 0, 0, 0};
-  for (int kind = 0; kind < (D.Sk > 0 ? kWgradKinds : 4); ++kind) {
-    GemmDesc g = wgrad_desc(D, kind, dummy, dummy);
-    g.groups = (const void* const*)dummy; g.ngroups = L;
-    if (!gemm_mfma_supported(g, wgrad_epi(D, kind, (float*)dummy, (float*)dummy, (float*)dummy))) return false;
+  for (int kind = 0; kind < wgrad_kinds(D); ++kind) {
+    GemmDesc g = wgrad_desc(D, kind, kAligned16, kAligned16);
+    g.groups = (const void* const*)kAligned16; g.ngroups = L;
+    if (!gemm_mfma_supported(g, wgrad_epi(D, kind, kNowhere))) return false;
   }
   return true;
 }
@@ -99,7 +77,7 @@ void carve_layers(Carver& cv, Layers& s) {
     s.bwd_ws_each = b;
     s.layer_ws = cv.take(b * (size_t)(s.L - 1));
     s.dx_more = cv.take(s.xbytes() * (size_t)(s.L - 1));
-    s.ptr_tab = cv.take<const void*>(sizeof(void*) * kWgradKinds * GEMM_GROUP_PTRS * (size_t)s.L);
+    s.ptr_tab = cv.take<const void*>(sizeof(void*) * WG_KINDS * GEMM_GROUP_PTRS * (size_t)s.L);
   }
 }
 
@@ -235,40 +213,39 @@ int layers_backward(const Layers& s, const void* enc_out, float* denc_acc, int a
   }
   if (s.grouped) {
     // one launch per kind of weight over all layers: problem n is layer L-1-n
-    std::vector<const void*> tab((size_t)kWgradKinds * s.L * GEMM_GROUP_PTRS, nullptr);
-    const int kinds = dec ? kWgradKinds : 4;
+    std::vector<const void*> tab((size_t)WG_KINDS * s.L * GEMM_GROUP_PTRS, nullptr);
+    const int kinds = wgrad_kinds(D);
     for (int n = 0; n < s.L; ++n) {
       const int l = s.L - 1 - n;
       Stash S;
       carve_stash(D, s.stash_of(l), &S);
       const BwdWs& W = bws[n];
-      const t5_block_grads& g = s.lg[l];
-      auto put = [&](int kind, const void* A, const void* B, float* o0, float* o1, float* o2) {
+      auto put = [&](int kind, const void* A, const void* B) {
         const void** t = &tab[((size_t)kind * s.L + n) * GEMM_GROUP_PTRS];
-        t[0] = A; t[1] = B; t[2] = o0; t[3] = o1; t[4] = o2;
+        const WgradOut o = wgrad_out(D, kind, &s.lg[l], dec ? &s.xg[l] : nullptr);
+        t[0] = A; t[1] = B; t[2] = o.p[0]; t[3] = o.p[1]; t[4] = o.p[2];
       };
       // with dropout the GEMMs of a dropped sublayer output read its masked gradient copy
       const bool drop = D.drop > 0.f;
-      put(0, S.a, drop ? W.dmask : ring(n), g.wo_ff, nullptr, nullptr);
-      put(1, S.n2, W.duw, g.wi0, D.mlp == ACT_RELU ? nullptr : g.wi1, nullptr);
-      put(2, S.c, drop ? W.dmask_a : (dec ? W.dh1_lp : W.dh_lp), g.wo, nullptr, nullptr);
-      put(3, S.n1, W.dqkv, g.wq, g.wk, g.wv);
+      put(WG_WO_FF, S.a, drop ? W.dmask : ring(n));
+      put(WG_WI, S.n2, W.duw);
+      put(WG_WO, S.c, drop ? W.dmask_a : (dec ? W.dh1_lp : W.dh_lp));
+      put(WG_QKV, S.n1, W.dqkv);
       if (dec) {
-        const t5_cross_grads& x = s.xg[l];
-        put(4, S.cx, drop ? W.dmask_x : W.dh_lp, x.xo, nullptr, nullptr);
-        put(5, S.nx, W.dqx, x.xq, nullptr, nullptr);
-        put(6, enc_out, W.dkvx, x.xk, x.xv, nullptr);
+        put(WG_XO, S.cx, drop ? W.dmask_x : W.dh_lp);
+        put(WG_XQ, S.nx, W.dqx);
+        put(WG_XKV, enc_out, W.dkvx);
       }
     }
     T5_STEP("wgrad_table", launch_fill_ptrs(tab.data(), kinds * s.L * GEMM_GROUP_PTRS, s.ptr_tab, st));
-    static const char* const names[kWgradKinds] = {"gemm_dwo_ff", "gemm_dwi", "gemm_dwo", "gemm_dwqkv",
+    static const char* const names[WG_KINDS] = {"gemm_dwo_ff", "gemm_dwi", "gemm_dwo", "gemm_dwqkv",
                                                    "gemm_dxo", "gemm_dxq", "gemm_dxkv"};
     for (int kind = 0; kind < kinds; ++kind) {
       const void** t = &tab[(size_t)kind * s.L * GEMM_GROUP_PTRS];
       GemmDesc g = wgrad_desc(D, kind, t[0], t[1]);
       g.groups = s.ptr_tab + (size_t)kind * s.L * GEMM_GROUP_PTRS;
       g.ngroups = s.L;
-      const GemmEpi e = wgrad_epi(D, kind, (float*)t[2], (float*)t[3], (float*)t[4]);
+      const GemmEpi e = wgrad_epi(D, kind, wgrad_out(D, kind, &s.lg[s.L - 1], dec ? &s.xg[s.L - 1] : nullptr));
       if (!gemm_mfma_supported(g, e)) return T5_ERR_UNSUPPORTED;  // checked for the shapes when the plan was made
       T5_STEP(names[kind], launch_gemm_mfma(g, e, st));
     }

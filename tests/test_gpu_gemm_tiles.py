@@ -58,6 +58,27 @@ def test_tile_families_k_contiguous(M, N, K, tile):
     _check_gemm(M, N, K, True)
 
 
+def _wgrad_plan(M, N, K, ngr=1):
+    """Tile and k-slices that wgrad_plan gives a weight gradient (ngr of them in one launch)."""
+    def tiles(b):
+        return -(-M // b) * -(-N // b) * ngr
+    nk, best = K // 64, None
+    for sp in range(1, 33):
+        if sp > 1 and nk // sp < 8:
+            break
+        w256, w128 = tiles(256) * sp, tiles(128) * sp
+        r256, rem = -(-w256 // 256), w128 % 512
+        k256 = 1.45 * r256 * nk / sp
+        atomics = (0.145 if ngr == 1 and r256 >= 4 else 0.193) * w256 if sp > 1 else 8.0
+        c256 = k256 + 5.0 + (max(17.4 * (r256 - 1), atomics - k256 * (r256 - 1) / r256) if ngr > 1 else atomics)
+        rounds = w128 // 512 * 1.75 + (1.75 if rem > 256 else 1.0 if rem else 0.0)
+        c128 = (0.62 if ngr > 1 and w128 > 512 else 0.58) * rounds * nk / sp + (0.048 * w128 if sp > 1 else 0.0) + 3.0
+        for cost, tile in ((c128, 128), (c256, 256)):
+            if best is None or cost < best[0]:
+                best = (cost, tile, sp)
+    return best[1:]
+
+
 @pytest.mark.parametrize("M,N,K", [(768, 768, 8960), (2048, 768, 14592), (1024, 512, 32768), (4096, 2048, 4096), (8, 8, 64)])
 def test_split_plans_m_contiguous(M, N, K):
     _check_gemm(M, N, K, False)
@@ -181,28 +202,54 @@ def test_stored_and_packed_weights_give_the_same_layer(d, heads, dk, f, batch, s
     assert torch.isfinite(y0.float()).all() and torch.equal(y0, y)
 
 
-@pytest.mark.parametrize("d,f,batch,seq", [(768, 2048, 1, 40), (768, 2048, 4, 128), (512, 1024, 9, 333), (2048, 2560, 2, 150),
-                                           (768, 2048, 40, 333)])
-def test_weight_gradients_overwrite_what_the_buffers_hold(d, f, batch, seq):
+def _layer_weights(cfg, gen):
+    """Weights of a layer (with cross-attention where cfg.enc_seq > 0) in bf16, fan-in scaled."""
+    d, i, f = cfg.d_model, cfg.n_heads * cfg.d_kv, cfg.d_ff
+    shapes = dict(ln1_scale=(d,), wq=(d, i), wk=(d, i), wv=(d, i), wo=(i, d), rel_table=(32, cfg.n_heads), ln2_scale=(d,),
+                  wi0=(d, f), wi1=(d, f), wo_ff=(f, d))
+    if cfg.mlp == "relu":
+        del shapes["wi1"]
+    if cfg.enc_seq:
+        shapes.update(lnx_scale=(d,), xq=(d, i), xk=(d, i), xv=(d, i), xo=(i, d))
+    rnd = lambda *n: torch.randn(n, generator=gen, device="cuda").bfloat16()  # noqa: E731
+    return {k: rnd(*n) * (1.0 if len(n) == 1 else n[0] ** -0.5) for k, n in shapes.items()}
+
+
+# (the decoder layers: the encoder's side sliced and the decoder's whole, and the other way round)
+@pytest.mark.parametrize("d,f,batch,seq,enc,mlp,det", [(768, 2048, 1, 40, 0, "geglu_tanh", False), (768, 2048, 4, 128, 0, "geglu_tanh", False),
+                                                       (512, 1024, 9, 333, 0, "geglu_tanh", False), (2048, 2560, 2, 150, 0, "geglu_tanh", False),
+                                                       (768, 2048, 40, 333, 0, "geglu_tanh", False),
+                                                       (512, 1024, 9, 333, 0, "relu", False), (768, 2048, 4, 128, 0, "relu", False),
+                                                       (512, 1024, 4, 50, 1100, "geglu_tanh", False), (512, 1024, 4, 1100, 50, "relu", False),
+                                                       (512, 1024, 9, 333, 0, "geglu_tanh", True), (512, 1024, 4, 50, 1100, "relu", True),
+                                                       (512, 1024, 4, 1100, 50, "geglu_tanh", True)])
+def test_weight_gradients_overwrite_what_the_buffers_hold(d, f, batch, seq, enc, mlp, det):
     """Gradients that one slice stores whole are not cleared first, sliced ones are: either way nothing of what the buffers
     held is left, and with accumulate it stays.  (float32 atomics: sums in another order, 1e-6 of the largest value.)"""
     import paper_2203_17189_amd as P
     from paper_2203_17189_amd import binding as B
-    cfg = SI.BlockConfig("overwrite", 97, batch, seq, d, 4, 64, f, attn_scale=0.125)
-    w, x, dy = make_case(replace(cfg, batch=1, seq=32))
-    dw, _, _ = upload_case(replace(cfg, batch=1, seq=32), w, x, dy)
+    cfg = SI.BlockConfig("overwrite", 97, batch, seq, d, 4, 64, f, attn_scale=0.125, enc_seq=enc, causal=enc > 0, mlp=mlp,
+                         deterministic=det)
+    if enc:  # dXk | dXv against dXq and dXo
+        assert (_wgrad_plan(d, 512, batch * enc)[1] > 1) == (enc > seq) and (_wgrad_plan(d, 256, batch * seq)[1] > 1) == (seq > enc)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(batch)
+    dw = _layer_weights(cfg, gen)
     dx, ddy = [torch.randn((batch, seq, d), generator=gen, device="cuda").bfloat16() for _ in range(2)]
-    _, stash = P.t5_block_fwd(cfg, dx, dw)
+    e = torch.randn((batch, enc, d), generator=gen, device="cuda").bfloat16() if enc else None
+    stash = P.t5_decoder_block_fwd(cfg, dx, e, dw)[1] if enc else P.t5_block_fwd(cfg, dx, dw)[1]
     out = []
     for fill, acc in ((0.0, False), (float("nan"), False), (3.0, True)):
-        g = B.alloc_grads(cfg, dw)
+        g = B.alloc_decoder_grads(cfg, dw) if enc else B.alloc_grads(cfg, dw)
         for v in g.values():
             v.fill_(fill)
-        P.t5_block_bwd(cfg, ddy, dx, dw, stash, grads=g, accumulate=acc)
+        if enc:
+            P.t5_decoder_block_bwd(cfg, ddy, dx, e, dw, stash, grads=g, accumulate=acc)
+        else:
+            P.t5_block_bwd(cfg, ddy, dx, dw, stash, grads=g, accumulate=acc)
         out.append(g)
     for k, v in out[0].items():
+        assert torch.isfinite(v).all(), k
         tol = 4e-6 * float(v.abs().max()) + 4e-6
         assert float((out[1][k] - v).abs().max()) <= tol, k
         assert float((out[2][k] - 3.0 - v).abs().max()) <= tol + 4e-6, k  # (one rounding at 3 more)
