@@ -1,5 +1,5 @@
 """GPU parity of the bf16 MFMA GEMM building block against numpy float64 matmul on the same
-bf16-rounded inputs: both operand orientations, both tile configurations, ragged M/N, split-k."""
+bf16-rounded inputs: both operand orientations, ragged M/N, split-k (the tiles by name: test_gpu_gemm_tiles)."""
 import numpy as np
 import pytest
 import torch

@@ -79,9 +79,65 @@ def _wgrad_plan(M, N, K, ngr=1):
     return best[1:]
 
 
-@pytest.mark.parametrize("M,N,K", [(768, 768, 8960), (2048, 768, 14592), (1024, 512, 32768), (4096, 2048, 4096), (8, 8, 64)])
-def test_split_plans_m_contiguous(M, N, K):
+@pytest.mark.parametrize("M,N,K,tile,slices", [(768, 768, 8960, 128, 7), (2048, 768, 14592, 128, 5), (1024, 512, 32768, 128, 8),
+                                               (4096, 2048, 4096, 128, 1), (8, 8, 64, 128, 1),
+                                               (2048, 768, 65536, 256, 10), (768, 4096, 13312, 256, 5),
+                                               (2056, 760, 65536, 256, 9),   # last tiles of 8 rows and 248 columns
+                                               (5120, 2048, 4416, 256, 1), (5112, 2056, 8960, 256, 1), (2048, 10240, 16384, 256, 3)])
+def test_split_plans_m_contiguous(M, N, K, tile, slices):
+    assert _wgrad_plan(M, N, K) == (tile, slices)
     _check_gemm(M, N, K, False)
+
+
+@pytest.mark.parametrize("batch,seq,slices", [(11, 407, 1), (41, 409, 3)])
+def test_weight_gradients_over_a_ragged_number_of_tokens(batch, seq, slices):
+    """256x256 tiles, sliced and whole, over tokens that are not a multiple of the k-tile: the ungated layer's products
+    from the hidden activations that the layer itself has, in float64."""
+    import paper_2203_17189_amd as P
+    d, f, tokens = 2048, 5120, batch * seq
+    assert tokens % 64 and _wgrad_plan(d, f, tokens) == _wgrad_plan(f, d, tokens) == (256, slices)
+    cfg = SI.BlockConfig("ragged_wgrad", 98, batch, seq, d, 4, 64, f, attn_scale=0.125, mlp="relu")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    w = _layer_weights(cfg, gen)
+    w["wo"].zero_()  # the attention sublayer adds nothing: the feed-forward's input is x's norm
+    x, dy = [torch.randn((batch, seq, d), generator=gen, device="cuda").bfloat16() for _ in range(2)]
+    _, stash = P.t5_block_fwd(cfg, x, w)
+    _, g = P.t5_block_bwd(cfg, dy, x, w, stash)
+    xd = x.view(tokens, d).double()
+    n = (xd * torch.rsqrt(xd.square().mean(1, keepdim=True) + 1e-6) * w["ln2_scale"].double()).bfloat16().double()
+    u = n @ w["wi0"].double()
+    a = u.clamp(min=0).bfloat16().double()
+    du = ((dy.view(tokens, d).double() @ w["wo_ff"].double().t().contiguous()) * (a > 0)).bfloat16().double()
+    want = {"wo_ff": a.t().contiguous() @ dy.view(tokens, d).double(), "wi0": n.t().contiguous() @ du}
+    for k, v in want.items():
+        # single bf16 roundings of a, du and n that fall the other way, units that are zero on one side only
+        assert float((g[k].double() - v).norm() / v.norm()) <= 2e-3, k
+
+
+def test_grouped_weight_gradients_on_256x256_tiles():
+    """Twelve layers in grouped launches (256x256 tiles in two slices and 128x128 whole) against one launch a layer (remat), whose
+    activations are the same bits: float32 sums in another order."""
+    import paper_2203_17189_amd as P
+    from types import SimpleNamespace
+    blk = SI.BlockConfig("grouped", 99, 8, 512, 768, 12, 64, 2048, attn_scale=0.125, causal=True)
+    tokens, layers, vocab = 4096, 12, 512
+    assert [_wgrad_plan(*mn, tokens, layers) for mn in ((2048, 768), (768, 4096), (768, 768), (768, 2304))] == \
+        [(256, 2), (256, 2), (128, 1), (256, 2)]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+    ws = [_layer_weights(blk, gen) for _ in range(layers)]
+    rnd = lambda *n: torch.randn(n, generator=gen, device="cuda").bfloat16()  # noqa: E731
+    w = dict(embedding=rnd(vocab, 768), rel_table=ws[0]["rel_table"], final_scale=rnd(768), logits_w=rnd(768, vocab) * 0.05,
+             layers=[{k: v for k, v in lw.items() if k != "rel_table"} for lw in ws])
+    tok, tgt = [torch.randint(0, vocab, (8, 512), generator=gen, device="cuda", dtype=torch.int32) for _ in range(2)]
+    out = []
+    for remat in (0, 1):
+        c = SimpleNamespace(block=blk, n_layers=layers, vocab=vocab, tied_logits=0, remat=remat, z_loss=0.0)
+        out.append(P.t5_stack_loss_and_grad(c, tok, tgt, w)[1]["layers"])
+    for a, b in zip(*out):
+        for k in ("wq", "wk", "wv", "wo", "wi0", "wi1", "wo_ff"):
+            assert float((a[k] - b[k]).norm() / b[k].norm()) <= 2e-6, k
 
 
 def test_weights_off_16_bytes():
