@@ -29,16 +29,23 @@ def test_256_tiles_every_loop_remainder(nk):
     _check_gemm(8192, 2048, 64 * nk, True)
 
 
-def _tile(M, N, K):
-    """The tile that a plain store of these sizes gets (rounds over the 256 compute units, as launch_layout counts them)."""
+def _tile(M, N, K, resid=False):
+    """The tile that a plain store, or one with residual, of these sizes gets (rounds over the 256 compute units, as
+    launch_layout counts them)."""
     def tiles(bm, bn):
         return -(-M // bm) * -(-N // bn)
     t128 = tiles(128, 128)
     if t128 <= 256:
         return "64x64" if tiles(64, 64) <= 256 else "128x64" if tiles(128, 64) <= 256 else "128x128"
     rem = t128 % 512
-    c128 = ((0.40 if N % 256 else 0.53) if K < 640 else 0.62) * (t128 // 512 + (1.0 if rem > 256 else 1.0 if rem and K >= 1024 else 0.65 if rem else 0.0))
-    return "256x256" if -(-tiles(256, 256) // 256) <= c128 else "128x128, two per unit"
+    w = (0.49 if K <= 768 else 0.56) if resid else (0.40 if N % 256 else 0.53) if K < 640 else 0.62
+    c128 = w * (t128 // 512 + (1.0 if rem > 256 else 1.0 if rem and K >= 1024 else 0.65 if rem else 0.0))
+    c256 = -(-tiles(256, 256) // 256)
+    if N % 192 == 0 and 0.88 * -(-tiles(256, 192) // 256) < min(c256, c128):
+        return "256x192"
+    if resid and K <= 512 and tiles(256, 256) >= 192:
+        return "256x128"
+    return "256x256" if c256 <= c128 else "128x128, two per unit"
 
 
 @pytest.mark.parametrize("M,N,K,tile", [(1332, 768, 768, "64x64"),
@@ -197,16 +204,20 @@ def test_rows_do_not_depend_on_the_last_tile(full, ragged, seq, mlp, rate):
 
 @pytest.mark.parametrize("nk", [10, 11, 12, 13, 14, 15])
 def test_256x192_tiles_every_loop_remainder(nk):
+    assert _tile(14500, 768, 64 * nk) == "256x192"
     _check_gemm(14500, 768, 64 * nk, True)  # 57 x 3 tiles of 256x256 in one round, 57 x 4 of 256x192 too; a last row tile of 164
 
 
 def test_256x192_tiles_with_residual():
-    """A layer of 114 sequences (256x192 tiles in every product of 768 columns) against its two halves (128x128 tiles): the
-    same sums in another order, so what differs are single bf16 roundings: the bar of a result against the exact one."""
+    """A layer of 114 sequences (256x192 tiles in every product of 768 columns: both with residual, the gradients of both
+    norms' outputs) against its two halves (128x128 tiles): the same sums in another order, so what differs are single bf16 roundings:
+    the bar of a result against the exact one."""
     import numpy as np
     import paper_2203_17189_amd as P
     from parity_util import STATED_BF16, rel_err
-    cfg = SI.BlockConfig("tiles_192", 95, 114, 128, 768, 12, 64, 1024, attn_scale=0.125)
+    cfg = SI.BlockConfig("tiles_192", 95, 114, 128, 768, 16, 64, 1024, attn_scale=0.125)
+    for k, resid in ((1024, True), (2048, False), (3072, False)):
+        assert _tile(114 * 128, 768, k, resid) == "256x192" and _tile(57 * 128, 768, k, resid) == "128x128, two per unit"
     w, x, dy = make_case(replace(cfg, batch=2))
     dw, dx, ddy = upload_case(replace(cfg, batch=2), w, x, dy)
     gen = torch.Generator(device="cuda")
@@ -222,6 +233,28 @@ def test_256x192_tiles_with_residual():
     for i in range(2):
         e = rel_err(whole[i], np.concatenate([h[i] for h in halves]))
         assert e[0] <= STATED_BF16[0] and e[1] <= STATED_BF16[1], e
+
+
+@pytest.mark.parametrize("mlp", ["geglu_tanh", "relu"])
+def test_256x192_rows_do_not_depend_on_the_last_tile(mlp):
+    """y and dx of 255 sequences (14535 rows: 199 in the last row tile) are, bit for bit, those of the same sequences among 256
+    (57 full row tiles)."""
+    import paper_2203_17189_amd as P
+    cfg = SI.BlockConfig("last_rows_192", 94, 256, 57, 768, 16, 64, 1024, attn_scale=0.125, mlp=mlp)
+    for b in (255, 256):
+        assert _tile(b * 57, 768, 1024, True) == _tile(b * 57, 768, 3072) == "256x192"
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    dw = _layer_weights(cfg, gen)
+    x, dy = [torch.randn((256, 57, 768), generator=gen, device="cuda").bfloat16() for _ in range(2)]
+    out = []
+    for b in (256, 255):
+        c = replace(cfg, batch=b)
+        y, stash = P.t5_block_fwd(c, x[:b].contiguous(), dw)
+        dx, _ = P.t5_block_bwd(c, dy[:b].contiguous(), x[:b].contiguous(), dw, stash)
+        out.append((y[:255].clone(), dx[:255].clone()))
+    assert torch.isfinite(out[1][0].float()).all()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
 
 @pytest.mark.parametrize("d,heads,dk,f,batch,seq,enc,mlp", [(128, 2, 64, 192, 1, 40, 0, "geglu_tanh"),   # 64x64 tiles
