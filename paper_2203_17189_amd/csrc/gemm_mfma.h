@@ -829,11 +829,15 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
 }
 
 // Tile size and k split of a weight-gradient GEMM (EPI_SPLIT_F32): the cheapest of both tiles with up to 32 slices.  In
-// microseconds: a workgroup's k-tile of 64 takes 0.54 to 0.6 with 128x128 tiles and a compute unit to itself (1.75 times that
-// with two on one) and 1.45 with 256x256, and the float atomics of all slices run at 340 G/s whatever the split, a quarter of
-// them behind the products of four and more rounds; without slices the tiles leave by plain stores.  Model / measured: 768 x 4096 over 8991 tokens 256x256 in five slices 96 / 98, 128x128 unsliced
-// 79 / 82; over 512 tokens 256x256 25 / 43, 128x128 7 / 13; 2048 x 768 over 65536, 256x256 in ten 199 / 198; 512 x 1024 over
-// 32768, 128x128 in eight 50 / 52, in sixteen 58 / 60; 768 x 768 over 8991 in seven 26 / 27.
+// microseconds: a workgroup's k-tile of 64 takes 0.58 with 128x128 tiles and a compute unit to itself (measured 0.54 to 0.60; 1.75 times
+// that with two on one) and 1.45 with 256x256; the float atomics of all slices run at 340 G/s whatever the split; without
+// slices the tiles leave by plain stores.  Model / measured with operands from memory: 768 x 4096 over 8960 tokens 256x256 in five
+// slices 92 / 94, 128x128 unsliced 84 / 80; over 512 tokens 256x256 25 / 21, 128x128 8 / 11; 2048 x 768 over 65536, 256x256 in ten
+// 200 / 200; 512 x 1024 over 32768, 128x128 in eight 52 / 50, in sixteen 60 / 58; 768 x 768 over 8960 in seven 27 / 27.
+// From four rounds of 256x256 tiles on a quarter of the atomics hides behind the products of the rounds that follow.  2048 x 10240 over
+// 16384: in three slices, four rounds, 612, in two 600, 128x128 731, which a full charge would take.  With the quarter off
+// at two and three rounds already, 1024 x 5632 over 13440 would go to five slices (two rounds, 197; two slices in one round 161), 5120 x
+// 2048 over 8960 to three (two rounds, 224; unsliced 167), 2048 x 6144 over 19200 to four (three rounds, 453; unsliced 390).
 // Grouped launches run many rounds: the atomics hide behind the products of the rounds that follow, but for 17 us each, and
 // 128x128 tiles take 0.62 a k-tile (12 x 768 x 4096 over 16384: 1260 us with those, 1080 with 256x256).
 void wgrad_plan(const GemmDesc& g, const GemmEpi& e, int ngr, bool& big, int& split_k) {
@@ -948,7 +952,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
       }
       return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
     }
-    if constexpr (EPI_T == EPI_STORE || EPI_T == EPI_RESID) {  // (with dropout it would spill)
+    if constexpr (EPI_T == EPI_STORE || EPI_T == EPI_RESID) {  // (the dropout copies are not built: 14592 x 768 x 2048 with residual 65 us, 59 like this)
       if (g.N % 192 == 0) {
         const double c192 = 0.88 * (double)(((int64_t)ceil_div(g.M, 256) * (g.N / 192) + 255) / 256);
         if (c192 < c256 && c192 < c128) return launch_cfg<256, 192, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);

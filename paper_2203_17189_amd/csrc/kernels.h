@@ -134,15 +134,16 @@ hipError_t launch_split_reduce(const SplitJobs& jobs, hipStream_t st);
 bool gemm_mfma_supported(const GemmDesc& g, const GemmEpi& e);
 hipError_t launch_gemm_mfma(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 // its epilogue families
-// ... and with the weights as they are stored (a_kc, !b_kc, one segment, nsrc as below), for problems of a few hundred rows
-bool gemm_direct_supported(const GemmDesc& g, const GemmEpi& e);
-hipError_t launch_gemm_direct(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_store(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_resid(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_geglu_fwd(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_geglu_bwd(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_split(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 hipError_t launch_gemm_mfma_split_grouped(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
+// The forward products with the weights as they are stored (a_kc, !b_kc, one segment, columns of nsrc matrices), for problems of a
+// few hundred rows.
+bool gemm_direct_supported(const GemmDesc& g, const GemmEpi& e);
+hipError_t launch_gemm_direct(const GemmDesc& g, const GemmEpi& e, hipStream_t st);
 // k-slices of a weight gradient (EPI_SPLIT_F32) on that kernel; one slice without accumulate needs no cleared output.
 int gemm_wgrad_slices(const GemmDesc& g, const GemmEpi& e);
 // Bytes of the partial-sum buffer (GemmEpi::aux0) that launch_gemm_mfma would use for this EPI_SPLIT_F32 problem (0: no split).
