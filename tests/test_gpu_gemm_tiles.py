@@ -78,7 +78,7 @@ def _wgrad_plan(M, N, K, ngr=1):
         k256 = 1.45 * r256 * nk / sp
         atomics = (0.145 if ngr == 1 and r256 >= 4 else 0.193) * w256 if sp > 1 else 8.0
         c256 = k256 + 5.0 + (max(17.4 * (r256 - 1), atomics - k256 * (r256 - 1) / r256) if ngr > 1 else atomics)
-        rounds = w128 // 512 * 1.75 + (1.75 if rem > 256 else 1.0 if rem else 0.0)
+        rounds = w128 // 512 * 1.75 + ((1.6 if ngr == 1 and sp > 1 else 1.75) if rem > 256 else 1.0 if rem else 0.0)
         c128 = (0.62 if ngr > 1 and w128 > 512 else 0.58) * rounds * nk / sp + (0.048 * w128 if sp > 1 else 0.0) + 3.0
         for cost, tile in ((c128, 128), (c256, 256)):
             if best is None or cost < best[0]:
