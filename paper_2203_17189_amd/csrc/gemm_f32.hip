@@ -544,7 +544,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_f32x3_kernel(GemmDesc g,
       const int q = tid + i * NT;
       const int r = A_KC ? q / (BK / 4) : tid % BM, k = A_KC ? (q % (BK / 4)) * 4 : (wka + i * (NT / BM)) * 4;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) ra[i][x] *= k + x < left ? kUp : 0.f;
+      for (int x = 0; x < 4; ++x) ra[i][x] *= k + (A_KC ? 0 : x) < left ? kUp : 0.f;  // (k-contiguous: k % 4 == 0)
       const Split3 s = split3(ra[i]);
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(st + p * A_PL + r * LD + k * 2) = s.p[p];
