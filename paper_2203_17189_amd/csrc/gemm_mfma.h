@@ -830,11 +830,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
 
 // Tile size and k split of a weight-gradient GEMM (EPI_SPLIT_F32): the cheapest of both tiles with up to 32 slices.  In
 // microseconds: a workgroup's k-tile of 64 takes 0.58 with 128x128 tiles and a compute unit to itself (measured 0.54 to 0.62; 1.75 times
-// that with two on every unit, 1.6 with two slices' tiles on some) and 1.45 with 256x256; the float atomics of all slices run
+// that with two on every unit, 1.65 with two slices' tiles on up to 224 of them) and 1.45 with 256x256; the float atomics of all slices run
 // at 340 G/s whatever the split; without slices the tiles leave by plain stores.  Model / measured with operands from
 // memory: 768 x 4096 over 8960 tokens 256x256 in five slices 92 / 94, 128x128 unsliced 84 / 80; over 512 tokens 256x256 25 / 21, 128x128
-// 8 / 11; 768 x 2304 over 20480, 128x128 in four (432 workgroups) 98 / 90, 256x256 in nine 104 / 103; 2048 x 768 over 28672, 128x128 in five
-// 109 / 102, 256x256 in ten 116 / 116; over 65536, 256x256 in ten 200 / 200; 512 x 1024 over 32768, 128x128 in eight 52 / 50, in sixteen
+// 8 / 11; 768 x 2304 over 20480, 128x128 in four (432 workgroups) 100 / 90, 256x256 in nine 104 / 103; 2048 x 768 over 28672, 128x128 in five
+// 112 / 102, 256x256 in ten 116 / 116; over 65536, 256x256 in ten 200 / 200; 512 x 1024 over 32768, 128x128 in eight 52 / 50, in sixteen
 // 60 / 58; 768 x 768 over 8960 in seven 27 / 27.  256x256 tiles that leave a quarter of the units idle take 1.2 a k-tile in short
 // runs, but not under the power limit of long ones: charged so, a layer of d 1024 over 32768 tokens went from 3.1 to 3.2 ms.
 // From four rounds of 256x256 tiles on a quarter of the atomics hides behind the products of the rounds that follow.  2048 x 10240 over
@@ -857,7 +857,7 @@ void wgrad_plan(const GemmDesc& g, const GemmEpi& e, int ngr, bool& big, int& sp
     const double r256 = (double)((w256 + 255) / 256);
     const double k256 = 1.45 * r256 * nk / sp, atomics = sp > 1 ? (ngr <= 1 && r256 >= 4.0 ? 0.145 : 0.193) * (double)w256 : 8.0;
     const double c256 = k256 + 5.0 + (ngr > 1 ? std::max(17.4 * (r256 - 1.0), atomics - k256 * (r256 - 1.0) / r256) : atomics);
-    const double rounds = (double)(w128 / 512) * 1.75 + (rem > 256 ? (ngr <= 1 && sp > 1 ? 1.6 : 1.75) : rem > 0 ? 1.0 : 0.0);
+    const double rounds = (double)(w128 / 512) * 1.75 + (rem > 256 ? (ngr <= 1 && sp > 1 && rem <= 480 ? 1.65 : 1.75) : rem > 0 ? 1.0 : 0.0);
     const double c128 = (ngr > 1 && w128 > 512 ? 0.62 : 0.58) * rounds * nk / sp + (sp > 1 ? 0.048 * (double)w128 : 0.0) + 3.0;
     if (best < 0.0 || c128 < best) { best = c128; big = false; split_k = sp; }
     if (c256 < best) { best = c256; big = true; split_k = sp; }

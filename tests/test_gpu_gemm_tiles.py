@@ -78,7 +78,7 @@ def _wgrad_plan(M, N, K, ngr=1):
         k256 = 1.45 * r256 * nk / sp
         atomics = (0.145 if ngr == 1 and r256 >= 4 else 0.193) * w256 if sp > 1 else 8.0
         c256 = k256 + 5.0 + (max(17.4 * (r256 - 1), atomics - k256 * (r256 - 1) / r256) if ngr > 1 else atomics)
-        rounds = w128 // 512 * 1.75 + ((1.6 if ngr == 1 and sp > 1 else 1.75) if rem > 256 else 1.0 if rem else 0.0)
+        rounds = w128 // 512 * 1.75 + ((1.65 if ngr == 1 and sp > 1 and rem <= 480 else 1.75) if rem > 256 else 1.0 if rem else 0.0)
         c128 = (0.62 if ngr > 1 and w128 > 512 else 0.58) * rounds * nk / sp + (0.048 * w128 if sp > 1 else 0.0) + 3.0
         for cost, tile in ((c128, 128), (c256, 256)):
             if best is None or cost < best[0]:
@@ -87,7 +87,7 @@ def _wgrad_plan(M, N, K, ngr=1):
 
 
 @pytest.mark.parametrize("M,N,K,tile,slices", [(768, 768, 8960, 128, 7), (2048, 768, 14592, 128, 5), (1024, 512, 32768, 128, 8),
-                                               (4096, 2048, 4096, 128, 1), (8, 8, 64, 128, 1),
+                                               (4096, 2048, 4096, 128, 1), (8, 8, 64, 128, 1), (768, 2304, 20480, 128, 4),
                                                (2048, 768, 65536, 256, 10), (768, 4096, 13312, 256, 5),
                                                (2056, 760, 65536, 256, 9),   # last tiles of 8 rows and 248 columns
                                                (5120, 2048, 4416, 256, 1), (5112, 2056, 8960, 256, 1), (2048, 10240, 16384, 256, 3)])
