@@ -134,7 +134,8 @@ __global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_fwd_diag_kernel(const
 // Backward.  Each wave walks rows; lane keeps float32 partial sums of dg for its columns
 // (NV vectors of VEC columns); the workgroup's four waves are combined through LDS and written to
 // dg_partial[blockIdx.x][d]; rmsnorm_dg_reduce_kernel sums the partial rows in a fixed order.
-template <typename TX, typename TG, typename TR, typename TL, int VEC, int NV>
+// EARLY: the residual's row is requested before the row's sum too.
+template <typename TX, typename TG, typename TR, typename TL, int VEC, int NV, bool EARLY>
 __global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_bwd_kernel(
     const TX* __restrict__ x, const TG* __restrict__ g, const float* __restrict__ r,
     const float* __restrict__ dn, const TR* __restrict__ resid, float* __restrict__ out_f32,
@@ -156,9 +157,6 @@ __global__ __launch_bounds__(kNormWaves * 64) void rmsnorm_bwd_kernel(
     float dot = 0.f;
     // x * r and dn * g of the row stay in registers for the second pass: x and dn are read once
     float xh[NV][VEC], dgn[NV][VEC];
-    // so does the residual's row: requested behind the sum it is one more round trip to memory (d 2048, 32768 rows: 394 -> 354 us both;
-    // narrower rows are 2 % slower that way, wider ones have no registers)
-    constexpr bool EARLY = NV == 4;
     float re[EARLY ? NV : 1][VEC];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
@@ -288,11 +286,11 @@ hipError_t fwd_dispatch(const void* x, const void* g, void* n, float* r, int T, 
   return hipGetLastError();
 }
 
-template <typename TX, typename TG, typename TR, typename TL, int VEC, int NV>
+template <typename TX, typename TG, typename TR, typename TL, int VEC, int NV, bool EARLY = false>
 hipError_t bwd_launch(const void* x, const void* g, const float* r, const float* dn, const void* resid,
                       float* out_f32, void* out_lp, float* dg_partial, int T, int d, int grid,
                       hipStream_t st) {
-  rmsnorm_bwd_kernel<TX, TG, TR, TL, VEC, NV><<<grid, kNormWaves * 64, sizeof(float) * kNormWaves * d, st>>>(
+  rmsnorm_bwd_kernel<TX, TG, TR, TL, VEC, NV, EARLY><<<grid, kNormWaves * 64, sizeof(float) * kNormWaves * d, st>>>(
       (const TX*)x, (const TG*)g, r, dn, (const TR*)resid, out_f32, (TL*)out_lp, dg_partial, T, d);
   return hipGetLastError();
 }
@@ -307,6 +305,11 @@ hipError_t bwd_dispatch(const void* x, const void* g, const float* r, const floa
     const int nv = ceil_div(d, 512);
     if (nv <= 1) T5MI_BWD(8, 1);
     if (nv <= 2) T5MI_BWD(8, 2);
+    // Requested behind the row's sum, the residual's row is one more round trip to memory; requested early it takes registers that
+    // a third workgroup on a compute unit would have.  Early pays where even three on each are more than one round (d 2048, both norms
+    // of a layer: 13000 rows 184 -> 166 us, 32000 387 -> 350; 9000, 563 workgroups, 115 -> 146; 4000 63 -> 65).  Narrower rows are
+    // 2 % slower that way, wider ones have no registers.
+    if (nv <= 4 && nv > 2 && grid > 768) return bwd_launch<TX, TG, TR, TL, 8, 4, true>(x, g, r, dn, resid, out_f32, out_lp, dg_partial, T, d, grid, st);
     if (nv <= 4) T5MI_BWD(8, 4);
     if (nv <= 8) T5MI_BWD(8, 8);
     if (nv <= 16) T5MI_BWD(8, 16);

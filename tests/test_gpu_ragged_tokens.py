@@ -64,3 +64,38 @@ def test_backward_stays_inside_its_workspace(batch, seq, deterministic):
     buf = torch.full((n + (4 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
     P.t5_block_bwd(cfg, ddy, dx, dw, stash, workspace=buf[:n])
     assert bool((buf[n:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_norm_backward_does_not_depend_on_when_the_residual_is_read(dtype):
+    """1025 to 2048 columns: from 12289 rows on the backward of the norms requests the residual's row early.  dx of 12304 rows
+    is that of the same sequences in two smaller batches (bf16: bit for bit, the general-shape kernels form a row's products
+    by themselves; float32 products go by the number of rows), and the scale gradients are the sums of theirs."""
+    import torch
+    import paper_2203_17189_amd as P
+    cfg = SI.BlockConfig("norm_rows", 93, 769, 16, 1032, 1, 8, 24, dtype=dtype, attn_scale=0.25)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *n: torch.randn(n, generator=gen, device="cuda")  # noqa: E731
+    d, i, f = 1032, 8, 24
+    w = dict(ln1_scale=1 + 0.1 * rnd(d), wq=rnd(d, i) / 90, wk=rnd(d, i) / 32, wv=rnd(d, i) / 32, wo=rnd(i, d) / 3, rel_table=rnd(32, 1),
+             ln2_scale=1 + 0.1 * rnd(d), wi0=rnd(d, f) / 32, wi1=rnd(d, f) / 32, wo_ff=rnd(f, d) / 5)
+    w = {k: v.to(dt) for k, v in w.items()}
+    x, dy = [rnd(769, 16, d).to(dt) for _ in range(2)]
+
+    def run(a, b):
+        from dataclasses import replace
+        c = replace(cfg, batch=b - a)
+        xs, dys = x[a:b].contiguous(), dy[a:b].contiguous()
+        _, stash = P.t5_block_fwd(c, xs, w)
+        dx, g = P.t5_block_bwd(c, dys, xs, w, stash)
+        return dx, g["ln1_scale"].double(), g["ln2_scale"].double()
+    whole, parts = run(0, 769), [run(0, 400), run(400, 769)]
+    assert torch.isfinite(whole[0].float()).all()
+    both = torch.cat([p[0] for p in parts])
+    assert torch.equal(whole[0], both) or dtype == "f32" and float((whole[0] - both).norm() / both.norm()) <= 2e-6
+    for k in (1, 2):
+        want = parts[0][k] + parts[1][k]
+        # float32 sums of 12304 rows in another order
+        assert float((whole[k] - want).abs().max()) <= 1e-5 * float(want.abs().max()) + 1e-6
