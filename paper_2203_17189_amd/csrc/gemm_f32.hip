@@ -69,8 +69,8 @@ __device__ __forceinline__ f32x4 ld4(const float* base, size_t off, int nv) {
   }
 }
 
-// Epilogue of a wavefront's MI x NI tiles from (mw, nw) on: register r of a 32x32 tile is row (r/4)*8 + half*4 + r%4, column lane%32: a wavefront writes
-// 128-byte runs of two rows.  Operands of the epilogue are fetched for a whole row of tiles before the first store:
+// Epilogue of a wavefront's MI x NI tiles from (mw, nw) on: register r of a 32x32 tile is row (r/4)*8 + half*4 + r%4,
+// column lane%32: a wavefront writes 128-byte runs of two rows.  Operands of the epilogue are fetched for a whole row of tiles before the first store:
 // the compiler cannot move a load across a store that might alias it, and one at a time each costs a round trip
 // (the gated-GELU backward at 64 tokens: 23 us, most of it here).
 template <bool FULL, int MI, int NI, int EPI>
@@ -714,12 +714,13 @@ hipError_t launch_x3(const GemmDesc& g, const GemmEpi& e, int split_k, hipStream
 // launch is read for the first time as often as not, so: every wavefront takes its own batches of 32 k straight into registers
 // in the order of the instruction's operands, the next batch on its way (no staging, no barrier), the operands of the
 // epilogue are requested before the products, the wavefronts' sums meet in LDS once, in pairs, and all of them
-// share the epilogue.  A wavefront keeps the two halves of its batches apart, so that no more than 16 k of a batch follow one
-// another in a sum: with one accumulator the weight gradients over 64 tokens had 2.5e-7 of error, now 2.2e-7.  (The kernel it replaced staged through LDS and left the epilogue, a branch an element, to one of
+// share the epilogue.  (The kernel it replaced staged through LDS and left the epilogue, a branch an element, to one of
 // four wavefronts.)  Layer of d 64, 64 tokens: its 12 products 132 -> 86 us, 140 -> 104 us in all; dn2 of d 768, 200 tokens
 // (k 4096) 66 -> 42 us.  Eight wavefronts from 128 k on: with fewer k some of them would have nothing to do.
-// One workgroup has a compute unit, hence two wavefronts a SIMD: left to aim at four, the compiler holds back the loads (200 x 768 x 2048
-// with residual 26 us, 22 like this).
+// A wavefront keeps the two halves of its batches apart, so that no more than 16 k of a batch follow one another in a sum:
+// with one accumulator the weight gradients over 64 tokens had 2.5e-7 of error, now 2.2e-7.
+// One workgroup has a compute unit, hence two wavefronts a SIMD: left to aim at four, the compiler holds back the loads
+// (200 x 768 x 2048 with residual 26 us, 22 like this).
 template <int WK, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(WK * 64) __attribute__((amdgpu_waves_per_eu(WK / 4, 2))) void gemm_f32_small_kernel(GemmDesc g, GemmEpi e) {
   constexpr bool GF = EPI == EPI_GEGLU_FWD;
@@ -993,8 +994,8 @@ hipError_t launch_kind(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
   //   128x128, 4000 tokens: qkv of d 512 (288 tiles) 62 / 57, dn2 of d 768 (192) 247 / 201, wi of d 768 (1024) 231 / 187;
   //            with 128 tiles (4000 x 512 x 2048) 85 / 104, but 80 on 64x64 ones;
   //   64x64:   1024 x 512 x 2048 (128 tiles) 57 / 46, 200 x 2048 x 768 (128) 27 / 23; with n-contiguous weights no faster
-  //            (800 x 768 x 2048 61 / 61, 1200 x 2304 x 768 54 / 60) nor over few tokens (gradient of 768 x 4096 over 200 32 / 35, over 400 42 / 52): their
-  //            sums lose half as much.
+  //            (800 x 768 x 2048 61 / 61, 1200 x 2304 x 768 54 / 60) nor over few tokens (gradient of 768 x 4096 over 200
+  //            32 / 35, over 400 42 / 52): their sums lose half as much.
   // The gated inputs need 64 columns a wavefront, which 64x64 tiles of four do not have.  32x32 tiles with the
   // reduction over the wavefronts where even the 64x64 ones leave half the chip idle.  From 64 of those on the 32x32 ones are two
   // rounds of workgroups: products with k-contiguous weights (gradients of the norms' outputs) take 32x64 tiles instead, one

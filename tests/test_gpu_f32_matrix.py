@@ -194,8 +194,8 @@ def test_split_products_of_an_infinite_weight(d, value):
     assert rel_err(y1[:, keep], y0[:, keep])[0] <= TOL_F32[0]
 
 
-# As SPLIT_CASES, at lengths that put several sequences into every tile of rows: (the ungated form's products are one
-# matrix wide, one segment), 64 x 64 and 128 x 128 tiles, weight gradients whole and in slices that start inside k
+# As SPLIT_CASES, at lengths that put several sequences into every tile of rows: 64 x 64 and 128 x 128 tiles, one and several segments
+# and matrices side by side, weight gradients whole and in slices that start inside k
 MIXED_CASES = [replace(C, batch=208, seq=20, d_model=132, n_heads=3, d_kv=20, d_ff=260, mlp="relu", name="f32_mixed"),
                replace(C, batch=208, seq=20, d_model=388, n_heads=6, d_kv=52, d_ff=772, causal=True, name="f32_mixed"),
                replace(C, batch=20, seq=20, d_model=516, n_heads=9, d_kv=64, d_ff=1536, name="f32_mixed")]
@@ -228,7 +228,8 @@ def test_small_gradients_beside_ordinary_ones(cfg, power):
 @pytest.mark.parametrize("cfg", MIXED_CASES, ids=MIXED_IDS)
 def test_weights_of_mixed_magnitude(cfg):
     """Channels of q, v and hidden units times 2^114 or 2^-114, undone by k, wo and wo_ff: y and dx are those of the plain
-    weights, every gradient that of its weight over the factor."""
+    weights, every gradient that of its weight over the factor.  (Split products form results with operands from 2^112 or sums from
+    2^96 on again: in every kind of product of a layer, beside results that they do not.)"""
     w, x, dy = make_case(cfg)
     y, saved = O.block_fwd(cfg, x, w)
     dx, g = O.block_bwd(cfg, dy, w, saved)
