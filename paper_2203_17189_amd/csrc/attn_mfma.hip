@@ -20,8 +20,10 @@
 // fetched from the last valid row, keys past the end are masked like causal ones, and queries past the end
 // are neither stored nor counted in the bias gradient.
 //
-// The bias is Toeplitz: bias[h,i,j] = diag[h][j - i + S - 1].  Each workgroup stages the slice of
-// the per-head diagonal vector it can touch (S + tile - 1 floats) in LDS.
+// The bias is Toeplitz: bias[h,i,j] = diag[h][j - i + S - 1], and constant from the first distance of the last bucket
+// on.  Each workgroup stages the diagonals up to there in LDS (BiasWin), or, where that window would be long, the
+// slice of the per-head diagonal vector it can touch (S + tile - 1 floats).
+#include <type_traits>
 #include "kernels.h"
 
 namespace t5mi {
@@ -201,6 +203,49 @@ __device__ __forceinline__ void fill_bias_slice(float* dg, const float* __restri
   }
 }
 
+// Window of diagonals (WIN).  A 32x32 sub-tile of scores whose first key lies m after its first query (m a multiple of
+// 32) touches the diagonals m - 31 .. m + 31; from |m| = M on they all have the bias of the last bucket, so m is clamped
+// to [-M, M] and a window of 2M + 63 values serves any length.  Causal: the diagonals of later keys hold -infinity, which
+// is the mask, and m = 32 stands for all sub-tiles that are masked whole.  The window is held four times, copy c shifted
+// by c values: whatever the lane's diagonal modulo 4, the bias of four neighbouring diagonals is then one aligned 16-byte
+// read.  (An LDS instruction takes the same 4-5 cycles for 4 and for 16 bytes a lane; read one by one the bias values were
+// half of the forward's LDS instructions, a third of the others'.)  The copies are 16 banks apart, so that 16 neighbouring
+// lanes (4 copies x 4 positions) meet no bank twice.
+// Against the slice of S + 127 diagonals with mask instructions, us: dq 16 x 2048 causal, 16 heads of 128 channels 911 -> 622
+// (80 instead of 84 KB: two workgroups on a compute unit), 1 x 4096, 32 heads of 64 channels 285 -> 256; causal forward
+// 32 x 512, 12 heads 46 -> 40, 8 x 2048 111 -> 98 (no mask to compute: 126 registers instead of 167); the others 1-3 %.
+struct BiasWin {
+  int M, top, stride;  // top: largest m that is told apart
+  __host__ __device__ BiasWin(int S, int far, bool causal) {
+    M = ((far < S ? far : S) + 31 + 31) / 32 * 32;
+    top = causal ? 32 : M;
+    stride = (M + top + 63 - 16 + 63) / 64 * 64 + 16;
+  }
+  __host__ __device__ int floats() const { return 4 * stride; }
+  // offset in a copy that belongs to a sub-tile
+  __device__ __forceinline__ int at(int m) const { return (m < -M ? -M : m > top ? top : m) + M; }
+  // 256 threads; in log2 units
+  template <bool CAUSAL>
+  __device__ __forceinline__ void fill(float* win, const float* __restrict__ diag_h, int S, int tid) const {
+    for (int t = tid; t < M + top + 63; t += 256) {
+      const int delta = t - M - 31;
+      int idx = delta + S - 1;
+      idx = idx < 0 ? 0 : idx > 2 * S - 2 ? 2 * S - 2 : idx;  // (past the ends: masked, or constant)
+      const float v = CAUSAL && delta > 0 ? -INFINITY : diag_h[idx] * kLog2e;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (t >= c) win[c * stride + t - c] = v;
+    }
+  }
+  // a lane's base: the diagonals u .. u + 3 of the window of a sub-tile are the four values from lane(win, u) + at(m) on
+  __device__ __forceinline__ const float* lane(const float* win, int u) const { return win + (u & 3) * stride + (u & ~3); }
+};
+// The window is used while its copies stay under 10 KB (two thirds of a K tile with 128 channels): distances up to 225,
+// causal 449, or as many positions.
+inline bool attn_bias_window(const AttnDims& a) {
+  return a.bias && BiasWin(a.S, a.far, a.causal != 0).floats() * sizeof(float) <= 10240;
+}
+
 // Registers R.. of a 32x32 ds sub-tile (S^T layout), each rotated across the 32 lanes of its half by
 // its key offset, summed into `tot`; `lo` gets the part whose source query did not wrap around
 // (lp = 31 - query index of the receiving lane).  The rotation amount must be an immediate.
@@ -256,14 +301,14 @@ __device__ __forceinline__ float max_across_halves(float x) {
 // ------------------------------------------------------------------------------------------------
 // Forward.  grid (ceil(S/128), H, B), 256 threads; wave w owns queries i0 + 32w + lane%32.
 // ------------------------------------------------------------------------------------------------
-template <int DK, bool CAUSAL, bool BIAS, bool DROP>
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
 __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const float* __restrict__ diag,
                                                             bf16* __restrict__ c, float* __restrict__ lse,
                                                             AttnDims a) {
   constexpr int BR = 128, BC = 64, KS = DK / 16, CT = DK / 32;
   constexpr int TILE = BC * DK * 2, STG = 2 * TILE;  // a stage holds a K tile then a V tile
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  float* dg = reinterpret_cast<float*>(smem + 2 * STG);  // [S + BR - 1], log2 units (BIAS only)
+  float* dg = reinterpret_cast<float*>(smem + 2 * STG);  // window, or [S + BR - 1], log2 units (BIAS only)
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -289,13 +334,18 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(qf[kk]));
   }
-  if constexpr (BIAS) {
+  const BiasWin win(S, a.far, CAUSAL);
+  if constexpr (WIN) {
+    win.fill<CAUSAL>(dg, diag + (size_t)h * (2 * S - 1), S, tid);
+  } else if constexpr (BIAS) {
     const float* dgh = diag + (size_t)h * (2 * S - 1);
     fill_bias_slice(dg, dgh, S + BR - 1, tid, [&](int t) {
       const int idx = t - (i0 + BR - 1) + (S - 1);  // delta + S - 1
       return idx < 0 ? 0 : idx;                     // only reachable by clamped (unused) queries
     });
   }
+  const int i_w0 = i0 + wave * 32;                               // first query of this wave
+  const float* dgw = win.lane(dg, 31 - (lane & 31) + (g << 2));  // (WIN)
   const float sc = a.scale * kLog2e;
   const int dg_base = BR - 1 - i_loc;  // dg[dg_base + j] = bias(j - i)
   uint32_t k1 = 0;  // dropout row key of this lane's query
@@ -357,7 +407,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
     float mx = -INFINITY;
     // only tiles that reach above the diagonal of this wave's queries pay for the mask (wave-uniform)
     // (and the tile that reaches past the last key)
-    const bool on_diag = (CAUSAL && j0 + BC - 1 > i0 + wave * 32) || j0 + BC > Sk;
+    // (causal with the window: the mask is in the bias, and a key past the end comes after every query)
+    const bool on_diag = CAUSAL && WIN ? false : (CAUSAL && j0 + BC - 1 > i_w0) || j0 + BC > Sk;
+    const float* dgt[BC / 32];
+#pragma unroll
+    for (int kt = 0; kt < BC / 32; ++kt) dgt[kt] = dgw + win.at(j0 + kt * 32 - i_w0);
     if (on_diag) {
 #pragma unroll
       for (int kt = 0; kt < BC / 32; ++kt)
@@ -366,7 +420,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
           const int j = j0 + kt * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
           // (a masked key's bias slot may lie outside the slice: clamp the index, the value is discarded)
           const int jb = j < Sk ? j : Sk - 1;
-          float s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + jb]) : sT[kt][r] * sc;
+          float s;
+          if constexpr (WIN) s = fmaf(sT[kt][r], sc, (*reinterpret_cast<const f32x4*>(dgt[kt] + ((r >> 2) << 3)))[r & 3]);
+          else s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + jb]) : sT[kt][r] * sc;
           if ((CAUSAL && j > i) || j >= Sk) s = -INFINITY;
           sT[kt][r] = s;
           mx = fmaxf(mx, s);
@@ -377,7 +433,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int j = j0 + kt * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-          const float s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + j]) : sT[kt][r] * sc;
+          float s;
+          if constexpr (WIN) s = fmaf(sT[kt][r], sc, (*reinterpret_cast<const f32x4*>(dgt[kt] + ((r >> 2) << 3)))[r & 3]);
+          else s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + j]) : sT[kt][r] * sc;
           sT[kt][r] = s;
           mx = fmaxf(mx, s);
         }
@@ -448,7 +506,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
 // every offset lies in the saturated last bucket (|delta| >= far) skip all that and add into one
 // scalar per lane; it is credited to the outermost diagonal, which is in the same bucket.
 // ------------------------------------------------------------------------------------------------
-template <int DK, bool CAUSAL, bool BIAS, bool DROP>
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
 __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mfma_kernel(AttnIO io,
                                                                const bf16* __restrict__ o,
                                                                const bf16* __restrict__ dout,
@@ -457,16 +515,18 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
                                                                float* __restrict__ dvec,
                                                                float* __restrict__ ddiag,
                                                                float* __restrict__ ddiag_part,
-                                                               AttnDims a, int far) {
+                                                               AttnDims a) {
   constexpr int BR = 128, BC = 64, KS = DK / 16, CT = DK / 32;
   constexpr int TILE = BC * DK * 2, STG = 2 * TILE;  // a stage holds a K tile then a V tile
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  float* dg = reinterpret_cast<float*>(smem + 2 * STG);  // [S + BR - 1] bias, log2 units
+  const int far = a.far;
+  const BiasWin win(a.S, far, CAUSAL);
+  float* dg = reinterpret_cast<float*>(smem + 2 * STG);  // bias, log2 units: window, or [S + BR - 1]
   // Diagonal windows [4 waves][2 lane halves][W].  A sub-tile at key offset j0s - i_w0 = 32 m from
   // the wave's queries is resolved per diagonal for |m| <= nb; its slot u (0..62) lives at
   // (m + nb) * 32 + u, which is diagonal delta = 32 m + u - 31 (+ 4 for the upper lane half).
   const int nb = BIAS ? attn_dq_window_blocks(a.S, far) : 0, W = 32 * (2 * nb + 2);
-  float* ddg_all = dg + (a.S + BR - 1);
+  float* ddg_all = dg + (WIN ? win.floats() : a.S + BR - 1);
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -523,12 +583,16 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
   };
   if constexpr (BIAS) {
     const float* dgh = diag + (size_t)h * (2 * S - 1);
-    fill_bias_slice(dg, dgh, S + BR - 1, tid, [&](int t) {
-      const int idx = t - (i0 + BR - 1) + (S - 1);  // delta + S - 1
-      return idx < 0 ? 0 : idx;                     // only reachable by queries past the end
-    });
+    if constexpr (WIN)
+      win.fill<CAUSAL>(dg, dgh, S, tid);
+    else
+      fill_bias_slice(dg, dgh, S + BR - 1, tid, [&](int t) {
+        const int idx = t - (i0 + BR - 1) + (S - 1);  // delta + S - 1
+        return idx < 0 ? 0 : idx;                     // only reachable by queries past the end
+      });
     for (int t = tid; t < 8 * W; t += 256) ddg_all[t] = 0.f;
   }
+  const float* dgw = win.lane(dg, 31 - i_lw + (g << 2));  // (WIN)
   const float sc = a.scale * kLog2e;
   const int dg_base = BR - 1 - i_loc;
   float far_neg = 0.f, far_pos = 0.f;
@@ -568,7 +632,16 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
       // MFMA operands as well, or seeding the accumulators with -lse and -dvec, costs more registers
       // than the third wave per SIMD they displace is worth (measured).
       float bias[16];
-      if constexpr (BIAS) {
+      if constexpr (WIN) {
+        const float* bp = dgw + win.at(j0s - i_w0);
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          const f32x4 b4 = *reinterpret_cast<const f32x4*>(bp + rq * 8);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bias[rq * 4 + e] = b4[e];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      } else if constexpr (BIAS) {
         if (j0s + 32 <= Sk) {
           // every key of the sub-tile exists: one address per lane and sixteen constant offsets (with the
           // clamp below each value costs four address instructions, a third of the kernel's vector work)
@@ -605,7 +678,7 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
       // (all wave-uniform)
       uint32_t kx = 0;
       if constexpr (DROP) kx = k1 ^ (uint32_t)(j0s | (g << 2));
-      if ((CAUSAL && j0s + 31 > i_w0) || j0s + 32 > Sk || i_w0 + 32 > S) {
+      if ((CAUSAL && !WIN && j0s + 31 > i_w0) || j0s + 32 > Sk || i_w0 + 32 > S) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int j = j0s + ((r >> 2) << 3) + (g << 2) + (r & 3);
@@ -753,30 +826,23 @@ __global__ __launch_bounds__(256) void attn_ddiag_reduce_kernel(const float* __r
 // ------------------------------------------------------------------------------------------------
 // dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
 // ------------------------------------------------------------------------------------------------
-// With 64 channels two workgroups share a compute unit and the bias values are requested ahead.  THREE: the bias-free form
-// without dropout has registers for a third (164), see bwd_launch.
-template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool THREE>
+// Two forms.  This one takes a tile at a time from two stages: without the causal mask (64 channels), where two or three
+// waves per SIMD cover for each other, and with dropout, whose masks take the registers.
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool THREE, bool WIN>
 __global__ __launch_bounds__(256, DK == 64 ? (THREE ? 3 : 2) : 1)
 void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
                               const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
   constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
   constexpr int TILE = BQ * DK * 2, STG = 2 * TILE;  // a stage holds a Q tile then a dO tile
-  // How the queries past the end of a ragged last tile come to probability zero: by a masked copy of the element loop,
-  // or from the accumulator seeds.  Without the copy (and its branch) an iteration is one block that the compiler
-  // schedules whole.  Causal, 64 channels: 8 x 2048 tokens, 12 heads 181 -> 156 us, 1 x 1024 35 -> 29, 32 x 512 65 -> 62
-  // (three waves per SIMD without bias values ahead: 190, 44, 66); 128 channels, 16 x 2048 971 -> 960.  The non-causal
-  // 64-channel form with bias keeps it: without it 32 x 1024 tokens with 32 heads gain (630 -> 602 us) but 128 x 512 with
-  // 12 heads lose (361 -> 371 us).  The bias-free form has both, see bwd_launch.
-  constexpr bool TAIL_MASK = DK == 64 && !CAUSAL && (BIAS || (!DROP && !THREE));
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // The score and dP accumulators start from -lse/scale and -dvec, so that the MFMA results are
   // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
   float* lse_all = reinterpret_cast<float*>(smem + 2 * STG);  // [2 stages][BQ]  -lse / scale
   float* dv_all = lse_all + 2 * BQ;                           // [2 stages][BQ]  -dvec
   uint32_t* key_all = reinterpret_cast<uint32_t*>(dv_all + 2 * BQ);  // [2 stages][BQ] dropout row keys (DROP only)
-  // [-BQ, S + BCK - 1) log2 units (BIAS only); the BQ entries in front are only ever read for queries past the
-  // end of a ragged last tile, whose probabilities are set to zero
-  float* dg = dv_all + 2 * BQ + (DROP ? 2 * BQ : 0) + BQ;
+  // Window, or [-BQ, S + BCK - 1), log2 units (BIAS only); the slice's BQ entries in front are only ever read for
+  // queries past the end of a ragged last tile, whose probabilities are set to zero
+  float* dg = dv_all + 2 * BQ + (DROP ? 2 * BQ : 0) + (WIN ? 0 : BQ);
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -785,46 +851,12 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   int kt_, h, b;
   decode_block((Sk + BCK - 1) / BCK, a.H, a.B, kt_, h, b);
   const int j0 = kt_ * BCK;
+  const int j_w0 = j0 + wave * 32;
   const int j_loc = wave * 32 + (lane & 31);
   const int j = j0 + j_loc;
   const int j_ld = j < Sk ? j : Sk - 1;
   const bf16* base = (const bf16*)io.q + (size_t)b * S * ld + h * DK;
   const bf16* dobase = dout + (size_t)b * S * I + h * DK;
-
-  bf16x8 kf[KS], vf[KS];
-  {
-    const bf16* krow = (const bf16*)io.k + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
-    const bf16* vrow = (const bf16*)io.v + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      kf[kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16 + g * 8);
-      vf[kk] = *reinterpret_cast<const bf16x8*>(vrow + kk * 16 + g * 8);
-    }
-    // The compiler waits for these loads where they are first used, and that is inside the loop: its
-    // s_waitcnt vmcnt(n) there would run in every iteration and, since the counter also counts the tile DMA
-    // issued at the top of the iteration, stall the first matrix instructions until the whole DMA has landed.
-    // An empty use here moves the wait in front of the loop.
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(kf[kk]), "v"(vf[kk]));
-  }
-  if constexpr (BIAS) {
-    // dg[t] = bias(delta) for delta = t + j0 - (S - 1), t in [0, S + BCK - 1)
-    const float* dgh = diag + (size_t)h * (2 * S - 1);
-    for (int t = tid; t < S + BCK - 1; t += 256) {
-      int idx = t + j0;  // delta + S - 1
-      idx = idx > 2 * S - 2 ? 2 * S - 2 : idx;
-      dg[t] = dgh[idx] * kLog2e;
-    }
-    if (tid < BQ) dg[tid - BQ] = 0.f;
-  }
-  const float sc = a.scale * kLog2e;
-  // dg index of (query i, key j): (j - i) - (j0 - (S-1)) = j_loc + (S - 1 - i)
-  f32x16 dkT[CT], dvT[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dkT[ct][r] = 0.f; dvT[ct][r] = 0.f; }
-
   const int it_begin = CAUSAL ? (j0 / BQ) : 0;
   const size_t srow = ((size_t)b * a.H + h) * S;
   // Q/dO tiles (DMA) and the matching lse / dvec slices are double buffered.
@@ -837,8 +869,6 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   const int it_tail = S % BQ ? S / BQ : -1;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
   const int n_it = (S + BQ - 1) / BQ;
-  (it_begin == it_tail ? tq_tail : tq).issue(lds0, base + (size_t)it_begin * BQ * ld, wave);
-  (it_begin == it_tail ? tdo_tail : tdo).issue(lds0 + TILE, dobase + (size_t)it_begin * BQ * I, wave);
   // The -lse / scale and -dvec slices of a query tile (written by the dq kernel) travel by DMA as well, one
   // instruction each from waves 0 and 1.  Fetched with ordinary loads they put compiler-made vmcnt waits into
   // the loop, and since those count the tile DMA issued just before them, every iteration waited out the
@@ -846,162 +876,166 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   const float* ndvec = dvec + srow;
   const float* nlse = dvec + (size_t)a.B * a.H * S + srow;
   const uint32_t lds_lse = lds0 + 2 * STG, lds_dv = lds_lse + 2 * BQ * 4;
-  auto issue_rows = [&](int stage, int q_first) __attribute__((always_inline)) {
+  auto issue = [&](int stage, int it) __attribute__((always_inline)) {
+    const int q_first = it * BQ;
+    const uint32_t dst = lds0 + stage * STG;
+    (it == it_tail ? tq_tail : tq).issue(dst, base + (size_t)q_first * ld, wave);
+    (it == it_tail ? tdo_tail : tdo).issue(dst + TILE, dobase + (size_t)q_first * I, wave);
     const int qi = q_first + lane < S ? q_first + lane : S - 1;  // (rows past the end are masked)
     if (wave == 0) dma_64f(lds_lse + stage * BQ * 4, nlse, (uint32_t)qi * 4u);
     if (wave == 1) dma_64f(lds_dv + stage * BQ * 4, ndvec, (uint32_t)qi * 4u);
+    if constexpr (DROP) {
+      if (tid < BQ) {
+        const int qk = q_first + tid < S ? q_first + tid : S - 1;
+        key_all[stage * BQ + tid] = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + qk)));
+      }
+    }
   };
-  issue_rows(0, it_begin * BQ);
-  if constexpr (DROP) {
-    if (tid < BQ) {
-      const int qi = it_begin * BQ + tid < S ? it_begin * BQ + tid : S - 1;
-      key_all[tid] = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + qi)));
+
+  bf16x8 kf[KS], vf[KS];
+  {
+    const bf16* krow = (const bf16*)io.k + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
+    const bf16* vrow = (const bf16*)io.v + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      kf[kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16 + g * 8);
+      vf[kk] = *reinterpret_cast<const bf16x8*>(vrow + kk * 16 + g * 8);
     }
   }
-  for (int it = it_begin; it < n_it; ++it) {
-    const int q0 = it * BQ;
-    const int st = (it - it_begin) & 1;
-    dma_wait_barrier();  // tile `it` and its lse / dvec slices landed; other stage is free
-    if (!TAIL_MASK && q0 + BQ > S) {
-      // queries past the end: their score accumulators start from the infinity that makes their probabilities zero
-      if (tid < BQ && q0 + tid >= S) lse_all[st * BQ + tid] = sc > 0.f ? -INFINITY : INFINITY;
+  // The compiler waits for these loads where they are first used, and that is inside the loop: its
+  // s_waitcnt vmcnt(n) there would run in every iteration and, since the counter also counts the tile DMA
+  // issued at the top of the iteration, stall the first matrix instructions until the whole DMA has landed.
+  // An empty use here moves the wait in front of the loop.
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(kf[kk]), "v"(vf[kk]));
+  const BiasWin win(S, a.far, CAUSAL);
+  if constexpr (WIN) {
+    win.fill<CAUSAL>(dg, diag + (size_t)h * (2 * S - 1), S, tid);
+  } else if constexpr (BIAS) {
+    // dg[t] = bias(delta) for delta = t + j0 - (S - 1), t in [0, S + BCK - 1)
+    const float* dgh = diag + (size_t)h * (2 * S - 1);
+    for (int t = tid; t < S + BCK - 1; t += 256) {
+      int idx = t + j0;  // delta + S - 1
+      idx = idx > 2 * S - 2 ? 2 * S - 2 : idx;
+      dg[t] = dgh[idx] * kLog2e;
+    }
+    if (tid < BQ) dg[tid - BQ] = 0.f;
+  }
+  const float sc = a.scale * kLog2e;
+  // (WIN) the four diagonals of queries 8 rq + 4 g + 0..3 of a sub-tile, the last query's first
+  const float* dgw = win.lane(dg, 28 + (lane & 31) - (g << 2));
+  // dg index of (query i, key j): (j - i) - (j0 - (S-1)) = j_loc + (S - 1 - i)
+  f32x16 dkT[CT], dvT[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { dkT[ct][r] = 0.f; dvT[ct][r] = 0.f; }
+
+  // How the queries past the end of a ragged last tile come to probability zero: by a masked copy of the element loop, or
+  // from the score accumulators' seeds, the infinity that makes exp2 zero.  Without the copy (and its branch) an iteration
+  // is one block that the compiler schedules whole; with dropout, and bias-free with two waves, the copy is faster.
+  constexpr bool TAIL_MASK = DK == 64 && !CAUSAL && (BIAS ? DROP : !DROP && !THREE);
+  auto mask_tail = [&](int stage, int it) __attribute__((always_inline)) {
+    if (!TAIL_MASK && it == it_tail) {
+      if (tid < BQ && it * BQ + tid >= S) lse_all[stage * BQ + tid] = sc > 0.f ? -INFINITY : INFINITY;
       __syncthreads();
     }
-    uint32_t nkey = 0;
-    const bool more = it + 1 < n_it;
-    if (more) {
-      const uint32_t nxt = lds0 + (st ^ 1) * STG;
-      (it + 1 == it_tail ? tq_tail : tq).issue(nxt, base + (size_t)(q0 + BQ) * ld, wave);
-      (it + 1 == it_tail ? tdo_tail : tdo).issue(nxt + TILE, dobase + (size_t)(q0 + BQ) * I, wave);
-      issue_rows(st ^ 1, q0 + BQ);
-      if constexpr (DROP) {
-        if (tid < BQ) {
-          const int qi = q0 + BQ + tid < S ? q0 + BQ + tid : S - 1;
-          nkey = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + qi)));
-        }
-      }
-    }
-    const char* Qt = smem + st * STG;
+  };
+  // s = S - lse / scale, dp = dP - dvec of sub-tile qb of the tile in `stage`
+  auto scores = [&](int stage, int qb, f32x16& s, f32x16& dp) __attribute__((always_inline)) {
+    const char* Qt = smem + stage * STG;
     const char* Dt = Qt + TILE;
-    const float* lse_s = lse_all + st * BQ;
-    const float* dv_s = dv_all + st * BQ;
-    const uint32_t* key_s = key_all + st * BQ;
-    bf16x8 qr[KS], dr[KS];
+    const float* lse_s = lse_all + stage * BQ;
+    const float* dv_s = dv_all + stage * BQ;
 #pragma unroll
-    for (int qb = 0; qb < BQ / 32; ++qb) {
-      // bias values and accumulator seeds are requested before the MFMAs so that their LDS latency
-      // is hidden behind the matrix work instead of stalling the softmax arithmetic (read at first use they
-      // put an LDS round trip on every sub-tile's dependent chain: 651 -> 635 us at 64 channels, the sixteen
-      // registers are there at two waves per SIMD)
-      float bias[16];
-      // Bias of (query i, key j) sits at dg[j_loc + S - 1 - i].  Where every query of the tile exists the sixteen
-      // values of a lane are one pointer and constant offsets: register r belongs to query
-      // q0 + qb*32 + 4g + c_r with c_r = 8*(r/4) + r%4 <= 27, so bq[27 - c_r] with bq 27 below the first.
-      // (a query past the end of a ragged tile reads at most BQ - 1 entries below dg[0]: the padding)
-      const float* bq = dg + (j_loc + S - 1 - q0 - qb * 32 - (g << 2) - 27);
-      if constexpr (BIAS) {
+    for (int rq = 0; rq < 4; ++rq) {
+      const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + qb * 32 + rq * 8 + g * 4);
+      const f32x4 d4 = *reinterpret_cast<const f32x4*>(dv_s + qb * 32 + rq * 8 + g * 4);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) bias[r] = bq[27 - (((r >> 2) << 3) + (r & 3))];
-      }
-      f32x16 s, dp;
-      // likewise the row operands of the tile's second sub-tile, requested before the dV / dK products of
-      // the first
-      constexpr bool ROWS_AHEAD = DK == 128;
+      // with dropout dP is rescaled before dvec is subtracted: it starts from zero
+      for (int e = 0; e < 4; ++e) { s[rq * 4 + e] = l4[e]; dp[rq * 4 + e] = DROP ? 0.f : d4[e]; }
+    }
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Qt, qb * 32, kk, lane), kf[kk], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Dt, qb * 32, kk, lane), vf[kk], dp, 0, 0, 0);
+    }
+  };
+  auto load_bias = [&](int q0, float (&bias)[16]) __attribute__((always_inline)) {  // q0: first query of the sub-tile
+    if constexpr (WIN) {
+      const float* bp = dgw + win.at(j_w0 - q0);
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
-        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + qb * 32 + rq * 8 + g * 4);
-        const f32x4 d4 = *reinterpret_cast<const f32x4*>(dv_s + qb * 32 + rq * 8 + g * 4);
+        const f32x4 b4 = *reinterpret_cast<const f32x4*>(bp - rq * 8);
 #pragma unroll
-        // with dropout dP is rescaled before dvec is subtracted: it starts from zero
-        for (int e = 0; e < 4; ++e) { s[rq * 4 + e] = l4[e]; dp[rq * 4 + e] = DROP ? 0.f : d4[e]; }
+        for (int e = 0; e < 4; ++e) bias[rq * 4 + e] = b4[3 - e];
       }
-      if constexpr (BIAS) __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);  // 8 bias + 4 seed reads first
+    } else if constexpr (BIAS) {
+      // Register r belongs to query q0 + 4g + c_r with c_r = 8*(r/4) + r%4 <= 27, so bq[27 - c_r] with bq 27 below the
+      // first.  (a query past the end of a ragged tile reads at most BQ - 1 entries below dg[0]: the padding)
+      const float* bq = dg + (j_loc + S - 1 - q0 - (g << 2) - 27);
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        const bool pre = ROWS_AHEAD && qb == 1;
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pre ? qr[kk] : frag_rows<DK>(Qt, qb * 32, kk, lane), kf[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pre ? dr[kk] : frag_rows<DK>(Dt, qb * 32, kk, lane), vf[kk], dp, 0, 0, 0);
-      }
-
-      // with 128 channels (one wave per SIMD, registers to spare) the transposed Q and dO operands of the
-      // dV / dK products are requested before the softmax arithmetic, which then covers their LDS
-      // latency; with 64 channels the second wave on the SIMD covers it and the registers are not there
-      constexpr bool TR_AHEAD = DK == 128;
-      bf16x8 dtr[2][CT], qtr[2][CT];
-      if constexpr (TR_AHEAD) {
+      for (int r = 0; r < 16; ++r) bias[r] = bq[27 - (((r >> 2) << 3) + (r & 3))];
+    }
+  };
+  // P and dS of a sub-tile, in place of s and dp
+  auto softmax = [&](auto tail, int stage, int qb, int q0, f32x16& s, f32x16& dp, const float (&bias)[16])
+      __attribute__((always_inline)) {
+    const float* dv_s = dv_all + stage * BQ;
+    const uint32_t* key_s = key_all + stage * BQ;
 #pragma unroll
-        for (int mm = 0; mm < 2; ++mm)
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
-            dtr[mm][ct] = frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane);
-            qtr[mm][ct] = frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane);
-          }
-      }
-      // some key here lies after some query (with 64 channels the causal form masks always: see above), or the tile
-      // reaches past the last query and is not seeded (both wave-uniform)
-      if ((TAIL_MASK && q0 + BQ > S) || (CAUSAL && (DK == 64 || j0 + wave * 32 + 31 > q0 + qb * 32))) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-          const int i = q0 + il;
-          float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r]))
-                         : fast_exp2(s[r] * sc);
-          if ((CAUSAL && j > i) || (TAIL_MASK && i >= S)) p = 0.f;
-          if constexpr (DROP) {
-            const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
-            s[r] = keep ? p : 0.f;
-            dp[r] = p * ((keep ? dp[r] * a.drop.scale : 0.f) + dv_s[il]);
-          } else {
-            s[r] = p;
-            dp[r] = p * dp[r];
-          }
-        }
+    for (int r = 0; r < 16; ++r) {
+      const int ir = ((r >> 2) << 3) + (g << 2) + (r & 3), il = qb * 32 + ir;
+      float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
+      if ((CAUSAL && !WIN && j > q0 + ir) || (decltype(tail)::value && q0 + ir >= S)) p = 0.f;
+      if constexpr (DROP) {
+        const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
+        s[r] = keep ? p : 0.f;
+        dp[r] = p * ((keep ? dp[r] * a.drop.scale : 0.f) + dv_s[il]);
       } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-          const int i = q0 + il;
-          const float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r]))
-                               : fast_exp2(s[r] * sc);
-          if constexpr (DROP) {
-            const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
-            s[r] = keep ? p : 0.f;
-            dp[r] = p * ((keep ? dp[r] * a.drop.scale : 0.f) + dv_s[il]);
-          } else {
-            s[r] = p;
-            dp[r] = p * dp[r];
-          }
-        }
-      }
-      if constexpr (ROWS_AHEAD) {
-        if (qb == 0) {
-#pragma unroll
-          for (int kk = 0; kk < KS; ++kk) {
-            qr[kk] = frag_rows<DK>(Qt, 32, kk, lane);
-            dr[kk] = frag_rows<DK>(Dt, 32, kk, lane);
-          }
-        }
-      }
-#pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        const bf16x8 pf = pack8(s, mm * 8), dsf = pack8(dp, mm * 8);
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          dvT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              TR_AHEAD ? dtr[mm][ct] : frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane), pf, dvT[ct], 0, 0, 0);
-          dkT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              TR_AHEAD ? qtr[mm][ct] : frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane), dsf, dkT[ct], 0, 0, 0);
-        }
+        s[r] = p;
+        dp[r] = p * dp[r];
       }
     }
-    if constexpr (DROP) {
-      if (more && tid < BQ) key_all[(st ^ 1) * BQ + tid] = nkey;
+  };
+  issue(0, it_begin);
+  for (int it = it_begin; it < n_it; ++it) {
+    const int st = (it - it_begin) & 1, q0 = it * BQ;
+    dma_wait_barrier();  // tile `it` and its lse / dvec slices landed; the other stage is free
+    mask_tail(st, it);
+    if (it + 1 < n_it) issue(st ^ 1, it + 1);
+    const char* Qt = smem + st * STG;
+    const char* Dt = Qt + TILE;
+    // with bias, the score products of both sub-tiles first: 32 x 1024 tokens, 32 heads 609 -> 590 us
+    constexpr bool BOTH = BIAS && !DROP;
+    f32x16 s[2], dp[2];
+    float bias[2][16];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      if (qb == 0 || !BOTH) {
+        load_bias(q0 + qb * 32, bias[qb]);
+        scores(st, qb, s[qb], dp[qb]);
+      }
+      if (qb == 0 && BOTH) {
+        load_bias(q0 + 32, bias[1]);
+        scores(st, 1, s[1], dp[1]);
+      }
+      if (TAIL_MASK && q0 + qb * 32 + 32 > S) softmax(std::true_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
+      else softmax(std::false_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
+#pragma unroll
+      for (int mm = 0; mm < 2; ++mm) {
+        const bf16x8 pf = pack8(s[qb], mm * 8), dsf = pack8(dp[qb], mm * 8);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          dvT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane), pf, dvT[ct], 0, 0, 0);
+          dkT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane), dsf, dkT[ct], 0, 0, 0);
+        }
+      }
     }
   }
   __syncthreads();  // every wave is done with the tiles
   {
     char* stage = smem + wave * 32 * (DK * 2 + 16);
-    const int j_w0 = j0 + wave * 32;
     const size_t row0 = (size_t)b * Sk + j_w0;
     store_rows<DK>(stage, dkT, a.scale, (bf16*)io.dk + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv, Sk - j_w0, lane);
     store_rows<DK>(stage, dvT, DROP ? a.drop.scale : 1.f, (bf16*)io.dv + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv,
@@ -1009,10 +1043,230 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   }
 }
 
-size_t attn_bwd_dq_lds_bytes(const AttnDims& a, int far) {
+// ------------------------------------------------------------------------------------------------
+// dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
+// ------------------------------------------------------------------------------------------------
+// The pipelined form (128 channels, and causal; no dropout).  A unit is 32 queries x 32 keys; its dV / dK products follow the
+// score products of the next unit and run beside that unit's softmax arithmetic, across the tiles' barriers too (a ring of
+// three tile stages).  With 128 channels one wave has a SIMD to itself, and in program order matrix and vector unit took
+// turns (28 % and 26 % busy): 16 x 2048 tokens causal, 16 heads 950 -> 843 us, 8 x 2048 not causal 740 -> 650; 64 channels
+// causal, 8 x 2048, 12 heads 167 -> 148, 32 x 512 67 -> 62.  64 channels without the mask: 1-4 % slower than the other form.
+template <int DK, bool CAUSAL, bool BIAS, bool WIN>
+__global__ __launch_bounds__(256, DK == 64 ? 2 : 1)
+void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
+                              const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
+  constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
+  constexpr int TILE = BQ * DK * 2, STG = 2 * TILE;  // a stage holds a Q tile then a dO tile
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  // The score and dP accumulators start from -lse/scale and -dvec, so that the MFMA results are
+  // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
+  float* lse_all = reinterpret_cast<float*>(smem + 3 * STG);  // [3 stages][BQ]  -lse / scale
+  float* dv_all = lse_all + 3 * BQ;                           // [3 stages][BQ]  -dvec
+  // Window, or [-BQ, S + BCK - 1), log2 units (BIAS only); the slice's BQ entries in front are only ever read for
+  // queries past the end of a ragged last tile, whose probabilities are set to zero
+  float* dg = dv_all + 3 * BQ + (WIN ? 0 : BQ);
+
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = a.S, Sk = a.Sk, I = a.H * DK;
+  const size_t ld = (size_t)io.ldq, ldkv = (size_t)io.ldkv;
+  int kt_, h, b;
+  decode_block((Sk + BCK - 1) / BCK, a.H, a.B, kt_, h, b);
+  const int j0 = kt_ * BCK;
+  const int j_w0 = j0 + wave * 32;            // first key of this wave
+  const int j_loc = wave * 32 + (lane & 31);
+  const bf16* base = (const bf16*)io.q + (size_t)b * S * ld + h * DK;
+  const bf16* dobase = dout + (size_t)b * S * I + h * DK;
+  const int it_begin = CAUSAL ? (j0 / BQ) : 0;
+  const size_t srow = ((size_t)b * a.H + h) * S;
+  // Q/dO tiles (DMA) and the matching lse / dvec slices are double buffered.
+  // tq_tail / tdo_tail: the last tile of a query sequence that does not fill it
+  TileDma<DK, BQ> tq, tdo, tq_tail, tdo_tail;
+  tq.init(wave, lane, ld);
+  tdo.init(wave, lane, (size_t)I);
+  tq_tail.init(wave, lane, ld, S % BQ ? S % BQ : BQ);
+  tdo_tail.init(wave, lane, (size_t)I, S % BQ ? S % BQ : BQ);
+  const int it_tail = S % BQ ? S / BQ : -1;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+  const int n_it = (S + BQ - 1) / BQ;
+  // The -lse / scale and -dvec slices of a query tile (written by the dq kernel) travel by DMA as well, one
+  // instruction each from waves 0 and 1.  Fetched with ordinary loads they put compiler-made vmcnt waits into
+  // the loop, and since those count the tile DMA issued just before them, every iteration waited out the
+  // whole DMA latency at its first matrix instruction.
+  const float* ndvec = dvec + srow;
+  const float* nlse = dvec + (size_t)a.B * a.H * S + srow;
+  const uint32_t lds_lse = lds0 + 3 * STG, lds_dv = lds_lse + 3 * BQ * 4;
+  auto issue = [&](int stage, int it) __attribute__((always_inline)) {
+    const int q_first = it * BQ;
+    const uint32_t dst = lds0 + stage * STG;
+    (it == it_tail ? tq_tail : tq).issue(dst, base + (size_t)q_first * ld, wave);
+    (it == it_tail ? tdo_tail : tdo).issue(dst + TILE, dobase + (size_t)q_first * I, wave);
+    const int qi = q_first + lane < S ? q_first + lane : S - 1;  // (rows past the end are masked)
+    if (wave == 0) dma_64f(lds_lse + stage * BQ * 4, nlse, (uint32_t)qi * 4u);
+    if (wave == 1) dma_64f(lds_dv + stage * BQ * 4, ndvec, (uint32_t)qi * 4u);
+  };
+
+  issue(0, it_begin);
+  bf16x8 kf[KS], vf[KS];
+  {
+    const int j = j0 + j_loc, j_ld = j < Sk ? j : Sk - 1;
+    const bf16* krow = (const bf16*)io.k + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
+    const bf16* vrow = (const bf16*)io.v + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      kf[kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16 + g * 8);
+      vf[kk] = *reinterpret_cast<const bf16x8*>(vrow + kk * 16 + g * 8);
+    }
+  }
+  const BiasWin win(S, a.far, CAUSAL);
+  if constexpr (WIN) {
+    win.fill<CAUSAL>(dg, diag + (size_t)h * (2 * S - 1), S, tid);
+  } else if constexpr (BIAS) {
+    // dg[t] = bias(delta) for delta = t + j0 - (S - 1), t in [0, S + BCK - 1)
+    const float* dgh = diag + (size_t)h * (2 * S - 1);
+    for (int t = tid; t < S + BCK - 1; t += 256) {
+      int idx = t + j0;  // delta + S - 1
+      idx = idx > 2 * S - 2 ? 2 * S - 2 : idx;
+      dg[t] = dgh[idx] * kLog2e;
+    }
+    if (tid < BQ) dg[tid - BQ] = 0.f;
+  }
+  // The compiler waits for these loads where they are first used, and that is inside the loop: its
+  // s_waitcnt vmcnt(n) there would run in every iteration and, since the counter also counts the tile DMA
+  // issued at the top of the iteration, stall the first matrix instructions until the whole DMA has landed.
+  // An empty use here moves the wait in front of the loop.
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(kf[kk]), "v"(vf[kk]));
+  const float sc = a.scale * kLog2e;
+  // (WIN) the four diagonals of queries 8 rq + 4 g + 0..3 of a sub-tile, the last query's first
+  const float* dgw = win.lane(dg, 28 + (lane & 31) - (g << 2));
+  // dg index of (query i, key j): (j - i) - (j0 - (S-1)) = j_loc + (S - 1 - i)
+  f32x16 dkT[CT], dvT[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { dkT[ct][r] = 0.f; dvT[ct][r] = 0.f; }
+
+  // queries past the end: their score accumulators start from the infinity that makes their probabilities zero
+  auto mask_tail = [&](int stage, int it) __attribute__((always_inline)) {
+    if (it == it_tail) {
+      if (tid < BQ && it * BQ + tid >= S) lse_all[stage * BQ + tid] = sc > 0.f ? -INFINITY : INFINITY;
+      __syncthreads();
+    }
+  };
+  // s = S - lse / scale, dp = dP - dvec of sub-tile qb of the tile in `stage`
+  auto scores = [&](int stage, int qb, f32x16& s, f32x16& dp) __attribute__((always_inline)) {
+    const char* Qt = smem + stage * STG;
+    const char* Dt = Qt + TILE;
+    const float* lse_s = lse_all + stage * BQ;
+    const float* dv_s = dv_all + stage * BQ;
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + qb * 32 + rq * 8 + g * 4);
+      const f32x4 d4 = *reinterpret_cast<const f32x4*>(dv_s + qb * 32 + rq * 8 + g * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { s[rq * 4 + e] = l4[e]; dp[rq * 4 + e] = d4[e]; }
+    }
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Qt, qb * 32, kk, lane), kf[kk], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Dt, qb * 32, kk, lane), vf[kk], dp, 0, 0, 0);
+    }
+  };
+  auto load_bias = [&](int q0, float (&bias)[16]) __attribute__((always_inline)) {  // q0: first query of the sub-tile
+    if constexpr (WIN) {
+      const float* bp = dgw + win.at(j_w0 - q0);
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) {
+        const f32x4 b4 = *reinterpret_cast<const f32x4*>(bp - rq * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias[rq * 4 + e] = b4[3 - e];
+      }
+    } else if constexpr (BIAS) {
+      // Register r belongs to query q0 + 4g + c_r with c_r = 8*(r/4) + r%4 <= 27, so bq[27 - c_r] with bq 27 below the
+      // first.  (a query past the end of a ragged tile reads at most BQ - 1 entries below dg[0]: the padding)
+      const float* bq = dg + (j_loc + S - 1 - q0 - (g << 2) - 27);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) bias[r] = bq[27 - (((r >> 2) << 3) + (r & 3))];
+    }
+  };
+  // half mm of P and dS of a unit (its queries 16 mm ..) as operands of the dV and dK products
+  auto softmax = [&](int stage, int qb, int q0, int mm, const f32x16& s, const f32x16& dp, const float (&bias)[16],
+                     bf16x8& pf, bf16x8& dsf) __attribute__((always_inline)) {
+    const float* dv_s = dv_all + stage * BQ;
+    const int j = j0 + j_loc;
+#pragma unroll
+    for (int r = mm * 8; r < mm * 8 + 8; ++r) {
+      float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
+      if (CAUSAL && !WIN && j - q0 > ((r >> 2) << 3) + (g << 2) + (r & 3)) p = 0.f;
+      pf[r & 7] = (bf16)p;
+      dsf[r & 7] = (bf16)(p * dp[r]);
+    }
+  };
+  auto outer = [&](int stage, int qb, int mm, const bf16x8& pf, const bf16x8& dsf) __attribute__((always_inline)) {
+    const char* Qt = smem + stage * STG;
+    const char* Dt = Qt + TILE;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      dvT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane), pf, dvT[ct], 0, 0, 0);
+      dkT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane), dsf, dkT[ct], 0, 0, 0);
+    }
+  };
+  // A unit is 32 queries x 32 keys.  Step n of the pipeline: the score products of unit n, then the dV / dK products of unit
+  // n - 1 beside the softmax arithmetic of unit n.
+  bf16x8 pf[2], dsf[2];      // of the unit whose products are still to come
+  auto step = [&](int pst, int pv, int stage, int v, int q0) __attribute__((always_inline)) {
+    const int qb = v;
+    f32x16 s, dp;
+    float bias[16];
+    bf16x8 pn[2], dn[2];
+    load_bias(q0 + qb * 32, bias);
+    scores(stage, qb, s, dp);
+    if (pv >= 0) {
+#pragma unroll
+      for (int mm = 0; mm < 2; ++mm) outer(pst, pv, mm, pf[mm], dsf[mm]);
+    }
+#pragma unroll
+    for (int mm = 0; mm < 2; ++mm) softmax(stage, qb, q0 + qb * 32, mm, s, dp, bias, pn[mm], dn[mm]);
+#pragma unroll
+    for (int mm = 0; mm < 2; ++mm) { pf[mm] = pn[mm]; dsf[mm] = dn[mm]; }
+  };
+
+  dma_wait_barrier();
+  mask_tail(0, it_begin);
+  if (it_begin + 1 < n_it) issue(1, it_begin + 1);
+  step(0, -1, 0, 0, it_begin * BQ);
+  int st = 0;
+  for (int it = it_begin;; ++it) {
+    const int q0 = it * BQ;
+    step(st, 0, st, 1, q0);
+    if (it + 1 == n_it) break;
+    const int nst = st == 2 ? 0 : st + 1;
+    dma_wait_barrier();  // tile it + 1 has landed; every wave is done with tile it - 1
+    mask_tail(nst, it + 1);
+    if (it + 2 < n_it) issue(nst == 2 ? 0 : nst + 1, it + 2);
+    step(st, 1, nst, 0, q0 + BQ);
+    st = nst;
+  }
+#pragma unroll
+  for (int mm = 0; mm < 2; ++mm) outer(st, 1, mm, pf[mm], dsf[mm]);
+  __syncthreads();  // every wave is done with the tiles
+  char* stage = smem + wave * 32 * (DK * 2 + 16);
+  {
+    const int j_b0 = j_w0;
+    const size_t row0 = (size_t)b * Sk + j_b0;
+    store_rows<DK>(stage, dkT, a.scale, (bf16*)io.dk + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv, Sk - j_b0, lane);
+    store_rows<DK>(stage, dvT, 1.f, (bf16*)io.dv + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv,
+                   Sk - j_b0, lane);
+  }
+}
+
+// (win: bias from a window of diagonals)
+size_t attn_bwd_dq_lds_bytes(const AttnDims& a, bool win) {
   if (!a.bias) return (size_t)4 * 64 * a.dk * 2;
-  const int W = 32 * (2 * attn_dq_window_blocks(a.S, far) + 2);
-  return (size_t)4 * 64 * a.dk * 2 + sizeof(float) * ((size_t)(a.S + 127) + 8 * (size_t)W);
+  const int W = 32 * (2 * attn_dq_window_blocks(a.S, a.far) + 2);
+  const size_t bias = win ? BiasWin(a.S, a.far, a.causal != 0).floats() : a.S + 127;
+  return (size_t)4 * 64 * a.dk * 2 + sizeof(float) * (bias + 8 * (size_t)W);
 }
 
 template <typename K>
@@ -1020,10 +1274,10 @@ hipError_t set_lds(K kern, size_t bytes) {
   return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <int DK, bool CAUSAL, bool BIAS, bool DROP = false>
-hipError_t fwd_launch(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a, hipStream_t st) {
-  auto kern = attn_fwd_mfma_kernel<DK, CAUSAL, BIAS, DROP>;
-  const size_t lds = 4 * 64 * DK * 2 + (BIAS ? sizeof(float) * (a.S + 127) : 0);
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
+hipError_t fwd_launch_as(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a, hipStream_t st) {
+  auto kern = attn_fwd_mfma_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
+  const size_t lds = 4 * 64 * DK * 2 + sizeof(float) * (WIN ? BiasWin(a.S, a.far, CAUSAL).floats() : BIAS ? a.S + 127 : 0);
   hipError_t e = set_lds(kern, lds);
   if (e != hipSuccess) return e;
   kern<<<dim3(((a.S + 127) / 128) * a.H * a.B), 256, lds, st>>>(io, diag, (bf16*)c, lse, a);
@@ -1031,38 +1285,60 @@ hipError_t fwd_launch(const AttnIO& io, const float* diag, void* c, float* lse, 
 }
 
 template <int DK, bool CAUSAL, bool BIAS, bool DROP = false>
-hipError_t bwd_launch(const AttnIO& io, const void* c, const void* dc, const float* diag, const float* lse,
-                      float* dvec, float* ddiag, float* ddiag_part, const AttnDims& a, int far, int phase,
+hipError_t fwd_launch(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a, hipStream_t st) {
+  if (BIAS && attn_bias_window(a)) return fwd_launch_as<DK, CAUSAL, BIAS, DROP, BIAS>(io, diag, c, lse, a, st);
+  return fwd_launch_as<DK, CAUSAL, BIAS, DROP, false>(io, diag, c, lse, a, st);
+}
+
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
+hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const float* diag, const float* lse,
+                      float* dvec, float* ddiag, float* ddiag_part, const AttnDims& a, int phase,
                       hipStream_t st) {
   hipError_t e = hipSuccess;
   if (phase == 1) {
-    auto kern = attn_bwd_dq_mfma_kernel<DK, CAUSAL, BIAS, DROP>;
-    const size_t lds = attn_bwd_dq_lds_bytes(a, far);
+    auto kern = attn_bwd_dq_mfma_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
+    const size_t lds = attn_bwd_dq_lds_bytes(a, WIN);
     if ((e = set_lds(kern, lds)) != hipSuccess) return e;
     kern<<<dim3(((a.S + 127) / 128) * a.H * a.B), 256, lds, st>>>(io, (const bf16*)c, (const bf16*)dc, diag, lse, dvec, ddiag,
-                                                          BIAS ? ddiag_part : nullptr, a, far);
+                                                          BIAS ? ddiag_part : nullptr, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (BIAS && ddiag_part) {
-      const int nb = attn_dq_window_blocks(a.S, far);
+      const int nb = attn_dq_window_blocks(a.S, a.far);
       attn_ddiag_reduce_kernel<<<a.H * ceil_div(32 * (2 * nb + 2) + 6, 64), 256, 0, st>>>(ddiag_part, ddiag, a.B, a.H,
                                                                                          a.S, nb);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
   if (phase == 2) {
-    const size_t lds = 4 * 64 * DK * 2 + sizeof(float) * (256 + (DROP ? 128 : 0) + (BIAS ? 64 + a.S + 127 : 0));
+    const size_t bias = sizeof(float) * (WIN ? BiasWin(a.S, a.far, CAUSAL).floats() : BIAS ? 64 + a.S + 127 : 0);
     const int wgs = ((a.Sk + 127) / 128) * a.H * a.B;
-    // Bias-free with 64 channels: beyond two workgroups per compute unit the form that lets a third in, up to there the
-    // one whose single workgroup is faster (1 x 1024 queries over 100 keys, 12 heads, 12 workgroups: 27 against 23 us;
-    // 384 workgroups 39 and 38; 768 61 and 65; 128 x 114 over 512, 6144 workgroups: 103 and 106).
-    constexpr bool CAN_THREE = DK == 64 && !BIAS && !DROP;
-    auto kern = CAN_THREE && wgs > 512 ? attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, CAN_THREE>
-                                       : attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, false>;
-    if ((e = set_lds(kern, lds)) != hipSuccess) return e;
-    kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+    if constexpr (!DROP && (DK == 128 || CAUSAL)) {
+      auto kern = attn_bwd_dkv_pipe_kernel<DK, CAUSAL, BIAS, WIN>;
+      const size_t lds = 3 * (2 * 64 * DK * 2 + sizeof(float) * 128) + bias;
+      if ((e = set_lds(kern, lds)) != hipSuccess) return e;
+      kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+    } else {
+      // Bias-free with 64 channels: beyond two workgroups per compute unit the form that lets a third in, up to there the
+      // one whose single workgroup is faster (1 x 1024 queries over 100 keys, 12 heads, 12 workgroups: 27 against 23 us;
+      // 384 workgroups 39 and 38; 768 61 and 65; 128 x 114 over 512, 6144 workgroups: 103 and 106).
+      constexpr bool CAN_THREE = DK == 64 && !BIAS && !DROP;
+      auto kern = CAN_THREE && wgs > 512 ? attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, CAN_THREE, WIN>
+                                         : attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, false, WIN>;
+      const size_t lds = 2 * (2 * 64 * DK * 2 + sizeof(float) * (128 + (DROP ? 64 : 0))) + bias;
+      if ((e = set_lds(kern, lds)) != hipSuccess) return e;
+      kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+template <int DK, bool CAUSAL, bool BIAS, bool DROP = false>
+hipError_t bwd_launch(const AttnIO& io, const void* c, const void* dc, const float* diag, const float* lse,
+                      float* dvec, float* ddiag, float* ddiag_part, const AttnDims& a, int phase, hipStream_t st) {
+  if (BIAS && attn_bias_window(a))
+    return bwd_launch_as<DK, CAUSAL, BIAS, DROP, BIAS>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+  return bwd_launch_as<DK, CAUSAL, BIAS, DROP, false>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
 }
 
 // 0: self-attention with bias, 1: the same with the causal mask, 2: cross-attention (no bias, no mask)
@@ -1070,9 +1346,9 @@ int attn_mode(const AttnDims& a) { return a.bias ? (a.causal ? 1 : 0) : 2; }
 
 }  // namespace
 
-bool attn_bwd_mfma_fits(const AttnDims& a, int far) {
+bool attn_bwd_mfma_fits(const AttnDims& a) {
   // the dq kernel keeps per-diagonal windows of about 2 * far entries in LDS
-  return attn_bwd_dq_lds_bytes(a, far < 1 ? 1 : far) <= (size_t)150 * 1024;
+  return attn_bwd_dq_lds_bytes(a, false) <= (size_t)150 * 1024;
 }
 
 bool attn_mfma_supported(const AttnDims& a) {
@@ -1112,33 +1388,32 @@ size_t attn_ddiag_part_bytes(const AttnDims& a) {
 }
 
 hipError_t launch_attn_bwd_mfma(const AttnIO& io, const void* c, const void* dc, const float* diag,
-                                const float* lse, float* dvec, float* ddiag, const AttnDims& a, int far,
-                                int phase, hipStream_t st, float* ddiag_part) {
+                                const float* lse, float* dvec, float* ddiag, const AttnDims& a, int phase,
+                                hipStream_t st, float* ddiag_part) {
   // phase 1: dq, dvec = rowsum(dO * O) and the bias-gradient diagonals (added into ddiag); phase 2: dk, dv
   // (reads the dvec phase 1 wrote).
-  // `far`: smallest distance that falls in the last (saturated) bucket; such offsets need no
+  // a.far: smallest distance that falls in the last (saturated) bucket; such offsets need no
   // per-diagonal resolution.  Never below 1, so offset 0 always takes the per-diagonal path.
   if (!attn_mfma_supported(a)) return hipErrorInvalidValue;
-  if (far < 1) far = 1;
   const int mode = attn_mode(a);
   if (a.drop.on) {
     if (a.dk == 64) {
-      if (mode == 0) return bwd_launch<64, false, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-      if (mode == 1) return bwd_launch<64, true, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-      return bwd_launch<64, false, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
+      if (mode == 0) return bwd_launch<64, false, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+      if (mode == 1) return bwd_launch<64, true, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+      return bwd_launch<64, false, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
     }
-    if (mode == 0) return bwd_launch<128, false, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-    if (mode == 1) return bwd_launch<128, true, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-    return bwd_launch<128, false, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
+    if (mode == 0) return bwd_launch<128, false, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+    if (mode == 1) return bwd_launch<128, true, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+    return bwd_launch<128, false, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
   }
   if (a.dk == 64) {
-    if (mode == 0) return bwd_launch<64, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-    if (mode == 1) return bwd_launch<64, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-    return bwd_launch<64, false, false>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
+    if (mode == 0) return bwd_launch<64, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+    if (mode == 1) return bwd_launch<64, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+    return bwd_launch<64, false, false>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
   }
-  if (mode == 0) return bwd_launch<128, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-  if (mode == 1) return bwd_launch<128, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
-  return bwd_launch<128, false, false>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, far, phase, st);
+  if (mode == 0) return bwd_launch<128, false, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+  if (mode == 1) return bwd_launch<128, true, true>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
+  return bwd_launch<128, false, false>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
 }
 
 }  // namespace t5mi

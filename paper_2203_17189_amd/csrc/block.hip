@@ -81,10 +81,9 @@ int t5_block_kernel_path(const t5_block_cfg* cfg, int32_t enc_seq) {
   int path = 0;
   if (fused_fwd_ok(D)) path |= T5_PATH_MFMA_GEMM;
   const AttnDims ad = self_dims(cfg, D);
-  const int far = lut.n_thr > 0 ? lut.thr[lut.n_thr - 1] : lut.max_exact;
   if (D.ty == IN_BF16 && attn_mfma_supported(ad)) {
     path |= T5_PATH_MFMA_ATTN_FWD;
-    if (attn_bwd_mfma_fits(ad, far)) path |= T5_PATH_MFMA_ATTN_BWD;
+    if (attn_bwd_mfma_fits(ad)) path |= T5_PATH_MFMA_ATTN_BWD;
   }
   if (enc_seq > 0 && D.ty == IN_BF16 && attn_mfma_supported(cross_dims(cfg, D))) path |= T5_PATH_MFMA_CROSS_ATTN;
   return path;
@@ -128,13 +127,12 @@ int t5_block_bwd(const t5_block_cfg* cfg, const void* dy, const void* x, const t
   carve_bwd(D, workspace, &W);
   const int acc = accumulate ? 1 : 0;
   const AttnDims ad = self_dims(cfg, D);
-  const int far = lut.n_thr > 0 ? lut.thr[lut.n_thr - 1] : lut.max_exact;
-  const bool attn_mfma = D.ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad, far);
+  const bool attn_mfma = D.ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad);
   W.fork = fork_begin(st, D.drop == 0.f && !D.det);
   ForkGuard guard(W.fork);
   T5_SUB(bwd_zero(D, dw, nullptr, W.ddiag, acc != 0, st));
   T5_SUB(bwd_mlp(D, dy, S.h, w, S, W, dw, acc, st));
-  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh, W.dh_lp, w, S, W, attn_mfma, far, dx, dw, nullptr, acc, st));
+  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh, W.dh_lp, w, S, W, attn_mfma, dx, dw, nullptr, acc, st));
   T5_TRY(guard.join());
   return T5_OK;
 }
@@ -186,14 +184,13 @@ int t5_decoder_block_bwd(const t5_block_cfg* cfg, int32_t enc_seq, const void* d
   carve_bwd(D, workspace, &W);
   const int acc = accumulate ? 1 : 0;
   const AttnDims ad = self_dims(cfg, D);
-  const int far = lut.n_thr > 0 ? lut.thr[lut.n_thr - 1] : lut.max_exact;
-  const bool attn_mfma = D.ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad, far);
+  const bool attn_mfma = D.ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad);
   W.fork = fork_begin(st, D.drop == 0.f && !D.det);
   ForkGuard guard(W.fork);
   T5_SUB(bwd_zero(D, dw, dxw, W.ddiag, acc != 0, st));
   T5_SUB(bwd_mlp(D, dy, S.h2, w, S, W, dw, acc, st));
   T5_SUB(bwd_cross_attn(cfg, D, enc, xw, S, W, denc, dxw, acc, st));
-  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh1, W.dh1_lp, w, S, W, attn_mfma, far, dx, dw, dxw, acc, st));
+  T5_SUB(bwd_self_attn(cfg, D, lut, x, W.dh1, W.dh1_lp, w, S, W, attn_mfma, dx, dw, dxw, acc, st));
   T5_TRY(guard.join());
   return T5_OK;
 }

@@ -39,6 +39,7 @@ struct Dims {
   float drop;     // dropout rate; 0: none
   uint64_t seed;  // dropout seed
   int det;        // 1: weight and bias-table gradients are summed in a fixed order
+  int far;        // smallest distance in the saturated last bucket of the relative positions
 };
 // Generator parameters of one of the block's dropout sites (off when the rate is 0).
 inline DropSite drop_site(const Dims& D, int site) { return make_drop_site(D.seed, site, D.drop); }
@@ -62,7 +63,8 @@ int validate_cfg(const t5_block_cfg* c, Dims* o, RelposLut* lut, int enc_seq = 0
   if (c->d_model > 8192 || (c->d_model % 8 != 0 && c->d_model > 1024)) return T5_ERR_UNSUPPORTED;
   if (c->dropout_rate > 0.f && T * c->n_heads > ((int64_t)1 << 32)) return T5_ERR_UNSUPPORTED;  // 32-bit row counter
   RelposLut tmp;
-  const int rc = relpos_build_lut(c->causal ? 0 : 1, c->num_buckets, c->max_distance, lut ? lut : &tmp);
+  if (!lut) lut = &tmp;
+  const int rc = relpos_build_lut(c->causal ? 0 : 1, c->num_buckets, c->max_distance, lut);
   if (rc != T5_OK) return rc;
   if (o) {
     o->B = c->batch; o->S = c->seq; o->d = c->d_model; o->H = c->n_heads; o->dk = c->d_kv; o->F = c->d_ff;
@@ -74,6 +76,7 @@ int validate_cfg(const t5_block_cfg* c, Dims* o, RelposLut* lut, int enc_seq = 0
     o->drop = c->dropout_rate;
     o->seed = ((uint64_t)c->dropout_seed_hi << 32) | c->dropout_seed_lo;
     o->det = c->deterministic;
+    o->far = std::max(1, lut->n_thr > 0 ? lut->thr[lut->n_thr - 1] : lut->max_exact);
     static_assert(T5_MLP_GEGLU_TANH == ACT_GELU_TANH && T5_MLP_RELU == ACT_RELU && T5_MLP_GEGLU_ERF == ACT_GELU_ERF,
                   "the config values are the kernels' activation codes");
   }
@@ -443,10 +446,10 @@ bool grads_present(const t5_block_grads* g, const Dims& D) {
 }
 
 AttnDims self_dims(const t5_block_cfg* cfg, const Dims& D) {
-  return AttnDims{D.B, D.S, D.H, D.dk, cfg->causal ? 1 : 0, cfg->attn_scale, D.S, 1, drop_site(D, DROP_ATTN_PROBS)};
+  return AttnDims{D.B, D.S, D.H, D.dk, cfg->causal ? 1 : 0, cfg->attn_scale, D.S, 1, drop_site(D, DROP_ATTN_PROBS), D.far};
 }
 AttnDims cross_dims(const t5_block_cfg* cfg, const Dims& D) {
-  return AttnDims{D.B, D.S, D.H, D.dk, 0, cfg->attn_scale, D.Sk, 0, drop_site(D, DROP_CROSS_PROBS)};
+  return AttnDims{D.B, D.S, D.H, D.dk, 0, cfg->attn_scale, D.Sk, 0, drop_site(D, DROP_CROSS_PROBS), 1};
 }
 AttnIO cross_io(const Dims& D, const Stash& S, const BwdWs* W) {
   AttnIO io;
@@ -768,8 +771,8 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   }
   const AttnIO io = cross_io(D, S, &W);
   if (ty == IN_BF16 && attn_mfma_supported(ad)) {
-    T5_STEP("xattn_bwd_dq", launch_attn_bwd_mfma(io, S.cx, W.dc, nullptr, S.lse_x, W.dvec, nullptr, ad, 1, 1, st));
-    T5_STEP("xattn_bwd_dkv", launch_attn_bwd_mfma(io, S.cx, W.dc, nullptr, S.lse_x, W.dvec, nullptr, ad, 1, 2, st));
+    T5_STEP("xattn_bwd_dq", launch_attn_bwd_mfma(io, S.cx, W.dc, nullptr, S.lse_x, W.dvec, nullptr, ad, 1, st));
+    T5_STEP("xattn_bwd_dkv", launch_attn_bwd_mfma(io, S.cx, W.dc, nullptr, S.lse_x, W.dvec, nullptr, ad, 2, st));
   } else {
     T5_STEP("xattn_bwd", launch_attn_bwd_simple(io, S.cx, W.dc, ty, nullptr, S.lse_x, W.dvec, nullptr, ad, st));
   }
@@ -806,7 +809,7 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
 // layer's norms (dxw: also the cross-attention sublayer's) and its own bias table have left.
 int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, const void* x, const float* dh,
                   const void* dh_lp, const t5_block_weights* w, const Stash& S, const BwdWs& W, bool attn_mfma,
-                  int far, void* dx, const t5_block_grads* dw, const t5_cross_grads* dxw, int acc, hipStream_t st,
+                  void* dx, const t5_block_grads* dw, const t5_cross_grads* dxw, int acc, hipStream_t st,
                   bool own_table = true) {
   const int T = (int)D.T, ty = D.ty;
   const size_t es = D.es;
@@ -827,9 +830,9 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   }
   const AttnIO io = attn_io_packed(S.qkv, W.dqkv, D.I, es);
   if (attn_mfma) {
-    T5_STEP("attn_bwd_dq", launch_attn_bwd_mfma(io, S.c, W.dc, S.diag, S.lse, W.dvec, W.ddiag, ad, far, 1, st,
+    T5_STEP("attn_bwd_dq", launch_attn_bwd_mfma(io, S.c, W.dc, S.diag, S.lse, W.dvec, W.ddiag, ad, 1, st,
                                                 W.ddiag_part));
-    T5_STEP("attn_bwd_dkv", launch_attn_bwd_mfma(io, S.c, W.dc, S.diag, S.lse, W.dvec, W.ddiag, ad, far, 2, st));
+    T5_STEP("attn_bwd_dkv", launch_attn_bwd_mfma(io, S.c, W.dc, S.diag, S.lse, W.dvec, W.ddiag, ad, 2, st));
   } else {
     T5_STEP("attn_bwd", launch_attn_bwd_simple(io, S.c, W.dc, ty, S.diag, S.lse, W.dvec, W.ddiag, ad, st));
   }

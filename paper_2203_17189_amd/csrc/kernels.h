@@ -195,6 +195,7 @@ struct AttnDims {
   int Sk;
   int bias;
   DropSite drop;  // dropout of the probabilities; row = (b*H + h)*S + i, column = j
+  int far;        // with bias: smallest distance in the last (saturated) bucket of its side, at least 1
 };
 // Operand placement.  Row (b*S + i) of q / dq starts at q + row*ldq, row (b*Sk + j) of k, v / dk, dv at
 // k + row*ldkv; head h occupies channels h*dk .. h*dk + dk - 1 of a row.  Element counts, not bytes.
@@ -230,9 +231,9 @@ hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc
 bool attn_mfma_supported(const AttnDims& a);
 hipError_t launch_attn_fwd_mfma(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a,
                                 hipStream_t st);
-// Whether the backward kernels take this problem with `far` (smallest distance in the saturated last
-// bucket); otherwise the simple backward is used (same saved tensors).
-bool attn_bwd_mfma_fits(const AttnDims& a, int far);
+// Whether the backward kernels take this problem (its `far` above all); otherwise the simple backward is used (same
+// saved tensors).
+bool attn_bwd_mfma_fits(const AttnDims& a);
 // phase 1: dq, the per-query scratch and the bias-gradient diagonals, ADDED into ddiag (the caller clears
 // it); phase 2: dk, dv (reads the scratch, so it runs after phase 1).  dvec here is 2 x [B,H,S] floats:
 // -rowsum(dO * O), then -lse / scale, the two per-query constants the dk/dv kernel stages by DMA.
@@ -241,8 +242,8 @@ bool attn_bwd_mfma_fits(const AttnDims& a, int far);
 // (bit-reproducible) instead of meeting in float atomics.
 size_t attn_ddiag_part_bytes(const AttnDims& a);
 hipError_t launch_attn_bwd_mfma(const AttnIO& io, const void* c, const void* dc, const float* diag,
-                                const float* lse, float* dvec, float* ddiag, const AttnDims& a, int far,
-                                int phase, hipStream_t st, float* ddiag_part = nullptr);
+                                const float* lse, float* dvec, float* ddiag, const AttnDims& a, int phase,
+                                hipStream_t st, float* ddiag_part = nullptr);
 
 // ------------------------------------------------------------------ ends of the layer stack
 // x[r, :] = E[tokens[r], :] (storage type); ids outside [0, vocab) are clamped into it.

@@ -182,8 +182,7 @@ int layers_backward(const Layers& s, const void* enc_out, float* denc_acc, int a
     T5_STEP("zero_grads", launch_zero_f32(z, st));
   }
   const AttnDims ad = self_dims(s.bc, D);
-  const int far = s.lut.n_thr > 0 ? s.lut.thr[s.lut.n_thr - 1] : s.lut.max_exact;
-  const bool attn_mfma = ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad, far);
+  const bool attn_mfma = ty == IN_BF16 && attn_mfma_supported(ad) && attn_bwd_mfma_fits(ad);
   for (int l = s.L - 1; l >= 0; --l) {
     const int n = s.L - 1 - l;  // layers processed so far
     BwdWs& BW = bws[s.grouped ? n : 0];
@@ -202,10 +201,10 @@ int layers_backward(const Layers& s, const void* enc_out, float* denc_acc, int a
     if (dec) {
       // the first layer processed stores its denc, the others add theirs to it
       T5_SUB(bwd_cross_attn(&bc, D, enc_out, &s.xw[l], S, BW, denc_acc, &s.xg[l], acc, st, true, l != s.L - 1));
-      T5_SUB(bwd_self_attn(&bc, D, s.lut, s.x_of(l), BW.dh1, BW.dh1_lp, &s.lw[l], S, BW, attn_mfma, far, dx,
+      T5_SUB(bwd_self_attn(&bc, D, s.lut, s.x_of(l), BW.dh1, BW.dh1_lp, &s.lw[l], S, BW, attn_mfma, dx,
                            &s.lg[l], &s.xg[l], acc, st, false));
     } else {
-      T5_SUB(bwd_self_attn(&bc, D, s.lut, s.x_of(l), BW.dh, BW.dh_lp, &s.lw[l], S, BW, attn_mfma, far, dx,
+      T5_SUB(bwd_self_attn(&bc, D, s.lut, s.x_of(l), BW.dh, BW.dh_lp, &s.lw[l], S, BW, attn_mfma, dx,
                            &s.lg[l], nullptr, acc, st, false));
     }
     // the next layer rewrites the workspace (and, with remat, the stash) the side GEMMs read
