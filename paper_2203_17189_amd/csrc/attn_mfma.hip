@@ -10,11 +10,13 @@
 // operands use the same permutation, and the V^T operand is fetched with that permutation by the
 // LDS transpose load.  The dk/dv kernel mirrors this with one key per lane (S = Q K^T).
 //
-// Dropout of the probabilities (DROP): the keep decision of element
-// ((b*H + h)*S + i, j) is regenerated from the counter-based generator where P is formed -- the lane
-// that owns a query (forward, dq) hashes its row key once, the dk/dv kernel stages the row keys of a
-// query tile in LDS beside -lse and -dvec.  The factor 1/(1 - rate) of the kept probabilities is applied
-// to the finished O and dV accumulators, and to dP before dvec is subtracted.
+// Dropout of the probabilities (DROP): the keep decision of element ((b*H + h)*S + i, j) comes from the counter-based
+// generator in the forward, which leaves it as a bit for the backward (AttnDims::keep; 1/16 of the bytes of a bf16 score):
+// one more instruction an element in the forward, two or three instead of nine in each kernel of the backward.  128 x 512
+// tokens, 12 heads: forward 242 -> 250 us, dq 399 -> 352, dk/dv 371 -> 318.  A lane of the forward and of dq owns a query and
+// 32 keys of a 64-key tile: one word a tile, which dq loads a tile ahead; the dk/dv kernel stages the words of its two key
+// tiles and a query tile in LDS by DMA.  The factor 1/(1 - rate) of the kept probabilities is applied to the finished O and
+// dV accumulators, and to dP before dvec is subtracted.
 //
 // Sequence lengths need not be multiples of the tile sizes: tiles are rounded up, rows past the end are
 // fetched from the last valid row, keys past the end are masked like causal ones, and queries past the end
@@ -285,6 +287,23 @@ __host__ __device__ inline int attn_dq_window_blocks(int S, int far) {
 // Floats per workgroup row of the reproducible bias-gradient buffer: a window is at most 64 * ceil(S / 32)
 // entries wide (+ 4 for the upper lane half) and two sums of the saturated buckets follow it.
 __host__ __device__ inline int attn_ddiag_part_stride(int S) { return 64 * ((S + 31) / 32) + 8; }
+// words between two key tiles of AttnDims::keep: two lane halves of a row of queries each
+__host__ __device__ inline size_t attn_keep_stride(int S) { return (size_t)2 * ((S + 127) / 128 * 128); }
+// the words of a key tile and lane half, one per query
+__device__ __forceinline__ uint32_t* keep_row(const AttnDims& a, size_t bh, int tile, int half) {
+  const size_t stride = attn_keep_stride(a.S);
+  return a.keep + (bh * ((a.Sk + 63) / 64) + tile) * stride + half * (stride / 2);
+}
+// word << 1 | this lane's bit of the wave's mask, as one add with carry
+__device__ __forceinline__ uint32_t shift_in(uint32_t word, uint64_t mask) {
+  uint32_t r;
+  uint64_t carry_out;
+  asm("v_addc_co_u32 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry_out) : "v"(word), "s"(mask));
+  return r;
+}
+// all ones where bit 31 - n of the word is set, else 0 (the builtin: a shift and a test become a comparison and selects)
+__device__ __forceinline__ int keep_mask(uint32_t word, int n) { return __builtin_amdgcn_sbfe(word, 31 - n, 1); }
+__device__ __forceinline__ float keep_if(int mask, float x) { return __builtin_bit_cast(float, mask & __builtin_bit_cast(int, x)); }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // max(x of this lane, x of the lane 32 away).  v_permlane32_swap exchanges lanes 32..63 of its first operand with
 // lanes 0..31 of its second: started from two copies of x, every lane then holds its own value in one of the two
@@ -350,6 +369,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
   const int dg_base = BR - 1 - i_loc;  // dg[dg_base + j] = bias(j - i)
   uint32_t k1 = 0;  // dropout row key of this lane's query
   if constexpr (DROP) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)(((size_t)b * a.H + h) * S + i_ld)));
+  // this lane's words (rows of queries are padded to whole workgroups)
+  uint32_t* keep_q = DROP ? keep_row(a, (size_t)b * a.H + h, 0, g) + i : nullptr;
 
   f32x16 oT[CT];
 #pragma unroll
@@ -447,7 +468,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
     const float alpha = fast_exp2(m - base);
     m = m_new;
     float ls = 0.f;
-    uint32_t kx = 0;
+    uint32_t kx = 0, kept = 0;
     if constexpr (DROP) kx = k1 ^ (uint32_t)(j0 | (g << 2));
 #pragma unroll
     for (int kt = 0; kt < BC / 32; ++kt)
@@ -458,11 +479,16 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
         if constexpr (DROP) {
           // (key index = tile start | lane half << 2 | constant of the register, disjoint bits)
           const uint32_t c = (uint32_t)(kt * 32 + ((r >> 2) << 3) + (r & 3));
-          sT[kt][r] = drop_keep16(a.drop, kx ^ c) ? p : 0.f;
+          const bool keep = drop_keep16(a.drop, kx ^ c);
+          kept = shift_in(kept, __builtin_amdgcn_ballot_w64(keep));
+          float pk = keep ? p : 0.f;
+          asm("" : "+v"(pk));  // (a select of the bf16 values instead would cost a conversion and a permute each)
+          sT[kt][r] = pk;
         } else {
           sT[kt][r] = p;
         }
       }
+    if constexpr (DROP) keep_q[jt * attn_keep_stride(S)] = kept;
     l = l * alpha + ls;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
@@ -507,7 +533,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
 // scalar per lane; it is credited to the outermost diagonal, which is in the same bucket.
 // ------------------------------------------------------------------------------------------------
 template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
-__global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mfma_kernel(AttnIO io,
+// (three waves per SIMD with 64 channels; with dropout and without the causal mask they would spill: 32 x 512 tokens, 12
+// heads, causal 86 -> 75 us, 128 x 512 not causal 351 -> 393)
+__global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void attn_bwd_dq_mfma_kernel(AttnIO io,
                                                                const bf16* __restrict__ o,
                                                                const bf16* __restrict__ dout,
                                                                const float* __restrict__ diag,
@@ -573,13 +601,18 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
     dvec[(size_t)a.B * a.H * S + srow] = lse_q * (-1.f / a.scale);
   }
   const float nlse2 = -lse_q * kLog2e, ndv = -dsum;
-  uint32_t k1 = 0;  // dropout row key of this lane's query
-  if constexpr (DROP) k1 = drop_row_pre(drop_row_key(a.drop, (uint32_t)srow));
+  // this lane's words of keep decisions, and that of the next key tile
+  const uint32_t* keep_q = DROP ? keep_row(a, (size_t)b * a.H + h, 0, g) + i : nullptr;
+  uint32_t kept_next = DROP ? keep_q[0] : 0;
   // dP of a kept probability carries the factor 1/(1 - rate); that of a dropped one is zero
-  // (kx: row key with the sub-tile's key index and the lane half in it, r: result register)
-  auto dp_masked = [&](float dp, uint32_t kx, int r) {
-    if constexpr (DROP) return drop_keep16(a.drop, kx ^ (uint32_t)(((r >> 2) << 3) + (r & 3))) ? dp * a.drop.scale : 0.f;
-    else return dp;
+  auto dp_masked = [&](float dp, uint32_t kept, int n) {
+    if constexpr (DROP) {
+      int mask = keep_mask(kept, n);
+      asm("" : "+v"(mask));  // (a constant bit would become a test and a select)
+      return keep_if(mask, dp * a.drop.scale);
+    } else {
+      return dp;
+    }
   };
   if constexpr (BIAS) {
     const float* dgh = diag + (size_t)h * (2 * S - 1);
@@ -614,9 +647,13 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
   for (int jt = 0; jt < n_kv; ++jt) {
     const int j0 = jt * BC;
     dma_wait_barrier();  // tile jt landed; every wave is done with the other stage
+    // (an empty use: the compiler's wait for the word belongs here, before the next tile's DMA is on its way)
+    const uint32_t kept = kept_next;
+    if constexpr (DROP) asm volatile("" ::"v"(kept));
     if (jt + 1 < n_kv) {
       const uint32_t nxt = lds0 + ((jt + 1) & 1) * STG;
       const TileDma<DK, BC>& tn = jt + 1 == jt_tail ? td_tail : td;
+      if constexpr (DROP) kept_next = keep_q[(jt + 1) * attn_keep_stride(S)];
       tn.issue(nxt, kbase + (size_t)(j0 + BC) * ld, wave);
       tn.issue(nxt + TILE, vbase + (size_t)(j0 + BC) * ld, wave);
     }
@@ -676,21 +713,19 @@ __global__ __launch_bounds__(256, DK == 64 && !DROP ? 3 : 2) void attn_bwd_dq_mf
       __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
       // sub-tile reaches above the diagonal, past the last key, or this wave holds queries past the end
       // (all wave-uniform)
-      uint32_t kx = 0;
-      if constexpr (DROP) kx = k1 ^ (uint32_t)(j0s | (g << 2));
       if ((CAUSAL && !WIN && j0s + 31 > i_w0) || j0s + 32 > Sk || i_w0 + 32 > S) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int j = j0s + ((r >> 2) << 3) + (g << 2) + (r & 3);
           float p = BIAS ? fast_exp2(fmaf(sT[r], sc, bias[r]) + nlse2) : fast_exp2(fmaf(sT[r], sc, nlse2));
           if ((CAUSAL && j > i) || j >= Sk || !q_ok) p = 0.f;
-          sT[r] = p * (dp_masked(dpT[r], kx, r) + ndv);
+          sT[r] = p * (dp_masked(dpT[r], kept, kt * 16 + r) + ndv);
         }
       } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float p = BIAS ? fast_exp2(fmaf(sT[r], sc, bias[r]) + nlse2) : fast_exp2(fmaf(sT[r], sc, nlse2));
-          sT[r] = p * (dp_masked(dpT[r], kx, r) + ndv);
+          sT[r] = p * (dp_masked(dpT[r], kept, kt * 16 + r) + ndv);
         }
       }
       // ---- bias gradient of this 32x32 sub-tile (wave-uniform branches)
@@ -826,8 +861,8 @@ __global__ __launch_bounds__(256) void attn_ddiag_reduce_kernel(const float* __r
 // ------------------------------------------------------------------------------------------------
 // dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
 // ------------------------------------------------------------------------------------------------
-// Two forms.  This one takes a tile at a time from two stages: without the causal mask (64 channels), where two or three
-// waves per SIMD cover for each other, and with dropout, whose masks take the registers.
+// Two forms.  This one takes a tile at a time from two stages: 64 channels without the causal mask, where two or three
+// waves per SIMD cover for each other, or with dropout (causal 32 x 512, 12 heads: 68 us, the other form 72).
 template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool THREE, bool WIN>
 __global__ __launch_bounds__(256, DK == 64 ? (THREE ? 3 : 2) : 1)
 void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
@@ -839,10 +874,11 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
   float* lse_all = reinterpret_cast<float*>(smem + 2 * STG);  // [2 stages][BQ]  -lse / scale
   float* dv_all = lse_all + 2 * BQ;                           // [2 stages][BQ]  -dvec
-  uint32_t* key_all = reinterpret_cast<uint32_t*>(dv_all + 2 * BQ);  // [2 stages][BQ] dropout row keys (DROP only)
+  // [2 stages][2 key tiles][2][BQ] keep decisions (DROP only)
+  uint32_t* keep_all = reinterpret_cast<uint32_t*>(dv_all + 2 * BQ);
   // Window, or [-BQ, S + BCK - 1), log2 units (BIAS only); the slice's BQ entries in front are only ever read for
   // queries past the end of a ragged last tile, whose probabilities are set to zero
-  float* dg = dv_all + 2 * BQ + (DROP ? 2 * BQ : 0) + (WIN ? 0 : BQ);
+  float* dg = dv_all + 2 * BQ + (DROP ? 8 * BQ : 0) + (WIN ? 0 : BQ);
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -876,6 +912,11 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   const float* ndvec = dvec + srow;
   const float* nlse = dvec + (size_t)a.B * a.H * S + srow;
   const uint32_t lds_lse = lds0 + 2 * STG, lds_dv = lds_lse + 2 * BQ * 4;
+  // wave w fetches half w & 1 of key tile w >> 1 (past the last key: of the last tile, for keys that are not stored)
+  const uint32_t lds_keep = lds_dv + 2 * BQ * 4;
+  const int keep_jt = min(j0 / 64 + (wave >> 1), (Sk + 63) / 64 - 1);
+  const uint32_t* keep_w = DROP ? keep_row(a, (size_t)b * a.H + h, keep_jt, wave & 1) : nullptr;
+  const int keep_n = (wave & 1) * 16 + ((lane >> 3) & 3) * 4 + (lane & 3);  // this lane's key in a word
   auto issue = [&](int stage, int it) __attribute__((always_inline)) {
     const int q_first = it * BQ;
     const uint32_t dst = lds0 + stage * STG;
@@ -884,12 +925,7 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
     const int qi = q_first + lane < S ? q_first + lane : S - 1;  // (rows past the end are masked)
     if (wave == 0) dma_64f(lds_lse + stage * BQ * 4, nlse, (uint32_t)qi * 4u);
     if (wave == 1) dma_64f(lds_dv + stage * BQ * 4, ndvec, (uint32_t)qi * 4u);
-    if constexpr (DROP) {
-      if (tid < BQ) {
-        const int qk = q_first + tid < S ? q_first + tid : S - 1;
-        key_all[stage * BQ + tid] = drop_row_pre(drop_row_key(a.drop, (uint32_t)(srow + qk)));
-      }
-    }
+    if constexpr (DROP) dma_64f(lds_keep + (stage * 4 + wave) * BQ * 4, keep_w + q_first, (uint32_t)lane * 4u);
   };
 
   bf16x8 kf[KS], vf[KS];
@@ -982,16 +1018,16 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   auto softmax = [&](auto tail, int stage, int qb, int q0, f32x16& s, f32x16& dp, const float (&bias)[16])
       __attribute__((always_inline)) {
     const float* dv_s = dv_all + stage * BQ;
-    const uint32_t* key_s = key_all + stage * BQ;
+    const uint32_t* keep_s = keep_all + (stage * 4 + (wave & 2) + ((lane >> 2) & 1)) * BQ;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int ir = ((r >> 2) << 3) + (g << 2) + (r & 3), il = qb * 32 + ir;
       float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
       if ((CAUSAL && !WIN && j > q0 + ir) || (decltype(tail)::value && q0 + ir >= S)) p = 0.f;
       if constexpr (DROP) {
-        const bool keep = drop_keep16(a.drop, key_s[il] ^ (uint32_t)j);
-        s[r] = keep ? p : 0.f;
-        dp[r] = p * ((keep ? dp[r] * a.drop.scale : 0.f) + dv_s[il]);
+        const int mask = keep_mask(keep_s[il], keep_n);
+        s[r] = keep_if(mask, p);
+        dp[r] = p * (keep_if(mask, dp[r] * a.drop.scale) + dv_s[il]);
       } else {
         s[r] = p;
         dp[r] = p * dp[r];
@@ -1046,12 +1082,12 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
 // ------------------------------------------------------------------------------------------------
 // dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
 // ------------------------------------------------------------------------------------------------
-// The pipelined form (128 channels, and causal; no dropout).  A unit is 32 queries x 32 keys; its dV / dK products follow the
+// The pipelined form (128 channels, and 64 causal without dropout).  A unit is 32 queries x 32 keys; its dV / dK products follow the
 // score products of the next unit and run beside that unit's softmax arithmetic, across the tiles' barriers too (a ring of
 // three tile stages).  With 128 channels one wave has a SIMD to itself, and in program order matrix and vector unit took
 // turns (28 % and 26 % busy): 16 x 2048 tokens causal, 16 heads 950 -> 843 us, 8 x 2048 not causal 740 -> 650; 64 channels
 // causal, 8 x 2048, 12 heads 167 -> 148, 32 x 512 67 -> 62.  64 channels without the mask: 1-4 % slower than the other form.
-template <int DK, bool CAUSAL, bool BIAS, bool WIN>
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
 __global__ __launch_bounds__(256, DK == 64 ? 2 : 1)
 void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
                               const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
@@ -1062,9 +1098,11 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
   float* lse_all = reinterpret_cast<float*>(smem + 3 * STG);  // [3 stages][BQ]  -lse / scale
   float* dv_all = lse_all + 3 * BQ;                           // [3 stages][BQ]  -dvec
+  // [3 stages][2 key tiles][2][BQ] keep decisions (DROP only)
+  uint32_t* keep_all = reinterpret_cast<uint32_t*>(dv_all + 3 * BQ);
   // Window, or [-BQ, S + BCK - 1), log2 units (BIAS only); the slice's BQ entries in front are only ever read for
   // queries past the end of a ragged last tile, whose probabilities are set to zero
-  float* dg = dv_all + 3 * BQ + (WIN ? 0 : BQ);
+  float* dg = dv_all + 3 * BQ + (DROP ? 12 * BQ : 0) + (WIN ? 0 : BQ);
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1096,6 +1134,11 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   const float* ndvec = dvec + srow;
   const float* nlse = dvec + (size_t)a.B * a.H * S + srow;
   const uint32_t lds_lse = lds0 + 3 * STG, lds_dv = lds_lse + 3 * BQ * 4;
+  // wave w fetches half w & 1 of key tile w >> 1 (past the last key: of the last tile, for keys that are not stored)
+  const uint32_t lds_keep = lds_dv + 3 * BQ * 4;
+  const int keep_jt = min(j0 / 64 + (wave >> 1), (Sk + 63) / 64 - 1);
+  const uint32_t* keep_w = DROP ? keep_row(a, (size_t)b * a.H + h, keep_jt, wave & 1) : nullptr;
+  const int keep_n = (wave & 1) * 16 + ((lane >> 3) & 3) * 4 + (lane & 3);  // this lane's key in a word
   auto issue = [&](int stage, int it) __attribute__((always_inline)) {
     const int q_first = it * BQ;
     const uint32_t dst = lds0 + stage * STG;
@@ -1104,6 +1147,7 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
     const int qi = q_first + lane < S ? q_first + lane : S - 1;  // (rows past the end are masked)
     if (wave == 0) dma_64f(lds_lse + stage * BQ * 4, nlse, (uint32_t)qi * 4u);
     if (wave == 1) dma_64f(lds_dv + stage * BQ * 4, ndvec, (uint32_t)qi * 4u);
+    if constexpr (DROP) dma_64f(lds_keep + (stage * 4 + wave) * BQ * 4, keep_w + q_first, (uint32_t)lane * 4u);
   };
 
   issue(0, it_begin);
@@ -1165,7 +1209,7 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
       const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + qb * 32 + rq * 8 + g * 4);
       const f32x4 d4 = *reinterpret_cast<const f32x4*>(dv_s + qb * 32 + rq * 8 + g * 4);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { s[rq * 4 + e] = l4[e]; dp[rq * 4 + e] = d4[e]; }
+      for (int e = 0; e < 4; ++e) { s[rq * 4 + e] = l4[e]; dp[rq * 4 + e] = DROP ? 0.f : d4[e]; }
     }
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
@@ -1194,13 +1238,21 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   auto softmax = [&](int stage, int qb, int q0, int mm, const f32x16& s, const f32x16& dp, const float (&bias)[16],
                      bf16x8& pf, bf16x8& dsf) __attribute__((always_inline)) {
     const float* dv_s = dv_all + stage * BQ;
+    const uint32_t* keep_s = keep_all + (stage * 4 + (wave & 2) + ((lane >> 2) & 1)) * BQ;
     const int j = j0 + j_loc;
 #pragma unroll
     for (int r = mm * 8; r < mm * 8 + 8; ++r) {
       float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
       if (CAUSAL && !WIN && j - q0 > ((r >> 2) << 3) + (g << 2) + (r & 3)) p = 0.f;
-      pf[r & 7] = (bf16)p;
-      dsf[r & 7] = (bf16)(p * dp[r]);
+      if constexpr (DROP) {
+        const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+        const int mask = keep_mask(keep_s[il], keep_n);
+        pf[r & 7] = (bf16)keep_if(mask, p);
+        dsf[r & 7] = (bf16)(p * (keep_if(mask, dp[r] * a.drop.scale) + dv_s[il]));
+      } else {
+        pf[r & 7] = (bf16)p;
+        dsf[r & 7] = (bf16)(p * dp[r]);
+      }
     }
   };
   auto outer = [&](int stage, int qb, int mm, const bf16x8& pf, const bf16x8& dsf) __attribute__((always_inline)) {
@@ -1256,7 +1308,7 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
     const int j_b0 = j_w0;
     const size_t row0 = (size_t)b * Sk + j_b0;
     store_rows<DK>(stage, dkT, a.scale, (bf16*)io.dk + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv, Sk - j_b0, lane);
-    store_rows<DK>(stage, dvT, 1.f, (bf16*)io.dv + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv,
+    store_rows<DK>(stage, dvT, DROP ? a.drop.scale : 1.f, (bf16*)io.dv + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv,
                    Sk - j_b0, lane);
   }
 }
@@ -1312,9 +1364,9 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
   if (phase == 2) {
     const size_t bias = sizeof(float) * (WIN ? BiasWin(a.S, a.far, CAUSAL).floats() : BIAS ? 64 + a.S + 127 : 0);
     const int wgs = ((a.Sk + 127) / 128) * a.H * a.B;
-    if constexpr (!DROP && (DK == 128 || CAUSAL)) {
-      auto kern = attn_bwd_dkv_pipe_kernel<DK, CAUSAL, BIAS, WIN>;
-      const size_t lds = 3 * (2 * 64 * DK * 2 + sizeof(float) * 128) + bias;
+    if constexpr (DK == 128 || (CAUSAL && !DROP)) {
+      auto kern = attn_bwd_dkv_pipe_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
+      const size_t lds = 3 * (2 * 64 * DK * 2 + sizeof(float) * (128 + (DROP ? 256 : 0))) + bias;
       if ((e = set_lds(kern, lds)) != hipSuccess) return e;
       kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
     } else {
@@ -1324,7 +1376,7 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
       constexpr bool CAN_THREE = DK == 64 && !BIAS && !DROP;
       auto kern = CAN_THREE && wgs > 512 ? attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, CAN_THREE, WIN>
                                          : attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, false, WIN>;
-      const size_t lds = 2 * (2 * 64 * DK * 2 + sizeof(float) * (128 + (DROP ? 64 : 0))) + bias;
+      const size_t lds = 2 * (2 * 64 * DK * 2 + sizeof(float) * (128 + (DROP ? 256 : 0))) + bias;
       if ((e = set_lds(kern, lds)) != hipSuccess) return e;
       kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
     }
@@ -1361,7 +1413,7 @@ bool attn_mfma_supported(const AttnDims& a) {
 
 hipError_t launch_attn_fwd_mfma(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a,
                                 hipStream_t st) {
-  if (!attn_mfma_supported(a)) return hipErrorInvalidValue;
+  if (!attn_mfma_supported(a) || (a.drop.on && !a.keep)) return hipErrorInvalidValue;
   const int mode = attn_mode(a);
   if (a.drop.on) {
     if (a.dk == 64) {
@@ -1383,6 +1435,10 @@ hipError_t launch_attn_fwd_mfma(const AttnIO& io, const float* diag, void* c, fl
   return fwd_launch<128, false, false>(io, diag, c, lse, a, st);
 }
 
+size_t attn_keep_bytes(const AttnDims& a) {
+  return a.drop.on ? (size_t)a.B * a.H * ((a.Sk + 63) / 64) * attn_keep_stride(a.S) * sizeof(uint32_t) : 0;
+}
+
 size_t attn_ddiag_part_bytes(const AttnDims& a) {
   return (size_t)a.B * a.H * ((a.S + 127) / 128) * (size_t)attn_ddiag_part_stride(a.S) * sizeof(float);
 }
@@ -1394,7 +1450,7 @@ hipError_t launch_attn_bwd_mfma(const AttnIO& io, const void* c, const void* dc,
   // (reads the dvec phase 1 wrote).
   // a.far: smallest distance that falls in the last (saturated) bucket; such offsets need no
   // per-diagonal resolution.  Never below 1, so offset 0 always takes the per-diagonal path.
-  if (!attn_mfma_supported(a)) return hipErrorInvalidValue;
+  if (!attn_mfma_supported(a) || (a.drop.on && !a.keep)) return hipErrorInvalidValue;
   const int mode = attn_mode(a);
   if (a.drop.on) {
     if (a.dk == 64) {

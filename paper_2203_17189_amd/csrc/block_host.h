@@ -98,6 +98,7 @@ struct Carver {
 
 struct Stash {
   float *r1, *r2, *lse, *h, *diag;
+  uint32_t *keep, *keep_x;  // AttnDims::keep of the two attentions
   // gp = w * gelu'(u) and gl = gelu(u) are the saved factors of the gated GELU (u, w: the wi_0 / wi_1
   // projections); the simple path uses the two buffers for u and w first and converts them in place.
   void *n1, *qkv, *c, *n2, *gp, *gl, *a;
@@ -105,6 +106,14 @@ struct Stash {
   float *rx, *lse_x, *h2;
   void *nx, *qx, *kvx, *cx;  // qx [T, I]; kvx [Te, 2I] (k | v per encoder token); cx [T, I]
 };
+// AttnDims::keep of a layer's self-attention or, cross, of its cross-attention: bytes, 0 where the kernels don't use it.
+size_t keep_bytes(const Dims& D, bool cross) {
+  if (D.drop == 0.f || D.ty != IN_BF16) return 0;
+  AttnDims ad;
+  std::memset(&ad, 0, sizeof(ad));
+  ad.B = D.B; ad.S = D.S; ad.H = D.H; ad.dk = D.dk; ad.Sk = cross ? D.Sk : D.S; ad.bias = !cross; ad.drop.on = 1;
+  return attn_mfma_supported(ad) ? attn_keep_bytes(ad) : 0;
+}
 size_t carve_stash(const Dims& D, void* base, Stash* s) {
   Carver cv(base);
   Stash t;
@@ -121,7 +130,9 @@ size_t carve_stash(const Dims& D, void* base, Stash* s) {
   t.gp = cv.take((size_t)D.T * D.F * D.es);
   t.gl = cv.take((size_t)D.T * D.F * D.es);
   t.a = cv.take((size_t)D.T * D.F * D.es);
+  t.keep = cv.take<uint32_t>(keep_bytes(D, false));
   if (D.Sk > 0) {
+    t.keep_x = cv.take<uint32_t>(keep_bytes(D, true));
     t.rx = cv.take<float>(D.T * 4);
     t.lse_x = cv.take<float>((size_t)D.B * D.H * D.S * 4);
     t.h2 = cv.take<float>((size_t)D.T * D.d * 4);
@@ -446,10 +457,10 @@ bool grads_present(const t5_block_grads* g, const Dims& D) {
 }
 
 AttnDims self_dims(const t5_block_cfg* cfg, const Dims& D) {
-  return AttnDims{D.B, D.S, D.H, D.dk, cfg->causal ? 1 : 0, cfg->attn_scale, D.S, 1, drop_site(D, DROP_ATTN_PROBS), D.far};
+  return AttnDims{D.B, D.S, D.H, D.dk, cfg->causal ? 1 : 0, cfg->attn_scale, D.S, 1, drop_site(D, DROP_ATTN_PROBS), D.far, nullptr};
 }
 AttnDims cross_dims(const t5_block_cfg* cfg, const Dims& D) {
-  return AttnDims{D.B, D.S, D.H, D.dk, 0, cfg->attn_scale, D.Sk, 0, drop_site(D, DROP_CROSS_PROBS), 1};
+  return AttnDims{D.B, D.S, D.H, D.dk, 0, cfg->attn_scale, D.Sk, 0, drop_site(D, DROP_CROSS_PROBS), 1, nullptr};
 }
 AttnIO cross_io(const Dims& D, const Stash& S, const BwdWs* W) {
   AttnIO io;
@@ -538,7 +549,8 @@ int fwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
                   bool own_table = true) {
   const int T = (int)D.T, ty = D.ty;
   const size_t es = D.es;
-  const AttnDims ad = self_dims(cfg, D);
+  AttnDims ad = self_dims(cfg, D);
+  ad.keep = S.keep;
   if (own_table && W.direct) {
     T5_STEP("rmsnorm_fwd", launch_rmsnorm_fwd_diag(x, w->ln1_scale, S.n1, S.r1, T, D.d, cfg->rms_eps, w->rel_table, S.diag, D.S,
                                                    D.H, lut, st));
@@ -581,7 +593,8 @@ int fwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
                    const Stash& S, const FwdWs& W, bool fused, hipStream_t st) {
   const int T = (int)D.T, Te = (int)D.Te, ty = D.ty;
   const size_t es = D.es;
-  const AttnDims ad = cross_dims(cfg, D);
+  AttnDims ad = cross_dims(cfg, D);
+  ad.keep = S.keep_x;
   T5_STEP("rmsnorm_fwd", launch_rmsnorm_fwd(S.h, IN_F32, xw->lnx_scale, S.nx, ty, S.rx, T, D.d, cfg->rms_eps, st));
   if (W.direct) {
     T5_STEP("gemm_xq", run_direct(T, D.I, D.d, S.nx, &xw->xq, 1, epi(EPI_STORE, S.qx, D.I, ty), st));
@@ -754,7 +767,8 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
                    bool denc_f32 = false, bool denc_add = false) {
   const int T = (int)D.T, Te = (int)D.Te, ty = D.ty;
   const size_t es = D.es;
-  const AttnDims ad = cross_dims(cfg, D);
+  AttnDims ad = cross_dims(cfg, D);
+  ad.keep = S.keep_x;
   const void* dh_op = ty == IN_BF16 ? (const void*)W.dh_lp : (const void*)W.dh;
   if (D.drop > 0.f) {
     T5_STEP("dropout_dh", launch_dropout_apply(drop_site(D, DROP_CROSS_OUT), dh_op, W.dmask_x, ty, T, D.d, st));
@@ -813,7 +827,8 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
                   bool own_table = true) {
   const int T = (int)D.T, ty = D.ty;
   const size_t es = D.es;
-  const AttnDims ad = self_dims(cfg, D);
+  AttnDims ad = self_dims(cfg, D);
+  ad.keep = S.keep;
   const void* dh_op = ty == IN_BF16 ? dh_lp : (const void*)dh;
   if (D.drop > 0.f) {
     T5_STEP("dropout_dh", launch_dropout_apply(drop_site(D, DROP_ATTN_OUT), dh_op, W.dmask_a, ty, T, D.d, st));

@@ -196,6 +196,10 @@ struct AttnDims {
   int bias;
   DropSite drop;  // dropout of the probabilities; row = (b*H + h)*S + i, column = j
   int far;        // with bias: smallest distance in the last (saturated) bucket of its side, at least 1
+  // MFMA kernels, with dropout: the keep decisions of the probabilities, attn_keep_bytes() that the forward writes and the
+  // backward reads.  Word [b*H + h][j / 64][(j >> 2) & 1][i], rows of S rounded up to 128 words; key j has bit
+  // 31 - 16 * ((j >> 5) & 1) - 4 * ((j >> 3) & 3) - (j & 3).
+  uint32_t* keep;
 };
 // Operand placement.  Row (b*S + i) of q / dq starts at q + row*ldq, row (b*Sk + j) of k, v / dk, dv at
 // k + row*ldkv; head h occupies channels h*dk .. h*dk + dk - 1 of a row.  Element counts, not bytes.
@@ -229,6 +233,7 @@ hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, fl
 hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
                                float* dvec, float* ddiag, const AttnDims& a, hipStream_t st);
 bool attn_mfma_supported(const AttnDims& a);
+size_t attn_keep_bytes(const AttnDims& a);  // of AttnDims::keep (0 without dropout)
 hipError_t launch_attn_fwd_mfma(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a,
                                 hipStream_t st);
 // Whether the backward kernels take this problem (its `far` above all); otherwise the simple backward is used (same
