@@ -138,6 +138,9 @@ __device__ __forceinline__ void cursor_next(KCursor& c, const char*& abase, cons
 // EPI_T: the epilogue kind, plus EPI_DROP when the result passes a dropout site (a separate instantiation,
 // so that the kernels without dropout keep their register budget).
 constexpr int EPI_DROP = 8;
+// k-tiles of 64 in three stages of A and two of B: the whole LDS for 256x256 tiles, half of it for 128x128
+template <int BM, int BN, int NS, int BK>
+constexpr bool ab_ring = BK == 64 && NS == 3 && (BM == 256 || (BM == 128 && BN == 128));
 // ... plus EPI_GROUP for a grouped launch (several problems of one shape, operands from a pointer table).
 constexpr int EPI_GROUP = 16;
 template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, int EPI_T, int NS, int MINW, int BK>
@@ -147,7 +150,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
   constexpr bool DROP = (EPI_T & EPI_DROP) != 0;
   constexpr bool GROUP = (EPI_T & EPI_GROUP) != 0;
   constexpr int NW = WM * WN;
-  constexpr bool AB32 = BK == 64 && NS == 3 && BM == 256;  // three stages of A and two of B (see ab_loop)
+  constexpr bool AB32 = ab_ring<BM, BN, NS, BK>;  // three stages of A and two of B (see ab_loop)
   constexpr int TMW = BM / WM, TNW = BN / WN;
   constexpr int MI = TMW / 32, NI = TNW / 32;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
@@ -469,14 +472,15 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_mfma_kernel(GemmDesc 
     // tile t in A stage sa and B stage sb; an: A of tile t+2, bn: B of tile t+1
     auto ktile = [&](int sa, int sb) __attribute__((always_inline)) {
       constexpr int QA = A_DMA / 2 / MI;  // A's DMA instructions per group of MFMAs
+      constexpr int G1 = MI > 2 ? 1 : 0;  // the gaps that move the cursors
       constexpr int HB = B_DMA / 2;       // B's: half in each of two k-steps, over the groups (256x192 tiles: 0 1 1 1)
       static_assert(QA * 2 * MI == A_DMA && HB * 2 == B_DMA, "shares of the groups");
       const char *a2 = an, *b2 = bn;
       step(0, sa, sb, 1, [&](int i) __attribute__((always_inline)) { dma_b(bn, sb ^ 1, HB + i * HB / MI, HB + (i + 1) * HB / MI); },
-           [&](int i) __attribute__((always_inline)) { if (i == 1) cursor_bases<MULTI>(kb, skip, b2); if (i == 2) cursor_counts<MULTI>(kb); });
+           [&](int i) __attribute__((always_inline)) { if (i == G1) cursor_bases<MULTI>(kb, skip, b2); if (i == G1 + 1) cursor_counts<MULTI>(kb); });
       step(1, sa, sb, 2, [&](int i) __attribute__((always_inline)) { dma_a(an, (sa + 2) % 3, i * QA, (i + 1) * QA); }, no_gap);
       step(0, sa, sb, 3, [&](int i) __attribute__((always_inline)) { dma_a(an, (sa + 2) % 3, A_DMA / 2 + i * QA, A_DMA / 2 + (i + 1) * QA); },
-           [&](int i) __attribute__((always_inline)) { if (i == 1) cursor_bases<MULTI>(ka, a2, skip); if (i == 2) cursor_counts<MULTI>(ka); });
+           [&](int i) __attribute__((always_inline)) { if (i == G1) cursor_bases<MULTI>(ka, a2, skip); if (i == G1 + 1) cursor_counts<MULTI>(ka); });
       an = a2; bn = b2;
       // tile t+1 has landed but for nothing (only A of tile t+2, requested last, may be in flight), and this
       // wavefront's reads of tile t are done
@@ -872,7 +876,7 @@ bool split_partials_ok(const GemmDesc& g, const GemmEpi& e) {
 template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, int EPI, int NS = 4, int MINW = 1, int BK = 32>
 hipError_t launch_cfg(const GemmDesc& g, const GemmEpi& e, int split_k, hipStream_t st) {
   auto kern = gemm_mfma_kernel<BM, BN, WM, WN, A_KC, B_KC, EPI, NS, MINW, BK>;
-  constexpr int lds_loop = (BK == 64 && NS == 3 && BM == 256 ? 3 * BM + 2 * BN : NS * (BM + BN)) * BK * 2;
+  constexpr int lds_loop = (ab_ring<BM, BN, NS, BK> ? 3 * BM + 2 * BN : NS * (BM + BN)) * BK * 2;
   constexpr int lds_epi = WM * WN * 64 * (BN / WN + 8) * 4;
   constexpr int lds = lds_loop > lds_epi ? lds_loop : lds_epi;
   // once per instantiation; setting it twice is harmless, so a relaxed flag is enough
@@ -921,7 +925,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    fastest where its last round over the 256 compute units is full (32768 x 6144 x 2048: 646 us against 770); also
     //    for the residual epilogue with dropout (32768 x 2048 x 5120 557 us against 675 with 128x128 and 736 with 256x128;
     //    65536 x 768 x 2048 209, 231, 242);
-    //  * 128x128, two workgroups per compute unit, two stages: a round of 512 tiles costs w of a 256x256 round, which
+    //  * 128x128, two workgroups per compute unit: a round of 512 tiles costs w of a 256x256 round, which
     //    is four times the work for w = 0.62 (plain store and gated-GELU forward; 0.53 at K < 640, 0.40 for a plain store
     //    whose last 256 columns are not all there: 12800 x 1152 x 512 40 us with 256x256, 25 with this, 25600 rows 59 and
     //    43), 0.56 and 0.49 (K <= 768)
@@ -929,7 +933,11 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    costs 0.65 of a full one, as much as a full one from K = 1024 on.  The cheaper sum of rounds is taken
     //    (14592 x 768 x 2304, 171 against 684 tiles: 59 us against 68; 8991 x 768 x 4096, 108 against 426: 92 against 64).
     //    The gated-GELU backward, two tensors in and two out, always takes it (32768 x 5120 x 2048: 1149 us with 256x256,
-    //    850 with 256x128, 753 with this);
+    //    850 with 256x128, 761 with this in two stages, 730 with three stages of A and two of B, which fill the half of the
+    //    LDS that a workgroup has: a tile's requests spread over the whole period between two barriers).  The others have
+    //    those stages from K = 1024 on (8991 x 768 x 4096 64.7 -> 59.5 us, 8991 x 768 x 2304 41.6 -> 38.6, 2048 x 10240 x 2048
+    //    gated 108 -> 101) and two up to there, where the longer ramp costs as much as it gives (8991 x 2304 x 768 42 -> 41 and
+    //    46 in two runs, 32768 x 1152 x 512 54 -> 51 and 57);
     //  * 256x192, the same loop with three quarters of the columns, where that fills rounds that 256x256 leaves part empty
     //    (widths of 768: 16384 x 768 is 192 tiles of 256x256 and 256 of these).  A round costs 0.88 of a 256x256 one, not
     //    0.75: more units share the power and the L2.  k 4096 98 -> 92 us, 2048 62 -> 57, 768 30 -> 26; 16384 x 2304 x 768,
@@ -966,7 +974,8 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
         return launch_cfg<256, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 2>(g, e, 1, st);
     if constexpr (EPI != EPI_GEGLU_BWD)
       if (c256 <= c128) return launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
-    return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 2, 1, 64>(g, e, 1, st);
+    if (EPI == EPI_GEGLU_BWD || K >= 1024) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
+    if constexpr (EPI != EPI_GEGLU_BWD) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 2, 1, 64>(g, e, 1, st);
   }
 }
 

@@ -40,6 +40,7 @@ hipError_t launch_direct(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     }
     return launch_cfg<128, 128, 2, 2, true, false, EPI, 4, 1>(g, e, 1, st);
   }
+  // (three stages of A and two of B lose here: 8192 x 2048 x 512 gated 32 -> 37 us)
   return launch_cfg<128, 128, 2, 2, true, false, EPI, 2, 1, 64>(g, e, 1, st);
 }
 

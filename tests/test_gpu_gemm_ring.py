@@ -1,0 +1,28 @@
+"""128x128 tiles of the bf16 GEMM with three stages of A and two of B: every remainder of the loop's six-tile rounds, and the
+gated-GELU backward, which always takes them, with as few k-tiles as a layer can have."""
+import pytest
+
+import synth_inputs as SI
+from oracle import t5_oracle as O
+from parity_util import block_floors, check_bf16, make_case, rel_err, run_block_gpu
+from test_gpu_gemm_tiles import _check_gemm, _tile
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nk", range(16, 22))
+def test_every_loop_remainder(nk):
+    assert _tile(5000, 1032, 64 * nk) == "128x128, two per unit"   # last tiles of 8 rows and 8 columns
+    _check_gemm(5000, 1032, 64 * nk, True)
+
+
+@pytest.mark.parametrize("d_model", [64, 128, 192])   # one, two and three k-tiles
+def test_gated_gelu_backward_few_k_tiles(d_model):
+    # 4224 x 1024: 264 tiles, more than one per compute unit
+    cfg = SI.BlockConfig(f"gemm_ring_{d_model}", 64, 64, 66, d_model, 1, 64, 1024, attn_scale=0.125)
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
+    check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
