@@ -944,9 +944,11 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    three rounds of each: 73 -> 69; 8991 x 2304 x 768, two rounds against 2.5 of 128x128: 42 with those, 50 with this;
     //  * 256x128, two workgroups, k-tiles of 32 in three stages: gated-GELU forward up to K = 704, residual up to K = 512
     //    (32768 x 512 x 384: 31 us against 32 and 34);
-    //  * up to 256 tiles of 128x128 (one per compute unit): latency counts, so more stages (k-tiles of 32 in four) and,
+    //  * up to 256 tiles of 128x128 (one per compute unit): latency counts, so more stages (four of 64, 128 KB) and,
     //    while they fit one round, smaller tiles, 128x64 and 64x64 (1332 x 768 x 2048 with residual: 37 us -> 21;
-    //    1332 x 768 x 768: 25 -> 18).
+    //    1332 x 768 x 768: 25 -> 18).  What bounds them is the path from L2 to LDS, 65 GB/s a compute unit with rows of 128 bytes:
+    //    four stages of 32 (rows of 64 bytes) took 39.9 us for 3648 x 768 x 4096, these 31.9; k 2304 30.4 and 25.3, 2048 29.5 and
+    //    25.3, 768 14.8 and 13.5; three stages of 64 43.
     int64_t K = 0;
     for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
     const double last = K >= 1024 ? 1.0 : 0.65;
@@ -961,7 +963,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
         if ((int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 64) <= 256)
           return launch_cfg<128, 64, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
       }
-      return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
+      return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1, 64>(g, e, 1, st);
     }
     if constexpr (EPI_T == EPI_STORE || EPI_T == EPI_RESID) {  // (the dropout copies are not built: 14592 x 768 x 2048 with residual 65 us, 59 like this)
       if (g.N % 192 == 0) {

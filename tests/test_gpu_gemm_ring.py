@@ -26,3 +26,22 @@ def test_gated_gelu_backward_few_k_tiles(d_model):
     gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
     errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
     check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
+
+
+@pytest.mark.parametrize("nk", range(1, 7))
+def test_one_tile_per_unit_every_loop_remainder(nk):
+    """Four stages of 64: as many k-tiles as there are stages, fewer, more; last tiles of 64 rows and 8 columns."""
+    assert _tile(3648, 776, 64 * nk) == "128x128"
+    _check_gemm(3648, 776, 64 * nk, True)
+
+
+@pytest.mark.parametrize("d_ff", [1024, 1088])
+def test_stored_weights_one_tile_per_unit(d_ff):
+    """2100 x 1024 outputs, 136 tiles, over 1024 and d_ff: the forward products that read weights as they are stored."""
+    cfg = SI.BlockConfig(f"gemm_stored_{d_ff}", 65, 30, 70, 1024, 16, 64, d_ff, attn_scale=0.125)
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
+    check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
