@@ -38,8 +38,9 @@ hipError_t launch_direct(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
       if ((int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64) <= 256) return launch_cfg<64, 64, 1, 2, true, false, EPI, 4, 1, 64>(g, e, 1, st);
       if ((int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 64) <= 256) return launch_cfg<128, 64, 2, 2, true, false, EPI, 3, 1, 64>(g, e, 1, st);
     }
-    // (four stages of 64 from K = 1024 on: 4000 x 768 x 2048 with residual 27.8 -> 25.6 us; x 768 15.0 with 32, 15.9 with 64)
-    if (g.seg[0].K >= 1024) return launch_cfg<128, 128, 2, 2, true, false, EPI, 4, 1, 64>(g, e, 1, st);
+    // (four stages of 64 from K = 2048 on: 4000 x 768 x 2048 with residual 27.8 -> 25.6 us, 3500 x 1024 x 2816 39.8 -> 34.4;
+    // 3500 x 1024 x 1024 18.6 with 32, 20.5 with 64)
+    if (g.seg[0].K >= 2048) return launch_cfg<128, 128, 2, 2, true, false, EPI, 4, 1, 64>(g, e, 1, st);
     return launch_cfg<128, 128, 2, 2, true, false, EPI, 4, 1>(g, e, 1, st);
   }
   // (three stages of A and two of B lose here: 8192 x 2048 x 512 gated 32 -> 37 us)

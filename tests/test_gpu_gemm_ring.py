@@ -35,9 +35,9 @@ def test_one_tile_per_unit_every_loop_remainder(nk):
     _check_gemm(3648, 776, 64 * nk, True)
 
 
-@pytest.mark.parametrize("d_ff", [1024, 1088])
+@pytest.mark.parametrize("d_ff", [2048, 2112])
 def test_stored_weights_one_tile_per_unit(d_ff):
-    """2100 x 1024 outputs, 136 tiles, over 1024 and d_ff: the forward products that read weights as they are stored."""
+    """2100 x 1024 outputs, 136 tiles, over d_ff: the forward products that read weights as they are stored."""
     cfg = SI.BlockConfig(f"gemm_stored_{d_ff}", 65, 30, 70, 1024, 16, 64, d_ff, attn_scale=0.125)
     w, x, dy = make_case(cfg)
     y, saved = O.block_fwd(cfg, x, w)
