@@ -294,12 +294,19 @@ __device__ __forceinline__ uint32_t* keep_row(const AttnDims& a, size_t bh, int 
   const size_t stride = attn_keep_stride(a.S);
   return a.keep + (bh * ((a.Sk + 63) / 64) + tile) * stride + half * (stride / 2);
 }
-// word << 1 | this lane's bit of the wave's mask, as one add with carry
-__device__ __forceinline__ uint32_t shift_in(uint32_t word, uint64_t mask) {
-  uint32_t r;
+// word << 4 | this lane's bits of four of the wave's masks, each as one add with carry.  A vector instruction that reads a scalar
+// register as a mask needs two wait states after the vector instruction that wrote it, and the compiler does not count them
+// into an asm block: they stand at its head, once for the four.
+__device__ __forceinline__ uint32_t shift_in4(uint32_t word, const uint64_t (&mask)[4]) {
   uint64_t carry_out;
-  asm("v_addc_co_u32 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry_out) : "v"(word), "s"(mask));
-  return r;
+  asm("s_nop 1\n\t"
+      "v_addc_co_u32 %0, %1, %0, %0, %2\n\t"
+      "v_addc_co_u32 %0, %1, %0, %0, %3\n\t"
+      "v_addc_co_u32 %0, %1, %0, %0, %4\n\t"
+      "v_addc_co_u32 %0, %1, %0, %0, %5"
+      : "+v"(word), "=&s"(carry_out)
+      : "s"(mask[0]), "s"(mask[1]), "s"(mask[2]), "s"(mask[3]));
+  return word;
 }
 // all ones where bit 31 - n of the word is set, else 0 (the builtin: a shift and a test become a comparison and selects)
 __device__ __forceinline__ int keep_mask(uint32_t word, int n) { return __builtin_amdgcn_sbfe(word, 31 - n, 1); }
@@ -469,6 +476,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
     m = m_new;
     float ls = 0.f;
     uint32_t kx = 0, kept = 0;
+    uint64_t keeps[4];
     if constexpr (DROP) kx = k1 ^ (uint32_t)(j0 | (g << 2));
 #pragma unroll
     for (int kt = 0; kt < BC / 32; ++kt)
@@ -480,7 +488,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
           // (key index = tile start | lane half << 2 | constant of the register, disjoint bits)
           const uint32_t c = (uint32_t)(kt * 32 + ((r >> 2) << 3) + (r & 3));
           const bool keep = drop_keep16(a.drop, kx ^ c);
-          kept = shift_in(kept, __builtin_amdgcn_ballot_w64(keep));
+          keeps[r & 3] = __builtin_amdgcn_ballot_w64(keep);
+          if ((r & 3) == 3) kept = shift_in4(kept, keeps);
           float pk = keep ? p : 0.f;
           asm("" : "+v"(pk));  // (a select of the bf16 values instead would cost a conversion and a permute each)
           sT[kt][r] = pk;
