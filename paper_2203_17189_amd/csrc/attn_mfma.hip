@@ -216,6 +216,8 @@ __device__ __forceinline__ void fill_bias_slice(float* dg, const float* __restri
 // Against the slice of S + 127 diagonals with mask instructions, us: dq 16 x 2048 causal, 16 heads of 128 channels 911 -> 622
 // (80 instead of 84 KB: two workgroups on a compute unit), 1 x 4096, 32 heads of 64 channels 285 -> 256; causal forward
 // 32 x 512, 12 heads 46 -> 40, 8 x 2048 111 -> 98 (no mask to compute: 126 registers instead of 167); the others 1-3 %.
+// A masked score that is infinite or NaN would pass that bias, so where the diagonal cuts a sub-tile the kernels also choose:
+// queries and keys, finite or not, add nothing through a masked score.
 struct BiasWin {
   int M, top, stride;  // top: largest m that is told apart
   __host__ __device__ BiasWin(int S, int far, bool causal) {
@@ -293,6 +295,14 @@ __host__ __device__ inline size_t attn_keep_stride(int S) { return (size_t)2 * (
 __device__ __forceinline__ uint32_t* keep_row(const AttnDims& a, size_t bh, int tile, int half) {
   const size_t stride = attn_keep_stride(a.S);
   return a.keep + (bh * ((a.Sk + 63) / 64) + tile) * stride + half * (stride / 2);
+}
+// Whether `here` holds in any lane of a workgroup of four wavefronts.  flags: 16 bytes of LDS that no wavefront uses.
+__device__ __forceinline__ bool any_in_workgroup(bool here, char* flags, int wave, int lane) {
+  const bool mine = __builtin_amdgcn_ballot_w64(here) != 0;
+  if (lane == 0) reinterpret_cast<int*>(flags)[wave] = mine;
+  __syncthreads();
+  const int4 f = *reinterpret_cast<const int4*>(flags);
+  return __builtin_amdgcn_readfirstlane(f.x | f.y | f.z | f.w) != 0;
 }
 // word << 4 | this lane's bits of four of the wave's masks, each as one add with carry.  A vector instruction that reads a scalar
 // register as a mask needs two wait states after the vector instruction that wrote it, and the compiler does not count them
@@ -380,11 +390,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
   uint32_t* keep_q = DROP ? keep_row(a, (size_t)b * a.H + h, 0, g) + i : nullptr;
 
   f32x16 oT[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oT[ct][r] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m, l;
 
   int n_kv = (Sk + BC - 1) / BC;
   if (CAUSAL) {
@@ -398,124 +404,146 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
   td_tail.init(wave, lane, ld, Sk % BC ? Sk % BC : BC);
   const int jt_tail = Sk % BC ? Sk / BC : -1;  // index of the ragged tile, if there is one
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
-  (jt_tail == 0 ? td_tail : td).issue(lds0, kbase, wave);
-  (jt_tail == 0 ? td_tail : td).issue(lds0 + TILE, vbase, wave);
-  for (int jt = 0; jt < n_kv; ++jt) {
-    const int j0 = jt * BC;
-    dma_wait_barrier();  // tile jt landed; every wave is done with the other stage
-    if (jt + 1 < n_kv) {
-      const uint32_t nxt = lds0 + ((jt + 1) & 1) * STG;
-      const TileDma<DK, BC>& tn = jt + 1 == jt_tail ? td_tail : td;
-      tn.issue(nxt, kbase + (size_t)(j0 + BC) * ld, wave);
-      tn.issue(nxt + TILE, vbase + (size_t)(j0 + BC) * ld, wave);
-    }
-    const char* Kt = smem + (jt & 1) * STG;
-    const char* Vt = Kt + TILE;
-
-    f32x16 sT[BC / 32];
+  // select: masked scores count as zero before the window's -infinity is added.  Without dropout the tiles are gone through
+  // without it, and only a workgroup that finds a NaN in its sums (which a masked score that is not finite leaves there) takes
+  // them a second time: the branch around the select cuts the loop's block in two (64 channels, 1 x 1024 tokens, 12 heads 18
+  // -> 21 us, 4 x 333 10 -> 11, 64 x 512, 6 heads 38.1 -> 40.4; like this 18, 10 and 38.4).  With dropout it costs nothing.
+  constexpr bool TWICE = CAUSAL && WIN && !DROP;
 #pragma unroll
-    for (int kt = 0; kt < BC / 32; ++kt) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sT[kt][r] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk)
-        sT[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Kt, kt * 32, kk, lane), qf[kk], sT[kt],
-                                                        0, 0, 0);
-    }
-    if constexpr (DK == 128) {
-      // K operands requested two contraction steps ahead of the products that use them
-      __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-#pragma unroll
-      for (int q = 0; q + 3 < (BC / 32) * KS; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
-    }
-    float mx = -INFINITY;
-    // only tiles that reach above the diagonal of this wave's queries pay for the mask (wave-uniform)
-    // (and the tile that reaches past the last key)
-    // (causal with the window: the mask is in the bias, and a key past the end comes after every query)
-    const bool on_diag = CAUSAL && WIN ? false : (CAUSAL && j0 + BC - 1 > i_w0) || j0 + BC > Sk;
-    const float* dgt[BC / 32];
-#pragma unroll
-    for (int kt = 0; kt < BC / 32; ++kt) dgt[kt] = dgw + win.at(j0 + kt * 32 - i_w0);
-    if (on_diag) {
-#pragma unroll
-      for (int kt = 0; kt < BC / 32; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = j0 + kt * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-          // (a masked key's bias slot may lie outside the slice: clamp the index, the value is discarded)
-          const int jb = j < Sk ? j : Sk - 1;
-          float s;
-          if constexpr (WIN) s = fmaf(sT[kt][r], sc, (*reinterpret_cast<const f32x4*>(dgt[kt] + ((r >> 2) << 3)))[r & 3]);
-          else s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + jb]) : sT[kt][r] * sc;
-          if ((CAUSAL && j > i) || j >= Sk) s = -INFINITY;
-          sT[kt][r] = s;
-          mx = fmaxf(mx, s);
-        }
-    } else {
-#pragma unroll
-      for (int kt = 0; kt < BC / 32; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = j0 + kt * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-          float s;
-          if constexpr (WIN) s = fmaf(sT[kt][r], sc, (*reinterpret_cast<const f32x4*>(dgt[kt] + ((r >> 2) << 3)))[r & 3]);
-          else s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + j]) : sT[kt][r] * sc;
-          sT[kt][r] = s;
-          mx = fmaxf(mx, s);
-        }
-    }
-    mx = max_across_halves(mx);
-    const float m_new = fmaxf(m, mx);
-    // (a bias table may mask all keys so far, with -inf or with the lowest number: then there is no maximum yet)
-    const float base = BIAS && m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = fast_exp2(m - base);
-    m = m_new;
-    float ls = 0.f;
-    uint32_t kx = 0, kept = 0;
-    uint64_t keeps[4];
-    if constexpr (DROP) kx = k1 ^ (uint32_t)(j0 | (g << 2));
-#pragma unroll
-    for (int kt = 0; kt < BC / 32; ++kt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = fast_exp2(sT[kt][r] - base);
-        ls += p;  // the normaliser is that of the undropped probabilities
-        if constexpr (DROP) {
-          // (key index = tile start | lane half << 2 | constant of the register, disjoint bits)
-          const uint32_t c = (uint32_t)(kt * 32 + ((r >> 2) << 3) + (r & 3));
-          const bool keep = drop_keep16(a.drop, kx ^ c);
-          keeps[r & 3] = __builtin_amdgcn_ballot_w64(keep);
-          if ((r & 3) == 3) kept = shift_in4(kept, keeps);
-          float pk = keep ? p : 0.f;
-          asm("" : "+v"(pk));  // (a select of the bf16 values instead would cost a conversion and a permute each)
-          sT[kt][r] = pk;
-        } else {
-          sT[kt][r] = p;
-        }
-      }
-    if constexpr (DROP) keep_q[jt * attn_keep_stride(S)] = kept;
-    l = l * alpha + ls;
+  for (int select = CAUSAL && WIN && !TWICE; select < (CAUSAL && WIN ? 2 : 1); ++select) {
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) oT[ct][r] *= alpha;
-#pragma unroll
-    for (int kt = 0; kt < BC / 32; ++kt)
-#pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        const bf16x8 pf = pack8(sT[kt], mm * 8);
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-          oT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Vt, kt * 32 + mm * 16, ct * 32, lane),
-                                                          pf, oT[ct], 0, 0, 0);
+      for (int r = 0; r < 16; ++r) oT[ct][r] = 0.f;
+    m = -INFINITY;
+    l = 0.f;
+    (jt_tail == 0 ? td_tail : td).issue(lds0, kbase, wave);
+    (jt_tail == 0 ? td_tail : td).issue(lds0 + TILE, vbase, wave);
+    for (int jt = 0; jt < n_kv; ++jt) {
+      const int j0 = jt * BC;
+      dma_wait_barrier();  // tile jt landed; every wave is done with the other stage
+      if (jt + 1 < n_kv) {
+        const uint32_t nxt = lds0 + ((jt + 1) & 1) * STG;
+        const TileDma<DK, BC>& tn = jt + 1 == jt_tail ? td_tail : td;
+        tn.issue(nxt, kbase + (size_t)(j0 + BC) * ld, wave);
+        tn.issue(nxt + TILE, vbase + (size_t)(j0 + BC) * ld, wave);
       }
+      const char* Kt = smem + (jt & 1) * STG;
+      const char* Vt = Kt + TILE;
+
+      f32x16 sT[BC / 32];
+#pragma unroll
+      for (int kt = 0; kt < BC / 32; ++kt) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sT[kt][r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+          sT[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Kt, kt * 32, kk, lane), qf[kk], sT[kt],
+                                                          0, 0, 0);
+      }
+      if constexpr (DK == 128) {
+        // K operands requested two contraction steps ahead of the products that use them
+        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+        for (int q = 0; q + 3 < (BC / 32) * KS; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+      }
+      float mx = -INFINITY;
+      // only tiles that reach above the diagonal of this wave's queries pay for the mask (wave-uniform)
+      // (and the tile that reaches past the last key)
+      // (causal with the window: the mask is in the bias, and a key past the end comes after every query)
+      const bool on_diag = CAUSAL && WIN ? false : (CAUSAL && j0 + BC - 1 > i_w0) || j0 + BC > Sk;
+      const float* dgt[BC / 32];
+#pragma unroll
+      for (int kt = 0; kt < BC / 32; ++kt) dgt[kt] = dgw + win.at(j0 + kt * 32 - i_w0);
+      if (select && j0 + BC - 1 > i_w0) {  // (wave-uniform)
+#pragma unroll
+        for (int kt = 0; kt < BC / 32; ++kt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (kt * 32 + ((r >> 2) << 3) + (r & 3) > i - j0 - (g << 2)) sT[kt][r] = 0.f;
+      }
+      if (on_diag) {
+#pragma unroll
+        for (int kt = 0; kt < BC / 32; ++kt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int j = j0 + kt * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+            // (a masked key's bias slot may lie outside the slice: clamp the index, the value is discarded)
+            const int jb = j < Sk ? j : Sk - 1;
+            float s;
+            if constexpr (WIN) s = fmaf(sT[kt][r], sc, (*reinterpret_cast<const f32x4*>(dgt[kt] + ((r >> 2) << 3)))[r & 3]);
+            else s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + jb]) : sT[kt][r] * sc;
+            if ((CAUSAL && j > i) || j >= Sk) s = -INFINITY;
+            sT[kt][r] = s;
+            mx = fmaxf(mx, s);
+          }
+      } else {
+#pragma unroll
+        for (int kt = 0; kt < BC / 32; ++kt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int j = j0 + kt * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+            float s;
+            if constexpr (WIN) s = fmaf(sT[kt][r], sc, (*reinterpret_cast<const f32x4*>(dgt[kt] + ((r >> 2) << 3)))[r & 3]);
+            else s = BIAS ? fmaf(sT[kt][r], sc, dg[dg_base + j]) : sT[kt][r] * sc;
+            sT[kt][r] = s;
+            mx = fmaxf(mx, s);
+          }
+      }
+      mx = max_across_halves(mx);
+      const float m_new = fmaxf(m, mx);
+      // (a bias table may mask all keys so far, with -inf or with the lowest number: then there is no maximum yet)
+      const float base = BIAS && m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = fast_exp2(m - base);
+      m = m_new;
+      float ls = 0.f;
+      uint32_t kx = 0, kept = 0;
+      uint64_t keeps[4];
+      if constexpr (DROP) kx = k1 ^ (uint32_t)(j0 | (g << 2));
+#pragma unroll
+      for (int kt = 0; kt < BC / 32; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float p = fast_exp2(sT[kt][r] - base);
+          ls += p;  // the normaliser is that of the undropped probabilities
+          if constexpr (DROP) {
+            // (key index = tile start | lane half << 2 | constant of the register, disjoint bits)
+            const uint32_t c = (uint32_t)(kt * 32 + ((r >> 2) << 3) + (r & 3));
+            const bool keep = drop_keep16(a.drop, kx ^ c);
+            keeps[r & 3] = __builtin_amdgcn_ballot_w64(keep);
+            if ((r & 3) == 3) kept = shift_in4(kept, keeps);
+            float pk = keep ? p : 0.f;
+            asm("" : "+v"(pk));  // (a select of the bf16 values instead would cost a conversion and a permute each)
+            sT[kt][r] = pk;
+          } else {
+            sT[kt][r] = p;
+          }
+        }
+      if constexpr (DROP) keep_q[jt * attn_keep_stride(S)] = kept;
+      l = l * alpha + ls;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oT[ct][r] *= alpha;
+#pragma unroll
+      for (int kt = 0; kt < BC / 32; ++kt)
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm) {
+          const bf16x8 pf = pack8(sT[kt], mm * 8);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            oT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Vt, kt * 32 + mm * 16, ct * 32, lane),
+                                                            pf, oT[ct], 0, 0, 0);
+        }
+    }
+    __syncthreads();  // every wave is done with the tiles
+    if (TWICE && !select && !any_in_workgroup(__builtin_isnan(l), smem + 2 * STG - 16, wave, lane)) break;
   }
   const float l_tot = l + __shfl_xor(l, 32, 64);
-  __syncthreads();  // every wave is done with the tiles
   store_rows<DK>(smem + wave * 32 * (DK * 2 + 16), oT, (DROP ? a.drop.scale : 1.f) / l_tot,
                  c + ((size_t)b * S + i0 + wave * 32) * I + h * DK, (size_t)I, S - i0 - wave * 32, lane);
   if (i < S) {
@@ -722,7 +750,7 @@ __global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void at
       __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
       // sub-tile reaches above the diagonal, past the last key, or this wave holds queries past the end
       // (all wave-uniform)
-      if ((CAUSAL && !WIN && j0s + 31 > i_w0) || j0s + 32 > Sk || i_w0 + 32 > S) {
+      if ((CAUSAL && j0s + 31 > i_w0) || j0s + 32 > Sk || i_w0 + 32 > S) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int j = j0s + ((r >> 2) << 3) + (g << 2) + (r & 3);
@@ -1006,6 +1034,14 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Dt, qb * 32, kk, lane), vf[kk], dp, 0, 0, 0);
     }
   };
+  // The scores of keys after their query: the infinity that makes exp2 zero, or with the window, whose bias is -infinity
+  // there, zero.
+  auto mask_later = [&](int q0, f32x16& s) __attribute__((always_inline)) {
+    const float gone = WIN ? 0.f : sc > 0.f ? -INFINITY : INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (((r >> 2) << 3) + (r & 3) < j0 + j_loc - q0 - (g << 2)) s[r] = gone;
+  };
   auto load_bias = [&](int q0, float (&bias)[16]) __attribute__((always_inline)) {  // q0: first query of the sub-tile
     if constexpr (WIN) {
       const float* bp = dgw + win.at(j_w0 - q0);
@@ -1032,7 +1068,7 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
     for (int r = 0; r < 16; ++r) {
       const int ir = ((r >> 2) << 3) + (g << 2) + (r & 3), il = qb * 32 + ir;
       float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
-      if ((CAUSAL && !WIN && j > q0 + ir) || (decltype(tail)::value && q0 + ir >= S)) p = 0.f;
+      if (decltype(tail)::value && q0 + ir >= S) p = 0.f;
       if constexpr (DROP) {
         const int mask = keep_mask(keep_s[il], keep_n);
         s[r] = keep_if(mask, p);
@@ -1044,36 +1080,44 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
     }
   };
   issue(0, it_begin);
-  for (int it = it_begin; it < n_it; ++it) {
-    const int st = (it - it_begin) & 1, q0 = it * BQ;
-    dma_wait_barrier();  // tile `it` and its lse / dvec slices landed; the other stage is free
-    mask_tail(st, it);
-    if (it + 1 < n_it) issue(st ^ 1, it + 1);
-    const char* Qt = smem + st * STG;
-    const char* Dt = Qt + TILE;
-    // with bias, the score products of both sub-tiles first: 32 x 1024 tokens, 32 heads 609 -> 590 us
-    constexpr bool BOTH = BIAS && !DROP;
-    f32x16 s[2], dp[2];
-    float bias[2][16];
+  // diag: the tiles that the diagonal cuts have a loop of their own, so that the other loop has no branch (one loop with a branch
+  // around the mask: causal 64 x 512, 6 heads 70 -> 71 us, 1 x 1024, 12 heads 27 -> 29)
+  int it = it_begin;
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      if (qb == 0 || !BOTH) {
-        load_bias(q0 + qb * 32, bias[qb]);
-        scores(st, qb, s[qb], dp[qb]);
-      }
-      if (qb == 0 && BOTH) {
-        load_bias(q0 + 32, bias[1]);
-        scores(st, 1, s[1], dp[1]);
-      }
-      if (TAIL_MASK && q0 + qb * 32 + 32 > S) softmax(std::true_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
-      else softmax(std::false_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
+  for (int diag = CAUSAL ? 1 : 0; diag >= 0; --diag) {
+    for (const int end = diag ? min(it_begin + BCK / BQ, n_it) : n_it; it < end; ++it) {
+      const int st = (it - it_begin) & 1, q0 = it * BQ;
+      dma_wait_barrier();  // tile `it` and its lse / dvec slices landed; the other stage is free
+      mask_tail(st, it);
+      if (it + 1 < n_it) issue(st ^ 1, it + 1);
+      const char* Qt = smem + st * STG;
+      const char* Dt = Qt + TILE;
+      // with bias, the score products of both sub-tiles first: 32 x 1024 tokens, 32 heads 609 -> 590 us
+      constexpr bool BOTH = BIAS && !DROP && !CAUSAL;
+      f32x16 s[2], dp[2];
+      float bias[2][16];
 #pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        const bf16x8 pf = pack8(s[qb], mm * 8), dsf = pack8(dp[qb], mm * 8);
+      for (int qb = 0; qb < 2; ++qb) {
+        if (diag && q0 + qb * 32 < j_w0) continue;  // masked whole for this wave
+        if (qb == 0 || !BOTH) {
+          load_bias(q0 + qb * 32, bias[qb]);
+          scores(st, qb, s[qb], dp[qb]);
+          if (diag) mask_later(q0 + qb * 32, s[qb]);
+        }
+        if (qb == 0 && BOTH) {
+          load_bias(q0 + 32, bias[1]);
+          scores(st, 1, s[1], dp[1]);
+        }
+        if (TAIL_MASK && q0 + qb * 32 + 32 > S) softmax(std::true_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
+        else softmax(std::false_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          dvT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane), pf, dvT[ct], 0, 0, 0);
-          dkT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane), dsf, dkT[ct], 0, 0, 0);
+        for (int mm = 0; mm < 2; ++mm) {
+          const bf16x8 pf = pack8(s[qb], mm * 8), dsf = pack8(dp[qb], mm * 8);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            dvT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane), pf, dvT[ct], 0, 0, 0);
+            dkT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane), dsf, dkT[ct], 0, 0, 0);
+          }
         }
       }
     }
@@ -1226,6 +1270,14 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Dt, qb * 32, kk, lane), vf[kk], dp, 0, 0, 0);
     }
   };
+  // The scores of keys after their query: the infinity that makes exp2 zero, or with the window, whose bias is -infinity
+  // there, zero.
+  auto mask_later = [&](int q0, f32x16& s) __attribute__((always_inline)) {
+    const float gone = WIN ? 0.f : sc > 0.f ? -INFINITY : INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (((r >> 2) << 3) + (r & 3) < j0 + j_loc - q0 - (g << 2)) s[r] = gone;
+  };
   auto load_bias = [&](int q0, float (&bias)[16]) __attribute__((always_inline)) {  // q0: first query of the sub-tile
     if constexpr (WIN) {
       const float* bp = dgw + win.at(j_w0 - q0);
@@ -1248,11 +1300,9 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
                      bf16x8& pf, bf16x8& dsf) __attribute__((always_inline)) {
     const float* dv_s = dv_all + stage * BQ;
     const uint32_t* keep_s = keep_all + (stage * 4 + (wave & 2) + ((lane >> 2) & 1)) * BQ;
-    const int j = j0 + j_loc;
 #pragma unroll
     for (int r = mm * 8; r < mm * 8 + 8; ++r) {
       float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
-      if (CAUSAL && !WIN && j - q0 > ((r >> 2) << 3) + (g << 2) + (r & 3)) p = 0.f;
       if constexpr (DROP) {
         const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
         const int mask = keep_mask(keep_s[il], keep_n);
@@ -1276,37 +1326,54 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   // A unit is 32 queries x 32 keys.  Step n of the pipeline: the score products of unit n, then the dV / dK products of unit
   // n - 1 beside the softmax arithmetic of unit n.
   bf16x8 pf[2], dsf[2];      // of the unit whose products are still to come
-  auto step = [&](int pst, int pv, int stage, int v, int q0) __attribute__((always_inline)) {
-    const int qb = v;
+  // unit qb of the tile in `stage`, whose first query is q0, behind unit pqb of `pst` (-1: none)
+  auto step = [&](auto diag, int pst, int pqb, int stage, int qb, int q0) __attribute__((always_inline)) {
     f32x16 s, dp;
     float bias[16];
     bf16x8 pn[2], dn[2];
     load_bias(q0 + qb * 32, bias);
     scores(stage, qb, s, dp);
-    if (pv >= 0) {
+    if constexpr (decltype(diag)::value) mask_later(q0 + qb * 32, s);
+    if (pqb >= 0) {
 #pragma unroll
-      for (int mm = 0; mm < 2; ++mm) outer(pst, pv, mm, pf[mm], dsf[mm]);
+      for (int mm = 0; mm < 2; ++mm) outer(pst, pqb, mm, pf[mm], dsf[mm]);
     }
 #pragma unroll
     for (int mm = 0; mm < 2; ++mm) softmax(stage, qb, q0 + qb * 32, mm, s, dp, bias, pn[mm], dn[mm]);
 #pragma unroll
     for (int mm = 0; mm < 2; ++mm) { pf[mm] = pn[mm]; dsf[mm] = dn[mm]; }
   };
-
-  dma_wait_barrier();
-  mask_tail(0, it_begin);
-  if (it_begin + 1 < n_it) issue(1, it_begin + 1);
-  step(0, -1, 0, 0, it_begin * BQ);
-  int st = 0;
-  for (int it = it_begin;; ++it) {
+  // tile `it` has landed in `stage`; every wave is done with tile it - 2
+  auto enter = [&](int stage, int it) __attribute__((always_inline)) {
+    dma_wait_barrier();
+    mask_tail(stage, it);
+    if (it + 1 < n_it) issue(stage == 2 ? 0 : stage + 1, it + 1);
+  };
+  // Causal, the diagonal cuts the w-th unit of wave w, which begins there (the units before it have no visible key): waves 2 and
+  // 3 in the second tile, 1 and 3 with a tile's second unit.  The loop has no mask and no branch inside a step (with a select
+  // in every unit, slice of diagonals: 2 x 8192 tokens, 8 heads of 128 channels 851 us, 600 like this; with a branch around
+  // it, 16 x 2048, 16 heads 740 -> 825, like this 755).
+  constexpr std::bool_constant<CAUSAL> cut{};
+  constexpr std::false_type all{};
+  int it = it_begin, st = 0, second = 0;
+  enter(0, it);
+  if constexpr (CAUSAL) {
+    if (wave >= 2 && it + 1 < n_it) {
+      enter(1, ++it);
+      st = 1;
+    }
+    second = wave & 1;
+    asm("" : "+s"(second));  // (known, it would become a copy of the loop)
+  }
+  step(cut, 0, -1, st, second, it * BQ);
+  for (;; ++it) {
     const int q0 = it * BQ;
-    step(st, 0, st, 1, q0);
+    if (!CAUSAL || !second) step(all, st, 0, st, 1, q0);
+    second = 0;
     if (it + 1 == n_it) break;
     const int nst = st == 2 ? 0 : st + 1;
-    dma_wait_barrier();  // tile it + 1 has landed; every wave is done with tile it - 1
-    mask_tail(nst, it + 1);
-    if (it + 2 < n_it) issue(nst == 2 ? 0 : nst + 1, it + 2);
-    step(st, 1, nst, 0, q0 + BQ);
+    enter(nst, it + 1);
+    step(all, st, 1, nst, 0, q0 + BQ);
     st = nst;
   }
 #pragma unroll
