@@ -570,9 +570,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnIO io, const 
 // scalar per lane; it is credited to the outermost diagonal, which is in the same bucket.
 // ------------------------------------------------------------------------------------------------
 template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
-// (three waves per SIMD with 64 channels; with dropout and without the causal mask they would spill: 32 x 512 tokens, 12
-// heads, causal 86 -> 75 us, 128 x 512 not causal 351 -> 393)
-__global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void attn_bwd_dq_mfma_kernel(AttnIO io,
+// (three waves per SIMD with 64 channels; with dropout only causal and with the window: the others would spill.  32 x 512
+// tokens, 12 heads, causal 86 -> 75 us, 128 x 512 not causal 351 -> 393; slice, causal, 2 x 4096 253 us with either)
+__global__ __launch_bounds__(256, DK == 64 && (!DROP || (CAUSAL && WIN)) ? 3 : 2) void attn_bwd_dq_mfma_kernel(AttnIO io,
                                                                const bf16* __restrict__ o,
                                                                const bf16* __restrict__ dout,
                                                                const float* __restrict__ diag,
@@ -582,6 +582,11 @@ __global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void at
                                                                float* __restrict__ ddiag_part,
                                                                AttnDims a) {
   constexpr int BR = 128, BC = 64, KS = DK / 16, CT = DK / 32;
+  // The causal form with dropout has no register to spare for the third wave: the keep words by a uniform base and one 32-bit
+  // offset, the ragged tile's offsets formed where it is fetched (with both kept, 6 registers with the window and 9 with the
+  // slice were spilled, and reloaded between the tiles' DMA: slice, 2 x 4096 tokens, 12 heads 310 -> 253 us, 32 x 620 137 ->
+  // 115; window, 1 x 4096 154 -> 144, 4 x 333 20.0 -> 17.7).
+  constexpr bool LEAN = DK == 64 && DROP && CAUSAL;
   constexpr int TILE = BC * DK * 2, STG = 2 * TILE;  // a stage holds a K tile then a V tile
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int far = a.far;
@@ -639,8 +644,9 @@ __global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void at
   }
   const float nlse2 = -lse_q * kLog2e, ndv = -dsum;
   // this lane's words of keep decisions, and that of the next key tile
-  const uint32_t* keep_q = DROP ? keep_row(a, (size_t)b * a.H + h, 0, g) + i : nullptr;
-  uint32_t kept_next = DROP ? keep_q[0] : 0;
+  const uint32_t* keep_q = DROP ? keep_row(a, (size_t)b * a.H + h, 0, LEAN ? 0 : g) + (LEAN ? 0 : i) : nullptr;  // (+ keep_i)
+  const uint32_t keep_i = LEAN ? (uint32_t)(g * (int)(attn_keep_stride(S) / 2) + i) : 0;
+  uint32_t kept_next = DROP ? keep_q[keep_i] : 0;
   // dP of a kept probability carries the factor 1/(1 - rate); that of a dropped one is zero
   auto dp_masked = [&](float dp, uint32_t kept, int n) {
     if constexpr (DROP) {
@@ -676,11 +682,26 @@ __global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void at
   const int n_kv = ((CAUSAL && i0 + BR < Sk ? i0 + BR : Sk) + BC - 1) / BC;
   TileDma<DK, BC> td, td_tail;  // td_tail: the last tile of a key sequence that does not fill it
   td.init(wave, lane, ld);
-  td_tail.init(wave, lane, ld, Sk % BC ? Sk % BC : BC);
+  if constexpr (!LEAN) td_tail.init(wave, lane, ld, Sk % BC ? Sk % BC : BC);
   const int jt_tail = Sk % BC ? Sk / BC : -1;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
-  (jt_tail == 0 ? td_tail : td).issue(lds0, kbase, wave);
-  (jt_tail == 0 ? td_tail : td).issue(lds0 + TILE, vbase, wave);
+  auto issue = [&](int jt) __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + (jt & 1) * STG;
+    const bf16 *kt = kbase + (size_t)(jt * BC) * ld, *vt = vbase + (size_t)(jt * BC) * ld;
+    if (LEAN && jt == jt_tail) {
+      int rows = Sk % BC;
+      asm volatile("" : "+s"(rows));  // (opaque: its offsets stay out of the loop's registers)
+      TileDma<DK, BC> tail;
+      tail.init(wave, lane, ld, rows);
+      tail.issue(dst, kt, wave);
+      tail.issue(dst + TILE, vt, wave);
+    } else {
+      const TileDma<DK, BC>& t = !LEAN && jt == jt_tail ? td_tail : td;
+      t.issue(dst, kt, wave);
+      t.issue(dst + TILE, vt, wave);
+    }
+  };
+  issue(0);
   for (int jt = 0; jt < n_kv; ++jt) {
     const int j0 = jt * BC;
     dma_wait_barrier();  // tile jt landed; every wave is done with the other stage
@@ -688,11 +709,8 @@ __global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void at
     const uint32_t kept = kept_next;
     if constexpr (DROP) asm volatile("" ::"v"(kept));
     if (jt + 1 < n_kv) {
-      const uint32_t nxt = lds0 + ((jt + 1) & 1) * STG;
-      const TileDma<DK, BC>& tn = jt + 1 == jt_tail ? td_tail : td;
-      if constexpr (DROP) kept_next = keep_q[(jt + 1) * attn_keep_stride(S)];
-      tn.issue(nxt, kbase + (size_t)(j0 + BC) * ld, wave);
-      tn.issue(nxt + TILE, vbase + (size_t)(j0 + BC) * ld, wave);
+      if constexpr (DROP) kept_next = (keep_q + (jt + 1) * attn_keep_stride(S))[keep_i];
+      issue(jt + 1);
     }
     const char* Kt = smem + (jt & 1) * STG;
     const char* Vt = Kt + TILE;
@@ -755,7 +773,8 @@ __global__ __launch_bounds__(256, DK == 64 && (!DROP || CAUSAL) ? 3 : 2) void at
         for (int r = 0; r < 16; ++r) {
           const int j = j0s + ((r >> 2) << 3) + (g << 2) + (r & 3);
           float p = BIAS ? fast_exp2(fmaf(sT[r], sc, bias[r]) + nlse2) : fast_exp2(fmaf(sT[r], sc, nlse2));
-          if ((CAUSAL && j > i) || j >= Sk || !q_ok) p = 0.f;
+          // (causal, a key past the end comes after every query)
+          if (CAUSAL ? j > (q_ok ? i : -1) : j >= Sk || !q_ok) p = 0.f;
           sT[r] = p * (dp_masked(dpT[r], kept, kt * 16 + r) + ndv);
         }
       } else {

@@ -42,7 +42,10 @@ WAVES = [("attn_fwd_f32_kernelILi32ELi[124]ELb1", 3), ("attn_fwd_f32_kernelILi64
          ("attn_bwd_(dq|dkv)_f32_kernelILi(32ELi[124]|64ELi4)E", 2),
          ("attn_(fwd|bwd_dq|bwd_dkv)_f32_kernelILi(32|64)E", 1),
          ("attn_bwd_dkv_mfma_kernelILi64ELb0ELb0ELb0ELb1E", 3), ("attn_bwd_dkv_mfma_kernelILi64E", 2),
-         ("attn_bwd_dq_mfma_kernelILi64ELb[01]ELb[01]ELb0E", 3), ("attn_fwd_mfma_kernel", 2)]
+         ("attn_bwd_dq_mfma_kernelILi64ELb[01]ELb[01]ELb0E", 3), ("attn_fwd_mfma_kernel", 2),
+         # dropout: three with the causal mask and the window of diagonals, else two
+         ("attn_bwd_dq_mfma_kernelILi64ELb1ELb1ELb1ELb1E", 3), ("attn_bwd_dq_mfma_kernel", 2),
+         ("attn_bwd_dkv_pipe_kernelILi64E", 2), ("attn_bwd_dkv_pipe_kernel", 1)]
 
 
 @pytest.mark.skipif(not os.path.exists(READELF), reason="needs llvm-readelf")
