@@ -25,6 +25,7 @@
 // The bias is Toeplitz: bias[h,i,j] = diag[h][j - i + S - 1], and constant from the first distance of the last bucket
 // on.  Each workgroup stages the diagonals up to there in LDS (BiasWin), or, where that window would be long, the
 // slice of the per-head diagonal vector it can touch (S + tile - 1 floats).
+#include <algorithm>
 #include <type_traits>
 #include "kernels.h"
 
@@ -244,12 +245,6 @@ struct BiasWin {
   // a lane's base: the diagonals u .. u + 3 of the window of a sub-tile are the four values from lane(win, u) + at(m) on
   __device__ __forceinline__ const float* lane(const float* win, int u) const { return win + (u & 3) * stride + (u & ~3); }
 };
-// The window is used while its copies stay under 10 KB (two thirds of a K tile with 128 channels): distances up to 225,
-// causal 449, or as many positions.
-inline bool attn_bias_window(const AttnDims& a) {
-  return a.bias && BiasWin(a.S, a.far, a.causal != 0).floats() * sizeof(float) <= 10240;
-}
-
 // Registers R.. of a 32x32 ds sub-tile (S^T layout), each rotated across the 32 lanes of its half by
 // its key offset, summed into `tot`; `lo` gets the part whose source query did not wrap around
 // (lp = 31 - query index of the receiving lane).  The rotation amount must be an immediate.
@@ -1408,13 +1403,8 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   }
 }
 
-// (win: bias from a window of diagonals)
-size_t attn_bwd_dq_lds_bytes(const AttnDims& a, bool win) {
-  if (!a.bias) return (size_t)4 * 64 * a.dk * 2;
-  const int W = 32 * (2 * attn_dq_window_blocks(a.S, a.far) + 2);
-  const size_t bias = win ? BiasWin(a.S, a.far, a.causal != 0).floats() : a.S + 127;
-  return (size_t)4 * 64 * a.dk * 2 + sizeof(float) * (bias + 8 * (size_t)W);
-}
+// Whether dk/dv takes the pipelined form.
+constexpr bool dkv_pipe(int dk, bool causal, bool drop) { return dk == 128 || (causal && !drop); }
 
 template <typename K>
 hipError_t set_lds(K kern, size_t bytes) {
@@ -1424,7 +1414,7 @@ hipError_t set_lds(K kern, size_t bytes) {
 template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
 hipError_t fwd_launch_as(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a, hipStream_t st) {
   auto kern = attn_fwd_mfma_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
-  const size_t lds = 4 * 64 * DK * 2 + sizeof(float) * (WIN ? BiasWin(a.S, a.far, CAUSAL).floats() : BIAS ? a.S + 127 : 0);
+  const size_t lds = attn_lds_bytes(a, ATTN_FWD, WIN);
   hipError_t e = set_lds(kern, lds);
   if (e != hipSuccess) return e;
   kern<<<dim3(((a.S + 127) / 128) * a.H * a.B), 256, lds, st>>>(io, diag, (bf16*)c, lse, a);
@@ -1433,7 +1423,7 @@ hipError_t fwd_launch_as(const AttnIO& io, const float* diag, void* c, float* ls
 
 template <int DK, bool CAUSAL, bool BIAS, bool DROP = false>
 hipError_t fwd_launch(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a, hipStream_t st) {
-  if (BIAS && attn_bias_window(a)) return fwd_launch_as<DK, CAUSAL, BIAS, DROP, BIAS>(io, diag, c, lse, a, st);
+  if (BIAS && attn_bias_window(a, ATTN_FWD)) return fwd_launch_as<DK, CAUSAL, BIAS, DROP, BIAS>(io, diag, c, lse, a, st);
   return fwd_launch_as<DK, CAUSAL, BIAS, DROP, false>(io, diag, c, lse, a, st);
 }
 
@@ -1444,7 +1434,7 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
   hipError_t e = hipSuccess;
   if (phase == 1) {
     auto kern = attn_bwd_dq_mfma_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
-    const size_t lds = attn_bwd_dq_lds_bytes(a, WIN);
+    const size_t lds = attn_lds_bytes(a, ATTN_BWD_DQ, WIN);
     if ((e = set_lds(kern, lds)) != hipSuccess) return e;
     kern<<<dim3(((a.S + 127) / 128) * a.H * a.B), 256, lds, st>>>(io, (const bf16*)c, (const bf16*)dc, diag, lse, dvec, ddiag,
                                                           BIAS ? ddiag_part : nullptr, a);
@@ -1457,11 +1447,10 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
     }
   }
   if (phase == 2) {
-    const size_t bias = sizeof(float) * (WIN ? BiasWin(a.S, a.far, CAUSAL).floats() : BIAS ? 64 + a.S + 127 : 0);
+    const size_t lds = attn_lds_bytes(a, ATTN_BWD_DKV, WIN);
     const int wgs = ((a.Sk + 127) / 128) * a.H * a.B;
-    if constexpr (DK == 128 || (CAUSAL && !DROP)) {
+    if constexpr (dkv_pipe(DK, CAUSAL, DROP)) {
       auto kern = attn_bwd_dkv_pipe_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
-      const size_t lds = 3 * (2 * 64 * DK * 2 + sizeof(float) * (128 + (DROP ? 256 : 0))) + bias;
       if ((e = set_lds(kern, lds)) != hipSuccess) return e;
       kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
     } else {
@@ -1471,7 +1460,6 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
       constexpr bool CAN_THREE = DK == 64 && !BIAS && !DROP;
       auto kern = CAN_THREE && wgs > 512 ? attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, CAN_THREE, WIN>
                                          : attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, false, WIN>;
-      const size_t lds = 2 * (2 * 64 * DK * 2 + sizeof(float) * (128 + (DROP ? 256 : 0))) + bias;
       if ((e = set_lds(kern, lds)) != hipSuccess) return e;
       kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
     }
@@ -1483,7 +1471,7 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
 template <int DK, bool CAUSAL, bool BIAS, bool DROP = false>
 hipError_t bwd_launch(const AttnIO& io, const void* c, const void* dc, const float* diag, const float* lse,
                       float* dvec, float* ddiag, float* ddiag_part, const AttnDims& a, int phase, hipStream_t st) {
-  if (BIAS && attn_bias_window(a))
+  if (BIAS && attn_bias_window(a, phase == 1 ? ATTN_BWD_DQ : ATTN_BWD_DKV))
     return bwd_launch_as<DK, CAUSAL, BIAS, DROP, BIAS>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
   return bwd_launch_as<DK, CAUSAL, BIAS, DROP, false>(io, c, dc, diag, lse, dvec, ddiag, ddiag_part, a, phase, st);
 }
@@ -1493,10 +1481,39 @@ int attn_mode(const AttnDims& a) { return a.bias ? (a.causal ? 1 : 0) : 2; }
 
 }  // namespace
 
-bool attn_bwd_mfma_fits(const AttnDims& a) {
-  // the dq kernel keeps per-diagonal windows of about 2 * far entries in LDS
-  return attn_bwd_dq_lds_bytes(a, false) <= (size_t)150 * 1024;
+size_t attn_lds_bytes(const AttnDims& a, AttnPass pass, bool window) {
+  const bool pipe = pass == ATTN_BWD_DKV && dkv_pipe(a.dk, a.causal != 0, a.drop.on != 0);
+  const int stages = pipe ? 3 : 2;
+  size_t floats = (size_t)stages * 2 * 64 * a.dk / 2;  // two bf16 tiles of 64 rows each
+  if (pass == ATTN_BWD_DKV) floats += stages * (128 + (a.drop.on ? 256 : 0));  // -lse, -dvec; keep words
+  if (!a.bias) return floats * sizeof(float);
+  if (window) floats += BiasWin(a.S, a.far, a.causal != 0).floats();
+  else floats += a.S + 127 + (pass == ATTN_BWD_DKV ? 64 : 0);
+  // the dq kernel keeps per-diagonal windows of about 2 * far entries for each half wavefront
+  if (pass == ATTN_BWD_DQ) floats += 8 * 32 * (2 * (size_t)attn_dq_window_blocks(a.S, a.far) + 2);
+  return floats * sizeof(float);
 }
+
+int attn_workgroups_per_unit(const AttnDims& a, AttnPass pass, bool window) {
+  // (of four wavefronts: one on each SIMD.  What the registers allow: launch bounds, forward as built)
+  int by_registers = 2;
+  if (pass == ATTN_FWD && a.dk == 64) by_registers = a.causal && window ? 4 : 3;
+  if (pass == ATTN_BWD_DQ && a.dk == 64) by_registers = !a.drop.on || (a.causal && window) ? 3 : 2;
+  if (pass == ATTN_BWD_DKV && a.dk == 128) by_registers = 1;
+  return std::min(by_registers, (int)((size_t)160 * 1024 / attn_lds_bytes(a, pass, window)));
+}
+
+// The window is used while its copies stay under 10 KB (two thirds of a K tile with 128 channels: distances up to 225,
+// causal 449, or as many positions) and do not keep a workgroup off the compute unit.  The latter is a matter of dq, which has
+// windows of diagonal sums beside it: not causal, 64 x 512 tokens, 16 heads of 128 channels, distance 130 (two workgroups
+// with the slice, one with the window) 469 us with the window, 328 with the slice; 32 x 256, 12 heads of 64, distance 166
+// (three and two) 34 and 28; causal, distance 216, 31 and 26.
+bool attn_bias_window(const AttnDims& a, AttnPass pass) {
+  return a.bias && BiasWin(a.S, a.far, a.causal != 0).floats() * sizeof(float) <= 10240 &&
+         attn_workgroups_per_unit(a, pass, true) >= attn_workgroups_per_unit(a, pass, false);
+}
+
+bool attn_bwd_mfma_fits(const AttnDims& a) { return attn_lds_bytes(a, ATTN_BWD_DQ, false) <= (size_t)150 * 1024; }
 
 bool attn_mfma_supported(const AttnDims& a) {
   // Any lengths from 32 up (tiles are rounded up and their tails masked); LDS holds the diagonal slice

@@ -233,6 +233,11 @@ hipError_t launch_attn_fwd_f32(const AttnIO& io, const float* diag, float* c, fl
 hipError_t launch_attn_bwd_f32(const AttnIO& io, const float* c, const float* dc, const float* diag, const float* lse,
                                float* dvec, float* ddiag, const AttnDims& a, hipStream_t st);
 bool attn_mfma_supported(const AttnDims& a);
+// Where a kernel takes its bias from: a window of diagonals, or the slice of every diagonal that a workgroup can touch.
+enum AttnPass { ATTN_FWD, ATTN_BWD_DQ, ATTN_BWD_DKV };
+bool attn_bias_window(const AttnDims& a, AttnPass pass);
+size_t attn_lds_bytes(const AttnDims& a, AttnPass pass, bool window);
+int attn_workgroups_per_unit(const AttnDims& a, AttnPass pass, bool window);  // that share a compute unit
 size_t attn_keep_bytes(const AttnDims& a);  // of AttnDims::keep (0 without dropout)
 hipError_t launch_attn_fwd_mfma(const AttnIO& io, const float* diag, void* c, float* lse, const AttnDims& a,
                                 hipStream_t st);

@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 BASE = SI.BlockConfig("bias_window", 2, 620, 64, 128, 2, 64, 128, attn_scale=0.125)
 
 
-# 620 positions: nearly every sub-tile beyond the window, a few, or (4096) the slice, for windows of up to 592 values
-@pytest.mark.parametrize("max_distance", [20, 128, 4096])
+# 620 positions: nearly every sub-tile beyond the window, a few, or (4096) the slice, for windows of up to 592 values; with 256
+# and 64 channels dq has the slice and the others the window
+@pytest.mark.parametrize("max_distance", [20, 128, 256, 4096])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d_kv", [64, 128])
 def test_window_and_slice(d_kv, causal, max_distance):
