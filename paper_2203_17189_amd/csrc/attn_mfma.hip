@@ -913,9 +913,10 @@ __global__ __launch_bounds__(256) void attn_ddiag_reduce_kernel(const float* __r
 // dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
 // ------------------------------------------------------------------------------------------------
 // Two forms.  This one takes a tile at a time from two stages: 64 channels without the causal mask, where two or three
-// waves per SIMD cover for each other, or with dropout (causal 32 x 512, 12 heads: 68 us, the other form 72).
+// waves per SIMD cover for each other, or with dropout (causal 32 x 512, 12 heads: 68 us, the other form 72), or with a slice
+// beside which three stages would be too much (dkv_takes_pipe).
 template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool THREE, bool WIN>
-__global__ __launch_bounds__(256, DK == 64 ? (THREE ? 3 : 2) : 1)
+__global__ __launch_bounds__(256, THREE ? 3 : 2)
 void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
                               const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
   constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
@@ -1403,8 +1404,18 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   }
 }
 
-// Whether dk/dv takes the pipelined form.
+// Whether dk/dv has a pipelined form.
 constexpr bool dkv_pipe(int dk, bool causal, bool drop) { return dk == 128 || (causal && !drop); }
+size_t dkv_lds_bytes(const AttnDims& a, bool window, int stages) {
+  size_t floats = stages * ((size_t)64 * a.dk + 128 + (a.drop.on ? 256 : 0));  // Q and dO tiles, -lse, -dvec, keep words
+  if (a.bias) floats += window ? BiasWin(a.S, a.far, a.causal != 0).floats() : 64 + a.S + 127;
+  return floats * sizeof(float);
+}
+// It is taken where its third stage does not keep the second workgroup of 64 channels off the compute unit, as it does beside
+// the slice of more than 7617 positions (causal, 12 heads, 4 x 7680: 1100 us, the other form 797; 4 x 7168: 685 and 696).
+bool dkv_takes_pipe(const AttnDims& a, bool window) {
+  return dkv_pipe(a.dk, a.causal != 0, a.drop.on != 0) && (a.dk == 128 || 2 * dkv_lds_bytes(a, window, 3) <= (size_t)160 * 1024);
+}
 
 template <typename K>
 hipError_t set_lds(K kern, size_t bytes) {
@@ -1450,10 +1461,14 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
     const size_t lds = attn_lds_bytes(a, ATTN_BWD_DKV, WIN);
     const int wgs = ((a.Sk + 127) / 128) * a.H * a.B;
     if constexpr (dkv_pipe(DK, CAUSAL, DROP)) {
-      auto kern = attn_bwd_dkv_pipe_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
-      if ((e = set_lds(kern, lds)) != hipSuccess) return e;
-      kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
-    } else {
+      if (DK == 128 || WIN || dkv_takes_pipe(a, WIN)) {
+        auto kern = attn_bwd_dkv_pipe_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
+        if ((e = set_lds(kern, lds)) != hipSuccess) return e;
+        kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+        return hipGetLastError();
+      }
+    }
+    if constexpr (DK == 64 && !(dkv_pipe(DK, CAUSAL, DROP) && WIN)) {
       // Bias-free with 64 channels: beyond two workgroups per compute unit the form that lets a third in, up to there the
       // one whose single workgroup is faster (1 x 1024 queries over 100 keys, 12 heads, 12 workgroups: 27 against 23 us;
       // 384 workgroups 39 and 38; 768 61 and 65; 128 x 114 over 512, 6144 workgroups: 103 and 106).
@@ -1462,8 +1477,8 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
                                          : attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, false, WIN>;
       if ((e = set_lds(kern, lds)) != hipSuccess) return e;
       kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -1482,13 +1497,10 @@ int attn_mode(const AttnDims& a) { return a.bias ? (a.causal ? 1 : 0) : 2; }
 }  // namespace
 
 size_t attn_lds_bytes(const AttnDims& a, AttnPass pass, bool window) {
-  const bool pipe = pass == ATTN_BWD_DKV && dkv_pipe(a.dk, a.causal != 0, a.drop.on != 0);
-  const int stages = pipe ? 3 : 2;
-  size_t floats = (size_t)stages * 2 * 64 * a.dk / 2;  // two bf16 tiles of 64 rows each
-  if (pass == ATTN_BWD_DKV) floats += stages * (128 + (a.drop.on ? 256 : 0));  // -lse, -dvec; keep words
+  if (pass == ATTN_BWD_DKV) return dkv_lds_bytes(a, window, dkv_takes_pipe(a, window) ? 3 : 2);
+  size_t floats = 2 * (size_t)64 * a.dk;  // two stages of a K and a V tile
   if (!a.bias) return floats * sizeof(float);
-  if (window) floats += BiasWin(a.S, a.far, a.causal != 0).floats();
-  else floats += a.S + 127 + (pass == ATTN_BWD_DKV ? 64 : 0);
+  floats += window ? BiasWin(a.S, a.far, a.causal != 0).floats() : a.S + 127;
   // the dq kernel keeps per-diagonal windows of about 2 * far entries for each half wavefront
   if (pass == ATTN_BWD_DQ) floats += 8 * 32 * (2 * (size_t)attn_dq_window_blocks(a.S, a.far) + 2);
   return floats * sizeof(float);

@@ -1,5 +1,6 @@
 """Where the bf16 attention kernels take their bias from: the window of diagonals is chosen only where its LDS leaves a compute
-unit as many workgroups as the slice does, for every distance of the last bucket, length and form.  Host code only."""
+unit as many workgroups as the slice does, for every distance of the last bucket, length and form, and dk/dv with 64 channels
+always has two.  Host code only."""
 import os
 import shutil
 import subprocess
@@ -12,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
-def test_window_costs_no_workgroup(tmp_path):
+def test_workgroups_per_unit(tmp_path):
     exe, lib = str(tmp_path / "attention_plan"), os.path.dirname(os.path.abspath(P.__file__))
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17", "-x", "hip",
                         os.path.join(HERE, "attention_plan", "driver.cpp"), "-o", exe, "-L", lib, "-l:libt5mi.so",
