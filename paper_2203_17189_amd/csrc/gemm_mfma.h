@@ -937,7 +937,11 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    LDS that a workgroup has: a tile's requests spread over the whole period between two barriers).  The others have
     //    those stages from K = 1024 on (8991 x 768 x 4096 64.7 -> 59.5 us, 8991 x 768 x 2304 41.6 -> 38.6, 2048 x 10240 x 2048
     //    gated 108 -> 101) and two up to there, where the longer ramp costs as much as it gives (8991 x 2304 x 768 42 -> 41 and
-    //    46 in two runs, 32768 x 1152 x 512 54 -> 51 and 57);
+    //    46 in two runs, 32768 x 1152 x 512 54 -> 51 and 57).  A plain store whose round leaves many units with one workgroup
+    //    keeps two stages: from K = 1025 up to 384 tiles, from 3072 up to 480 (us with two stages and with the ring, 264 tiles of
+    //    5592 x 768: k 1280 20.6 and 22.1, 3072 36.9 and 39.0; 368 of 2904 x 2048: 1536 23.4 and 23.9, 3072 40.6 and 42.1; 464 of
+    //    3672 x 2048: 2048 33.8 and 33.3, 3072 46.6 and 46.9; 1024 up to 464 tiles 2-5 % less with the ring; several rounds,
+    //    16896 x 1024 x 2048: 83 and 80).  With residual the ring is faster there too (6000 x 768 x 2048, 282 tiles: 35 and 30);
     //  * 256x192, the same loop with three quarters of the columns, where that fills rounds that 256x256 leaves part empty
     //    (widths of 768: 16384 x 768 is 192 tiles of 256x256 and 256 of these).  A round costs 0.88 of a 256x256 one, not
     //    0.75: more units share the power and the L2.  k 4096 98 -> 92 us, 2048 62 -> 57, 768 30 -> 26; 16384 x 2304 x 768,
@@ -948,7 +952,9 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    while they fit one round, smaller tiles, 128x64 and 64x64 (1332 x 768 x 2048 with residual: 37 us -> 21;
     //    1332 x 768 x 768: 25 -> 18).  What bounds them is the path from L2 to LDS, 65 GB/s a compute unit with rows of 128 bytes:
     //    four stages of 32 (rows of 64 bytes) took 39.9 us for 3648 x 768 x 4096, these 31.9; k 2304 30.4 and 25.3, 2048 29.5 and
-    //    25.3, 768 14.8 and 13.5; three stages of 64 43.
+    //    25.3; three stages of 64 43.  The longer ramp of 64 pays from K = 1025 on, with 192 tiles or more from 768 on (us with 32
+    //    and with 64: 160 tiles of 2520 x 1024: k 512 7.8 and 8.9, 1024 11.0 and 11.9, 1280 15.7 and 13.4; 228 of 4824 x 768: 512 8.7
+    //    and 9.5, 768 11.2 and 11.1, 1024 13.3 and 12.8), in the gated-GELU backward always (from k 512 on measured: 3 % and more).
     int64_t K = 0;
     for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
     const double last = K >= 1024 ? 1.0 : 0.65;
@@ -963,7 +969,9 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
         if ((int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 64) <= 256)
           return launch_cfg<128, 64, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
       }
-      return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1, 64>(g, e, 1, st);
+      if (EPI == EPI_GEGLU_BWD || K > 1024 || (K >= 768 && t128 >= 192))
+        return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1, 64>(g, e, 1, st);
+      if constexpr (EPI != EPI_GEGLU_BWD) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
     }
     if constexpr (EPI_T == EPI_STORE || EPI_T == EPI_RESID) {  // (the dropout copies are not built: 14592 x 768 x 2048 with residual 65 us, 59 like this)
       if (g.N % 192 == 0) {
@@ -976,7 +984,8 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
         return launch_cfg<256, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 2>(g, e, 1, st);
     if constexpr (EPI != EPI_GEGLU_BWD)
       if (c256 <= c128) return launch_cfg<256, 256, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
-    if (EPI == EPI_GEGLU_BWD || K >= 1024) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
+    const bool part = EPI == EPI_STORE && K > 1024 && (t128 <= 384 || (K >= 3072 && t128 <= 480));
+    if (EPI == EPI_GEGLU_BWD || (K >= 1024 && !part)) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
     if constexpr (EPI != EPI_GEGLU_BWD) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 2, 1, 64>(g, e, 1, st);
   }
 }

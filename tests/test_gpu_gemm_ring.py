@@ -10,16 +10,19 @@ from test_gpu_gemm_tiles import _check_gemm, _tile
 pytestmark = pytest.mark.gpu
 
 
+# last tiles of 8 rows and 8 columns.  5000 rows: 360 tiles, two stages but for the first; 6024: 432, the ring
+@pytest.mark.parametrize("M", [5000, 6024])
 @pytest.mark.parametrize("nk", range(16, 22))
-def test_every_loop_remainder(nk):
-    assert _tile(5000, 1032, 64 * nk) == "128x128, two per unit"   # last tiles of 8 rows and 8 columns
-    _check_gemm(5000, 1032, 64 * nk, True)
+def test_every_loop_remainder(nk, M):
+    assert _tile(M, 1032, 64 * nk) == "128x128, two per unit"
+    _check_gemm(M, 1032, 64 * nk, True)
 
 
+# 4224 x 1024: 264 tiles, more than one per compute unit; 3968: 248, and four stages of 64
+@pytest.mark.parametrize("seq", [66, 62])
 @pytest.mark.parametrize("d_model", [64, 128, 192])   # one, two and three k-tiles
-def test_gated_gelu_backward_few_k_tiles(d_model):
-    # 4224 x 1024: 264 tiles, more than one per compute unit
-    cfg = SI.BlockConfig(f"gemm_ring_{d_model}", 64, 64, 66, d_model, 1, 64, 1024, attn_scale=0.125)
+def test_gated_gelu_backward_few_k_tiles(d_model, seq):
+    cfg = SI.BlockConfig(f"gemm_ring_{d_model}", 64, 64, seq, d_model, 1, 64, 1024, attn_scale=0.125)
     w, x, dy = make_case(cfg)
     y, saved = O.block_fwd(cfg, x, w)
     dx, g = O.block_bwd(cfg, dy, w, saved)
@@ -28,9 +31,10 @@ def test_gated_gelu_backward_few_k_tiles(d_model):
     check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
 
 
-@pytest.mark.parametrize("nk", range(1, 7))
+@pytest.mark.parametrize("nk", [*range(1, 7), *range(12, 17)])
 def test_one_tile_per_unit_every_loop_remainder(nk):
-    """Four stages of 64: as many k-tiles as there are stages, fewer, more; last tiles of 64 rows and 8 columns."""
+    """Four stages, of 32 and from 12 k-tiles of 64 on of those: as many k-tiles as there are stages, fewer, more; last tiles of
+    64 rows and 8 columns."""
     assert _tile(3648, 776, 64 * nk) == "128x128"
     _check_gemm(3648, 776, 64 * nk, True)
 
