@@ -721,6 +721,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
   if (D.mlp == ACT_RELU) {
     {  // du = (dy Wo_ff^T) where a > 0
       GemmDesc g = gemm1(T, D.F, D.d, dy, D.d, 1, w->wo_ff, D.d, 1, ty);
+      g.beside = W.fork.on;
       GemmEpi e = epi(EPI_RESID, du_p, D.F, ty);
       e.aux0 = S.a; e.aux_type = ty; e.aux_mask = 1; e.drop = drop_site(D, DROP_MLP_HIDDEN);
       T5_STEP("gemm_da_relu_bwd", run_gemm(g, e, st));
@@ -732,11 +733,13 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
     }
     {  // dn2 = du Wi0^T
       GemmDesc g = gemm1(T, D.d, D.F, du_p, D.F, 1, w->wi0, D.F, 1, ty);
+      g.beside = W.fork.on;
       T5_STEP("gemm_dn2", run_gemm(g, epi(EPI_STORE, W.dn, D.d, IN_F32), st));
     }
   } else {
     {  // da = dy Wo_ff^T, fused with the gated-GELU backward: du = da w gelu'(u), dw = da gelu(u)
       GemmDesc g = gemm1(T, D.F, D.d, dy, D.d, 1, w->wo_ff, D.d, 1, ty);
+      g.beside = W.fork.on;
       GemmEpi e = epi(EPI_GEGLU_BWD, du_p, 2 * D.F, ty);
       e.out1 = dw_p; e.aux0 = S.gp; e.aux1 = S.gl; e.aux_type = ty; e.ld_aux = D.F;
       T5_STEP("gemm_da_geglu_bwd", run_gemm(g, e, st));
@@ -748,6 +751,7 @@ int bwd_mlp(const Dims& D, const void* dy, const float* hin, const t5_block_weig
     }
     {  // dn2 = du Wi0^T + dw Wi1^T
       GemmDesc g = gemm1(T, D.d, D.F, du_p, 2 * D.F, 1, w->wi0, D.F, 1, ty);
+      g.beside = W.fork.on;
       g.nseg = 2;
       g.seg[1] = GemmSeg{dw_p, w->wi1, 2 * D.F, D.F, D.F};
       T5_STEP("gemm_dn2", run_gemm(g, epi(EPI_STORE, W.dn, D.d, IN_F32), st));
@@ -781,6 +785,7 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   }
   {  // dcx = dh2 Xo^T
     GemmDesc g = gemm1(T, D.I, D.d, dh_op, D.d, 1, xw->xo, D.d, 1, ty);
+    g.beside = W.fork.on;
     T5_STEP("gemm_dcx", run_gemm(g, epi(EPI_STORE, W.dc, D.I, ty), st));
   }
   const AttnIO io = cross_io(D, S, &W);
@@ -801,6 +806,7 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   }
   {  // denc = dk Xk^T + dv Xv^T
     GemmDesc g = gemm1(Te, D.d, D.I, W.dkvx, 2 * D.I, 1, xw->xk, D.I, 1, ty);
+    g.beside = W.fork.on;
     g.nseg = 2;
     g.seg[1] = GemmSeg{at(W.dkvx, (size_t)D.I, es), xw->xv, 2 * D.I, D.I, D.I};
     GemmEpi e = epi(denc_add ? EPI_RESID : EPI_STORE, denc, D.d, denc_f32 ? IN_F32 : ty);
@@ -809,6 +815,7 @@ int bwd_cross_attn(const t5_block_cfg* cfg, const Dims& D, const void* enc, cons
   }
   {  // dnx = dq Xq^T
     GemmDesc g = gemm1(T, D.d, D.I, W.dqx, D.I, 1, xw->xq, D.I, 1, ty);
+    g.beside = W.fork.on;
     T5_STEP("gemm_dnx", run_gemm(g, epi(EPI_STORE, W.dn, D.d, IN_F32), st));
   }
   // dh1 = dh2 + RMSNormBwd(h, lnx_scale, dnx)
@@ -841,6 +848,7 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   }
   {  // dc = dh Wo^T
     GemmDesc g = gemm1(T, D.I, D.d, dh_op, D.d, 1, w->wo, D.d, 1, ty);
+    g.beside = W.fork.on;
     T5_STEP("gemm_dc", run_gemm(g, epi(EPI_STORE, W.dc, D.I, ty), st));
   }
   const AttnIO io = attn_io_packed(S.qkv, W.dqkv, D.I, es);
@@ -859,6 +867,7 @@ int bwd_self_attn(const t5_block_cfg* cfg, const Dims& D, const RelposLut& lut, 
   }
   {  // dn1 = dq Wq^T + dk Wk^T + dv Wv^T
     GemmDesc g = gemm1(T, D.d, D.I, W.dqkv, 3 * D.I, 1, w->wq, D.I, 1, ty);
+    g.beside = W.fork.on;
     g.nseg = 3;
     g.seg[1] = GemmSeg{at(W.dqkv, (size_t)D.I, es), w->wk, 3 * D.I, D.I, D.I};
     g.seg[2] = GemmSeg{at(W.dqkv, (size_t)2 * D.I, es), w->wv, 3 * D.I, D.I, D.I};

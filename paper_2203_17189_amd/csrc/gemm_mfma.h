@@ -955,6 +955,10 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    25.3; three stages of 64 43.  The longer ramp of 64 pays from K = 1025 on, with 192 tiles or more from 768 on (us with 32
     //    and with 64: 160 tiles of 2520 x 1024: k 512 7.8 and 8.9, 1024 11.0 and 11.9, 1280 15.7 and 13.4; 228 of 4824 x 768: 512 8.7
     //    and 9.5, 768 11.2 and 11.1, 1024 13.3 and 12.8), in the gated-GELU backward always (from k 512 on measured: 3 % and more).
+    //    Beside launches on another stream, whose workgroups find no room on a unit with 128 KB taken, only from 5120 on (backward
+    //    with the weight gradients overlapped, us with 32 and with 64 throughout: d 768, k 768, 2304 and 4096, 4096 tokens 253 and
+    //    261, 5000 tokens 297 and 309; d 2048, k 2048, 6144 and 10240, 2000 tokens 590 and 536; d 1024, k 1024, 3072 and 5632, 3500
+    //    tokens 339 and 332, like this 310 where 64 throughout takes 317);
     int64_t K = 0;
     for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
     const double last = K >= 1024 ? 1.0 : 0.65;
@@ -969,9 +973,9 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
         if ((int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 64) <= 256)
           return launch_cfg<128, 64, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
       }
-      if (EPI == EPI_GEGLU_BWD || K > 1024 || (K >= 768 && t128 >= 192))
+      if (!(g.beside && K < 5120) && (EPI == EPI_GEGLU_BWD || K > 1024 || (K >= 768 && t128 >= 192)))
         return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1, 64>(g, e, 1, st);
-      if constexpr (EPI != EPI_GEGLU_BWD) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
+      return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
     }
     if constexpr (EPI_T == EPI_STORE || EPI_T == EPI_RESID) {  // (the dropout copies are not built: 14592 x 768 x 2048 with residual 65 us, 59 like this)
       if (g.N % 192 == 0) {

@@ -94,6 +94,7 @@ struct GemmDesc {
   GemmSeg seg[3];
   int a_kc, b_kc;
   int in_type;  // element type of A and B
+  int beside;   // other launches (a backward's weight gradients, on their own stream) run beside this one
   // Several problems of one shape in one launch (EPI_SPLIT_F32 with accumulate, one segment, MFMA kernel only):
   // groups is a DEVICE array of ngroups x GEMM_GROUP_PTRS pointers {A, B, out0, out1, out2}, which replace
   // seg[0].A / .B and the epilogue's outputs for the workgroups of that problem.  ngroups <= 1: one problem.

@@ -37,15 +37,18 @@ def _close(a, b, what):
 BLK = SI.BlockConfig("ovl_bf16", 90, batch=4, seq=256, d_model=256, n_heads=4, d_kv=64, d_ff=512, attn_scale=0.125)
 
 
-def test_block_backward_overlapped_equals_serial(overlap):
+# 3500 x 768: products of one tile a compute unit, which take shallower stages beside the side stream (the same sums)
+@pytest.mark.parametrize("blk", [BLK, replace(BLK, name="ovl_one_tile", batch=14, seq=250, d_model=768, d_ff=1024)],
+                         ids=lambda c: c.name)
+def test_block_backward_overlapped_equals_serial(overlap, blk):
     P = overlap
-    w, x, dy = make_case(BLK)
-    dw, tx, tdy = upload_case(BLK, w, x, dy)
-    y, stash = P.t5_block_fwd(BLK, tx, dw)
-    runs = [P.t5_block_bwd(BLK, tdy, tx, dw, stash) for _ in range(3)]     # back to back, no host sync in between
+    w, x, dy = make_case(blk)
+    dw, tx, tdy = upload_case(blk, w, x, dy)
+    y, stash = P.t5_block_fwd(blk, tx, dw)
+    runs = [P.t5_block_bwd(blk, tdy, tx, dw, stash) for _ in range(3)]     # back to back, no host sync in between
     torch.cuda.synchronize()
     P.t5_wgrad_overlap_enable(False)
-    dx0, g0 = P.t5_block_bwd(BLK, tdy, tx, dw, stash)
+    dx0, g0 = P.t5_block_bwd(blk, tdy, tx, dw, stash)
     torch.cuda.synchronize()
     for dx, g in runs:
         assert torch.equal(dx, dx0)
