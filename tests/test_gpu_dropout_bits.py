@@ -30,6 +30,24 @@ def test_self_attention(d_kv, causal, seq):
     check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
 
 
+@pytest.mark.parametrize("max_distance", [128, 4096])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d_kv", [64, 128])
+def test_beside_either_form_of_the_bias(d_kv, causal, max_distance):
+    """620 positions, ten key tiles to a row of words: the bias from the window of diagonals, or (4096) from the slice, which
+    lies behind the keep words in LDS."""
+    import paper_2203_17189_amd as P
+    cfg = replace(BASE, batch=2, seq=620, causal=causal, d_kv=d_kv, attn_scale=d_kv ** -0.5, max_distance=max_distance,
+                  name=f"dropout_bits_bias_{d_kv}_{int(causal)}_{max_distance}")
+    assert P.t5_block_kernel_path(cfg) & P.PATH_MFMA_ATTN_BWD
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
+    check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
+
+
 @pytest.mark.parametrize("seq,enc_seq", [(33, 100), (129, 35), (64, 129)])
 def test_cross_attention(seq, enc_seq):
     import paper_2203_17189_amd as P

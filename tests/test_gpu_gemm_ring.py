@@ -18,6 +18,20 @@ def test_every_loop_remainder(nk, M):
     _check_gemm(M, 1032, 64 * nk, True)
 
 
+# 6400 x 1024, 400 tiles: the gradient behind the feed-forward is a sum of two products over d_ff, that behind the attention of
+# three over 384; the runs' ends fall on every tile of the loop's rounds of six, and A's cursor passes them a tile before B's
+@pytest.mark.parametrize("d_ff", [576, 640, 704, 768, 832, 896])
+def test_several_runs_of_k(d_ff):
+    assert _tile(6400, 1024, 2 * d_ff) == _tile(6400, 1024, 3 * 384) == "128x128, two per unit"
+    cfg = SI.BlockConfig(f"gemm_ring_runs_{d_ff}", 67, 64, 100, 1024, 6, 64, d_ff, attn_scale=0.125)
+    w, x, dy = make_case(cfg)
+    y, saved = O.block_fwd(cfg, x, w)
+    dx, g = O.block_bwd(cfg, dy, w, saved)
+    gy, gdx, gg = run_block_gpu(cfg, w, x, dy)
+    errs = {"y": rel_err(gy, y), "dx": rel_err(gdx, dx), **{n: rel_err(gg[n], g[n]) for n in g}}
+    check_bf16(cfg.name, errs, block_floors(cfg, w, x, dy, (y, dx, g)))
+
+
 # 4224 x 1024: 264 tiles, more than one per compute unit; 3968: 248, and four stages of 64
 @pytest.mark.parametrize("seq", [66, 62])
 @pytest.mark.parametrize("d_model", [64, 128, 192])   # one, two and three k-tiles
