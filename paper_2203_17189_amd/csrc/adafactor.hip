@@ -21,8 +21,8 @@ namespace t5mi {
 
 namespace {
 
-constexpr int TR = 64;    // tile rows
-constexpr int TCV = 256;  // tile cols when vectorised (64 lanes x 4)
+constexpr int TR = 64;   // tile rows
+constexpr int TC = 256;  // tile columns, four to a lane
 // A tile's workgroup has sixteen wavefronts of four rows, whose loads are all in flight at once.  (With four wavefronts of sixteen
 // rows eight workgroups shared a compute unit: the 2961 tiles of a d 2048 layer were 1.45 rounds, the second half empty; stats
 // 57 -> 52 us, apply 118 -> 112; norms stay at 82, 4.7 TB/s.)
@@ -38,27 +38,42 @@ struct AfWs {
   float* scal;     // [4]: 0 = coef
 };
 
-template <int VEC>
-__device__ __forceinline__ void ldv(const float* __restrict__ p, float (&v)[VEC]) {
-  if constexpr (VEC == 4) {
-    f32x4 t = *reinterpret_cast<const f32x4*>(p);
+// A lane's four columns: neighbours, read and written as 16 bytes, where rows are a multiple of 16 bytes (V4), else 64 apart, so
+// that an instruction still covers 256 bytes of a row.  (Of rows that are no such multiple a tile had one column to a lane: a
+// quarter of the work for the same sixteen wavefronts, 4097 x 4095 147 -> 93 us, 32128 x 769 230 -> 162.)
+template <bool V4>
+struct AfCols {
+  int c0, n;  // first column of the lane, columns of the tensor
+  __device__ __forceinline__ AfCols(int bx, int lane, int64_t C) : c0(bx * TC + (V4 ? lane * 4 : lane)), n((int)C) {}
+  __device__ __forceinline__ bool any() const { return c0 < n; }
+  __device__ __forceinline__ bool has(int i) const { return V4 || c0 + 64 * i < n; }  // (where there are any)
+  // (past the end: the last column again, so that a row's loads are one block)
+  __device__ __forceinline__ uint32_t at(int i) const { return V4 ? c0 + i : min(c0 + 64 * i, n - 1); }
+  __device__ __forceinline__ static int slot(int lane, int i) { return V4 ? lane * 4 + i : lane + 64 * i; }  // in the tile
+  // row: the same in the whole wavefront
+  __device__ __forceinline__ void load(const float* __restrict__ row, float (&v)[4]) const {
+    if constexpr (V4) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>(row + at(0));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = t[i];
-  } else {
-    v[0] = p[0];
-  }
-}
-template <int VEC>
-__device__ __forceinline__ void stv(float* __restrict__ p, const float (&v)[VEC]) {
-  if constexpr (VEC == 4) {
-    f32x4 t;
+      for (int i = 0; i < 4; ++i) v[i] = t[i];
+    } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) t[i] = v[i];
-    *reinterpret_cast<f32x4*>(p) = t;
-  } else {
-    p[0] = v[0];
+      for (int i = 0; i < 4; ++i) v[i] = row[at(i)];
+    }
   }
-}
+  __device__ __forceinline__ void store(float* __restrict__ row, const float (&v)[4]) const {
+    if constexpr (V4) {
+      f32x4 t;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[i] = v[i];
+      *reinterpret_cast<f32x4*>(row + at(0)) = t;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (has(i)) row[at(i)] = v[i];
+    }
+  }
+};
 
 struct AfItem {
   float* w;
@@ -70,7 +85,7 @@ struct AfItem {
   float* m;  // momentum (nullable)
   int64_t R, C;
   AfWs ws;
-  int vec, ntc, ntr, factored;
+  int v4, ntc, ntr, factored;
 };
 struct AfBatch {
   AfItem it[AF_MAX_TENSORS];
@@ -91,29 +106,29 @@ __device__ __forceinline__ int af_find(const int* start, int b) {
 }
 
 // Wave w takes rows w, w + 16, ... of the tile; lanes span the columns.
-template <int VEC>
+template <bool V4>
 __device__ __forceinline__ void af_stats_tile(const AfItem& it, int bx, int by, float (*colred)[256]) {
   const float* __restrict__ g = it.g;
   const int64_t R = it.R, C = it.C;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t c0 = (int64_t)bx * 64 * VEC + lane * VEC;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const AfCols<V4> cols(bx, lane, C);
   const int64_t r0 = (int64_t)by * TR + wave;
-  float csum[VEC], v[RPW][VEC], rs[RPW];
+  float csum[4], v[RPW][4], rs[RPW];
 #pragma unroll
-  for (int i = 0; i < VEC; ++i) csum[i] = 0.f;
+  for (int i = 0; i < 4; ++i) csum[i] = 0.f;
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
     const int64_t r = r0 + NWV * q;
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) v[q][i] = 0.f;
-    if (c0 < C && r < R) ldv<VEC>(g + r * C + c0, v[q]);
+    for (int i = 0; i < 4; ++i) v[q][i] = 0.f;
+    if (cols.any() && r < R) cols.load(g + r * C, v[q]);
   }
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
     rs[q] = 0.f;
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-      const float x = v[q][i] * v[q][i];
+    for (int i = 0; i < 4; ++i) {
+      const float x = cols.has(i) ? v[q][i] * v[q][i] : 0.f;
       csum[i] += x;
       rs[q] += x;
     }
@@ -127,10 +142,10 @@ __device__ __forceinline__ void af_stats_tile(const AfItem& it, int bx, int by, 
     if (r < R) it.ws.rowpart[(int64_t)bx * R + r] = lane == 0 ? rs[0] : lane == 1 ? rs[1] : lane == 2 ? rs[2] : rs[3];
   }
 #pragma unroll
-  for (int i = 0; i < VEC; ++i) colred[wave][lane * VEC + i] = csum[i];
+  for (int i = 0; i < 4; ++i) colred[wave][cols.slot(lane, i)] = csum[i];
   __syncthreads();
-  for (int t = threadIdx.x; t < 64 * VEC; t += NT) {
-    const int64_t c = (int64_t)bx * 64 * VEC + t;
+  for (int t = threadIdx.x; t < TC; t += NT) {
+    const int64_t c = (int64_t)bx * TC + t;
     float s = 0.f;
 #pragma unroll
     for (int w = 0; w < NWV; ++w) s += colred[w][t];
@@ -145,8 +160,8 @@ __global__ __launch_bounds__(NT, 8) void af_stats_kernel(AfBatch b) {
   if (!it.factored) return;
   const int local = blockIdx.x - b.tile_start[ti];
   const int bx = local % it.ntc, by = local / it.ntc;
-  if (it.vec == 4) af_stats_tile<4>(it, bx, by, colred);
-  else af_stats_tile<1>(it, bx, by, colred);
+  if (it.v4) af_stats_tile<true>(it, bx, by, colred);
+  else af_stats_tile<false>(it, bx, by, colred);
 }
 
 // One thread per row and per column: folds the tile partials into the second-moment vectors.
@@ -189,7 +204,7 @@ __device__ __forceinline__ float af_mean_vrow(const float* __restrict__ rsum, in
 }
 
 // Per-tile sums of U*U and W*W.  FACT: U = g rfac cfac.  !FACT: updates v_full and U = g rsqrt(v).
-template <int VEC, bool FACT>
+template <bool V4, bool FACT>
 __device__ __forceinline__ void af_norms_tile(const AfItem& it, int bx, int by, int tile, float beta2, float eps1,
                                               float* red) {
   const float* __restrict__ g = it.g;
@@ -198,18 +213,18 @@ __device__ __forceinline__ void af_norms_tile(const AfItem& it, int bx, int by, 
   const float* __restrict__ v_row = it.v_row;
   const int64_t R = it.R, C = it.C;
   const AfWs& ws = it.ws;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t c0 = (int64_t)bx * 64 * VEC + lane * VEC;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const AfCols<V4> cols(bx, lane, C);
   const int64_t r0 = (int64_t)by * TR + wave;
-  float gv[RPW][VEC], wv[RPW][VEC];
+  float gv[RPW][4], wv[RPW][4];
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
     const int64_t r = r0 + NWV * q;
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) gv[q][i] = wv[q][i] = 0.f;
-    if (c0 < C && r < R) {
-      ldv<VEC>(g + r * C + c0, gv[q]);
-      ldv<VEC>(w + r * C + c0, wv[q]);
+    for (int i = 0; i < 4; ++i) gv[q][i] = wv[q][i] = 0.f;
+    if (cols.any() && r < R) {
+      cols.load(g + r * C, gv[q]);
+      cols.load(w + r * C, wv[q]);
     }
   }
   float inv_mean = 1.f;
@@ -219,9 +234,9 @@ __device__ __forceinline__ void af_norms_tile(const AfItem& it, int bx, int by, 
     if (tile == 0 && threadIdx.x == 0) ws.scal[1] = inv_mean;
   }
   float su = 0.f, sw = 0.f;
-  if (c0 < C) {
-    float cf[VEC];
-    if constexpr (FACT) ldv<VEC>(ws.cfac + c0, cf);
+  if (cols.any()) {
+    float cf[4];
+    if constexpr (FACT) cols.load(ws.cfac, cf);
 #pragma unroll
     for (int q = 0; q < RPW; ++q) {
       const int64_t r = r0 + NWV * q;
@@ -229,22 +244,22 @@ __device__ __forceinline__ void af_norms_tile(const AfItem& it, int bx, int by, 
       if constexpr (FACT) {
         const float rf = rsqrtf(v_row[r] * inv_mean);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
+        for (int i = 0; i < 4; ++i) {
           const float u = gv[q][i] * rf * cf[i];
-          su += u * u;
-          sw += wv[q][i] * wv[q][i];
+          su += cols.has(i) ? u * u : 0.f;
+          sw += cols.has(i) ? wv[q][i] * wv[q][i] : 0.f;
         }
       } else {
-        float vv[VEC];
-        ldv<VEC>(v_full + r * C + c0, vv);
+        float vv[4];
+        cols.load(v_full + r * C, vv);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
+        for (int i = 0; i < 4; ++i) {
           vv[i] = beta2 * vv[i] + (1.f - beta2) * (gv[q][i] * gv[q][i] + eps1);
           const float u = gv[q][i] * rsqrtf(vv[i]);
-          su += u * u;
-          sw += wv[q][i] * wv[q][i];
+          su += cols.has(i) ? u * u : 0.f;
+          sw += cols.has(i) ? wv[q][i] * wv[q][i] : 0.f;
         }
-        stv<VEC>(v_full + r * C + c0, vv);
+        cols.store(v_full + r * C, vv);
       }
     }
   }
@@ -262,12 +277,12 @@ __global__ __launch_bounds__(NT, 8) void af_norms_kernel(AfBatch b) {
   const AfItem& it = b.it[ti];
   const int local = blockIdx.x - b.tile_start[ti];
   const int bx = local % it.ntc, by = local / it.ntc;
-  if (it.vec == 4) {
-    if (it.factored) af_norms_tile<4, true>(it, bx, by, local, b.beta2, b.eps1, red);
-    else af_norms_tile<4, false>(it, bx, by, local, b.beta2, b.eps1, red);
+  if (it.v4) {
+    if (it.factored) af_norms_tile<true, true>(it, bx, by, local, b.beta2, b.eps1, red);
+    else af_norms_tile<true, false>(it, bx, by, local, b.beta2, b.eps1, red);
   } else {
-    if (it.factored) af_norms_tile<1, true>(it, bx, by, local, b.beta2, b.eps1, red);
-    else af_norms_tile<1, false>(it, bx, by, local, b.beta2, b.eps1, red);
+    if (it.factored) af_norms_tile<false, true>(it, bx, by, local, b.beta2, b.eps1, red);
+    else af_norms_tile<false, false>(it, bx, by, local, b.beta2, b.eps1, red);
   }
 }
 
@@ -293,7 +308,7 @@ __global__ __launch_bounds__(1024) void af_coef_kernel(AfBatch b, adafactor_cfg 
 }
 
 // W <- W - D - decay W,  D = alpha U, or with momentum m <- beta1 m + (1 - beta1) alpha U, D = m
-template <int VEC, bool FACT>
+template <bool V4, bool FACT>
 __device__ __forceinline__ void af_apply_tile(const AfItem& it, int bx, int by, float beta1, float decay) {
   float* __restrict__ w = it.w;
   const float* __restrict__ g = it.g;
@@ -303,50 +318,51 @@ __device__ __forceinline__ void af_apply_tile(const AfItem& it, int bx, int by, 
   float* __restrict__ mom = it.m;
   const int64_t R = it.R, C = it.C;
   const AfWs& ws = it.ws;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t c0 = (int64_t)bx * 64 * VEC + lane * VEC;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const AfCols<V4> cols(bx, lane, C);
   const int64_t r0 = (int64_t)by * TR + wave;
-  if (c0 >= C) return;
-  float gv[RPW][VEC], wv[RPW][VEC];
+  if (!cols.any()) return;
+  float gv[RPW][4], wv[RPW][4];
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
     const int64_t r = r0 + NWV * q;
     if (r < R) {
-      ldv<VEC>(g + r * C + c0, gv[q]);
-      ldv<VEC>(w + r * C + c0, wv[q]);
+      cols.load(g + r * C, gv[q]);
+      cols.load(w + r * C, wv[q]);
     }
   }
   const float coef = ws.scal[0];
-  float cf[VEC];
-  if constexpr (FACT) ldv<VEC>(ws.cfac + c0, cf);
+  float cf[4];
+  if constexpr (FACT) cols.load(ws.cfac, cf);
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
     const int64_t r = r0 + NWV * q;
     if (r >= R) break;
-    float dv[VEC];
+    float dv[4];
     if constexpr (FACT) {
       const float rf = rsqrtf(v_row[r] * ws.scal[1]) * coef;
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) dv[i] = gv[q][i] * rf * cf[i];
+      for (int i = 0; i < 4; ++i) dv[i] = gv[q][i] * rf * cf[i];
     } else {
-      float vv[VEC];
-      ldv<VEC>(v_full + r * C + c0, vv);
+      float vv[4];
+      cols.load(v_full + r * C, vv);
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) dv[i] = coef * gv[q][i] * rsqrtf(vv[i]);
+      for (int i = 0; i < 4; ++i) dv[i] = coef * gv[q][i] * rsqrtf(vv[i]);
     }
     if (mom) {
-      float mv[VEC];
-      ldv<VEC>(mom + r * C + c0, mv);
+      float mv[4];
+      cols.load(mom + r * C, mv);
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) { mv[i] = beta1 * mv[i] + (1.f - beta1) * dv[i]; dv[i] = mv[i]; }
-      stv<VEC>(mom + r * C + c0, mv);
+      for (int i = 0; i < 4; ++i) { mv[i] = beta1 * mv[i] + (1.f - beta1) * dv[i]; dv[i] = mv[i]; }
+      cols.store(mom + r * C, mv);
     }
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) wv[q][i] = wv[q][i] - dv[i] - decay * wv[q][i];
-    stv<VEC>(w + r * C + c0, wv[q]);
+    for (int i = 0; i < 4; ++i) wv[q][i] = wv[q][i] - dv[i] - decay * wv[q][i];
+    cols.store(w + r * C, wv[q]);
     if (lp) {
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) lp[r * C + c0 + i] = (bf16)wv[q][i];
+      for (int i = 0; i < 4; ++i)
+        if (cols.has(i)) (lp + r * C)[cols.at(i)] = (bf16)wv[q][i];
     }
   }
 }
@@ -356,23 +372,22 @@ __global__ __launch_bounds__(NT, 8) void af_apply_kernel(AfBatch b) {
   const AfItem& it = b.it[ti];
   const int local = blockIdx.x - b.tile_start[ti];
   const int bx = local % it.ntc, by = local / it.ntc;
-  if (it.vec == 4) {
-    if (it.factored) af_apply_tile<4, true>(it, bx, by, b.beta1, b.decay);
-    else af_apply_tile<4, false>(it, bx, by, b.beta1, b.decay);
+  if (it.v4) {
+    if (it.factored) af_apply_tile<true, true>(it, bx, by, b.beta1, b.decay);
+    else af_apply_tile<true, false>(it, bx, by, b.beta1, b.decay);
   } else {
-    if (it.factored) af_apply_tile<1, true>(it, bx, by, b.beta1, b.decay);
-    else af_apply_tile<1, false>(it, bx, by, b.beta1, b.decay);
+    if (it.factored) af_apply_tile<false, true>(it, bx, by, b.beta1, b.decay);
+    else af_apply_tile<false, false>(it, bx, by, b.beta1, b.decay);
   }
 }
 
 struct AfGeom {
-  int vec, ntc, ntr;
+  int ntc, ntr;
   int64_t ntiles;
 };
 AfGeom geom(int64_t R, int64_t C) {
   AfGeom g;
-  g.vec = (C % 4 == 0) ? 4 : 1;
-  g.ntc = ceil_div(C, 64 * g.vec);
+  g.ntc = ceil_div(C, TC);
   g.ntr = ceil_div(R, TR);
   g.ntiles = (int64_t)g.ntc * g.ntr;
   return g;
@@ -395,7 +410,11 @@ AfWs carve(void* ws, int64_t R, int64_t C, const AfGeom& g) {
 
 size_t adafactor_ws_bytes(int64_t R, int64_t C, int factored) {
   (void)factored;
-  const AfGeom g = geom(R, C);
+  AfGeom g = geom(R, C);
+  if (C % 4) {  // (the size callers know for such rows: room for tiles of 64 columns)
+    g.ntc = ceil_div(C, 64);
+    g.ntiles = (int64_t)g.ntc * g.ntr;
+  }
   size_t n = 0;
   n += align_up((size_t)g.ntc * R * 4) + align_up((size_t)g.ntr * C * 4);
   n += 2 * align_up((size_t)g.ntiles * 4) + align_up(R * 4) + align_up(C * 4) + align_up(16);
@@ -423,7 +442,7 @@ hipError_t launch_adafactor_multi(const AfTensor* t, int n, const adafactor_cfg&
     it.R = t[i].rows; it.C = t[i].cols;
     it.ws = carve(wp, it.R, it.C, g);
     wp += adafactor_ws_bytes(it.R, it.C, t[i].factored);
-    it.vec = g.vec; it.ntc = g.ntc; it.ntr = g.ntr; it.factored = t[i].factored ? 1 : 0;
+    it.v4 = it.C % 4 == 0; it.ntc = g.ntc; it.ntr = g.ntr; it.factored = t[i].factored ? 1 : 0;
     b.tile_start[i] = (int)tiles;
     b.fin_start[i] = (int)fins;
     tiles += g.ntiles;

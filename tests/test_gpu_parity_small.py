@@ -108,6 +108,13 @@ def test_adafactor_three_steps(rows, cols, factored):
         assert torch.equal(lp, dp.to(torch.bfloat16))
 
 
+# rows that are no multiple of 16 bytes: a tile's 256 columns are 64 apart in a lane
+@pytest.mark.parametrize("rows,cols,factored", [(65, 255, True), (63, 257, True), (64, 1, True), (5, 65, True), (130, 769, True),
+                                                (1, 63, False), (17, 321, False), (3, 1, False)])
+def test_adafactor_odd_columns(rows, cols, factored):
+    test_adafactor_three_steps(rows, cols, factored)
+
+
 @pytest.mark.parametrize("rows,cols,factored", [(513, 1027, True), (33, 7, False)])
 def test_adafactor_resume_from_saved_state_is_bit_identical(rows, cols, factored):
     """Checkpoint / resume on the device path: steps 1..3 straight through against steps 1..2, the parameter and
