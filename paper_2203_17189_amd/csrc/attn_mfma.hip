@@ -912,78 +912,103 @@ __global__ __launch_bounds__(256) void attn_ddiag_reduce_kernel(const float* __r
 // ------------------------------------------------------------------------------------------------
 // dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
 // ------------------------------------------------------------------------------------------------
-// Two forms.  This one takes a tile at a time from two stages: 64 channels without the causal mask, where two or three
-// waves per SIMD cover for each other, or with dropout (causal 32 x 512, 12 heads: 68 us, the other form 72), or with a slice
-// beside which three stages would be too much (dkv_takes_pipe).
-template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool THREE, bool WIN>
-__global__ __launch_bounds__(256, THREE ? 3 : 2)
-void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
-                              const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
-  constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
-  constexpr int TILE = BQ * DK * 2, STG = 2 * TILE;  // a stage holds a Q tile then a dO tile
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+// What the two forms of the kernel share: a workgroup's operands, a ring of NST stages of query tiles, and the steps over a
+// sub-tile of 32 queries x 32 keys.
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN, int NST>
+struct DkvTiles {
+  static constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
+  static constexpr int TILE = BQ * DK * 2, STG = 2 * TILE;  // a stage holds a Q tile then a dO tile
+  const AttnIO& io;
+  const AttnDims& a;
+  char* smem;
   // The score and dP accumulators start from -lse/scale and -dvec, so that the MFMA results are
   // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
-  float* lse_all = reinterpret_cast<float*>(smem + 2 * STG);  // [2 stages][BQ]  -lse / scale
-  float* dv_all = lse_all + 2 * BQ;                           // [2 stages][BQ]  -dvec
-  // [2 stages][2 key tiles][2][BQ] keep decisions (DROP only)
-  uint32_t* keep_all = reinterpret_cast<uint32_t*>(dv_all + 2 * BQ);
+  float* lse_all;      // [stages][BQ]  -lse / scale
+  float* dv_all;       // [stages][BQ]  -dvec
+  uint32_t* keep_all;  // [stages][2 key tiles][2][BQ] keep decisions (DROP only)
   // Window, or [-BQ, S + BCK - 1), log2 units (BIAS only); the slice's BQ entries in front are only ever read for
   // queries past the end of a ragged last tile, whose probabilities are set to zero
-  float* dg = dv_all + 2 * BQ + (DROP ? 8 * BQ : 0) + (WIN ? 0 : BQ);
+  float* dg;
+  const float* dgw;  // (WIN) the four diagonals of queries 8 rq + 4 g + 0..3 of a sub-tile, the last query's first
+  BiasWin win;
+  int tid, lane, g, wave, S, Sk, h, b;
+  int j0, j_w0, j_loc;  // first key of the workgroup and of this wave, this lane's key in the workgroup
+  int it_begin, it_tail, n_it;
+  float sc;
+  const bf16 *base, *dobase;
+  size_t ld, ldo;
+  TileDma<DK, BQ> tq, tdo, tq_tail, tdo_tail;  // _tail: the last tile of a query sequence that does not fill it
+  uint32_t lds0, lds_lse, lds_dv, lds_keep;
+  const float *ndvec, *nlse;
+  const uint32_t* keep_w;
+  int keep_n;  // this lane's key in a word
+  bf16x8 kf[KS], vf[KS];
+  f32x16 dkT[CT], dvT[CT];
 
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int S = a.S, Sk = a.Sk, I = a.H * DK;
-  const size_t ld = (size_t)io.ldq, ldkv = (size_t)io.ldkv;
-  int kt_, h, b;
-  decode_block((Sk + BCK - 1) / BCK, a.H, a.B, kt_, h, b);
-  const int j0 = kt_ * BCK;
-  const int j_w0 = j0 + wave * 32;
-  const int j_loc = wave * 32 + (lane & 31);
-  const int j = j0 + j_loc;
-  const int j_ld = j < Sk ? j : Sk - 1;
-  const bf16* base = (const bf16*)io.q + (size_t)b * S * ld + h * DK;
-  const bf16* dobase = dout + (size_t)b * S * I + h * DK;
-  const int it_begin = CAUSAL ? (j0 / BQ) : 0;
-  const size_t srow = ((size_t)b * a.H + h) * S;
-  // Q/dO tiles (DMA) and the matching lse / dvec slices are double buffered.
-  // tq_tail / tdo_tail: the last tile of a query sequence that does not fill it
-  TileDma<DK, BQ> tq, tdo, tq_tail, tdo_tail;
-  tq.init(wave, lane, ld);
-  tdo.init(wave, lane, (size_t)I);
-  tq_tail.init(wave, lane, ld, S % BQ ? S % BQ : BQ);
-  tdo_tail.init(wave, lane, (size_t)I, S % BQ ? S % BQ : BQ);
-  const int it_tail = S % BQ ? S / BQ : -1;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
-  const int n_it = (S + BQ - 1) / BQ;
-  // The -lse / scale and -dvec slices of a query tile (written by the dq kernel) travel by DMA as well, one
-  // instruction each from waves 0 and 1.  Fetched with ordinary loads they put compiler-made vmcnt waits into
-  // the loop, and since those count the tile DMA issued just before them, every iteration waited out the
-  // whole DMA latency at its first matrix instruction.
-  const float* ndvec = dvec + srow;
-  const float* nlse = dvec + (size_t)a.B * a.H * S + srow;
-  const uint32_t lds_lse = lds0 + 2 * STG, lds_dv = lds_lse + 2 * BQ * 4;
-  // wave w fetches half w & 1 of key tile w >> 1 (past the last key: of the last tile, for keys that are not stored)
-  const uint32_t lds_keep = lds_dv + 2 * BQ * 4;
-  const int keep_jt = min(j0 / 64 + (wave >> 1), (Sk + 63) / 64 - 1);
-  const uint32_t* keep_w = DROP ? keep_row(a, (size_t)b * a.H + h, keep_jt, wave & 1) : nullptr;
-  const int keep_n = (wave & 1) * 16 + ((lane >> 3) & 3) * 4 + (lane & 3);  // this lane's key in a word
-  auto issue = [&](int stage, int it) __attribute__((always_inline)) {
+  __device__ __forceinline__ DkvTiles(char* lds, const AttnIO& io_, const bf16* dout, const float* dvec, const AttnDims& a_)
+      : io(io_), a(a_), smem(lds), win(a_.S, a_.far, CAUSAL) {
+    lse_all = reinterpret_cast<float*>(smem + NST * STG);
+    dv_all = lse_all + NST * BQ;
+    keep_all = reinterpret_cast<uint32_t*>(dv_all + NST * BQ);
+    dg = dv_all + NST * BQ + (DROP ? NST * 4 * BQ : 0) + (WIN ? 0 : BQ);
+    tid = threadIdx.x; lane = tid & 63; g = lane >> 5;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    S = a.S; Sk = a.Sk;
+    ld = (size_t)io.ldq; ldo = (size_t)(a.H * DK);
+    int kt;
+    decode_block((Sk + BCK - 1) / BCK, a.H, a.B, kt, h, b);
+    j0 = kt * BCK;
+    j_w0 = j0 + wave * 32;
+    j_loc = wave * 32 + (lane & 31);
+    base = (const bf16*)io.q + (size_t)b * S * ld + h * DK;
+    dobase = dout + (size_t)b * S * ldo + h * DK;
+    it_begin = CAUSAL ? (j0 / BQ) : 0;
+    it_tail = S % BQ ? S / BQ : -1;
+    n_it = (S + BQ - 1) / BQ;
+    tq.init(wave, lane, ld);
+    tdo.init(wave, lane, ldo);
+    tq_tail.init(wave, lane, ld, S % BQ ? S % BQ : BQ);
+    tdo_tail.init(wave, lane, ldo, S % BQ ? S % BQ : BQ);
+    lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+    // The -lse / scale and -dvec slices of a query tile (written by the dq kernel) travel by DMA as well, one
+    // instruction each from waves 0 and 1.  Fetched with ordinary loads they put compiler-made vmcnt waits into
+    // the loop, and since those count the tile DMA issued just before them, every iteration waited out the
+    // whole DMA latency at its first matrix instruction.
+    const size_t srow = ((size_t)b * a.H + h) * S;
+    ndvec = dvec + srow;
+    nlse = dvec + (size_t)a.B * a.H * S + srow;
+    lds_lse = lds0 + NST * STG;
+    lds_dv = lds_lse + NST * BQ * 4;
+    // wave w fetches half w & 1 of key tile w >> 1 (past the last key: of the last tile, for keys that are not stored)
+    lds_keep = lds_dv + NST * BQ * 4;
+    const int keep_jt = min(j0 / 64 + (wave >> 1), (Sk + 63) / 64 - 1);
+    keep_w = DROP ? keep_row(a, (size_t)b * a.H + h, keep_jt, wave & 1) : nullptr;
+    keep_n = (wave & 1) * 16 + ((lane >> 3) & 3) * 4 + (lane & 3);
+  }
+
+  // what only the loop needs
+  __device__ __forceinline__ void begin() {
+    sc = a.scale * kLog2e;
+    dgw = win.lane(dg, 28 + (lane & 31) - (g << 2));
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { dkT[ct][r] = 0.f; dvT[ct][r] = 0.f; }
+  }
+  __device__ __forceinline__ void issue(int stage, int it) const {
     const int q_first = it * BQ;
     const uint32_t dst = lds0 + stage * STG;
     (it == it_tail ? tq_tail : tq).issue(dst, base + (size_t)q_first * ld, wave);
-    (it == it_tail ? tdo_tail : tdo).issue(dst + TILE, dobase + (size_t)q_first * I, wave);
+    (it == it_tail ? tdo_tail : tdo).issue(dst + TILE, dobase + (size_t)q_first * ldo, wave);
     const int qi = q_first + lane < S ? q_first + lane : S - 1;  // (rows past the end are masked)
     if (wave == 0) dma_64f(lds_lse + stage * BQ * 4, nlse, (uint32_t)qi * 4u);
     if (wave == 1) dma_64f(lds_dv + stage * BQ * 4, ndvec, (uint32_t)qi * 4u);
     if constexpr (DROP) dma_64f(lds_keep + (stage * 4 + wave) * BQ * 4, keep_w + q_first, (uint32_t)lane * 4u);
-  };
-
-  bf16x8 kf[KS], vf[KS];
-  {
-    const bf16* krow = (const bf16*)io.k + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
-    const bf16* vrow = (const bf16*)io.v + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
+  }
+  __device__ __forceinline__ void load_keys() {
+    const int j = j0 + j_loc, j_ld = j < Sk ? j : Sk - 1;
+    const bf16* krow = (const bf16*)io.k + ((size_t)b * Sk + j_ld) * (size_t)io.ldkv + h * DK;
+    const bf16* vrow = (const bf16*)io.v + ((size_t)b * Sk + j_ld) * (size_t)io.ldkv + h * DK;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       kf[kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16 + g * 8);
@@ -993,46 +1018,34 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   // The compiler waits for these loads where they are first used, and that is inside the loop: its
   // s_waitcnt vmcnt(n) there would run in every iteration and, since the counter also counts the tile DMA
   // issued at the top of the iteration, stall the first matrix instructions until the whole DMA has landed.
-  // An empty use here moves the wait in front of the loop.
+  // An empty use moves the wait in front of the loop.
+  __device__ __forceinline__ void wait_keys() const {
 #pragma unroll
-  for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(kf[kk]), "v"(vf[kk]));
-  const BiasWin win(S, a.far, CAUSAL);
-  if constexpr (WIN) {
-    win.fill<CAUSAL>(dg, diag + (size_t)h * (2 * S - 1), S, tid);
-  } else if constexpr (BIAS) {
-    // dg[t] = bias(delta) for delta = t + j0 - (S - 1), t in [0, S + BCK - 1)
-    const float* dgh = diag + (size_t)h * (2 * S - 1);
-    for (int t = tid; t < S + BCK - 1; t += 256) {
-      int idx = t + j0;  // delta + S - 1
-      idx = idx > 2 * S - 2 ? 2 * S - 2 : idx;
-      dg[t] = dgh[idx] * kLog2e;
-    }
-    if (tid < BQ) dg[tid - BQ] = 0.f;
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(kf[kk]), "v"(vf[kk]));
   }
-  const float sc = a.scale * kLog2e;
-  // (WIN) the four diagonals of queries 8 rq + 4 g + 0..3 of a sub-tile, the last query's first
-  const float* dgw = win.lane(dg, 28 + (lane & 31) - (g << 2));
-  // dg index of (query i, key j): (j - i) - (j0 - (S-1)) = j_loc + (S - 1 - i)
-  f32x16 dkT[CT], dvT[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dkT[ct][r] = 0.f; dvT[ct][r] = 0.f; }
-
-  // How the queries past the end of a ragged last tile come to probability zero: by a masked copy of the element loop, or
-  // from the score accumulators' seeds, the infinity that makes exp2 zero.  Without the copy (and its branch) an iteration
-  // is one block that the compiler schedules whole; with dropout, with the slice, and bias-free with two waves, the copy is
-  // faster (slice: 32 x 256 tokens, 12 heads 25.1 -> 23.9 us, 4 x 2048 124 -> 119, 4 x 333 13.2 -> 12.4; window: 128 x 512, 12
-  // heads 267 with the copy, 266 without, 32 x 1024, 32 heads 594 and 587).
-  constexpr bool TAIL_MASK = DK == 64 && !CAUSAL && (BIAS ? DROP || !WIN : !DROP && !THREE);
-  auto mask_tail = [&](int stage, int it) __attribute__((always_inline)) {
-    if (!TAIL_MASK && it == it_tail) {
+  __device__ __forceinline__ void fill_bias(const float* __restrict__ diag) const {
+    if constexpr (WIN) {
+      win.template fill<CAUSAL>(dg, diag + (size_t)h * (2 * S - 1), S, tid);
+    } else if constexpr (BIAS) {
+      // dg[t] = bias(delta) for delta = t + j0 - (S - 1), t in [0, S + BCK - 1)
+      const float* dgh = diag + (size_t)h * (2 * S - 1);
+      for (int t = tid; t < S + BCK - 1; t += 256) {
+        int idx = t + j0;  // delta + S - 1
+        idx = idx > 2 * S - 2 ? 2 * S - 2 : idx;
+        dg[t] = dgh[idx] * kLog2e;
+      }
+      if (tid < BQ) dg[tid - BQ] = 0.f;
+    }
+  }
+  // the score accumulators of queries past the end start from the infinity that makes exp2 zero
+  __device__ __forceinline__ void seed_tail(int stage, int it) const {
+    if (it == it_tail) {
       if (tid < BQ && it * BQ + tid >= S) lse_all[stage * BQ + tid] = sc > 0.f ? -INFINITY : INFINITY;
       __syncthreads();
     }
-  };
+  }
   // s = S - lse / scale, dp = dP - dvec of sub-tile qb of the tile in `stage`
-  auto scores = [&](int stage, int qb, f32x16& s, f32x16& dp) __attribute__((always_inline)) {
+  __device__ __forceinline__ void scores(int stage, int qb, f32x16& s, f32x16& dp) const {
     const char* Qt = smem + stage * STG;
     const char* Dt = Qt + TILE;
     const float* lse_s = lse_all + stage * BQ;
@@ -1050,16 +1063,16 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Qt, qb * 32, kk, lane), kf[kk], s, 0, 0, 0);
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Dt, qb * 32, kk, lane), vf[kk], dp, 0, 0, 0);
     }
-  };
+  }
   // The scores of keys after their query: the infinity that makes exp2 zero, or with the window, whose bias is -infinity
-  // there, zero.
-  auto mask_later = [&](int q0, f32x16& s) __attribute__((always_inline)) {
+  // there, zero.  q0: first query of the sub-tile.
+  __device__ __forceinline__ void mask_later(int q0, f32x16& s) const {
     const float gone = WIN ? 0.f : sc > 0.f ? -INFINITY : INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       if (((r >> 2) << 3) + (r & 3) < j0 + j_loc - q0 - (g << 2)) s[r] = gone;
-  };
-  auto load_bias = [&](int q0, float (&bias)[16]) __attribute__((always_inline)) {  // q0: first query of the sub-tile
+  }
+  __device__ __forceinline__ void load_bias(int q0, float (&bias)[16]) const {
     if constexpr (WIN) {
       const float* bp = dgw + win.at(j_w0 - q0);
 #pragma unroll
@@ -1069,269 +1082,33 @@ void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
         for (int e = 0; e < 4; ++e) bias[rq * 4 + e] = b4[3 - e];
       }
     } else if constexpr (BIAS) {
-      // Register r belongs to query q0 + 4g + c_r with c_r = 8*(r/4) + r%4 <= 27, so bq[27 - c_r] with bq 27 below the
-      // first.  (a query past the end of a ragged tile reads at most BQ - 1 entries below dg[0]: the padding)
+      // dg index of (query i, key j): (j - i) - (j0 - (S-1)) = j_loc + (S - 1 - i).  Register r belongs to query
+      // q0 + 4g + c_r with c_r = 8*(r/4) + r%4 <= 27, so bq[27 - c_r] with bq 27 below the first.  (a query past the
+      // end of a ragged tile reads at most BQ - 1 entries below dg[0]: the padding)
       const float* bq = dg + (j_loc + S - 1 - q0 - (g << 2) - 27);
 #pragma unroll
       for (int r = 0; r < 16; ++r) bias[r] = bq[27 - (((r >> 2) << 3) + (r & 3))];
     }
-  };
-  // P and dS of a sub-tile, in place of s and dp
-  auto softmax = [&](auto tail, int stage, int qb, int q0, f32x16& s, f32x16& dp, const float (&bias)[16])
-      __attribute__((always_inline)) {
-    const float* dv_s = dv_all + stage * BQ;
-    const uint32_t* keep_s = keep_all + (stage * 4 + (wave & 2) + ((lane >> 2) & 1)) * BQ;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int ir = ((r >> 2) << 3) + (g << 2) + (r & 3), il = qb * 32 + ir;
-      float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
-      if (decltype(tail)::value && q0 + ir >= S) p = 0.f;
-      if constexpr (DROP) {
-        const int mask = keep_mask(keep_s[il], keep_n);
-        s[r] = keep_if(mask, p);
-        dp[r] = p * (keep_if(mask, dp[r] * a.drop.scale) + dv_s[il]);
-      } else {
-        s[r] = p;
-        dp[r] = p * dp[r];
-      }
-    }
-  };
-  issue(0, it_begin);
-  // diag: the tiles that the diagonal cuts have a loop of their own, so that the other loop has no branch (one loop with a branch
-  // around the mask: causal 64 x 512, 6 heads 70 -> 71 us, 1 x 1024, 12 heads 27 -> 29)
-  int it = it_begin;
-#pragma unroll
-  for (int diag = CAUSAL ? 1 : 0; diag >= 0; --diag) {
-    for (const int end = diag ? min(it_begin + BCK / BQ, n_it) : n_it; it < end; ++it) {
-      const int st = (it - it_begin) & 1, q0 = it * BQ;
-      dma_wait_barrier();  // tile `it` and its lse / dvec slices landed; the other stage is free
-      mask_tail(st, it);
-      if (it + 1 < n_it) issue(st ^ 1, it + 1);
-      const char* Qt = smem + st * STG;
-      const char* Dt = Qt + TILE;
-      // with the window, the score products of both sub-tiles first: 32 x 1024 tokens, 32 heads 609 -> 590 us
-      constexpr bool BOTH = WIN && !DROP && !CAUSAL;
-      f32x16 s[2], dp[2];
-      float bias[2][16];
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
-        if (diag && q0 + qb * 32 < j_w0) continue;  // masked whole for this wave
-        if (qb == 0 || !BOTH) {
-          load_bias(q0 + qb * 32, bias[qb]);
-          scores(st, qb, s[qb], dp[qb]);
-          if (diag) mask_later(q0 + qb * 32, s[qb]);
-        }
-        if (qb == 0 && BOTH) {
-          load_bias(q0 + 32, bias[1]);
-          scores(st, 1, s[1], dp[1]);
-        }
-        if (TAIL_MASK && q0 + qb * 32 + 32 > S) softmax(std::true_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
-        else softmax(std::false_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
-#pragma unroll
-        for (int mm = 0; mm < 2; ++mm) {
-          const bf16x8 pf = pack8(s[qb], mm * 8), dsf = pack8(dp[qb], mm * 8);
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
-            dvT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane), pf, dvT[ct], 0, 0, 0);
-            dkT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane), dsf, dkT[ct], 0, 0, 0);
-          }
-        }
-      }
+  }
+  // P of element r of a sub-tile, and with its dropout decision the elements of P and dS that enter the products
+  __device__ __forceinline__ float prob(float s, float bias) const {
+    return BIAS ? fast_exp2(fmaf(s, sc, bias)) : fast_exp2(s * sc);
+  }
+  __device__ __forceinline__ void drop_elem(int stage, int qb, int r, float p, float dp, float& pd, float& ds) const {
+    if constexpr (DROP) {
+      const float* dv_s = dv_all + stage * BQ;
+      const uint32_t* keep_s = keep_all + (stage * 4 + (wave & 2) + ((lane >> 2) & 1)) * BQ;
+      const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
+      const int mask = keep_mask(keep_s[il], keep_n);
+      pd = keep_if(mask, p);
+      ds = p * (keep_if(mask, dp * a.drop.scale) + dv_s[il]);
+    } else {
+      pd = p;
+      ds = p * dp;
     }
   }
-  __syncthreads();  // every wave is done with the tiles
-  {
-    char* stage = smem + wave * 32 * (DK * 2 + 16);
-    const size_t row0 = (size_t)b * Sk + j_w0;
-    store_rows<DK>(stage, dkT, a.scale, (bf16*)io.dk + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv, Sk - j_w0, lane);
-    store_rows<DK>(stage, dvT, DROP ? a.drop.scale : 1.f, (bf16*)io.dv + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv,
-                   Sk - j_w0, lane);
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// dk and dv.  grid (Sk/128) * H * B; wave w owns keys j0 + 32w + lane%32; loops over query tiles.
-// ------------------------------------------------------------------------------------------------
-// The pipelined form (128 channels, and 64 causal without dropout).  A unit is 32 queries x 32 keys; its dV / dK products follow the
-// score products of the next unit and run beside that unit's softmax arithmetic, across the tiles' barriers too (a ring of
-// three tile stages).  With 128 channels one wave has a SIMD to itself, and in program order matrix and vector unit took
-// turns (28 % and 26 % busy): 16 x 2048 tokens causal, 16 heads 950 -> 843 us, 8 x 2048 not causal 740 -> 650; 64 channels
-// causal, 8 x 2048, 12 heads 167 -> 148, 32 x 512 67 -> 62.  64 channels without the mask: 1-4 % slower than the other form.
-template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
-__global__ __launch_bounds__(256, DK == 64 ? 2 : 1)
-void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
-                              const float* __restrict__ lse, const float* __restrict__ dvec, AttnDims a) {
-  constexpr int BCK = 128, BQ = 64, KS = DK / 16, CT = DK / 32;
-  constexpr int TILE = BQ * DK * 2, STG = 2 * TILE;  // a stage holds a Q tile then a dO tile
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  // The score and dP accumulators start from -lse/scale and -dvec, so that the MFMA results are
-  // already (s - lse/scale) and (dP - dvec): no per-element subtraction afterwards.
-  float* lse_all = reinterpret_cast<float*>(smem + 3 * STG);  // [3 stages][BQ]  -lse / scale
-  float* dv_all = lse_all + 3 * BQ;                           // [3 stages][BQ]  -dvec
-  // [3 stages][2 key tiles][2][BQ] keep decisions (DROP only)
-  uint32_t* keep_all = reinterpret_cast<uint32_t*>(dv_all + 3 * BQ);
-  // Window, or [-BQ, S + BCK - 1), log2 units (BIAS only); the slice's BQ entries in front are only ever read for
-  // queries past the end of a ragged last tile, whose probabilities are set to zero
-  float* dg = dv_all + 3 * BQ + (DROP ? 12 * BQ : 0) + (WIN ? 0 : BQ);
-
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int S = a.S, Sk = a.Sk, I = a.H * DK;
-  const size_t ld = (size_t)io.ldq, ldkv = (size_t)io.ldkv;
-  int kt_, h, b;
-  decode_block((Sk + BCK - 1) / BCK, a.H, a.B, kt_, h, b);
-  const int j0 = kt_ * BCK;
-  const int j_w0 = j0 + wave * 32;            // first key of this wave
-  const int j_loc = wave * 32 + (lane & 31);
-  const bf16* base = (const bf16*)io.q + (size_t)b * S * ld + h * DK;
-  const bf16* dobase = dout + (size_t)b * S * I + h * DK;
-  const int it_begin = CAUSAL ? (j0 / BQ) : 0;
-  const size_t srow = ((size_t)b * a.H + h) * S;
-  // Q/dO tiles (DMA) and the matching lse / dvec slices are double buffered.
-  // tq_tail / tdo_tail: the last tile of a query sequence that does not fill it
-  TileDma<DK, BQ> tq, tdo, tq_tail, tdo_tail;
-  tq.init(wave, lane, ld);
-  tdo.init(wave, lane, (size_t)I);
-  tq_tail.init(wave, lane, ld, S % BQ ? S % BQ : BQ);
-  tdo_tail.init(wave, lane, (size_t)I, S % BQ ? S % BQ : BQ);
-  const int it_tail = S % BQ ? S / BQ : -1;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
-  const int n_it = (S + BQ - 1) / BQ;
-  // The -lse / scale and -dvec slices of a query tile (written by the dq kernel) travel by DMA as well, one
-  // instruction each from waves 0 and 1.  Fetched with ordinary loads they put compiler-made vmcnt waits into
-  // the loop, and since those count the tile DMA issued just before them, every iteration waited out the
-  // whole DMA latency at its first matrix instruction.
-  const float* ndvec = dvec + srow;
-  const float* nlse = dvec + (size_t)a.B * a.H * S + srow;
-  const uint32_t lds_lse = lds0 + 3 * STG, lds_dv = lds_lse + 3 * BQ * 4;
-  // wave w fetches half w & 1 of key tile w >> 1 (past the last key: of the last tile, for keys that are not stored)
-  const uint32_t lds_keep = lds_dv + 3 * BQ * 4;
-  const int keep_jt = min(j0 / 64 + (wave >> 1), (Sk + 63) / 64 - 1);
-  const uint32_t* keep_w = DROP ? keep_row(a, (size_t)b * a.H + h, keep_jt, wave & 1) : nullptr;
-  const int keep_n = (wave & 1) * 16 + ((lane >> 3) & 3) * 4 + (lane & 3);  // this lane's key in a word
-  auto issue = [&](int stage, int it) __attribute__((always_inline)) {
-    const int q_first = it * BQ;
-    const uint32_t dst = lds0 + stage * STG;
-    (it == it_tail ? tq_tail : tq).issue(dst, base + (size_t)q_first * ld, wave);
-    (it == it_tail ? tdo_tail : tdo).issue(dst + TILE, dobase + (size_t)q_first * I, wave);
-    const int qi = q_first + lane < S ? q_first + lane : S - 1;  // (rows past the end are masked)
-    if (wave == 0) dma_64f(lds_lse + stage * BQ * 4, nlse, (uint32_t)qi * 4u);
-    if (wave == 1) dma_64f(lds_dv + stage * BQ * 4, ndvec, (uint32_t)qi * 4u);
-    if constexpr (DROP) dma_64f(lds_keep + (stage * 4 + wave) * BQ * 4, keep_w + q_first, (uint32_t)lane * 4u);
-  };
-
-  issue(0, it_begin);
-  bf16x8 kf[KS], vf[KS];
-  {
-    const int j = j0 + j_loc, j_ld = j < Sk ? j : Sk - 1;
-    const bf16* krow = (const bf16*)io.k + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
-    const bf16* vrow = (const bf16*)io.v + ((size_t)b * Sk + j_ld) * ldkv + h * DK;
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      kf[kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16 + g * 8);
-      vf[kk] = *reinterpret_cast<const bf16x8*>(vrow + kk * 16 + g * 8);
-    }
-  }
-  const BiasWin win(S, a.far, CAUSAL);
-  if constexpr (WIN) {
-    win.fill<CAUSAL>(dg, diag + (size_t)h * (2 * S - 1), S, tid);
-  } else if constexpr (BIAS) {
-    // dg[t] = bias(delta) for delta = t + j0 - (S - 1), t in [0, S + BCK - 1)
-    const float* dgh = diag + (size_t)h * (2 * S - 1);
-    for (int t = tid; t < S + BCK - 1; t += 256) {
-      int idx = t + j0;  // delta + S - 1
-      idx = idx > 2 * S - 2 ? 2 * S - 2 : idx;
-      dg[t] = dgh[idx] * kLog2e;
-    }
-    if (tid < BQ) dg[tid - BQ] = 0.f;
-  }
-  // The compiler waits for these loads where they are first used, and that is inside the loop: its
-  // s_waitcnt vmcnt(n) there would run in every iteration and, since the counter also counts the tile DMA
-  // issued at the top of the iteration, stall the first matrix instructions until the whole DMA has landed.
-  // An empty use here moves the wait in front of the loop.
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(kf[kk]), "v"(vf[kk]));
-  const float sc = a.scale * kLog2e;
-  // (WIN) the four diagonals of queries 8 rq + 4 g + 0..3 of a sub-tile, the last query's first
-  const float* dgw = win.lane(dg, 28 + (lane & 31) - (g << 2));
-  // dg index of (query i, key j): (j - i) - (j0 - (S-1)) = j_loc + (S - 1 - i)
-  f32x16 dkT[CT], dvT[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { dkT[ct][r] = 0.f; dvT[ct][r] = 0.f; }
-
-  // queries past the end: their score accumulators start from the infinity that makes their probabilities zero
-  auto mask_tail = [&](int stage, int it) __attribute__((always_inline)) {
-    if (it == it_tail) {
-      if (tid < BQ && it * BQ + tid >= S) lse_all[stage * BQ + tid] = sc > 0.f ? -INFINITY : INFINITY;
-      __syncthreads();
-    }
-  };
-  // s = S - lse / scale, dp = dP - dvec of sub-tile qb of the tile in `stage`
-  auto scores = [&](int stage, int qb, f32x16& s, f32x16& dp) __attribute__((always_inline)) {
-    const char* Qt = smem + stage * STG;
-    const char* Dt = Qt + TILE;
-    const float* lse_s = lse_all + stage * BQ;
-    const float* dv_s = dv_all + stage * BQ;
-#pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
-      const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + qb * 32 + rq * 8 + g * 4);
-      const f32x4 d4 = *reinterpret_cast<const f32x4*>(dv_s + qb * 32 + rq * 8 + g * 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { s[rq * 4 + e] = l4[e]; dp[rq * 4 + e] = DROP ? 0.f : d4[e]; }
-    }
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Qt, qb * 32, kk, lane), kf[kk], s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<DK>(Dt, qb * 32, kk, lane), vf[kk], dp, 0, 0, 0);
-    }
-  };
-  // The scores of keys after their query: the infinity that makes exp2 zero, or with the window, whose bias is -infinity
-  // there, zero.
-  auto mask_later = [&](int q0, f32x16& s) __attribute__((always_inline)) {
-    const float gone = WIN ? 0.f : sc > 0.f ? -INFINITY : INFINITY;
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (((r >> 2) << 3) + (r & 3) < j0 + j_loc - q0 - (g << 2)) s[r] = gone;
-  };
-  auto load_bias = [&](int q0, float (&bias)[16]) __attribute__((always_inline)) {  // q0: first query of the sub-tile
-    if constexpr (WIN) {
-      const float* bp = dgw + win.at(j_w0 - q0);
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        const f32x4 b4 = *reinterpret_cast<const f32x4*>(bp - rq * 8);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bias[rq * 4 + e] = b4[3 - e];
-      }
-    } else if constexpr (BIAS) {
-      // Register r belongs to query q0 + 4g + c_r with c_r = 8*(r/4) + r%4 <= 27, so bq[27 - c_r] with bq 27 below the
-      // first.  (a query past the end of a ragged tile reads at most BQ - 1 entries below dg[0]: the padding)
-      const float* bq = dg + (j_loc + S - 1 - q0 - (g << 2) - 27);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) bias[r] = bq[27 - (((r >> 2) << 3) + (r & 3))];
-    }
-  };
-  // half mm of P and dS of a unit (its queries 16 mm ..) as operands of the dV and dK products
-  auto softmax = [&](int stage, int qb, int q0, int mm, const f32x16& s, const f32x16& dp, const float (&bias)[16],
-                     bf16x8& pf, bf16x8& dsf) __attribute__((always_inline)) {
-    const float* dv_s = dv_all + stage * BQ;
-    const uint32_t* keep_s = keep_all + (stage * 4 + (wave & 2) + ((lane >> 2) & 1)) * BQ;
-#pragma unroll
-    for (int r = mm * 8; r < mm * 8 + 8; ++r) {
-      float p = BIAS ? fast_exp2(fmaf(s[r], sc, bias[r])) : fast_exp2(s[r] * sc);
-      if constexpr (DROP) {
-        const int il = qb * 32 + ((r >> 2) << 3) + (g << 2) + (r & 3);
-        const int mask = keep_mask(keep_s[il], keep_n);
-        pf[r & 7] = (bf16)keep_if(mask, p);
-        dsf[r & 7] = (bf16)(p * (keep_if(mask, dp[r] * a.drop.scale) + dv_s[il]));
-      } else {
-        pf[r & 7] = (bf16)p;
-        dsf[r & 7] = (bf16)(p * dp[r]);
-      }
-    }
-  };
-  auto outer = [&](int stage, int qb, int mm, const bf16x8& pf, const bf16x8& dsf) __attribute__((always_inline)) {
+  // the dV and dK products of queries 16 mm .. 16 mm + 15 of a sub-tile
+  __device__ __forceinline__ void outer(int stage, int qb, int mm, const bf16x8& pf, const bf16x8& dsf) {
     const char* Qt = smem + stage * STG;
     const char* Dt = Qt + TILE;
 #pragma unroll
@@ -1339,32 +1116,138 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
       dvT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Dt, qb * 32 + mm * 16, ct * 32, lane), pf, dvT[ct], 0, 0, 0);
       dkT[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr<DK>(Qt, qb * 32 + mm * 16, ct * 32, lane), dsf, dkT[ct], 0, 0, 0);
     }
+  }
+  __device__ __forceinline__ void store() const {
+    __syncthreads();  // every wave is done with the tiles
+    char* stage = smem + wave * 32 * (DK * 2 + 16);
+    const size_t row0 = (size_t)b * Sk + j_w0, ldd = (size_t)io.lddkv;
+    store_rows<DK>(stage, dkT, a.scale, (bf16*)io.dk + row0 * ldd + h * DK, ldd, Sk - j_w0, lane);
+    store_rows<DK>(stage, dvT, DROP ? a.drop.scale : 1.f, (bf16*)io.dv + row0 * ldd + h * DK, ldd, Sk - j_w0, lane);
+  }
+};
+
+// The first form takes a tile at a time from two stages: 64 channels without the causal mask, where two or three waves per
+// SIMD cover for each other, or with dropout (causal 32 x 512, 12 heads: 68 us, the other form 72), or with a slice beside
+// which three stages would be too much (dkv_takes_pipe).
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool THREE, bool WIN>
+__global__ __launch_bounds__(256, THREE ? 3 : 2)
+void attn_bwd_dkv_mfma_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
+                              const float* __restrict__ dvec, AttnDims a) {
+  static_assert(DK == 64, "128 channels have the pipelined form");
+  using Tiles = DkvTiles<DK, CAUSAL, BIAS, DROP, WIN, 2>;
+  constexpr int BCK = Tiles::BCK, BQ = Tiles::BQ;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  Tiles t(smem, io, dout, dvec, a);
+  t.load_keys();
+  t.wait_keys();
+  t.fill_bias(diag);
+  t.begin();
+
+  // How the queries past the end of a ragged last tile come to probability zero: by a masked copy of the element loop, or
+  // from the score accumulators' seeds.  Without the copy (and its branch) an iteration is one block that the compiler
+  // schedules whole; with dropout, with the slice, and bias-free with two waves, the copy is faster (slice: 32 x 256 tokens,
+  // 12 heads 25.1 -> 23.9 us, 4 x 2048 124 -> 119, 4 x 333 13.2 -> 12.4; window: 128 x 512, 12 heads 267 with the copy, 266
+  // without, 32 x 1024, 32 heads 594 and 587).
+  constexpr bool TAIL_MASK = !CAUSAL && (BIAS ? DROP || !WIN : !DROP && !THREE);
+  // P and dS of a sub-tile, in place of s and dp
+  auto softmax = [&](auto tail, int stage, int qb, int q0, f32x16& s, f32x16& dp, const float (&bias)[16])
+      __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float p = t.prob(s[r], bias[r]), pd, ds;
+      if (decltype(tail)::value && q0 + ((r >> 2) << 3) + (t.g << 2) + (r & 3) >= t.S) p = 0.f;
+      t.drop_elem(stage, qb, r, p, dp[r], pd, ds);
+      s[r] = pd;
+      dp[r] = ds;
+    }
   };
-  // A unit is 32 queries x 32 keys.  Step n of the pipeline: the score products of unit n, then the dV / dK products of unit
-  // n - 1 beside the softmax arithmetic of unit n.
-  bf16x8 pf[2], dsf[2];      // of the unit whose products are still to come
+  t.issue(0, t.it_begin);
+  // diag: the tiles that the diagonal cuts have a loop of their own, so that the other loop has no branch (one loop with a branch
+  // around the mask: causal 64 x 512, 6 heads 70 -> 71 us, 1 x 1024, 12 heads 27 -> 29)
+  int it = t.it_begin;
+#pragma unroll
+  for (int diag = CAUSAL ? 1 : 0; diag >= 0; --diag) {
+    for (const int end = diag ? min(t.it_begin + BCK / BQ, t.n_it) : t.n_it; it < end; ++it) {
+      const int st = (it - t.it_begin) & 1, q0 = it * BQ;
+      dma_wait_barrier();  // tile `it` and its lse / dvec slices landed; the other stage is free
+      if constexpr (!TAIL_MASK) t.seed_tail(st, it);
+      if (it + 1 < t.n_it) t.issue(st ^ 1, it + 1);
+      // with the window, the score products of both sub-tiles first: 32 x 1024 tokens, 32 heads 609 -> 590 us
+      constexpr bool BOTH = WIN && !DROP && !CAUSAL;
+      f32x16 s[2], dp[2];
+      float bias[2][16];
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        if (diag && q0 + qb * 32 < t.j_w0) continue;  // masked whole for this wave
+        if (qb == 0 || !BOTH) {
+          t.load_bias(q0 + qb * 32, bias[qb]);
+          t.scores(st, qb, s[qb], dp[qb]);
+          if (diag) t.mask_later(q0 + qb * 32, s[qb]);
+        }
+        if (qb == 0 && BOTH) {
+          t.load_bias(q0 + 32, bias[1]);
+          t.scores(st, 1, s[1], dp[1]);
+        }
+        if (TAIL_MASK && q0 + qb * 32 + 32 > t.S) softmax(std::true_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
+        else softmax(std::false_type{}, st, qb, q0 + qb * 32, s[qb], dp[qb], bias[qb]);
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm) t.outer(st, qb, mm, pack8(s[qb], mm * 8), pack8(dp[qb], mm * 8));
+      }
+    }
+  }
+  t.store();
+}
+
+// The pipelined form (128 channels, and 64 causal without dropout).  A unit is 32 queries x 32 keys; its dV / dK products follow the
+// score products of the next unit and run beside that unit's softmax arithmetic, across the tiles' barriers too (a ring of
+// three tile stages).  With 128 channels one wave has a SIMD to itself, and in program order matrix and vector unit took
+// turns (28 % and 26 % busy): 16 x 2048 tokens causal, 16 heads 950 -> 843 us, 8 x 2048 not causal 740 -> 650; 64 channels
+// causal, 8 x 2048, 12 heads 167 -> 148, 32 x 512 67 -> 62; with dropout, not causal, 8 x 2048, 16 heads of 128 827 -> 627.
+// 64 channels without the mask: 1-4 % slower than the other form.
+template <int DK, bool CAUSAL, bool BIAS, bool DROP, bool WIN>
+__global__ __launch_bounds__(256, DK == 64 ? 2 : 1)
+void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const float* __restrict__ diag,
+                              const float* __restrict__ dvec, AttnDims a) {
+  using Tiles = DkvTiles<DK, CAUSAL, BIAS, DROP, WIN, 3>;
+  constexpr int BQ = Tiles::BQ;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  Tiles t(smem, io, dout, dvec, a);
+  t.issue(0, t.it_begin);
+  t.load_keys();
+  t.fill_bias(diag);
+  t.wait_keys();
+  t.begin();
+
+  // Step n of the pipeline: the score products of unit n, then the dV / dK products of unit n - 1 beside the softmax
+  // arithmetic of unit n.
+  bf16x8 pf[2], dsf[2];  // P and dS of the unit whose products are still to come
   // unit qb of the tile in `stage`, whose first query is q0, behind unit pqb of `pst` (-1: none)
   auto step = [&](auto diag, int pst, int pqb, int stage, int qb, int q0) __attribute__((always_inline)) {
     f32x16 s, dp;
     float bias[16];
     bf16x8 pn[2], dn[2];
-    load_bias(q0 + qb * 32, bias);
-    scores(stage, qb, s, dp);
-    if constexpr (decltype(diag)::value) mask_later(q0 + qb * 32, s);
+    t.load_bias(q0 + qb * 32, bias);
+    t.scores(stage, qb, s, dp);
+    if constexpr (decltype(diag)::value) t.mask_later(q0 + qb * 32, s);
     if (pqb >= 0) {
 #pragma unroll
-      for (int mm = 0; mm < 2; ++mm) outer(pst, pqb, mm, pf[mm], dsf[mm]);
+      for (int mm = 0; mm < 2; ++mm) t.outer(pst, pqb, mm, pf[mm], dsf[mm]);
     }
 #pragma unroll
-    for (int mm = 0; mm < 2; ++mm) softmax(stage, qb, q0 + qb * 32, mm, s, dp, bias, pn[mm], dn[mm]);
+    for (int r = 0; r < 16; ++r) {
+      float pd, ds;
+      t.drop_elem(stage, qb, r, t.prob(s[r], bias[r]), dp[r], pd, ds);
+      pn[r >> 3][r & 7] = (bf16)pd;
+      dn[r >> 3][r & 7] = (bf16)ds;
+    }
 #pragma unroll
     for (int mm = 0; mm < 2; ++mm) { pf[mm] = pn[mm]; dsf[mm] = dn[mm]; }
   };
   // tile `it` has landed in `stage`; every wave is done with tile it - 2
   auto enter = [&](int stage, int it) __attribute__((always_inline)) {
     dma_wait_barrier();
-    mask_tail(stage, it);
-    if (it + 1 < n_it) issue(stage == 2 ? 0 : stage + 1, it + 1);
+    t.seed_tail(stage, it);
+    if (it + 1 < t.n_it) t.issue(stage == 2 ? 0 : stage + 1, it + 1);
   };
   // Causal, the diagonal cuts the w-th unit of wave w, which begins there (the units before it have no visible key): waves 2 and
   // 3 in the second tile, 1 and 3 with a tile's second unit.  The loop has no mask and no branch inside a step (with a select
@@ -1372,14 +1255,14 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
   // it, 16 x 2048, 16 heads 740 -> 825, like this 755).
   constexpr std::bool_constant<CAUSAL> cut{};
   constexpr std::false_type all{};
-  int it = it_begin, st = 0, second = 0;
+  int it = t.it_begin, st = 0, second = 0;
   enter(0, it);
   if constexpr (CAUSAL) {
-    if (wave >= 2 && it + 1 < n_it) {
+    if (t.wave >= 2 && it + 1 < t.n_it) {
       enter(1, ++it);
       st = 1;
     }
-    second = wave & 1;
+    second = t.wave & 1;
     asm("" : "+s"(second));  // (known, it would become a copy of the loop)
   }
   step(cut, 0, -1, st, second, it * BQ);
@@ -1387,23 +1270,15 @@ void attn_bwd_dkv_pipe_kernel(AttnIO io, const bf16* __restrict__ dout, const fl
     const int q0 = it * BQ;
     if (!CAUSAL || !second) step(all, st, 0, st, 1, q0);
     second = 0;
-    if (it + 1 == n_it) break;
+    if (it + 1 == t.n_it) break;
     const int nst = st == 2 ? 0 : st + 1;
     enter(nst, it + 1);
     step(all, st, 1, nst, 0, q0 + BQ);
     st = nst;
   }
 #pragma unroll
-  for (int mm = 0; mm < 2; ++mm) outer(st, 1, mm, pf[mm], dsf[mm]);
-  __syncthreads();  // every wave is done with the tiles
-  char* stage = smem + wave * 32 * (DK * 2 + 16);
-  {
-    const int j_b0 = j_w0;
-    const size_t row0 = (size_t)b * Sk + j_b0;
-    store_rows<DK>(stage, dkT, a.scale, (bf16*)io.dk + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv, Sk - j_b0, lane);
-    store_rows<DK>(stage, dvT, DROP ? a.drop.scale : 1.f, (bf16*)io.dv + row0 * (size_t)io.lddkv + h * DK, (size_t)io.lddkv,
-                   Sk - j_b0, lane);
-  }
+  for (int mm = 0; mm < 2; ++mm) t.outer(st, 1, mm, pf[mm], dsf[mm]);
+  t.store();
 }
 
 // Whether dk/dv has a pipelined form.
@@ -1466,7 +1341,7 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
       if (DK == 128 || WIN || dkv_takes_pipe(a, WIN)) {
         auto kern = attn_bwd_dkv_pipe_kernel<DK, CAUSAL, BIAS, DROP, WIN>;
         if ((e = set_lds(kern, lds)) != hipSuccess) return e;
-        kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+        kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, dvec, a);
         return hipGetLastError();
       }
     }
@@ -1474,11 +1349,11 @@ hipError_t bwd_launch_as(const AttnIO& io, const void* c, const void* dc, const 
       // Bias-free with 64 channels: beyond two workgroups per compute unit the form that lets a third in, up to there the
       // one whose single workgroup is faster (1 x 1024 queries over 100 keys, 12 heads, 12 workgroups: 27 against 23 us;
       // 384 workgroups 39 and 38; 768 61 and 65; 128 x 114 over 512, 6144 workgroups: 103 and 106).
-      constexpr bool CAN_THREE = DK == 64 && !BIAS && !DROP;
+      constexpr bool CAN_THREE = !BIAS && !DROP;
       auto kern = CAN_THREE && wgs > 512 ? attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, CAN_THREE, WIN>
                                          : attn_bwd_dkv_mfma_kernel<DK, CAUSAL, BIAS, DROP, false, WIN>;
       if ((e = set_lds(kern, lds)) != hipSuccess) return e;
-      kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, lse, dvec, a);
+      kern<<<dim3(wgs), 256, lds, st>>>(io, (const bf16*)dc, diag, dvec, a);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
