@@ -952,9 +952,12 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    while they fit one round, smaller tiles, 128x64 and 64x64 (1332 x 768 x 2048 with residual: 37 us -> 21;
     //    1332 x 768 x 768: 25 -> 18).  What bounds them is the path from L2 to LDS, 65 GB/s a compute unit with rows of 128 bytes:
     //    four stages of 32 (rows of 64 bytes) took 39.9 us for 3648 x 768 x 4096, these 31.9; k 2304 30.4 and 25.3, 2048 29.5 and
-    //    25.3; three stages of 64 43.  The longer ramp of 64 pays from K = 1025 on, with 192 tiles or more from 768 on (us with 32
-    //    and with 64: 160 tiles of 2520 x 1024: k 512 7.8 and 8.9, 1024 11.0 and 11.9, 1280 15.7 and 13.4; 228 of 4824 x 768: 512 8.7
-    //    and 9.5, 768 11.2 and 11.1, 1024 13.3 and 12.8), in the gated-GELU backward always (from k 512 on measured: 3 % and more).
+    //    25.3; three stages of 64 43.  The longer ramp of 64 pays from K = 1025 on, with 192 tiles or more from 768 on, for plain
+    //    stores always from 768 on, in the gated-GELU backward always (us with 32 and with 64, launched again and again: 160 tiles of
+    //    2520 x 1024: k 512 7.8 and 8.9, 1280 15.7 and 13.4; 228 of 4824 x 768: 512 8.7 and 9.5, 768 11.2 and 11.1, 1024 13.3 and 12.8.
+    //    Between the other launches of a layer's backward, which leave neither the code nor the operands near: plain store of 138, 156
+    //    and 174 tiles, N = K = 768 12.8, 12.9, 13.2 and 11.9, 12.0, 12.4, of 136, 160 and 176, N = K = 1024 15.1, 15.0, 15.5 and 13.6,
+    //    13.4, 14.1; with residual 160 tiles of N = K = 1024 17.2 and 18.0).
     //    Beside launches on another stream, whose workgroups find no room on a unit with 128 KB taken, only from 5120 on (backward
     //    with the weight gradients overlapped, us with 32 and with 64 throughout: d 768, k 768, 2304 and 4096, 4096 tokens 253 and
     //    261, 5000 tokens 297 and 309; d 2048, k 2048, 6144 and 10240, 2000 tokens 590 and 536; d 1024, k 1024, 3072 and 5632, 3500
@@ -973,7 +976,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
         if ((int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 64) <= 256)
           return launch_cfg<128, 64, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
       }
-      if (!(g.beside && K < 5120) && (EPI == EPI_GEGLU_BWD || K > 1024 || (K >= 768 && t128 >= 192)))
+      if (!(g.beside && K < 5120) && (EPI == EPI_GEGLU_BWD || K > 1024 || (K >= 768 && (EPI == EPI_STORE || t128 >= 192))))
         return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1, 64>(g, e, 1, st);
       return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI_T, 4, 1>(g, e, 1, st);
     }
