@@ -135,9 +135,10 @@ int t5_relpos_bucket(const int32_t* rel_pos, int32_t* bucket, int64_t n, int bid
  * mix32(x): x ^= x>>16; x *= 0x7FEB352D; x ^= x>>15; x *= 0x846CA68B; x ^= x>>16 (mod 2^32),
  *   keep(row, col) = mix32(mix32(k0 ^ row ^ seed_hi) ^ col) >= floor(rate * 2^32),
  *   k0 = mix32(seed_lo ^ site * 0x9E3779B9),
- * so the forward and backward kernels form the same mask from (seed, site, row, col); only that of the attention
- * probabilities is stored, in bfloat16, one bit each in the stash.  t5_dropout_keep writes that mask (1 = kept) for inspection and tests: keep is device
- * uint8 [rows, cols].  Errors: NULL -> T5_ERR_NULL; rows/cols < 0, rate outside [0, 1) -> T5_ERR_SHAPE.
+ * so the forward and backward kernels form the same mask from (seed, site, row, col).  One kind is stored as well: with
+ * bfloat16 activations the masks of the attention probabilities are bits in the stash, which grows by batch * n_heads *
+ * seq * keys / 8 bytes for each attention of a layer (seq rounded up to 128, keys to 64; 50 MB at 128 x 512 positions, 12
+ * heads).  t5_dropout_keep writes a site's mask (1 = kept) for inspection and tests: keep is device uint8 [rows, cols].  Errors: NULL -> T5_ERR_NULL; rows/cols < 0, rate outside [0, 1) -> T5_ERR_SHAPE.
  * Every entry point applies it when its block configuration has dropout_rate > 0.  The decoder layer adds
  * site 5 (cross-attention probabilities; row = (batch*n_heads + head)*seq + query, column = encoder
  * position) and site 6 (output of the cross-attention sublayer).  A stack runs layer l (0-based) with the
