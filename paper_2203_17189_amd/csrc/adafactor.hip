@@ -25,7 +25,7 @@ constexpr int TR = 64;   // tile rows
 constexpr int TC = 256;  // tile columns, four to a lane
 // A tile's workgroup has sixteen wavefronts of four rows, whose loads are all in flight at once.  (With four wavefronts of sixteen
 // rows eight workgroups shared a compute unit: the 2961 tiles of a d 2048 layer were 1.45 rounds, the second half empty; stats
-// 57 -> 52 us, apply 118 -> 112; norms stay at 82, 4.7 TB/s.)
+// 57 -> 52 us, norms 83 -> 81, apply 121 -> 106.)
 constexpr int NWV = 16, NT = NWV * 64, RPW = TR / NWV;
 
 struct AfWs {

@@ -930,7 +930,8 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    whose last 256 columns are not all there: 12800 x 1152 x 512 40 us with 256x256, 25 with this, 25600 rows 59 and
     //    43), 0.56 and 0.49 (K <= 768)
     //    with the residual epilogue, whose extra traffic the second workgroup hides; a last round of up to 256 tiles
-    //    costs 0.65 of a full one, as much as a full one from K = 1024 on.  The cheaper sum of rounds is taken
+    //    costs 0.65 of a full one, as much as a full one from K = 1024 on.  (w was fitted to two stages; the three-and-two ring below
+    //    makes a round up to 8 % shorter from K = 1024 on, for which it was not fitted again.)  The cheaper sum of rounds is taken
     //    (14592 x 768 x 2304, 171 against 684 tiles: 59 us against 68; 8991 x 768 x 4096, 108 against 426: 92 against 64).
     //    The gated-GELU backward, two tensors in and two out, always takes it (32768 x 5120 x 2048: 1149 us with 256x256,
     //    850 with 256x128, 761 with this in two stages, 730 with three stages of A and two of B, which fill the half of the
