@@ -38,9 +38,14 @@ hipError_t launch_direct(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
       if ((int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64) <= 256) return launch_cfg<64, 64, 1, 2, true, false, EPI, 4, 1, 64>(g, e, 1, st);
       if ((int64_t)ceil_div(g.M, 128) * ceil_div(g.N, 64) <= 256) return launch_cfg<128, 64, 2, 2, true, false, EPI, 3, 1, 64>(g, e, 1, st);
     }
-    // (four stages of 64 from K = 2048 on: 4000 x 768 x 2048 with residual 27.8 -> 25.6 us, 3500 x 1024 x 2816 39.8 -> 34.4;
-    // 3500 x 1024 x 1024 18.6 with 32, 20.5 with 64)
-    if (g.seg[0].K >= 2048) return launch_cfg<128, 128, 2, 2, true, false, EPI, 4, 1, 64>(g, e, 1, st);
+    // Four stages of 64 from K = 1536 on, with residual from above 1024 (us in a layer's forward with stages of 32 and with these.
+    // Residual, N = 768, 4000 rows: K 1280 21.1 and 20.4, 1536 23.2 and 22.2, 1792 25.4 and 23.9, 2048 28.1 and 25.9; N = 1024, 3500
+    // rows: 21.1 and 20.1, 23.4 and 21.9, 25.6 and 23.5, 28.1 and 25.0; 1024 in two runs 18.1 and 16.9, 18.6 and 20.5.  Queries,
+    // keys and values, N = 768, 5200 rows: 1024 14.4 and 14.8, 1280 16.8 and 16.4, 1536 18.8 and 17.9, 2048 22.1 and 21.2; 4000 rows: 1024
+    // 13.8 and 14.4, 1280 15.6 and 16.0, 1536 17.6 and 17.3, 2048 20.4 and 20.0.  Gated, N = 768, 4000 rows: 1024 14.8 and 15.3, 1280
+    // 16.2 and 16.8, 1536 17.9 and 17.7, 2048 21.1 and 20.1).
+    if (g.seg[0].K >= 1536 || (EPI == EPI_RESID && g.seg[0].K > 1024))
+      return launch_cfg<128, 128, 2, 2, true, false, EPI, 4, 1, 64>(g, e, 1, st);
     return launch_cfg<128, 128, 2, 2, true, false, EPI, 4, 1>(g, e, 1, st);
   }
   // (three stages of A and two of B lose here: 8192 x 2048 x 512 gated 32 -> 37 us)

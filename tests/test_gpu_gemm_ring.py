@@ -53,7 +53,7 @@ def test_one_tile_per_unit_every_loop_remainder(nk):
     _check_gemm(3648, 776, 64 * nk, True)
 
 
-@pytest.mark.parametrize("d_ff", [2048, 2112])
+@pytest.mark.parametrize("d_ff", [1024, 1088, 2048, 2112])  # stages of 32, and from above 1024 on of 64
 def test_stored_weights_one_tile_per_unit(d_ff):
     """2100 x 1024 outputs, 136 tiles, over d_ff: the forward products that read weights as they are stored."""
     cfg = SI.BlockConfig(f"gemm_stored_{d_ff}", 65, 30, 70, 1024, 16, 64, d_ff, attn_scale=0.125)
