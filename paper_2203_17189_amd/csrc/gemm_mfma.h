@@ -928,10 +928,13 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //  * 128x128, two workgroups per compute unit: a round of 512 tiles costs w of a 256x256 round, which
     //    is four times the work for w = 0.62 (plain store and gated-GELU forward; 0.53 at K < 640, 0.40 for a plain store
     //    whose last 256 columns are not all there: 12800 x 1152 x 512 40 us with 256x256, 25 with this, 25600 rows 59 and
-    //    43), 0.56 and 0.49 (K <= 768)
-    //    with the residual epilogue, whose extra traffic the second workgroup hides; a last round of up to 256 tiles
-    //    costs 0.65 of a full one, as much as a full one from K = 1024 on.  (w was fitted to two stages; the three-and-two ring below
-    //    makes a round up to 8 % shorter from K = 1024 on, for which it was not fitted again.)  The cheaper sum of rounds is taken
+    //    43), with the residual epilogue, whose extra traffic the second workgroup hides, 0.49 (K <= 768), 0.56, from K = 1024 on
+    //    0.52, above that 0.555 and from 2049 on 0.61.  A last round of up to 256 tiles costs 0.65 of a full one; as much as a
+    //    full one above K = 3072, and from 1024 on where there is only one before it.  (us with 256x256 and with this.  N = 2048, plain
+    //    store of 2096 tiles: K 1536 124 and 114, 2048 155 and 144, 3072 210 and 201, 4096 275 and 262, but 2128 of N = 1024 272 and 284;
+    //    of 2560: K 1536 130 and 131, 2048 161 and 164, 4096 284 and 296; of 640: 39 and 41, 47 and 51, 80 and 90.  Gated, K 2048, 2304
+    //    tiles 172 and 162, 2560 175 and 176.  Residual, 4352 tiles: K 1024 203 and 176, 2048 312 and 299, 4096 527 and 549; 2560 tiles:
+    //    123 and 112, 186 and 185, 313 and 329; 3584, K 2560 299 and 315; 520 of N = 1024, K 2048 55 and 60.)  The cheaper sum of rounds is taken
     //    (14592 x 768 x 2304, 171 against 684 tiles: 59 us against 68; 8991 x 768 x 4096, 108 against 426: 92 against 64).
     //    The gated-GELU backward, two tensors in and two out, always takes it (32768 x 5120 x 2048: 1149 us with 256x256,
     //    850 with 256x128, 761 with this in two stages, 730 with three stages of A and two of B, which fill the half of the
@@ -946,7 +949,10 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //  * 256x192, the same loop with three quarters of the columns, where that fills rounds that 256x256 leaves part empty
     //    (widths of 768: 16384 x 768 is 192 tiles of 256x256 and 256 of these).  A round costs 0.88 of a 256x256 one, not
     //    0.75: more units share the power and the L2.  k 4096 98 -> 92 us, 2048 62 -> 57, 768 30 -> 26; 16384 x 2304 x 768,
-    //    three rounds of each: 73 -> 69; 8991 x 2304 x 768, two rounds against 2.5 of 128x128: 42 with those, 50 with this;
+    //    three rounds of each: 73 -> 69; 8991 x 2304 x 768, two rounds against 2.5 of 128x128: 42 with those, 50 with this.
+    //    Above K = 1024 it is compared with 0.62 for every round of 128x128 that is begun, residual or not: two rounds of this against
+    //    three, the last one full or not, us: N = 768, residual, 22016 rows, K 2048 85 and 89, 4096 145 and 162; 32768 rows, 104 and
+    //    116, 175 and 206; plain store, 24576 rows, K 1536 65 and 65, 2304 85 and 90, 4096 133 and 144 (K 1024 53 and 49);
     //  * 256x128, two workgroups, k-tiles of 32 in three stages: gated-GELU forward up to K = 704, residual up to K = 512
     //    (32768 x 512 x 384: 31 us against 32 and 34);
     //  * up to 256 tiles of 128x128 (one per compute unit): latency counts, so more stages (four of 64, 128 KB) and,
@@ -965,11 +971,13 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     //    tokens 339 and 332, like this 310 where 64 throughout takes 317);
     int64_t K = 0;
     for (int s = 0; s < g.nseg; ++s) K += g.seg[s].K;
-    const double last = K >= 1024 ? 1.0 : 0.65;
-    const double w = EPI == EPI_RESID ? (K <= 768 ? 0.49 : 0.56) : K < 640 ? (EPI == EPI_STORE && g.N % 256 != 0 ? 0.40 : 0.53) : 0.62;
+    const double last = K > 3072 || (K >= 1024 && t128 <= 1024) ? 1.0 : 0.65;
+    const double w_resid = K <= 768 ? 0.49 : K < 1024 ? 0.56 : K == 1024 ? 0.52 : K <= 2048 ? 0.555 : 0.61;
+    const double w = EPI == EPI_RESID ? w_resid : K < 640 ? (EPI == EPI_STORE && g.N % 256 != 0 ? 0.40 : 0.53) : 0.62;
     const double c256 = (double)((t256 + 255) / 256);
     const int64_t rem = t128 % 512;
     const double c128 = w * ((double)(t128 / 512) + (rem > 256 ? 1.0 : rem > 0 ? last : 0.0));
+    const double c128_192 = K > 1024 ? 0.62 * (double)((t128 + 511) / 512) : c128;  // (against 256x192)
     if (t128 <= 256) {
       if constexpr (EPI != EPI_GEGLU_FWD) {  // (which needs 64 columns in a wavefront)
         if ((int64_t)ceil_div(g.M, 64) * ceil_div(g.N, 64) <= 256)
@@ -984,7 +992,7 @@ hipError_t launch_layout(const GemmDesc& g, const GemmEpi& e, hipStream_t st) {
     if constexpr (EPI_T == EPI_STORE || EPI_T == EPI_RESID) {  // (the dropout copies are not built: 14592 x 768 x 2048 with residual 65 us, 59 like this)
       if (g.N % 192 == 0) {
         const double c192 = 0.88 * (double)(((int64_t)ceil_div(g.M, 256) * (g.N / 192) + 255) / 256);
-        if (c192 < c256 && c192 < c128) return launch_cfg<256, 192, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
+        if (c192 < c256 && c192 < c128_192) return launch_cfg<256, 192, 2, 2, A_KC, B_KC, EPI_T, 3, 1, 64>(g, e, 1, st);
       }
     }
     if constexpr (EPI == EPI_GEGLU_FWD || EPI == EPI_RESID)

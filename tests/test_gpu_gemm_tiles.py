@@ -38,10 +38,12 @@ def _tile(M, N, K, resid=False):
     if t128 <= 256:
         return "64x64" if tiles(64, 64) <= 256 else "128x64" if tiles(128, 64) <= 256 else "128x128"
     rem = t128 % 512
-    w = (0.49 if K <= 768 else 0.56) if resid else (0.40 if N % 256 else 0.53) if K < 640 else 0.62
-    c128 = w * (t128 // 512 + (1.0 if rem > 256 else 1.0 if rem and K >= 1024 else 0.65 if rem else 0.0))
+    w = ((0.49 if K <= 768 else 0.56 if K < 1024 else 0.52 if K == 1024 else 0.555 if K <= 2048 else 0.61) if resid
+         else (0.40 if N % 256 else 0.53) if K < 640 else 0.62)
+    c128 = w * (t128 // 512 + (1.0 if rem > 256 or (rem and (K > 3072 or (K >= 1024 and t128 <= 1024))) else 0.65 if rem else 0.0))
+    c128_192 = 0.62 * -(-t128 // 512) if K > 1024 else c128
     c256 = -(-tiles(256, 256) // 256)
-    if N % 192 == 0 and 0.88 * -(-tiles(256, 192) // 256) < min(c256, c128):
+    if N % 192 == 0 and 0.88 * -(-tiles(256, 192) // 256) < min(c256, c128_192):
         return "256x192"
     if resid and K <= 512 and tiles(256, 256) >= 192:
         return "256x128"
