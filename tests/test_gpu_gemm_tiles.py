@@ -67,6 +67,16 @@ def test_tile_families_k_contiguous(M, N, K, tile):
     _check_gemm(M, N, K, True)
 
 
+# from K = 1024 on: a last round that is not full behind four full ones, and behind one; the first K that counts it as full; 256x192
+# against three rounds
+@pytest.mark.parametrize("M,N,K,tile", [(16777, 2048, 1024, "128x128, two per unit"), (18432, 2040, 3072, "128x128, two per unit"),
+                                        (16777, 2048, 3136, "256x256"), (8190, 1032, 1024, "256x256"),
+                                        (22001, 768, 1024, "128x128, two per unit"), (22001, 768, 1088, "256x192")])
+def test_tiles_of_several_rounds(M, N, K, tile):
+    assert _tile(M, N, K) == tile
+    _check_gemm(M, N, K, True)
+
+
 def _wgrad_plan(M, N, K, ngr=1):
     """Tile and k-slices that wgrad_plan gives a weight gradient (ngr of them in one launch)."""
     def tiles(b):
